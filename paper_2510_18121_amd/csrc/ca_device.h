@@ -220,6 +220,23 @@ __device__ __forceinline__ void mfma_settle(f32x16 &x, f32x16 &y, const f32x16 &
 __device__ __forceinline__ void mfma_chain_end(f32x16 &x, f32x16 &y, const f32x16 &c) {
   asm volatile("; chain end" : "+v"(x), "+v"(y) : "v"(c));
 }
+// d *= f for a result tuple that lives in the accumulation file, one element at a time through one architectural
+// register (left to the compiler, every tuple of the wave is copied over at once, which at two waves per SIMD spills).
+// The wait states stand for those between the MFMA that wrote the tuple and the first read, and between the last write and
+// an MFMA that reads it, which the compiler does not place around assembly.
+__device__ __forceinline__ void scale_acc(f32x16 &d, float f) {
+  float t;
+  asm volatile("s_nop 15" : "+a"(d));
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    float e = d[i];
+    asm volatile("v_accvgpr_read_b32 %1, %0\n\ts_nop 0\n\tv_mul_f32 %1, %1, %2\n\ts_nop 0\n\tv_accvgpr_write_b32 %0, %1"
+                 : "+a"(e), "=&v"(t)
+                 : "v"(f));
+    d[i] = e;
+  }
+  asm volatile("s_nop 4" : "+a"(d));
+}
 __device__ __forceinline__ void pin(float &v) { asm volatile("" : "+v"(v)); }
 // exp2(x * c - g) as one volatile asm statement: like pin() it stays where it is written in the instruction stream
 // (between the MFMAs of its slot), but without the wait state the compiler puts between an empty asm that "defines"

@@ -15,14 +15,20 @@
 // ds_read_b64_tr_b16.
 //
 // K and V tiles of 64 keys go from global memory straight into swizzled LDS tiles (global_load_lds), four stages
-// each.  With one wave per SIMD nothing hides a latency except the wave's own instructions, so tiles entirely below
-// the diagonal of the wave's rows run a three-stage software pipeline over 32-key blocks, written out slot by slot:
+// each.  With one wave per SIMD nothing hides a latency except the wave's own instructions, so the tiles run a
+// three-stage software pipeline over 32-key blocks, written out slot by slot:
 //   step k:  score MFMAs of block k+1  |  exponentials of block k  |  P V MFMAs of block k-1
 // every MFMA being followed by its share of the other work (one exponential, a row-sum addition, half a conversion,
 // one LDS fragment read for a later MFMA).  The score MFMAs are inline assembly with architectural destination
 // registers (the vector ALU reads the scores directly) and the Q fragments in the accumulation file.  The pipeline
-// keeps the running maximum it was entered with (see there); diagonal tiles take a general path with masking and
-// lazy rescaling of the accumulators.  The softmax runs in base 2 with scale*log2(e) folded into one FMA.
+// keeps the running maximum it was entered with (see there) and masks on the diagonal; tile 0 of a document's first rows
+// and units in which that maximum was outgrown take a general path with lazy rescaling of the accumulators.  The
+// softmax runs in base 2 with scale*log2(e) folded into one FMA.
+//
+// At head_dim 64 a tile has half the MFMAs for the same exponentials: the kernel is bound by its vector work and, with
+// one wave per SIMD, by its latencies.  Its 254 registers and 64 KB of LDS let two workgroups share a CU there, so that
+// one computes while the other waits: 190 -> 139 us on 16K tokens of 2K-token documents (16/16 heads), 855 -> 765 us
+// on 32K tokens of lone 120-row shards with contexts of up to 16K (8/2 heads).
 #include <atomic>
 #include <type_traits>
 
@@ -43,7 +49,7 @@ struct FwdSmem {
 constexpr int FWD_WAVES = 4;  // waves per workgroup; each owns two groups of 32 slots
 
 template <int D>
-__global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit *__restrict__ units,
+__global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel(const FwdUnit *__restrict__ units,
                                                                    const int32_t *__restrict__ slot_row,
                                                                    const int32_t *__restrict__ slot_pos,
                                                                    const bf16_t *__restrict__ Q,
@@ -69,7 +75,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, r = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, dh = (lane >> 4) & 1;
-  const int hk = u.head / (Hq / Hkv);
+  const int hk = __builtin_amdgcn_readfirstlane(u.head / (Hq / Hkv));  // (uniform, for scalar K/V addresses)
   // (wave, group x) -> 32-slot group and query head inside the unit: pair 2 wave + x takes slots 32 (pair / hp) ..
   // of head  head + pair % hp  (hp = 1 for a full tile, > 1 for a head-packed unit)
   const int hp_lg = __builtin_ctz(u.hp);
@@ -84,8 +90,8 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
   }
   const int wmax = max(wave_max(pos[0]), wave_max(pos[1])), wmin = min(wave_min(pos[0]), wave_min(pos[1]));
   const int n_tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
-  // tiles j < n_fast: tile j and the first 32 keys of tile j+1 are entirely visible to every row of this wave
-  const int n_fast = max(0, (wmin - 31) / FWD_BN);
+  const int n_fast = (wmin + 1) / FWD_BN;   // tiles j < n_fast are entirely visible to every row of this wave
+  const int n_seen = wmax / FWD_BN + 1;     // tiles from here on are seen by none of its rows
 
   // ---- direct global -> LDS tile loads.  Load n of this wave covers tile rows RPI*(wave + 4n) .. +RPI-1;
   // lane i fills physical chunk i % CH of row i / CH, so it fetches logical chunk (i % CH) ^ sw(row).
@@ -116,11 +122,14 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
   // Issue order K0 V0 K1 V1 K2 | V2 K3 | V3 K4 | ...: K runs three tiles ahead of the tile being multiplied, V two
   // (the pipelined path multiplies P V one block behind the scores, so a V tile is still read while the next K tile
   // is already in use)
-  issue_kv(kg, S::K_OFF, 0);
-  issue_kv(vg, S::V_OFF, 0);
-  issue_kv(kg, S::K_OFF, 1);
-  issue_kv(vg, S::V_OFF, 1);
-  issue_kv(kg, S::K_OFF, 2);
+  auto issue_first = [&]() __attribute__((always_inline)) {
+    issue_kv(kg, S::K_OFF, 0);
+    issue_kv(vg, S::V_OFF, 0);
+    issue_kv(kg, S::K_OFF, 1);
+    issue_kv(vg, S::V_OFF, 1);
+    issue_kv(kg, S::K_OFF, 2);
+  };
+  issue_first();
 
   // Q fragments: B operand of S^T = K Q^T; lane holds Q[row][16 s + 8 g .. +7].  They live in accumulation registers
   // (read by MFMAs only).
@@ -202,9 +211,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
     m[x] = m_cand;
     lsum[x] *= alpha;
 #pragma unroll
-    for (int b = 0; b < NDB; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[x][b][i] *= alpha;
+    for (int b = 0; b < NDB; ++b) scale_acc(acc[x][b], alpha);
   };
   auto rescale = [&](int x, float mx) __attribute__((always_inline)) {
     const float m_cand = fmaxf(m[x], mx * c);
@@ -258,18 +265,76 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
     issue_kv(kg, S::K_OFF, j + 3);
   };
 
+  // ------------------------------------------------------------------------------------------ general path
+  // the first tile of a document's first rows (below) and, after an overflow, whole units: mask, row maximum, lazy
+  // rescaling, nothing interleaved
+  auto general_block = [&](int jt, int kb) __attribute__((always_inline)) {
+    const int k0 = jt * FWD_BN + 32 * kb;
+    if (k0 > wmax) return;
+    f32x16 x[2];
+    scores_plain(uint32_t(kb * BLK), x[0], x[1]);
+    uint32_t pw[2][8];
+#pragma unroll
+    for (int gx = 0; gx < 2; ++gx) {
+      if (k0 + 31 > wmin) {  // some (row, key) of this block may be above the diagonal
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (k0 + (i >> 2) * 8 + 4 * g + (i & 3) > pos[gx]) x[gx][i] = -INFINITY;
+      }
+      // a row that sees no key of this block keeps m = -inf only if it has seen none at all, which cannot happen:
+      // every row sees key 0, and blocks are walked from key 0 on
+      rescale(gx, row_max(x[gx]));
+      exp_pack(gx, x[gx], pw[gx]);
+    }
+    const uint32_t vb = uint32_t(kb * BLK);
+    pv_plain(vb, pw[0], pw[1], true, true);
+    // The first rows of a document see a handful of keys, their output is as large as a single V row, and
+    // the 2^-9 relative rounding of P to bf16 then shows up at the 1e-2 level next to the output's own bf16
+    // rounding.  For the waves that hold such rows, the rounding residue of P is fed through the matrix pipe
+    // as a second bf16 operand (P = hi + lo), which makes P V as good as fp32 at negligible cost: it
+    // happens only in the first tile of the first query rows of each document.
+    if (jt == 0 && wmin < FWD_BN) {
+      uint32_t pl[2][8];
+#pragma unroll
+      for (int gx = 0; gx < 2; ++gx)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const uint32_t h = pw[gx][e];
+          pl[gx][e] = pack_bf16(x[gx][2 * e] - __uint_as_float(h << 16), x[gx][2 * e + 1] - __uint_as_float(h & 0xffff0000u));
+        }
+      pv_plain(vb, pl[0], pl[1], true, true);
+    }
+  };
+
+  auto general_tile = [&](int jt) __attribute__((always_inline)) {
+    top(jt);
+    general_block(jt, 0);
+    general_block(jt, 1);
+    advance_k();
+    advance_v();
+  };
+
+  int j = 0;
+  if (wmin < FWD_BN) {  // rows that see less than a tile: hi + lo P on tile 0
+    general_tile(0);
+    j = 1;
+  }
   // ------------------------------------------------------------------------------------------ pipelined path
-  // Tiles j < n_fast.  The pipeline exponentiates against the running maximum m as it stood when it was entered (the
-  // maximum of the first block): the loop holds no rescaling code, no row maximum and no exit (an exit alone costs the
+  // All other tiles the wave sees: without a mask as long as every row sees the whole tile (j < n_fast), with a mask up
+  // to its last one.  The diagonal used to take the general path, where nothing overlaps: 4.4 us per 64-key tile of a
+  // wave that the other waves of the workgroup waited for at the next tile's barrier, against 1.7 us here; masked
+  // pipelining took the kernel from 2.79 to 2.58 ms on 64K tokens of documents of a median of 2K tokens (32/8 heads,
+  // head_dim 128) and from 119 to 109 us on 4K tokens of 1K-token documents.
+  // The pipeline exponentiates against the running maximum m as it stood when it was entered (the maximum of the first
+  // block, or of tile 0): the loops hold no rescaling code, no row maximum and no exit (an exit alone costs the
   // register allocation of the loop dearly).  Probabilities relative to a stale m are merely larger numbers - bf16 and
   // fp32 carry the same exponent range, so neither P nor the accumulators lose accuracy - until one of them overflows;
   // that shows in the row sum.  If the row sum of any row of a workgroup has left the finite range, everything computed
   // here is thrown away and the unit is computed again by the general path alone (below), which rescales block by
-  // block.  A later score would have to exceed the first block's maximum by about 2^100 in probability for that (the row sum is
+  // block.  A later score would have to exceed that maximum by about 2^100 in probability for that (the row sum is
   // checked against 1e30, which leaves the accumulators, |V| times larger at most, well inside fp32).
-  int j = 0;
   bool outgrown = false;
-  if (n_fast > 0) {
+  if (j < n_seen) {
     // tuples: sc[k & 1][x] holds S(k) of group x, then its exponentials; packed P(k) goes to pp[k & 1][x]
     f32x16 sc[2][2];
     uint32_t pp[2][2][8];
@@ -280,11 +345,15 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
     // koff's stage, of the keys of S(k+1) (the second half of their fragments is fetched here) and of S(k+2) (the
     // first half, for the next step); vb: block offset of block k-1 in voff's stage.  PV = false leaves block k-1
     // out (first step).  NEXT_TILE: S(k+2) belongs to the tile after S(k+1)'s: koff moves on between the two phases.
+    // MASK: keys beyond a row's position get probability 0 (key0: position of block k's first key).
     auto step = [&](f32x16 (&E)[2], f32x16 (&N)[2], uint32_t (&PE)[2][8], const uint32_t (&PP)[2][8], uint32_t kn,
-                    uint32_t kb, uint32_t vb, const bool PV, const bool NEXT_TILE) __attribute__((always_inline)) {
+                    uint32_t kb, uint32_t vb, const bool PV, const bool NEXT_TILE, const bool MASK, int key0)
+                    __attribute__((always_inline)) {
       constexpr int TS = 2 * NS, TP = 4 * NDB, T = TS + TP;  // MFMA slots: score phase, P V phase
       constexpr int EPS = 32 / T;                            // exponentials per slot
       constexpr int H = NS / 2;
+      // register i holds key key0 + 4 g + 8 (i / 4) + i % 4: visible iff 8 (i / 4) + i % 4 <= vis
+      const int vis[2] = {pos[0] - key0 - 4 * g, pos[1] - key0 - 4 * g};
       float pend[2] = {0.f, 0.f};  // exponential of the previous slot, added to the row sum one slot later
       int pend_x = 0;
       // the vector work of slot q: exponential(s) e = q EPS .. of (group e / 16, register e % 16) with the row-sum
@@ -294,6 +363,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
         for (int e = q * EPS; e < (q + 1) * EPS; ++e) {
           const int x = e >> 4, i = e & 15;
           float v = E[x][i];
+          if (MASK) v = (i >> 2) * 8 + (i & 3) <= vis[x] ? v : -INFINITY;
           if (e == 0) exp2_fma_inplace_pinned(v, c, m[x]);
           else exp2_fma_add_inplace_pinned(v, c, m[x], lsum[pend_x], pend[(e - 1) & 1]);
           E[x][i] = v;
@@ -341,74 +411,39 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
       PE[1][7] = pack_bf16_pinned(E[1][14], E[1][15]);
     };
 
-    // prologue: S(0) and its maximum, which becomes m; first K fragments of block 1
+    // prologue: scores of the first tile's first block; on tile 0, which then every row sees, their maximum becomes m.
+    // First K fragments of the second block.  The first tile is always taken with the mask (one instance of these two
+    // steps instead of two; on a whole tile the mask changes nothing).
     scores_plain(0u, sc[0][0], sc[0][1]);
-    m[0] = row_max(sc[0][0]) * c;
-    m[1] = row_max(sc[0][1]) * c;
+    if (j == 0) {
+      m[0] = row_max(sc[0][0]) * c;
+      m[1] = row_max(sc[0][1]) * c;
+    }
 #pragma unroll
     for (int s = 0; s < NS / 2; ++s) ka[s] = lds_read8_at(koff[s] + uint32_t(BLK));
-    top(0);  // tile 1 of K has landed: blocks 2 and 3
-    step(sc[0], sc[1], pp[0], pp[1], uint32_t(BLK), 0u, uint32_t(BLK), false, true);  // S(1) | exp(0)
-    step(sc[1], sc[0], pp[1], pp[0], 0u, uint32_t(BLK), 0u, true, false);             // S(2) | exp(1) | P V(0)
-    for (j = 1; j < n_fast; ++j) {
+    top(j);  // the next tile of K has landed
+    step(sc[0], sc[1], pp[0], pp[1], uint32_t(BLK), 0u, uint32_t(BLK), false, true, true, FWD_BN * j);  // S(1) | exp(0)
+    step(sc[1], sc[0], pp[1], pp[0], 0u, uint32_t(BLK), 0u, true, false, true, FWD_BN * j + 32);       // S(2) | exp(1) | P V(0)
+    ++j;
+    for (; j < n_fast; ++j) {
       top(j);
-      step(sc[0], sc[1], pp[0], pp[1], uint32_t(BLK), 0u, uint32_t(BLK), true, true);  // S(2j+1) | exp(2j) | P V(2j-1)
-      advance_v();                                                                     // voff addresses tile j
-      step(sc[1], sc[0], pp[1], pp[0], 0u, uint32_t(BLK), 0u, true, false);            // S(2j+2) | exp(2j+1) | P V(2j)
+      step(sc[0], sc[1], pp[0], pp[1], uint32_t(BLK), 0u, uint32_t(BLK), true, true, false, 0);  // S(2j+1) | exp(2j) | P V(2j-1)
+      advance_v();                                                                               // voff addresses tile j
+      step(sc[1], sc[0], pp[1], pp[0], 0u, uint32_t(BLK), 0u, true, false, false, 0);            // S(2j+2) | exp(2j+1) | P V(2j)
     }
-    // drain: block 2 n_fast - 1 is exponentiated but not multiplied in (voff addresses its tile); the scores computed
-    // ahead, S(2 n_fast), are dropped: the general path computes them again, with its mask
+    for (; j < n_seen; ++j) {  // the same with the mask: the diagonal
+      top(j);
+      step(sc[0], sc[1], pp[0], pp[1], uint32_t(BLK), 0u, uint32_t(BLK), true, true, true, FWD_BN * j);
+      advance_v();
+      step(sc[1], sc[0], pp[1], pp[0], 0u, uint32_t(BLK), 0u, true, false, true, FWD_BN * j + 32);
+    }
+    // drain: the last block is exponentiated but not multiplied in (voff addresses its tile); the scores computed
+    // ahead, of a tile the wave does not see, are dropped
     pv_plain(uint32_t(BLK), pp[1][0], pp[1][1], true, true);
     advance_v();
     outgrown = __any(!(lsum[0] < 1.0e30f) || !(lsum[1] < 1.0e30f));  // also true for NaN
   }
-
-  // ------------------------------------------------------------------------------------------ general path
-  // diagonal tiles (mask), tiles some rows do not see at all, the first tile of a document
-  auto tail_block = [&](int jt, int kb) __attribute__((always_inline)) {
-    const int k0 = jt * FWD_BN + 32 * kb;
-    if (k0 > wmax) return;
-    f32x16 x[2];
-    scores_plain(uint32_t(kb * BLK), x[0], x[1]);
-    uint32_t pw[2][8];
-#pragma unroll
-    for (int gx = 0; gx < 2; ++gx) {
-      if (k0 + 31 > wmin) {  // some (row, key) of this block may be above the diagonal
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (k0 + (i >> 2) * 8 + 4 * g + (i & 3) > pos[gx]) x[gx][i] = -INFINITY;
-      }
-      // a row that sees no key of this block keeps m = -inf only if it has seen none at all, which cannot happen:
-      // every row sees key 0, and blocks are walked from key 0 on
-      rescale(gx, row_max(x[gx]));
-      exp_pack(gx, x[gx], pw[gx]);
-    }
-    const uint32_t vb = uint32_t(kb * BLK);
-    pv_plain(vb, pw[0], pw[1], true, true);
-    // The first rows of a document see a handful of keys, their output is as large as a single V row, and
-    // the 2^-9 relative rounding of P to bf16 then shows up at the 1e-2 level next to the output's own bf16
-    // rounding.  For the waves that hold such rows, the rounding residue of P is fed through the matrix pipe
-    // as a second bf16 operand (P = hi + lo), which makes P V as good as fp32 at negligible cost: it
-    // happens only in the first tile of the first query rows of each document.
-    if (jt == 0 && wmin < FWD_BN) {
-      uint32_t pl[2][8];
-#pragma unroll
-      for (int gx = 0; gx < 2; ++gx)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t h = pw[gx][e];
-          pl[gx][e] = pack_bf16(x[gx][2 * e] - __uint_as_float(h << 16), x[gx][2 * e + 1] - __uint_as_float(h & 0xffff0000u));
-        }
-      pv_plain(vb, pl[0], pl[1], true, true);
-    }
-  };
-  for (; j < n_tiles; ++j) {
-    top(j);
-    tail_block(j, 0);
-    tail_block(j, 1);
-    advance_k();
-    advance_v();
-  }
+  for (; j < n_tiles; ++j) top(j);  // tiles only other waves see: this wave's part of the loads
   wait_vmcnt<0>();  // nothing may still be writing LDS
   // Did the pipelined path of any wave of the workgroup meet a maximum beyond its window?  (The tiles are shared, so
   // the workgroup repeats the unit together or not at all.)  Flags go through the first bytes of LDS: every tile read
@@ -431,20 +466,10 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void ca_fwd_kernel(const FwdUnit
     }
     while (kst != 0) advance_k();
     while (vst != 0) advance_v();
-    issue_kv(kg, S::K_OFF, 0);
-    issue_kv(vg, S::V_OFF, 0);
-    issue_kv(kg, S::K_OFF, 1);
-    issue_kv(vg, S::V_OFF, 1);
-    issue_kv(kg, S::K_OFF, 2);
+    issue_first();
     wait_vmcnt<0>();
     barrier_nofence();
-    for (j = 0; j < n_tiles; ++j) {
-      top(j);
-      tail_block(j, 0);
-      tail_block(j, 1);
-      advance_k();
-      advance_v();
-    }
+    for (j = 0; j < n_tiles; ++j) general_tile(j);
     wait_vmcnt<0>();
     __syncthreads();  // the epilogue writes into the stages
   }
