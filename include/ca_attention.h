@@ -99,9 +99,20 @@ int ca_plan(const ca_batch_desc *desc, ca_plan_t **out);
 int ca_plan_workspace_bytes(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bwd_bytes);
 
 /*
+ * ca_plan_workspace_bytes_split: workspace with which the calls also cut long work units into pieces.  A batch with few
+ * long units (a lone shard with a long context, a small batch) leaves most of the GPU idle; given this much workspace
+ * ca_forward and ca_backward run such units as several workgroups, whose fp32 partial results (at most 256 MiB more than
+ * ca_plan_workspace_bytes, and never beyond CA_STATIC_WS_BYTES where that holds the batch otherwise) are added up by one
+ * more launch, in a fixed order.  With less, but at least ca_plan_workspace_bytes, the calls compute the same with whole
+ * units; the two differ in the order of fp32 sums.  Equal to ca_plan_workspace_bytes where nothing is cut.
+ */
+int ca_plan_workspace_bytes_split(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bwd_bytes);
+
+/*
  * ca_forward: O and LSE for every query row of every task, one fused launch on `hip_stream`.
  * q,k,v: device bf16 inputs; o: device bf16 output; lse: device fp32 output [n_q_heads][total_q].
- * ws: device workspace of at least fwd_bytes (may be NULL when fwd_bytes is 0), 256-byte aligned.
+ * ws: device workspace of at least fwd_bytes (may be NULL when fwd_bytes is 0), 256-byte aligned; used, if it is given, for
+ * partial results when it has the size ca_plan_workspace_bytes_split states.
  * Allocates nothing, never synchronises.
  */
 int ca_forward(const ca_plan_t *plan, const void *q, const void *k, const void *v, void *o, float *lse,
@@ -258,6 +269,17 @@ int ca_plan_info(const ca_plan_t *plan, int64_t *out, int n);
 int64_t ca_plan_rows(const ca_plan_t *plan, int32_t *rows, int32_t *pos);
 int64_t ca_plan_fwd_units(const ca_plan_t *plan, int32_t *units);
 int64_t ca_plan_bwd_units(const ca_plan_t *plan, int32_t *units);
+/* The lists the calls run when they cut units into pieces (ca_plan_workspace_bytes_split); empty where nothing is cut.
+ *  fwd_pieces : [n][8]  = the 5 fields above (kv row and keys of the piece's window), document position of the window's
+ *                         first key, block of partial results (-1: a whole unit), 0
+ *  bwd_pieces : [n][10] = the 10 fields above (slots of the piece's query blocks; follow = -1 - block of partial results,
+ *                         not negative in a whole unit); *n_workgroups (may be NULL): leading units that are one
+ *                         workgroup each
+ *  combine    : [n][6]  = {first block, blocks, first slot, first head, heads per unit, 0} of a cut forward / dQ unit, or
+ *                         with `backward` {first block, blocks, packed KV row of the first key, valid keys, KV head, 0} */
+int64_t ca_plan_fwd_pieces(const ca_plan_t *plan, int32_t *units);
+int64_t ca_plan_bwd_pieces(const ca_plan_t *plan, int32_t *units, int32_t *n_workgroups);
+int64_t ca_plan_combine_units(const ca_plan_t *plan, int32_t backward, int32_t *units);
 
 #ifdef __cplusplus
 }

@@ -17,7 +17,11 @@ class _CoreAttention(torch.autograd.Function):
         b = server.plan.batch
         o = torch.empty_like(q)
         lse = torch.empty((b.n_q_heads, b.total_q), dtype=torch.float32, device=q.device)
-        B.ca_forward(server.plan, q, k, v, o, lse, server.ws)
+        # partial results of the forward have memory of the call's own: forwards of one server may overlap in time (other
+        # streams, or another call's backward, which uses the server's workspace)
+        n = server.fwd_ws_bytes
+        ws = torch.empty(n, dtype=torch.uint8, device=q.device) if n else None
+        B.ca_forward(server.plan, q, k, v, o, lse, ws)
         ctx.save_for_backward(q, k, v, o, lse)
         ctx.server = server
         return o
@@ -44,6 +48,7 @@ class AttentionServer:
     def __init__(self, batch, device="cuda"):
         self.plan = B.ca_plan(batch)
         self.ws = B.alloc_workspace(self.plan, device)
+        self.fwd_ws_bytes = self.plan.workspace_bytes_split()[0]
 
     def __call__(self, q, k, v):
         return _CoreAttention.apply(q, k, v, self)

@@ -54,6 +54,7 @@ def lib() -> ctypes.CDLL:
         L.ca_plan.argtypes = [ctypes.POINTER(BatchDesc), ctypes.POINTER(vp)]
         L.ca_plan_upload.argtypes = [vp, vp]
         L.ca_plan_workspace_bytes.argtypes = [vp, ctypes.POINTER(sz), ctypes.POINTER(sz)]
+        L.ca_plan_workspace_bytes_split.argtypes = [vp, ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.ca_forward.argtypes = [vp] * 6 + [vp, sz, vp]
         L.ca_backward.argtypes = [vp] * 10 + [vp, sz, vp]
         L.ca_backward_static_ws.argtypes = [vp] * 10 + [vp]
@@ -66,8 +67,12 @@ def lib() -> ctypes.CDLL:
         L.ca_profile_enable.argtypes = [vp, ctypes.c_int]
         L.ca_profile_read.argtypes = [vp, vp]
         L.ca_plan_info.argtypes = [vp, vp, ctypes.c_int]
-        for f in (L.ca_plan_rows, L.ca_plan_fwd_units, L.ca_plan_bwd_units):
+        for f in (L.ca_plan_rows, L.ca_plan_fwd_units, L.ca_plan_bwd_units, L.ca_plan_fwd_pieces, L.ca_plan_bwd_pieces,
+                  L.ca_plan_combine_units):
             f.restype = ctypes.c_int64
+        L.ca_plan_fwd_pieces.argtypes = [vp, vp]
+        L.ca_plan_bwd_pieces.argtypes = [vp, vp, vp]
+        L.ca_plan_combine_units.argtypes = [vp, ctypes.c_int32, vp]
         L.ca_plan_rows.argtypes = [vp, vp, vp]
         L.ca_plan_fwd_units.argtypes = [vp, vp]
         L.ca_plan_bwd_units.argtypes = [vp, vp]
@@ -127,6 +132,12 @@ class Plan:
         _check(lib().ca_plan_workspace_bytes(self.handle, ctypes.byref(f), ctypes.byref(b)))
         return int(f.value), int(b.value)
 
+    def workspace_bytes_split(self):
+        """Workspace (forward, backward) with which the calls also cut long units into pieces."""
+        f, b = ctypes.c_size_t(), ctypes.c_size_t()
+        _check(lib().ca_plan_workspace_bytes_split(self.handle, ctypes.byref(f), ctypes.byref(b)))
+        return int(f.value), int(b.value)
+
     def info(self) -> dict:
         out = np.zeros(len(self.INFO_KEYS), np.int64)
         lib().ca_plan_info(self.handle, out.ctypes.data, len(out))
@@ -149,6 +160,19 @@ class Plan:
         u = np.zeros((n, 10), np.int32)
         lib().ca_plan_bwd_units(self.handle, u.ctypes.data)
         return u
+
+    def pieces(self) -> dict:
+        """The lists of units cut into pieces (arrays as in the header; empty where nothing is cut)."""
+        L, n_wg = lib(), ctypes.c_int32()
+        fwd = np.zeros((L.ca_plan_fwd_pieces(self.handle, None), 8), np.int32)
+        L.ca_plan_fwd_pieces(self.handle, fwd.ctypes.data)
+        bwd = np.zeros((L.ca_plan_bwd_pieces(self.handle, None, None), 10), np.int32)
+        L.ca_plan_bwd_pieces(self.handle, bwd.ctypes.data, ctypes.byref(n_wg))
+        out = {"fwd": fwd, "bwd": bwd, "bwd_workgroups": n_wg.value}
+        for key, backward in (("fwd_combine", 0), ("bwd_combine", 1)):
+            out[key] = np.zeros((L.ca_plan_combine_units(self.handle, backward, None), 6), np.int32)
+            L.ca_plan_combine_units(self.handle, backward, out[key].ctypes.data)
+        return out
 
     def profile_enable(self, on=True):
         _check(lib().ca_profile_enable(self.handle, 1 if on else 0))
@@ -249,9 +273,10 @@ def ca_backward_static_ws(plan: Plan, q, k, v, o, d_o, lse, dq, dk, dv, stream=N
 
 
 def alloc_workspace(plan: Plan, device="cuda"):
-    """A torch uint8 buffer big enough for both calls (torch's allocator returns 256-byte aligned blocks)."""
+    """A torch uint8 buffer big enough for both calls, with room for the partial results of units cut into pieces
+    (torch's allocator returns 256-byte aligned blocks)."""
     import torch
-    f, b = plan.workspace_bytes()
+    f, b = plan.workspace_bytes_split()
     return torch.empty(max(f, b, 256), dtype=torch.uint8, device=device)
 
 

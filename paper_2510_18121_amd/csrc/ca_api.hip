@@ -1,16 +1,21 @@
 // C-ABI entry points that touch the device: plan upload, forward and backward launches.
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <mutex>
+#include <new>
 #include <sstream>
+#include <type_traits>
 
 #include "ca_internal.h"
 
 namespace ca {
-hipError_t launch_fwd(const ca_plan_t *p, const void *q, const void *k, const void *v, void *o, float *lse,
+// parts / split: (there is) device memory for the partial results of the piece lists; otherwise the whole units are run
+hipError_t launch_fwd(const ca_plan_t *p, const void *q, const void *k, const void *v, void *o, float *lse, void *parts,
                       hipStream_t st);
 hipError_t launch_bwd(const ca_plan_t *p, const void *q, const void *k, const void *v, const void *o, const void *d_o,
-                      const float *lse, void *dq, void *dk, void *dv, void *ws, hipStream_t st, hipEvent_t *ev);
+                      const float *lse, void *dq, void *dk, void *dv, void *ws, bool split, hipStream_t st,
+                      hipEvent_t *ev);
 
 static int hip_fail(const char *what, hipError_t e) {
   std::ostringstream os;
@@ -55,16 +60,12 @@ static void free_device(ca_plan_t *p) {
   if (p->device < 0) return;
   int cur = -1;
   if (hipGetDevice(&cur) == hipSuccess && cur != p->device) (void)hipSetDevice(p->device);
-  if (p->d_slot_row) (void)hipFree(p->d_slot_row);
-  if (p->d_slot_pos) (void)hipFree(p->d_slot_pos);
-  if (p->d_block_rpk) (void)hipFree(p->d_block_rpk);
-  if (p->d_pos_kv) (void)hipFree(p->d_pos_kv);
-  p->d_block_rpk = p->d_pos_kv = nullptr;
-  if (p->d_fwd_units) (void)hipFree(p->d_fwd_units);
-  if (p->d_bwd_units) (void)hipFree(p->d_bwd_units);
-  p->d_slot_row = p->d_slot_pos = nullptr;
-  p->d_fwd_units = nullptr;
-  p->d_bwd_units = nullptr;
+  if (p->d_blob) (void)hipFree(p->d_blob);
+  p->d_blob = nullptr;
+  p->d_slot_row = p->d_slot_pos = p->d_block_rpk = p->d_pos_kv = nullptr;
+  p->d_fwd_units = p->d_fwd_pieces = nullptr;
+  p->d_bwd_units = p->d_bwd_pieces = nullptr;
+  p->d_fwd_combine = p->d_bwd_combine = nullptr;
   if (cur >= 0 && cur != p->device) (void)hipSetDevice(cur);
   p->device = -1;
 }
@@ -114,21 +115,45 @@ int ca_plan_upload(ca_plan_t *p, void *hip_stream) {
   int dev = -1;
   CA_HIP(hipGetDevice(&dev));
   p->device = dev;
-  auto up = [&](auto *&dst, const auto &src) -> hipError_t {
-    if (src.empty()) return hipSuccess;
-    const size_t bytes = src.size() * sizeof(src[0]);
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(&dst), bytes);
-    if (e != hipSuccess) return e;
-    return hipMemcpyAsync(dst, src.data(), bytes, hipMemcpyHostToDevice, st);
+  // all arrays in one block: one allocation, one copy
+  size_t bytes = 0;
+  auto place = [&](const auto &src) {
+    const size_t at = bytes;
+    bytes = (bytes + src.size() * sizeof(src[0]) + 255) / 256 * 256;
+    return at;
   };
-  hipError_t e;
-  if ((e = up(p->d_slot_row, p->slot_row)) != hipSuccess || (e = up(p->d_slot_pos, p->slot_pos)) != hipSuccess ||
-      (e = up(p->d_block_rpk, p->block_rpk)) != hipSuccess || (e = up(p->d_pos_kv, p->pos_kv)) != hipSuccess ||
-      (e = up(p->d_fwd_units, p->fwd_units)) != hipSuccess || (e = up(p->d_bwd_units, p->bwd_units)) != hipSuccess) {
+  const size_t at[10] = {place(p->slot_row),    place(p->slot_pos),   place(p->block_rpk),   place(p->pos_kv),
+                         place(p->fwd_units),   place(p->bwd_units),  place(p->fwd_pieces),  place(p->bwd_pieces),
+                         place(p->fwd_combine), place(p->bwd_combine)};
+  if (bytes == 0) return CA_OK;
+  try {
+    p->blob.assign(bytes, 0);
+  } catch (const std::bad_alloc &) {
+    free_device(p);
+    set_error("out of host memory while uploading the plan");
+    return CA_ERR_INVALID_ARG;
+  }
+  hipError_t e = hipMalloc(&p->d_blob, bytes);
+  if (e != hipSuccess) {
+    p->d_blob = nullptr;
     free_device(p);
     return hip_fail("plan upload", e);
   }
-  // the host vectors stay alive in the plan, so the asynchronous copies read valid memory
+  auto put = [&](const auto &src, auto *&dst, size_t off) {
+    using T = std::remove_reference_t<decltype(dst)>;
+    dst = reinterpret_cast<T>(static_cast<char *>(p->d_blob) + off);
+    if (!src.empty()) std::memcpy(p->blob.data() + off, src.data(), src.size() * sizeof(src[0]));
+  };
+  put(p->slot_row, p->d_slot_row, at[0]), put(p->slot_pos, p->d_slot_pos, at[1]);
+  put(p->block_rpk, p->d_block_rpk, at[2]), put(p->pos_kv, p->d_pos_kv, at[3]);
+  put(p->fwd_units, p->d_fwd_units, at[4]), put(p->bwd_units, p->d_bwd_units, at[5]);
+  put(p->fwd_pieces, p->d_fwd_pieces, at[6]), put(p->bwd_pieces, p->d_bwd_pieces, at[7]);
+  put(p->fwd_combine, p->d_fwd_combine, at[8]), put(p->bwd_combine, p->d_bwd_combine, at[9]);
+  if ((e = hipMemcpyAsync(p->d_blob, p->blob.data(), bytes, hipMemcpyHostToDevice, st)) != hipSuccess) {
+    free_device(p);
+    return hip_fail("plan upload", e);
+  }
+  // the host copy stays alive in the plan, so the asynchronous copy reads valid memory
   return CA_OK;
 }
 
@@ -221,7 +246,9 @@ int ca_forward(const ca_plan_t *p, const void *q, const void *k, const void *v, 
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   ca_plan_t *mp = const_cast<ca_plan_t *>(p);  // timing state only
   if (p->profile) (void)hipEventRecord(static_cast<hipEvent_t>(mp->ev[0]), st);
-  hipError_t e = launch_fwd(p, q, k, v, o, lse, st);
+  // with room for partial results (and only then) long units are cut into pieces
+  const bool split = p->ws_fwd_split > 0 && ws && ws_bytes >= p->ws_fwd_split && reinterpret_cast<uintptr_t>(ws) % 256 == 0;
+  hipError_t e = launch_fwd(p, q, k, v, o, lse, split ? ws : nullptr, st);
   if (e != hipSuccess) return hip_fail("forward launch", e);
   if (p->profile) {
     (void)hipEventRecord(static_cast<hipEvent_t>(mp->ev[1]), st);
@@ -244,7 +271,8 @@ int ca_backward(const ca_plan_t *p, const void *q, const void *k, const void *v,
     return CA_ERR_INVALID_ARG;
   }
   ca_plan_t *mp = const_cast<ca_plan_t *>(p);  // timing state only
-  hipError_t e = launch_bwd(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, static_cast<hipStream_t>(hip_stream),
+  const bool split = p->ws_bwd_split > p->ws_bwd && ws_bytes >= p->ws_bwd_split;
+  hipError_t e = launch_bwd(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, static_cast<hipStream_t>(hip_stream),
                             p->profile ? reinterpret_cast<hipEvent_t *>(&mp->ev[2]) : nullptr);
   if (e != hipSuccess) return hip_fail("backward launch", e);
   if (p->profile) mp->ev_bwd = true;

@@ -118,8 +118,8 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
                                                            const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
                                                            const float *__restrict__ l2_slot,
                                                            const float *__restrict__ delta_slot,
-                                                           bf16_t *__restrict__ dQ, int Hq, int Hkv, int64_t padded,
-                                                           float scale) {
+                                                           bf16_t *__restrict__ dQ, float *__restrict__ parts, int Hq,
+                                                           int Hkv, int64_t padded, float scale) {
   using S = DqSmem<D>;
   constexpr int NS = D / 16, NDB = D / 32, CH = D / 8, RPI = 64 / CH, NLD = FWD_BN / (8 * RPI), NST = S::NST;
   constexpr int ROWB = 2 * D;
@@ -130,13 +130,13 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, r = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, dh = (lane >> 4) & 1;
-  const int hk = u.head / (Hq / Hkv);
+  const int hk = __builtin_amdgcn_readfirstlane(u.head / (Hq / Hkv));  // (uniform, for scalar K/V addresses)
   // wave -> (32-slot group, query head) inside the unit, as in the forward kernel
   const int hp_lg = __builtin_ctz(u.hp);
   const int head = u.head + (wave & (u.hp - 1));
   const int slot = u.slot0 + (wave >> hp_lg) * 32 + r;
   const int row = slot_row[slot];
-  const int pos = slot_pos[slot];
+  const int pos = slot_pos[slot] - u.key0;  // counted from the first key of a piece's window (below 0: sees none of it)
   float l2 = l2_slot[int64_t(head) * padded + slot];
   float dl = delta_slot[int64_t(head) * padded + slot];
   const int wmax = wave_max(pos), wmin = wave_min(pos);
@@ -276,6 +276,16 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
     }
   }
   wait_vmcnt<0>();
+  if (u.part >= 0) {  // a piece: the accumulators as they stand
+    float *dst = parts + size_t(u.part) * (FWD_BM * D) + wave * (32 * D) + 4 * lane;
+#pragma unroll
+    for (int b = 0; b < NDB; ++b)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *reinterpret_cast<f32x4 *>(dst + (4 * b + q4) * 256) =
+            f32x4{acc[b][4 * q4], acc[b][4 * q4 + 1], acc[b][4 * q4 + 2], acc[b][4 * q4 + 3]};
+    return;
+  }
   // dQ of the wave's 32 rows, as whole lines through a patch of LDS (the stages are free once every wave is past its
   // last tile)
   __syncthreads();
@@ -311,8 +321,8 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
                                               const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
                                               const bf16_t *__restrict__ dOs, const float *__restrict__ l2_slot,
                                               const float *__restrict__ delta_slot, bf16_t *__restrict__ dK,
-                                              bf16_t *__restrict__ dV, int32_t *progress, int peer_stride, int Hq,
-                                              int Hkv, int64_t padded, float scale) {
+                                              bf16_t *__restrict__ dV, float *__restrict__ parts, int32_t *progress,
+                                              int peer_stride, int Hq, int Hkv, int64_t padded, float scale) {
   using S = DkvSmem<D>;
   constexpr int NS = D / 16, NDB = D / 32, CH = D / 8, RPI = 64 / CH, NST = S::NST;
   constexpr int NLD = BWD_BQ / (4 * RPI);  // direct loads per wave per Q (or dO) tile
@@ -848,7 +858,19 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   // store_tile_as_lines (stored straight from the accumulator layout, the 64 instructions per wave kept the CU's
   // address unit busy for longer than a short unit's steps take).  Written out here, with the addresses formed after
   // the LDS reads they wait for: the helper's order costs a chained unit a few tenths of a microsecond more.
-  {
+  if (!CHAIN && follow < 0) {  // a piece of a unit's query blocks: the accumulators as they stand
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      float *dst = parts + size_t(-1 - follow) * (FWD_BM * D) + (2 * wave + t) * (32 * D) + 4 * lane;
+#pragma unroll
+      for (int b = 0; b < NDB; ++b)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const f32x16 &a = t == 0 ? acc_dk[b] : acc_dv[b];
+          *reinterpret_cast<f32x4 *>(dst + (4 * b + q4) * 256) = f32x4{a[4 * q4], a[4 * q4 + 1], a[4 * q4 + 2], a[4 * q4 + 3]};
+        }
+    }
+  } else {
     const uint32_t patch = lds0 + S::OUT_OFF + wave * PATCH_BYTES;
     const uint32_t wr = patch + r * PATCH_ROW_BYTES + 8 * g;  // + 64 (b & 1) + 16 q4: values 32 b + 8 q4 + 4 g .. + 3
     const int orow = lane >> 3, ocol = lane & 7;          // the lane's row (+ 8 i) and 16-byte piece of the patch
@@ -893,16 +915,52 @@ __global__ __launch_bounds__(256, 1) void ca_bwd_dkv_kernel(const BwdUnit *__res
                                                             const float *__restrict__ l2_slot,
                                                             const float *__restrict__ delta_slot,
                                                             bf16_t *__restrict__ dK, bf16_t *__restrict__ dV,
-                                                            int32_t *progress, int peer_stride, int Hq, int Hkv,
-                                                            int64_t padded, float scale) {
+                                                            float *__restrict__ parts, int32_t *progress,
+                                                            int peer_stride, int Hq, int Hkv, int64_t padded,
+                                                            float scale) {
   const int me = int(blockIdx.x);  // index of the workgroup = index of its first unit
   const BwdUnit first = units[me];
   if (first.count <= 1)
-    dkv_workgroup<D, false>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, progress,
-                            peer_stride, Hq, Hkv, padded, scale);
+    dkv_workgroup<D, false>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
+                            progress, peer_stride, Hq, Hkv, padded, scale);
   else
-    dkv_workgroup<D, true>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, progress,
-                           peer_stride, Hq, Hkv, padded, scale);
+    dkv_workgroup<D, true>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
+                           progress, peer_stride, Hq, Hkv, padded, scale);
+}
+
+// Adds up the pieces of the cut units: dQ of the forward / dQ units (from parts_dq; 8 groups of 32 rows), then dK and dV of
+// the dK/dV units (from parts_kv; 4 groups of 32 keys, two tensors).  One workgroup per (unit, group, 64 columns); see
+// combine_parts.
+template <int D>
+__global__ __launch_bounds__(256) void ca_combine_bwd_kernel(const CombineUnit *__restrict__ units_dq, int n_dq,
+                                                             const CombineUnit *__restrict__ units_kv,
+                                                             const int32_t *__restrict__ slot_row,
+                                                             const float *__restrict__ parts_dq,
+                                                             const float *__restrict__ parts_kv,
+                                                             bf16_t *__restrict__ dQ, bf16_t *__restrict__ dK,
+                                                             bf16_t *__restrict__ dV, int Hq, int Hkv, float scale) {
+  constexpr int NH = D / 64;  // 64-column halves
+  __shared__ __attribute__((aligned(16))) float lds[COMBINE_LDS];
+  __shared__ float ml[4][64][2];
+  const int un = blockIdx.x / (8 * NH), h = blockIdx.x % NH, pair = (blockIdx.x / NH) % 8;
+  const bool kv = un >= n_dq;
+  const CombineUnit u = kv ? units_kv[un - n_dq] : units_dq[un];
+  const float *src = (kv ? parts_kv : parts_dq) + size_t(u.part0) * (FWD_BM * D) + pair * (32 * D) + h * (8 * 256);
+  const int row = threadIdx.x >> 3;  // the row of the tile this lane stores
+  bf16_t *dst;
+  float f = scale;
+  if (kv) {  // pair: (32 keys, dK or dV)
+    const int key = 32 * (pair >> 1) + row;
+    if (pair & 1) f = 1.f;
+    dst = key < u.b ? ((pair & 1) ? dV : dK) + (size_t(u.a + key) * Hkv + u.c) * D + 64 * h : nullptr;
+  } else {
+    const int head = u.b + (pair & (u.c - 1));
+    const int rw = slot_row[u.a + (pair >> __builtin_ctz(u.c)) * 32 + row];
+    dst = rw >= 0 ? dQ + (size_t(rw) * Hq + head) * D + 64 * h : nullptr;
+  }
+  float m, l;
+  combine_parts<false>(src, FWD_BM * D, nullptr, 0, u.n_parts, f, lds, ml, m, l,
+                       [&](int) __attribute__((always_inline)) { return dst; });
 }
 
 static void launch_fill(void *p, size_t bytes, hipStream_t st) {
@@ -927,7 +985,7 @@ static hipError_t set_smem(F kern, int bytes, int device, std::atomic<bool> *don
 template <int D>
 static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k, const void *v, const void *o,
                                const void *d_o, const float *lse, void *dq, void *dk, void *dv, void *ws,
-                               hipStream_t st, hipEvent_t *ev) {
+                               bool split, hipStream_t st, hipEvent_t *ev) {
   if (ev) (void)hipEventRecord(ev[0], st);
   const size_t q_elems = size_t(p->total_q) * p->hq * D, kv_elems = size_t(p->total_kv) * p->hkv * D;
   const int64_t padded = int64_t(p->slot_row.size());
@@ -938,6 +996,19 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
   bf16_t *q_sorted = reinterpret_cast<bf16_t *>(static_cast<char *>(ws) + p->ws_off_qs);
   bf16_t *do_sorted = reinterpret_cast<bf16_t *>(static_cast<char *>(ws) + p->ws_off_dos);
   int32_t *progress = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + p->ws_off_prog);
+  // partial results of cut units, where the caller's workspace has room for them
+  float *const parts_kv = split && p->n_bwd_parts > 0 ? reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_parts_kv) : nullptr;
+  float *const parts_dq = split && p->n_fwd_parts > 0 ? reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_parts_dq) : nullptr;
+  const int32_t n_dkv = parts_kv ? p->bwd_piece_workgroups : p->bwd_workgroups;
+  if (parts_kv) progress = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + p->ws_bwd);
+  auto combine = [&](bool dq_units, bool kv_units) {
+    const int c_dq = dq_units && parts_dq ? int(p->fwd_combine.size()) : 0, c_kv = kv_units && parts_kv ? int(p->bwd_combine.size()) : 0;
+    if (c_dq + c_kv > 0)
+      hipLaunchKernelGGL(ca_combine_bwd_kernel<D>, dim3(unsigned((c_dq + c_kv) * 8 * (D / 64))), dim3(256), 0, st,
+                         p->d_fwd_combine, c_dq, p->d_bwd_combine, p->d_slot_row, parts_dq, parts_kv,
+                         static_cast<bf16_t *>(dq), static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), p->hq, p->hkv,
+                         p->scale);
+  };
   // rows that belong to no work unit (KV outside every scheduled document, Q rows outside every task)
   if (!p->kv_covered) {
     launch_fill(dk, kv_elems * 2, st);
@@ -945,7 +1016,7 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
   }
   if (!p->q_covered) launch_fill(dq, q_elems * 2, st);
   if (padded > 0) {
-    const int n_progress = p->bwd_workgroups + 64;
+    const int n_progress = n_dkv + 64;
     const int64_t threads = std::max<int64_t>(padded * p->hq * (D / 8), n_progress);
     hipLaunchKernelGGL(ca_bwd_prep_kernel, dim3(unsigned((threads + 255) / 256)), dim3(256), 0, st, p->d_slot_row,
                        p->d_block_rpk, static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(o),
@@ -958,30 +1029,35 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
     static std::atomic<bool> done[16];
     hipError_t e = set_smem(kern, DkvSmem<D>::TOTAL, p->device, done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(unsigned(p->bwd_workgroups)), dim3(256), DkvSmem<D>::TOTAL, st, p->d_bwd_units,
-                       p->bwd_single, p->d_pos_kv, q_sorted, static_cast<const bf16_t *>(k),
-                       static_cast<const bf16_t *>(v), do_sorted, l2_kv, delta_kv, static_cast<bf16_t *>(dk),
-                       static_cast<bf16_t *>(dv), progress, p->peer_stride, p->hq, p->hkv, padded, p->scale);
+    hipLaunchKernelGGL(kern, dim3(unsigned(n_dkv)), dim3(256), DkvSmem<D>::TOTAL, st,
+                       parts_kv ? p->d_bwd_pieces : p->d_bwd_units, parts_kv ? p->bwd_piece_single : p->bwd_single,
+                       p->d_pos_kv, q_sorted, static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), do_sorted,
+                       l2_kv, delta_kv, static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_kv, progress,
+                       p->peer_stride, p->hq, p->hkv, padded, p->scale);
   }
+  if (p->shared_parts) combine(false, true);  // before the dQ pieces write over them
   if (ev) (void)hipEventRecord(ev[2], st);
   if (!p->fwd_units.empty()) {
     auto kern = ca_bwd_dq_kernel<D>;
     static std::atomic<bool> done[16];
     hipError_t e = set_smem(kern, DqSmem<D>::TOTAL, p->device, done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(unsigned(p->fwd_units.size())), dim3(512), DqSmem<D>::TOTAL, st, p->d_fwd_units,
-                       p->d_slot_row, p->d_slot_pos, static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k),
-                       static_cast<const bf16_t *>(v), static_cast<const bf16_t *>(d_o), l2_slot, delta_slot,
-                       static_cast<bf16_t *>(dq), p->hq, p->hkv, padded, p->scale);
+    hipLaunchKernelGGL(kern, dim3(unsigned(parts_dq ? p->fwd_pieces.size() : p->fwd_units.size())), dim3(512),
+                       DqSmem<D>::TOTAL, st, parts_dq ? p->d_fwd_pieces : p->d_fwd_units, p->d_slot_row, p->d_slot_pos,
+                       static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v),
+                       static_cast<const bf16_t *>(d_o), l2_slot, delta_slot, static_cast<bf16_t *>(dq), parts_dq, p->hq,
+                       p->hkv, padded, p->scale);
   }
+  combine(true, !p->shared_parts);
   if (ev) (void)hipEventRecord(ev[3], st);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd(const ca_plan_t *p, const void *q, const void *k, const void *v, const void *o, const void *d_o,
-                      const float *lse, void *dq, void *dk, void *dv, void *ws, hipStream_t st, hipEvent_t *ev) {
-  return p->d == 128 ? launch_bwd_t<128>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, st, ev)
-                     : launch_bwd_t<64>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, st, ev);
+                      const float *lse, void *dq, void *dk, void *dv, void *ws, bool split, hipStream_t st,
+                      hipEvent_t *ev) {
+  return p->d == 128 ? launch_bwd_t<128>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, st, ev)
+                     : launch_bwd_t<64>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, st, ev);
 }
 
 }  // namespace ca

@@ -326,4 +326,78 @@ __device__ __forceinline__ void store_tile_as_lines(uint32_t patch, const f32x16
   }
 }
 
+// ---- sums of partial results (the combine kernels).  One workgroup of four waves adds up the n_parts blocks of 32 rows x
+// 64 columns at `src` (fp32 in accumulator order: instruction k of the 8 of a block reads quad k, 1 KB), wave w taking
+// blocks w, w + 4, ..; so a sum of up to 8 pieces waits for memory about once.  The waves' sums meet in LDS, and wave w
+// stores rows 8 w .. 8 w + 7 of the tile as whole lines.  With STATS, `st` holds {m, l} per lane and block, and block i
+// counts with weight 2^(m_i - M); then m (M, of the lane's row) and l (the row's whole sum, of both lane halves) are set in
+// every wave.  Otherwise the blocks are added.  The order of additions is fixed.
+constexpr int COMBINE_ROW = 64 + 4;  // floats between the rows of a wave's sum in LDS
+constexpr int COMBINE_LDS = 4 * 32 * COMBINE_ROW;
+template <bool STATS, class F>
+__device__ __forceinline__ void combine_parts(const float *src, size_t src_stride, const float *st, size_t st_stride,
+                                              int n_parts, float f, float (&lds)[COMBINE_LDS], float (&ml)[4][64][2],
+                                              float &m, float &l, F dst_of_row) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, g = lane >> 5;
+  f32x4 acc[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float mw = -3.402823466e38f, lw = 0.f;
+#pragma unroll 2
+  for (int i = wave; i < n_parts; i += 4) {
+    float wgt = 1.f;
+    if (STATS) {
+      const f32x2 s = *reinterpret_cast<const f32x2 *>(st + size_t(i) * st_stride + 2 * lane);
+      const float mn = fmaxf(mw, s[0]), old = fast_exp2(mw - mn);
+      wgt = fast_exp2(s[0] - mn);
+      mw = mn, lw = lw * old + wgt * s[1];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] *= old;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(src + size_t(i) * src_stride + k * 256 + 4 * lane);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[k][e] = STATS ? fmaf(wgt, x[e], acc[k][e]) : acc[k][e] + x[e];
+    }
+  }
+  // quad k of lane (r, g): columns 8 k + 4 g .. + 3 of row r
+#pragma unroll
+  for (int k = 0; k < 8; ++k) *reinterpret_cast<f32x4 *>(&lds[(wave * 32 + r) * COMBINE_ROW + 8 * k + 4 * g]) = acc[k];
+  if (STATS) ml[wave][lane][0] = mw, ml[wave][lane][1] = lw;
+  __syncthreads();
+  const int orow = 8 * wave + (lane >> 3), ocol = 8 * (lane & 7);
+  float wt[4] = {1.f, 1.f, 1.f, 1.f}, inv = f;
+  if (STATS) {
+    auto of_row = [&](int row, float &mm, float &ll, float (&w)[4]) __attribute__((always_inline)) {
+      mm = fmaxf(fmaxf(ml[0][row][0], ml[1][row][0]), fmaxf(ml[2][row][0], ml[3][row][0]));
+      ll = 0.f;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        w[v] = fast_exp2(ml[v][row][0] - mm);  // (both lanes of a row have the same m)
+        ll += w[v] * (ml[v][row][1] + ml[v][row + 32][1]);
+      }
+    };
+    float mo, lo, unused[4];
+    of_row(orow, mo, lo, wt);
+    inv = 1.0f / lo;
+    of_row(r, m, l, unused);
+  }
+  float y[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) y[e] = 0.f;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(&lds[(v * 32 + orow) * COMBINE_ROW + ocol]);
+    const f32x4 b = *reinterpret_cast<const f32x4 *>(&lds[(v * 32 + orow) * COMBINE_ROW + ocol + 4]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] += wt[v] * a[e], y[4 + e] += wt[v] * b[e];
+  }
+  bf16_t *const dst = dst_of_row(orow);
+  if (dst)
+    *reinterpret_cast<u32x4 *>(dst + ocol) = u32x4{pack_bf16(y[0] * inv, y[1] * inv), pack_bf16(y[2] * inv, y[3] * inv),
+                                                   pack_bf16(y[4] * inv, y[5] * inv), pack_bf16(y[6] * inv, y[7] * inv)};
+}
+
 }  // namespace ca

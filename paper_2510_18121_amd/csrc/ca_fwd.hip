@@ -55,7 +55,8 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
                                                                    const bf16_t *__restrict__ Q,
                                                                    const bf16_t *__restrict__ K,
                                                                    const bf16_t *__restrict__ V, bf16_t *__restrict__ O,
-                                                                   float *__restrict__ LSE, int Hq, int Hkv,
+                                                                   float *__restrict__ LSE, float *__restrict__ parts,
+                                                                   float *__restrict__ stats, int Hq, int Hkv,
                                                                    int64_t total_q, float c /* scale * log2(e) */) {
   using S = FwdSmem<D>;
   constexpr int NS = D / 16;       // MFMA k-steps over head_dim
@@ -67,6 +68,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
   constexpr int ROWB = 2 * D;
   constexpr int BLK = 32 * ROWB;   // bytes of a 32-key block inside a tile
   constexpr float RESCALE_LOG2 = 8.0f;
+  constexpr float M_NONE = -3.402823466e38f;  // running maximum of a row that has seen no key: finite, so that -inf - m is -inf
   static_assert(FWD_BM == 64 * FWD_WAVES, "a workgroup covers one forward unit");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(CA_LDS char *)smem;  // LDS byte address of the dynamic segment
@@ -86,12 +88,14 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
     head[x] = u.head + (pair & (u.hp - 1));
     const int slot = u.slot0 + (pair >> hp_lg) * 32 + r;
     row[x] = slot_row[slot];
-    pos[x] = slot_pos[slot];
+    pos[x] = slot_pos[slot] - u.key0;  // counted from the first key of a piece's window (below 0: sees none of it)
   }
   const int wmax = max(wave_max(pos[0]), wave_max(pos[1])), wmin = min(wave_min(pos[0]), wave_min(pos[1]));
   const int n_tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
-  const int n_fast = (wmin + 1) / FWD_BN;   // tiles j < n_fast are entirely visible to every row of this wave
-  const int n_seen = wmax / FWD_BN + 1;     // tiles from here on are seen by none of its rows
+  // tiles j < n_fast are entirely visible to every row of this wave, tiles from n_seen on are seen by none of its rows
+  // (rows may see past the window of a piece; one that is not the unit's last has whole tiles only)
+  const int n_fast = min(wmin + 1, u.n_keys) / FWD_BN;
+  const int n_seen = wmax < 0 ? 0 : min(wmax / FWD_BN + 1, n_tiles);
 
   // ---- direct global -> LDS tile loads.  Load n of this wave covers tile rows RPI*(wave + 4n) .. +RPI-1;
   // lane i fills physical chunk i % CH of row i / CH, so it fetches logical chunk (i % CH) ^ sw(row).
@@ -174,7 +178,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
     for (int b = 0; b < NDB; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[x][b][i] = 0.f;
-  float m[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};
+  float m[2] = {M_NONE, M_NONE}, lsum[2] = {0.f, 0.f};
 
   // ------------------------------------------------------------------------------------------ building blocks
   // K fragments of a 32-key block (kb = byte offset of the block inside koff's stage)
@@ -207,7 +211,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
   // 2^RESCALE_LOG2; until then probabilities are taken relative to the stale m (they stay below
   // 2^RESCALE_LOG2, harmless in fp32 and bf16) and the accumulators need no multiply.
   auto rescale_to = [&](int x, float m_cand) __attribute__((always_inline)) {
-    const float alpha = m[x] == -INFINITY ? 0.f : fast_exp2(m[x] - m_cand);
+    const float alpha = m[x] == M_NONE ? 0.f : fast_exp2(m[x] - m_cand);
     m[x] = m_cand;
     lsum[x] *= alpha;
 #pragma unroll
@@ -281,8 +285,8 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
         for (int i = 0; i < 16; ++i)
           if (k0 + (i >> 2) * 8 + 4 * g + (i & 3) > pos[gx]) x[gx][i] = -INFINITY;
       }
-      // a row that sees no key of this block keeps m = -inf only if it has seen none at all, which cannot happen:
-      // every row sees key 0, and blocks are walked from key 0 on
+      // a row that sees no key of this block, having seen none before (in a piece that lies beyond its position), keeps
+      // m = M_NONE and gets probabilities 0
       rescale(gx, row_max(x[gx]));
       exp_pack(gx, x[gx], pw[gx]);
     }
@@ -457,7 +461,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
     // the whole unit again, every tile through the general path
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-      m[x] = -INFINITY;
+      m[x] = M_NONE;
       lsum[x] = 0.f;
 #pragma unroll
       for (int b = 0; b < NDB; ++b)
@@ -474,6 +478,20 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
     __syncthreads();  // the epilogue writes into the stages
   }
 
+  if (u.part >= 0) {  // a piece: the accumulators as they stand, 1 KB per store instruction
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      float *dst = parts + size_t(u.part) * (FWD_BM * D) + (2 * wave + x) * (32 * D) + 4 * lane;
+#pragma unroll
+      for (int b = 0; b < NDB; ++b)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          *reinterpret_cast<f32x4 *>(dst + (4 * b + q4) * 256) =
+              f32x4{acc[x][b][4 * q4], acc[x][b][4 * q4 + 1], acc[x][b][4 * q4 + 2], acc[x][b][4 * q4 + 3]};
+      *reinterpret_cast<f32x2 *>(stats + ((size_t(u.part) * 8 + 2 * wave + x) * 64 + lane) * 2) = f32x2{m[x], lsum[x]};
+    }
+    return;
+  }
   // epilogue: O = acc / l (bf16), LSE = ln 2 * (m + log2 l).  O leaves as whole lines through a patch of LDS (the
   // stages are free: every wave is past its last tile)
   static_assert(FWD_WAVES * PATCH_BYTES <= S::TOTAL, "patches fit in the stages");
@@ -490,9 +508,34 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
   }
 }
 
+// Adds up the pieces of the cut units: O = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i with M = max_i m_i, and LSE.
+// One workgroup per (unit, group of 32 rows, 64 columns); see combine_parts.
+template <int D>
+__global__ __launch_bounds__(256) void ca_combine_fwd_kernel(const CombineUnit *__restrict__ units,
+                                                             const int32_t *__restrict__ slot_row,
+                                                             const float *__restrict__ parts,
+                                                             const float *__restrict__ stats, bf16_t *__restrict__ O,
+                                                             float *__restrict__ LSE, int Hq, int64_t total_q) {
+  constexpr int NH = D / 64;  // 64-column halves
+  __shared__ __attribute__((aligned(16))) float lds[COMBINE_LDS];
+  __shared__ float ml[4][64][2];
+  const CombineUnit u = units[blockIdx.x / (8 * NH)];
+  const int h = blockIdx.x % NH, pair = (blockIdx.x / NH) % 8;
+  const int head = u.b + (pair & (u.c - 1));
+  const int32_t *const rows = slot_row + u.a + (pair >> __builtin_ctz(u.c)) * 32;
+  const int row = rows[threadIdx.x & 31], orow = rows[threadIdx.x >> 3];  // of the lane's row, and of the row it stores
+  float m = 0.f, l = 0.f;
+  combine_parts<true>(parts + size_t(u.part0) * (FWD_BM * D) + pair * (32 * D) + h * (8 * 256), FWD_BM * D,
+                      stats + (size_t(u.part0) * 8 + pair) * 128, 8 * 128, u.n_parts, 1.f, lds, ml, m, l,
+                      [&](int) __attribute__((always_inline)) -> bf16_t * {
+                        return orow >= 0 ? O + (size_t(orow) * Hq + head) * D + 64 * h : nullptr;
+                      });
+  if (h == 0 && threadIdx.x < 32 && row >= 0) LSE[size_t(head) * total_q + row] = 0.6931471805599453f * (m + fast_log2(l));
+}
+
 template <int D>
 static hipError_t launch_fwd_t(const ca_plan_t *p, const void *q, const void *k, const void *v, void *o, float *lse,
-                               hipStream_t st) {
+                               void *parts, hipStream_t st) {
   if (p->fwd_units.empty()) return hipSuccess;
   auto kern = ca_fwd_kernel<D>;
   static std::atomic<bool> attr_done[16];  // once per device; a second thread repeating the call is harmless
@@ -503,16 +546,22 @@ static hipError_t launch_fwd_t(const ca_plan_t *p, const void *q, const void *k,
     attr_done[p->device & 15].store(true, std::memory_order_release);
   }
   const float c = p->scale * 1.4426950408889634f;
-  hipLaunchKernelGGL(kern, dim3(unsigned(p->fwd_units.size())), dim3(64 * FWD_WAVES), FwdSmem<D>::TOTAL, st,
-                     p->d_fwd_units, p->d_slot_row, p->d_slot_pos, static_cast<const bf16_t *>(q),
-                     static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), lse,
-                     p->hq, p->hkv, p->total_q, c);
+  float *const pp = static_cast<float *>(parts);
+  float *const stats = pp ? pp + size_t(p->n_fwd_parts) * (FWD_BM * D) : nullptr;
+  hipLaunchKernelGGL(kern, dim3(unsigned(pp ? p->fwd_pieces.size() : p->fwd_units.size())), dim3(64 * FWD_WAVES),
+                     FwdSmem<D>::TOTAL, st, pp ? p->d_fwd_pieces : p->d_fwd_units, p->d_slot_row, p->d_slot_pos,
+                     static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v),
+                     static_cast<bf16_t *>(o), lse, pp, stats, p->hq, p->hkv, p->total_q, c);
+  if (pp) {
+    hipLaunchKernelGGL(ca_combine_fwd_kernel<D>, dim3(unsigned(p->fwd_combine.size() * 8 * (D / 64))), dim3(256), 0, st,
+                       p->d_fwd_combine, p->d_slot_row, pp, stats, static_cast<bf16_t *>(o), lse, p->hq, p->total_q);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_fwd(const ca_plan_t *p, const void *q, const void *k, const void *v, void *o, float *lse,
+hipError_t launch_fwd(const ca_plan_t *p, const void *q, const void *k, const void *v, void *o, float *lse, void *parts,
                       hipStream_t st) {
-  return p->d == 128 ? launch_fwd_t<128>(p, q, k, v, o, lse, st) : launch_fwd_t<64>(p, q, k, v, o, lse, st);
+  return p->d == 128 ? launch_fwd_t<128>(p, q, k, v, o, lse, parts, st) : launch_fwd_t<64>(p, q, k, v, o, lse, parts, st);
 }
 
 }  // namespace ca

@@ -27,7 +27,14 @@ struct FwdUnit {
   int32_t n_keys;   // keys the unit needs: max position + 1
   int32_t head;     // first query head
   int32_t hp;       // query heads per unit: 1, 2, 4 or 8
+  // Pieces (see CombineUnit).  A unit that attends a window of its keys: kv_row0 and n_keys are the window's, and key0
+  // is the document position of its first key (a multiple of FWD_BN).  Its results go, as they stand in the
+  // accumulators, to block `part` of the workspace's partial results; -1 in a unit that attends all its keys.
+  int32_t key0;
+  int32_t part;
+  int32_t reserved;
 };
+constexpr int FWD_UNIT_INTS = 5;  // leading fields reported by ca_plan_fwd_units
 
 struct BwdUnit {  // one (KV tile, KV head)
   int32_t slot_begin;  // first slot of the first q block that sees this KV tile
@@ -47,6 +54,26 @@ struct BwdUnit {  // one (KV tile, KV head)
   // the rows of 2 or 4 heads packed into each 64-row tile (the heads of a group add into the same dK and dV)
   int32_t heads;
 };
+// A piece of a unit's query blocks (see CombineUnit) runs alone, and its `follow` is -1 - (block of partial results).
+
+// Batches with few long units leave most of the 256 CUs idle: a lone 256-row shard with a 16K context is 32 workgroups of
+// 256 tiles each, a 4K-token batch has dK/dV workgroups of up to 200 steps at an average of 88 per CU.  For those the
+// planner makes a second list of units, in which long ones are cut into pieces along the loop they run (the keys of a
+// forward / dQ unit, the query blocks of a dK/dV unit).  A piece writes its fp32 accumulators to the workspace, and
+// ca_combine_* add the pieces of a unit up, in order (no atomics: bit-reproducible), and store the results.  Measured,
+// whole units against pieces: forward of that lone shard (32/8 heads, head_dim 128) 333 -> 75 us; forward + backward of
+// 1000 rows with a 130K context 10.4 -> 8.1 ms; of the 4K-token batch 592 -> 500 us; of documents of 512 and 1024 tokens
+// (4/2 heads, head_dim 64) 92 -> 48 us.
+struct CombineUnit {
+  int32_t part0, n_parts;  // blocks of partial results of the unit
+  // forward / dQ unit: first slot, first query head, hp.   dK/dV unit: first packed KV row, valid keys, KV head.
+  int32_t a, b, c, reserved;
+};
+// a block of partial results: FWD_BM x head_dim fp32 (a forward / dQ unit's rows, or dK and then dV of BWD_BN keys), in
+// the order of the accumulators: [wave and row group][32-column block][4 quads][64 lanes][4]; behind all blocks, for
+// forward, {running maximum, the lane's share of the row sum} as [block][8 row groups][64 lanes][2] fp32
+inline size_t part_bytes(int d) { return size_t(FWD_BM) * d * 4; }
+constexpr size_t FWD_STAT_BYTES = 8 * 64 * 2 * 4;
 
 }  // namespace ca
 
@@ -67,6 +94,15 @@ struct ca_plan {
   int32_t bwd_workgroups = 0;  // workgroups of the dK/dV kernel: the leading units of bwd_units
   int32_t bwd_single = 0;      // so many leading workgroups are units that run alone (only those pace each other)
   int64_t fwd_steps = 0, bwd_steps = 0;
+  // the lists with long units cut into pieces; empty where that gains nothing
+  std::vector<ca::FwdUnit> fwd_pieces;
+  std::vector<ca::BwdUnit> bwd_pieces;
+  std::vector<ca::CombineUnit> fwd_combine, bwd_combine;
+  int32_t bwd_piece_workgroups = 0, bwd_piece_single = 0;
+  int32_t n_fwd_parts = 0, n_bwd_parts = 0;
+  // workspace with which the piece lists are used: forward, and backward, where the parts lie behind ws_bwd
+  size_t ws_fwd_split = 0, ws_bwd_split = 0, ws_off_parts_kv = 0, ws_off_parts_dq = 0;
+  bool shared_parts = false;  // the dQ parts take the place of the dK/dV parts once those have been added up
   // workspace layout for backward: [Delta fp32 hq*padded_slots][log2e*LSE fp32 hq*padded_slots]
   int slot_align = ca::SLOT_ALIGN, heads_packed = 1;  // padding of a document's slots; hp of the packed units
   size_t ws_fwd = 0, ws_bwd = 0, ws_off_l2 = 0, ws_off_qs = 0, ws_off_dos = 0, ws_off_prog = 0;
@@ -75,9 +111,12 @@ struct ca_plan {
   bool q_covered = false, kv_covered = false;  // every packed Q row / KV row belongs to some unit
   // device copies
   int device = -1;
-  int32_t *d_slot_row = nullptr, *d_slot_pos = nullptr, *d_block_rpk = nullptr, *d_pos_kv = nullptr;
-  ca::FwdUnit *d_fwd_units = nullptr;
-  ca::BwdUnit *d_bwd_units = nullptr;
+  void *d_blob = nullptr;  // one allocation that holds all of the arrays below, copied from `blob`
+  std::vector<char> blob;
+  const int32_t *d_slot_row = nullptr, *d_slot_pos = nullptr, *d_block_rpk = nullptr, *d_pos_kv = nullptr;
+  const ca::FwdUnit *d_fwd_units = nullptr, *d_fwd_pieces = nullptr;
+  const ca::BwdUnit *d_bwd_units = nullptr, *d_bwd_pieces = nullptr;
+  const ca::CombineUnit *d_fwd_combine = nullptr, *d_bwd_combine = nullptr;
   // optional timing events (hipEvent_t, kept as void* so that host-only code needs no HIP header)
   bool profile = false;
   void *ev[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};

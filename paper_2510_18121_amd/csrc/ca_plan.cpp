@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <numeric>
 #include <sstream>
 
@@ -94,6 +95,80 @@ void validate(const ca_batch_desc *d) {
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
+// ---- cutting long units into pieces where a batch leaves the chip idle
+// A kernel's unit costs `fixed` plus `per_step` for each of its steps (tiles, or query blocks x heads), and the hardware
+// hands the units, sorted longest first, to whichever CU is free: the launch time is a list-scheduling makespan, which is
+// simulated here (32 CUs stand for 256 where every unit comes once for each of 8 heads).  Cutting every unit longer than T
+// steps into equal pieces evens the load out and costs a `fixed` per piece, the partial results (written by the pieces,
+// read once more to be added up) and another launch.  The T with the shortest total is taken, if it gains a tenth: at
+// 4K tokens of 1K-token documents (32/8 heads) the simulation gives 362 us for the dK/dV kernel's 256 whole units (measured
+// 325) and 210 us for 504 pieces of at most 60 steps.
+// The figures are microseconds measured on MI355X: per step 1.7 (forward), 2.6 (dQ) and 1.75 (dK/dV) at head_dim 128, 1.2,
+// 1.3 and 0.9 at 64; the fixed part is what a unit spends around its steps (descriptor, row indices, fragments, first
+// tiles, drain, results); partial results move at about 4 TB/s.
+constexpr int N_CU = 256;
+struct CutCost {
+  double per_step, fixed, launch;
+  int min_steps;
+};
+
+// units: (steps, how many of that size), longest first.  Returns the longest piece in steps, 0 to cut nothing.
+int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const CutCost &c, size_t bytes_per_part,
+                   size_t max_bytes) {
+  constexpr double BYTES_PER_US = 4e6;
+  double total = 0, steps_per_cu = 0;
+  int64_t longest = 0, same = N_CU;  // `same`: every size comes a multiple of this many times
+  for (const auto &[steps, count] : units) {
+    total += double(count) * (c.fixed + c.per_step * double(steps));
+    steps_per_cu += double(count) * double(steps) / N_CU;
+    longest = std::max(longest, steps);
+    same = std::gcd(same, count);
+  }
+  // no list of pieces can beat the mean load: most batches end here
+  if (c.fixed + c.per_step * double(longest) < 1.2 * total / N_CU) return 0;
+  std::vector<std::pair<double, int64_t>> sizes;  // (microseconds, how many / same)
+  std::vector<double> busy;
+  auto makespan = [&](double at_most) {  // of `sizes`; gives up beyond at_most
+    std::sort(sizes.begin(), sizes.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+    busy.assign(size_t(N_CU / same), 0.0);  // a heap, the least loaded CU first
+    double end = 0;
+    for (const auto &[us, n] : sizes)
+      for (int64_t i = 0; i < n; ++i) {
+        std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+        busy.back() += us;
+        end = std::max(end, busy.back());
+        if (end >= at_most) return end;
+        std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+      }
+    return end;
+  };
+  double best = 0;
+  int64_t best_t = 0;
+  int worse = 0;
+  // whole units first, then pieces from a little over the mean load downwards
+  for (double T = double(longest); T >= c.min_steps; T = std::min(T / 1.2, std::max(1.3 * steps_per_cu, 4.0 * c.min_steps))) {
+    const int64_t t = int64_t(T);
+    int64_t parts = 0;
+    double sum = 0;
+    sizes.clear();
+    for (const auto &[steps, count] : units) {
+      const int64_t k = (steps + t - 1) / t;
+      const double us = c.fixed + c.per_step * double(steps) / double(k);
+      sizes.push_back({us, count / same * k});
+      sum += us * double(count * k);
+      if (k > 1) parts += count * k;
+    }
+    const size_t bytes = size_t(parts) * bytes_per_part;
+    const double extra = parts ? c.launch + double(bytes) / BYTES_PER_US : 0.0;
+    if (parts && (bytes > max_bytes || sum / N_CU + extra >= best)) break;  // more and smaller pieces only cost more
+    const double us = makespan(parts ? best - extra : 1e30) + extra;
+    if (!parts) best = 0.9 * us;
+    else if (us < best) best = us, best_t = t, worse = 0;
+    else if (++worse == 3) break;
+  }
+  return best_t;
+}
+
 void schedule(ca_plan_t *p) {
   const int hq = p->hq, hkv = p->hkv, g = hq / hkv;
   // tasks of each document, by position
@@ -120,6 +195,7 @@ void schedule(ca_plan_t *p) {
   struct TileRef {
     int32_t cost;
     FwdUnit u;
+    int32_t part = -1, pieces = 1, piece = 0;  // in the piece list: first part of the unit's first head, pieces, which
   };
   std::vector<TileRef> ftiles;
   std::vector<BwdUnit> btiles;
@@ -163,12 +239,12 @@ void schedule(ca_plan_t *p) {
     for (; a + FWD_BM <= s1; a += FWD_BM) {
       if (p->slot_row[a] < 0) break;  // pure padding
       int32_t n_keys = p->slot_pos[a + FWD_BM - 1] + 1;
-      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, 1}});
+      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, 1, 0, -1, 0}});
     }
     for (; a < s1; a += sub) {
       if (p->slot_row[a] < 0) break;  // pure padding
       int32_t n_keys = p->slot_pos[a + sub - 1] + 1;
-      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, int32_t(hp)}});
+      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, int32_t(hp), 0, -1, 0}});
     }
     // backward KV tiles: every resident key of the document.  Keys beyond the last query position get a
     // unit without query blocks, which writes their zero gradient.
@@ -215,6 +291,29 @@ void schedule(ca_plan_t *p) {
   for (size_t blk = 0; blk < p->block_rpk.size(); ++blk)
     if (const int rpk = p->block_rpk[blk])
       for (int i = 0; i < BWD_BQ; ++i) p->pos_kv[blk * BWD_BQ + i] = p->slot_pos[blk * BWD_BQ + i % rpk];
+  auto base_workspace = [&]() {
+    // workspace of backward, all in slot order: per (head, slot) fp32 -Delta and log2(e)*LSE, then bf16 copies of Q
+    // and dO as [block of 64 slots][head][64][head_dim] (the dK/dV kernel re-reads their 64-slot tiles once per 128-key
+    // tile: in this layout a tile is one contiguous run and needs no row indices)
+    const size_t per = (size_t(padded) * hq * sizeof(float) + 255) / 256 * 256;
+    const size_t copy = (size_t(padded) * hq * p->d * 2 + 255) / 256 * 256;
+    p->ws_off_l2 = per;
+    p->ws_off_qs = 2 * per;
+    p->ws_off_dos = 2 * per + copy;
+    // ... and one progress counter per backward workgroup (plus a block of zeros), by which the dK/dV workgroups that walk
+    // the same Q/dO tiles keep within an L2 window of each other.  Workgroups go to the 8 XCDs round robin in index
+    // order (workgroup i to XCD (i + c) mod 8) and unit i has KV head i mod n_kv_heads, so units lcm(8, n_kv_heads)
+    // apart share both.
+    p->ws_off_delta_kv = 2 * per + 2 * copy;
+    p->ws_off_l2_kv = 3 * per + 2 * copy;
+    p->ws_off_prog = 4 * per + 2 * copy;
+    p->peer_stride = int(std::lcm<int64_t>(8, hkv));
+    return (p->ws_off_prog + (size_t(p->bwd_workgroups) + 64) * sizeof(int32_t) + 255) / 256 * 256;
+  };
+  // Partial results are bounded: a batch that fits the library's static workspace still does with them, a larger one
+  // needs at most this much more.
+  constexpr size_t MAX_CUT_BYTES = size_t(256) << 20;
+  size_t cut_budget = 0;
   p->bwd_steps = 0;
   for (auto &t : btiles) p->bwd_steps += int64_t(t.slot_end - t.slot_begin) / BWD_BQ * t.heads * hkv;
   {
@@ -247,51 +346,133 @@ void schedule(ca_plan_t *p) {
       a = b;
     }
     // workgroups are handed out in index order: longest first, a chain counting with all its steps
-    std::stable_sort(chains.begin(), chains.end(), [](const Chain &x, const Chain &y) { return x.steps > y.steps; });
-    size_t first_chain = chains.size();
-    for (size_t ci = chains.size(); ci-- > 0;)
-      if (chains[ci].b - chains[ci].a > 1) first_chain = ci;
-    p->bwd_workgroups = int32_t(chains.size() * hkv);
-    p->bwd_units.resize(size_t(p->bwd_workgroups));
-    p->bwd_units.reserve(btiles.size() * hkv);
-    p->bwd_single = int32_t(first_chain * hkv);
-    for (size_t ci = 0; ci < chains.size(); ++ci) {
-      const size_t a = chains[ci].a, b = chains[ci].b;
-      for (int h = 0; h < hkv; ++h) {
-        BwdUnit u = btiles[a];
-        u.kv_head = h;
-        u.count = int32_t(b - a);
-        u.follow = b - a > 1 ? int32_t(p->bwd_units.size()) : 0;
-        p->bwd_units[ci * hkv + h] = u;
-        for (size_t t = a + 1; t < b; ++t) {
-          BwdUnit f = btiles[t];
-          f.kv_head = h;
-          p->bwd_units.push_back(f);
+    auto lay_out = [&](std::vector<Chain> &list, const std::vector<BwdUnit> &tiles, std::vector<BwdUnit> &units,
+                       const std::vector<int32_t> &pieces, int32_t &workgroups, int32_t &single) {
+      // (pieces: 0, or how many pieces the unit is cut into; those have their first head's part in `follow`)
+      std::stable_sort(list.begin(), list.end(), [](const Chain &x, const Chain &y) { return x.steps > y.steps; });
+      size_t first_chain = list.size();
+      for (size_t ci = list.size(); ci-- > 0;)
+        if (list[ci].b - list[ci].a > 1) first_chain = ci;
+      workgroups = int32_t(list.size() * hkv);
+      units.reserve(tiles.size() * hkv);
+      units.resize(size_t(workgroups));
+      single = int32_t(first_chain * hkv);
+      for (size_t ci = 0; ci < list.size(); ++ci) {
+        const size_t a = list[ci].a, b = list[ci].b;
+        for (int h = 0; h < hkv; ++h) {
+          BwdUnit u = tiles[a];
+          u.kv_head = h;
+          u.count = int32_t(b - a);
+          if (!pieces.empty() && pieces[a] > 0) u.follow -= h * pieces[a];  // the pieces' parts of a head are neighbours
+          else u.follow = b - a > 1 ? int32_t(units.size()) : 0;
+          units[ci * hkv + h] = u;
+          for (size_t t = a + 1; t < b; ++t) {
+            BwdUnit f = tiles[t];
+            f.kv_head = h;
+            units.push_back(f);
+          }
         }
       }
+    };
+    lay_out(chains, btiles, p->bwd_units, {}, p->bwd_workgroups, p->bwd_single);
+    p->ws_bwd = base_workspace();
+    // the list in which long units that run alone are cut along their query blocks
+    cut_budget = p->ws_bwd <= CA_STATIC_WS_BYTES ? CA_STATIC_WS_BYTES - p->ws_bwd : MAX_CUT_BYTES;
+    std::vector<std::pair<int64_t, int64_t>> sizes;
+    for (auto &c : chains) {
+      if (!sizes.empty() && sizes.back().first == c.steps) sizes.back().second += hkv;
+      else sizes.push_back({c.steps, hkv});
     }
+    const CutCost cost_dkv = {p->d == 128 ? 1.75 : 0.9, 12.0, 5.0, 4};
+    const int64_t T = best_piece(sizes, cost_dkv, part_bytes(p->d), cut_budget - std::min<size_t>(cut_budget, 1 << 16));
+    if (T > 0) {
+      std::vector<BwdUnit> tiles;
+      std::vector<int32_t> pieces;
+      std::vector<Chain> list;
+      for (auto &c : chains) {
+        const BwdUnit &u = btiles[c.a];
+        const int64_t blocks = (u.slot_end - u.slot_begin) / BWD_BQ;
+        const int64_t k = c.b - c.a == 1 && c.steps > T ? std::min(blocks, (c.steps + T - 1) / T) : 1;
+        if (k <= 1) {
+          list.push_back({tiles.size(), tiles.size() + (c.b - c.a), c.steps});
+          tiles.insert(tiles.end(), btiles.begin() + c.a, btiles.begin() + c.b);
+          pieces.resize(tiles.size(), 0);
+          continue;
+        }
+        for (int64_t i = 0; i < k; ++i) {
+          BwdUnit v = u;
+          v.slot_begin = int32_t(u.slot_begin + blocks * i / k * BWD_BQ);
+          v.slot_end = int32_t(u.slot_begin + blocks * (i + 1) / k * BWD_BQ);
+          v.slot_full = std::min(std::max(u.slot_full, v.slot_begin), v.slot_end);
+          v.follow = -1 - (p->n_bwd_parts + int32_t(i));
+          list.push_back({tiles.size(), tiles.size() + 1, cost(v)});
+          tiles.push_back(v);
+          pieces.push_back(int32_t(k));
+        }
+        for (int h = 0; h < hkv; ++h, p->n_bwd_parts += int32_t(k))
+          p->bwd_combine.push_back({p->n_bwd_parts, int32_t(k), u.kv_row, u.n_valid, h, 0});
+      }
+      if (!p->bwd_combine.empty()) lay_out(list, tiles, p->bwd_pieces, pieces, p->bwd_piece_workgroups, p->bwd_piece_single);
+    }
+  }
+  {
+    // the list in which long forward / dQ units are cut along their keys (one list for both kernels: per step 1.7 and 2.6
+    // us at head_dim 128, the mean stands for both)
+    std::vector<std::pair<int64_t, int64_t>> sizes;
+    for (auto &t : ftiles) {
+      if (!sizes.empty() && sizes.back().first == t.cost) sizes.back().second += hq / t.u.hp;
+      else sizes.push_back({t.cost, hq / t.u.hp});
+    }
+    const CutCost cost_fwd = {p->d == 128 ? 2.1 : 1.25, 9.0, 5.0, 4};
+    const int64_t T = best_piece(sizes, cost_fwd, part_bytes(p->d) + FWD_STAT_BYTES, cut_budget - std::min<size_t>(cut_budget, 1 << 16));
+    if (T > 0) {
+      std::vector<TileRef> pieces;
+      for (auto &t : ftiles) {
+        const int64_t k = t.cost > T ? (t.cost + T - 1) / T : 1;
+        if (k <= 1) {
+          pieces.push_back(t);
+          continue;
+        }
+        for (int64_t i = 0; i < k; ++i) {
+          TileRef v = t;
+          const int32_t a = int32_t(t.cost * i / k), b = int32_t(t.cost * (i + 1) / k);  // tiles [a, b)
+          v.cost = b - a;
+          v.u.key0 = a * FWD_BN;
+          v.u.kv_row0 = t.u.kv_row0 + v.u.key0;
+          v.u.n_keys = std::min(t.u.n_keys, b * FWD_BN) - v.u.key0;
+          v.part = p->n_fwd_parts, v.pieces = int32_t(k), v.piece = int32_t(i);
+          pieces.push_back(v);
+        }
+        for (int i = 0; i < hq / t.u.hp; ++i, p->n_fwd_parts += int32_t(k))
+          p->fwd_combine.push_back({p->n_fwd_parts, int32_t(k), t.u.slot0, (i % hkv) * g + (i / hkv) * t.u.hp, t.u.hp, 0});
+      }
+      std::stable_sort(pieces.begin(), pieces.end(), [](const TileRef &a, const TileRef &b) { return a.cost > b.cost; });
+      for (auto &t : pieces)
+        for (int i = 0; i < hq / t.u.hp; ++i) {
+          FwdUnit u = t.u;
+          u.head = (i % hkv) * g + (i / hkv) * u.hp;
+          u.part = t.part < 0 ? -1 : t.part + i * t.pieces + t.piece;
+          p->fwd_pieces.push_back(u);
+        }
+    }
+  }
+  // workspace with which the piece lists are used
+  if (p->n_fwd_parts > 0) p->ws_fwd_split = size_t(p->n_fwd_parts) * (part_bytes(p->d) + FWD_STAT_BYTES);
+  p->ws_bwd_split = p->ws_bwd;
+  if (p->n_fwd_parts + p->n_bwd_parts > 0) {
+    // [progress counters of the dK/dV pieces][dK/dV parts][dQ parts], or, where that is beyond the budget, one region that
+    // the dQ parts use after the dK/dV parts have been added up (one launch more)
+    size_t at = p->ws_bwd;
+    if (p->n_bwd_parts > 0) at += (size_t(p->bwd_piece_workgroups) + 64) * sizeof(int32_t);
+    at = (at + 255) / 256 * 256;
+    p->ws_off_parts_kv = p->ws_off_parts_dq = at;
+    const size_t kv = size_t(p->n_bwd_parts) * part_bytes(p->d), dq = size_t(p->n_fwd_parts) * part_bytes(p->d);
+    p->shared_parts = kv > 0 && dq > 0 && at - p->ws_bwd + kv + dq > cut_budget;
+    if (!p->shared_parts) p->ws_off_parts_dq += kv;
+    p->ws_bwd_split = std::max(p->ws_off_parts_kv + kv, p->ws_off_parts_dq + dq);
   }
   p->q_covered = covered_q == p->total_q;
   p->kv_covered = covered_kv == p->total_kv;
-  // workspace of backward, all in slot order: per (head, slot) fp32 -Delta and log2(e)*LSE, then bf16 copies of Q
-  // and dO as [block of 64 slots][head][64][head_dim] (the dK/dV kernel re-reads their 64-slot tiles once per 128-key tile: in this
-  // layout a tile is one contiguous run and needs no row indices)
-  const size_t per = (size_t(padded) * hq * sizeof(float) + 255) / 256 * 256;
-  const size_t copy = (size_t(padded) * hq * p->d * 2 + 255) / 256 * 256;
-  p->ws_off_l2 = per;
-  p->ws_off_qs = 2 * per;
-  p->ws_off_dos = 2 * per + copy;
-  // ... and one progress counter per backward workgroup (plus a block of zeros), by which the dK/dV workgroups that walk
-  // the same Q/dO tiles keep within an L2 window of each other.  Workgroups go to the 8 XCDs round robin in index
-  // order (workgroup i to XCD (i + c) mod 8) and unit i has KV head i mod n_kv_heads, so units lcm(8, n_kv_heads)
-  // apart share both.
-  p->ws_off_delta_kv = 2 * per + 2 * copy;
-  p->ws_off_l2_kv = 3 * per + 2 * copy;
-  p->ws_off_prog = 4 * per + 2 * copy;
-  p->peer_stride = int(std::lcm<int64_t>(8, hkv));
-  p->ws_bwd = p->ws_off_prog + (size_t(p->bwd_workgroups) + 64) * sizeof(int32_t);
-  p->ws_bwd = (p->ws_bwd + 255) / 256 * 256;
-  p->ws_fwd = 0;
 }
 }  // namespace
 
@@ -335,6 +516,14 @@ int build_plan(const ca_batch_desc *desc, ca_plan_t **out) {
 }
 
 }  // namespace ca
+
+// the first n_fields ints of every entry of a schedule list
+template <class T>
+static int64_t leading_fields(const std::vector<T> &list, int32_t *out, size_t n_fields) {
+  if (out)
+    for (size_t i = 0; i < list.size(); ++i) std::memcpy(out + i * n_fields, &list[i], n_fields * sizeof(int32_t));
+  return int64_t(list.size());
+}
 
 extern "C" {
 
@@ -384,14 +573,36 @@ int64_t ca_plan_rows(const ca_plan_t *p, int32_t *rows, int32_t *pos) {
 
 int64_t ca_plan_fwd_units(const ca_plan_t *p, int32_t *units) {
   if (!p) return 0;
-  if (units) std::memcpy(units, p->fwd_units.data(), p->fwd_units.size() * sizeof(ca::FwdUnit));
-  return int64_t(p->fwd_units.size());
+  return leading_fields(p->fwd_units, units, ca::FWD_UNIT_INTS);
 }
 
 int64_t ca_plan_bwd_units(const ca_plan_t *p, int32_t *units) {
   if (!p) return 0;
-  if (units) std::memcpy(units, p->bwd_units.data(), p->bwd_units.size() * sizeof(ca::BwdUnit));
-  return int64_t(p->bwd_units.size());
+  return leading_fields(p->bwd_units, units, sizeof(ca::BwdUnit) / 4);
+}
+
+int64_t ca_plan_fwd_pieces(const ca_plan_t *p, int32_t *units) {
+  return p ? leading_fields(p->fwd_pieces, units, sizeof(ca::FwdUnit) / 4) : 0;
+}
+
+int64_t ca_plan_bwd_pieces(const ca_plan_t *p, int32_t *units, int32_t *n_workgroups) {
+  if (!p) return 0;
+  if (n_workgroups) *n_workgroups = p->bwd_piece_workgroups;
+  return leading_fields(p->bwd_pieces, units, sizeof(ca::BwdUnit) / 4);
+}
+
+int64_t ca_plan_combine_units(const ca_plan_t *p, int32_t backward, int32_t *units) {
+  return p ? leading_fields(backward ? p->bwd_combine : p->fwd_combine, units, sizeof(ca::CombineUnit) / 4) : 0;
+}
+
+int ca_plan_workspace_bytes_split(const ca_plan_t *p, size_t *fwd, size_t *bwd) {
+  if (!p) {
+    ca::set_error("plan is null");
+    return CA_ERR_INVALID_ARG;
+  }
+  if (fwd) *fwd = std::max(p->ws_fwd, p->ws_fwd_split);
+  if (bwd) *bwd = p->ws_bwd_split;
+  return CA_OK;
 }
 
 }  // extern "C"

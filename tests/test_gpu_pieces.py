@@ -1,0 +1,111 @@
+"""Work units cut into pieces (partial results in the workspace, added up by the combine kernels), against the oracle and
+against whole units: lone shards with long contexts, small batches, rows scattered so that some see none of a piece's keys,
+clipped windows, every head packing, both head_dims; the workspace sizes at which the calls change over; graph replays."""
+import numpy as np
+import pytest
+import torch
+
+import parity_util as P
+from paper_2510_18121_amd import binding as B
+from paper_2510_18121_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+BATCHES = {
+    # name: (documents, tasks, heads, KV heads, head_dim)
+    "lone ragged shard": ([5000], [(0, 4711, 289)], 8, 2, 128),
+    "lone ragged shard d64": ([5000], [(0, 4711, 289)], 8, 2, 64),
+    "one row": ([4099], [(0, 4098, 1)], 4, 1, 128),
+    "one document": ([2111], [(0, 0, 2111)], 4, 2, 128),
+    "one document d64, no GQA": ([1900], [(0, 0, 1900)], 3, 3, 64),
+    "GQA 8, two documents": ([1500, 700], [(0, 0, 811), (0, 811, 689), (1, 100, 600)], 8, 1, 128),
+    # the parts of dQ take the place of those of dK/dV, so that the batch still fits the static workspace
+    "shared parts": ([4400], [(0, 2300, 2100)], 8, 2, 128),
+    # one 256-slot tile holds rows at the document's start and at its end: windows some rows see in full, some not at all
+    "scattered rows": ([3000], [(0, 0, 3), (0, 70, 60), (0, 1000, 65), (0, 2040, 30), (0, 2900, 100)], 4, 4, 128),
+    "scattered rows d64": ([3000], [(0, 0, 3), (0, 70, 60), (0, 1000, 65), (0, 2040, 30), (0, 2900, 100)], 4, 4, 64),
+}
+
+
+def tensors_of(name):
+    docs, tasks, hq, hkv, d = BATCHES[name]
+    b = W.custom(docs, tasks, hq, hkv, d, seed=90)
+    return b, W.make_tensors(b, DEV)
+
+
+def run(b, t, ws_bytes_f, ws_bytes_b, plan):
+    q, k, v, d_o = t
+    o, dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, q, k, v))
+    lse = torch.full((b.n_q_heads, b.total_q), float("nan"), device=DEV)
+    # what the workspace held before must not matter
+    wf = torch.full((ws_bytes_f,), 255, dtype=torch.uint8, device=DEV) if ws_bytes_f else None
+    B.ca_forward(plan, q, k, v, o, lse, wf)
+    B.ca_backward(plan, q, k, v, o, d_o, lse, dq, dk, dv, torch.full((ws_bytes_b,), 255, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    return {"o": o, "lse": lse, "dq": dq, "dk": dk, "dv": dv}
+
+
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_pieces_match_the_oracle_and_whole_units(name):
+    b, t = tensors_of(name)
+    plan = B.ca_plan(b)
+    (f0, b0), (f1, b1) = plan.workspace_bytes(), plan.workspace_bytes_split()
+    assert f1 > 0 and b1 > b0, "the batch is there because its units are cut"
+    pc = plan.pieces()
+    n_parts = int(pc["fwd_combine"][:, 1].sum() + pc["bwd_combine"][:, 1].sum())
+    assert (b1 - b0 < n_parts * 256 * b.head_dim * 4) == (name == "shared parts")
+    cut, whole = run(b, t, f1, b1, plan), run(b, t, 0, b0, plan)
+    ref = P.run_oracle(b, *t)
+    for r, tag in ((cut, "pieces"), (whole, "whole units")):
+        e = P.errors(r, ref)
+        print(name, tag, e, flush=True)
+        P.assert_parity(e, (name, tag))
+    # one byte less than the pieces need: whole units, bit for bit, as without a workspace; more: pieces, and the same again
+    less, more = run(b, t, f1 - 1, b1 - 1, plan), run(b, t, f1 + 256, b1 + 256, plan)
+    for n in cut:
+        assert torch.equal(less[n], whole[n]), n
+        assert torch.equal(more[n], cut[n]), n
+
+
+def test_pieces_at_scores_that_outgrow_the_reference():
+    """A piece whose scores leave the finite range is repeated by the general path; its weight dominates the others'."""
+    b = W.custom([4000], [(0, 3800, 200)], 2, 1, 128, seed=91, scale=1.0)
+    q, k, v, _ = W.make_tensors(b, DEV)
+    q = torch.full_like(q, 1.0)
+    k = (k.float() * 0.01).to(torch.bfloat16)
+    k[2100:2110] = (200.0 * np.log(2.0)) / 128
+    plan = B.ca_plan(b)
+    assert plan.workspace_bytes_split()[0] > 0
+    hip = P.run_hip(b, q, k, v, plan=plan)
+    e = P.errors(hip, P.run_oracle(b, q, k, v))
+    print(e, flush=True)
+    assert e["o_err_over_bound"] <= 1.0 and e["lse_max_abs"] <= P.LSE_MAX_ABS, e
+
+
+def test_pieces_replay_from_a_graph():
+    b, (q, k, v, d_o) = tensors_of("lone ragged shard")
+    plan = B.ca_plan(b)
+    ws = B.alloc_workspace(plan, DEV)
+    assert ws.numel() == max(plan.workspace_bytes_split())
+    outs = [torch.empty_like(x) for x in (q, q, k, v)] + [torch.empty((b.n_q_heads, b.total_q), device=DEV)]
+    o, dq, dk, dv, lse = outs
+
+    def step():
+        B.ca_forward(plan, q, k, v, o, lse, ws)
+        B.ca_backward(plan, q, k, v, o, d_o, lse, dq, dk, dv, ws)
+
+    step()
+    torch.cuda.synchronize()
+    want = [t.clone() for t in outs]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for _ in range(3):
+        for t in outs:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for t, w in zip(outs, want):
+            assert torch.equal(t, w)
