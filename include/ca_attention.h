@@ -246,7 +246,8 @@ const char *ca_last_error(void); /* thread-local detail of the last failing call
  * n_bwd_units, fwd_kv_step, padded_rows, sum over forward units of KV steps, sum over backward units of
  * (q blocks x heads) steps, bwd_q_block_rows, slot_align (a document's rows are padded to this many slots),
  * heads_packed (query heads per head-packed forward unit), n_bwd_workgroups (workgroups of the dK/dV kernel: short
- * backward units are chained, see below).  n_q_tiles counts the full 256-slot tiles.
+ * backward units are chained, see below), joint_backward (1: the backward runs its dK/dV and dQ units in one launch, given
+ * the workspace of ca_plan_workspace_bytes_split and no timing).  n_q_tiles counts the full 256-slot tiles.
  * Returns the number of values available.
  */
 int ca_plan_info(const ca_plan_t *plan, int64_t *out, int n);

@@ -110,50 +110,52 @@ struct DqSmem {
   static constexpr int TOTAL = NST * STAGE;
 };
 
-template <int D>
-__global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__restrict__ units,
-                                                           const int32_t *__restrict__ slot_row,
-                                                           const int32_t *__restrict__ slot_pos,
-                                                           const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
-                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
-                                                           const float *__restrict__ l2_slot,
-                                                           const float *__restrict__ delta_slot,
-                                                           bf16_t *__restrict__ dQ, float *__restrict__ parts, int Hq,
-                                                           int Hkv, int64_t padded, float scale) {
+// The workgroup of W waves: all eight 32-row groups of the unit (W = 8), or groups 4 half .. 4 half + 3 of them.
+template <int D, int W>
+__device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, const int32_t *__restrict__ slot_row,
+                                             const int32_t *__restrict__ slot_pos, const bf16_t *__restrict__ Q,
+                                             const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
+                                             const bf16_t *__restrict__ dO, const float *__restrict__ l2_slot,
+                                             const float *__restrict__ delta_slot, bf16_t *__restrict__ dQ,
+                                             float *__restrict__ parts, int Hq, int Hkv, int64_t padded, float scale) {
   using S = DqSmem<D>;
-  constexpr int NS = D / 16, NDB = D / 32, CH = D / 8, RPI = 64 / CH, NLD = FWD_BN / (8 * RPI), NST = S::NST;
+  constexpr int NS = D / 16, NDB = D / 32, CH = D / 8, RPI = 64 / CH, NLD = FWD_BN / (W * RPI), NST = S::NST;
   constexpr int ROWB = 2 * D;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)(CA_LDS char *)smem;  // LDS byte address of the dynamic segment
-  const FwdUnit u = units[blockIdx.x];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, r = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, dh = (lane >> 4) & 1;
   const int hk = __builtin_amdgcn_readfirstlane(u.head / (Hq / Hkv));  // (uniform, for scalar K/V addresses)
-  // wave -> (32-slot group, query head) inside the unit, as in the forward kernel
-  const int hp_lg = __builtin_ctz(u.hp);
-  const int head = u.head + (wave & (u.hp - 1));
-  const int slot = u.slot0 + (wave >> hp_lg) * 32 + r;
+  // (group of the unit) -> (32-slot group, query head) inside the unit, as in the forward kernel
+  const int hp_lg = __builtin_ctz(u.hp), pair = W * half + wave;
+  const int head = u.head + (pair & (u.hp - 1));
+  const int slot = u.slot0 + (pair >> hp_lg) * 32 + r;
   const int row = slot_row[slot];
   const int pos = slot_pos[slot] - u.key0;  // counted from the first key of a piece's window (below 0: sees none of it)
   float l2 = l2_slot[int64_t(head) * padded + slot];
   float dl = delta_slot[int64_t(head) * padded + slot];
   const int wmax = wave_max(pos), wmin = wave_min(pos);
-  const int n_tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
+  // tiles some row of the workgroup sees (positions are sorted; at least one, which then is masked)
+  int n_tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
+  if (W < 8) {
+    const int last = slot_pos[u.slot0 + ((W * half + W - 1) >> hp_lg) * 32 + 31] - u.key0;
+    n_tiles = max(1, min(n_tiles, last / FWD_BN + 1));
+  }
   const float c = scale * LOG2E;
 
   // direct loads addressed as (scalar tile base) + (per-lane 32-bit offset); tiles past the end are fetched as the
   // last tile with rows clamped to the last key (constant number of loads per iteration, see the forward kernel)
   const uint32_t kv_row_bytes = uint32_t(Hkv) * D * 2;
-  const int ld_row0 = RPI * wave + lane / CH;  // + 8*RPI*n
+  const int ld_row0 = RPI * wave + lane / CH;  // + W*RPI*n
   const uint32_t ld_cbytes = uint32_t((lane % CH) ^ tile_sw<D>(ld_row0)) * 16;
-  const int last_tile = n_tiles - 1, last_key_in_tile = u.n_keys - 1 - last_tile * FWD_BN;
+  const int last_tile = n_tiles - 1, last_key_in_tile = min(FWD_BN, u.n_keys - last_tile * FWD_BN) - 1;
   uint32_t ld_off[NLD], ld_off_last[NLD];
 #pragma unroll
   for (int n = 0; n < NLD; ++n) {
-    ld_off[n] = uint32_t(ld_row0 + 8 * RPI * n) * kv_row_bytes + ld_cbytes;
-    ld_off_last[n] = uint32_t(min(ld_row0 + 8 * RPI * n, last_key_in_tile)) * kv_row_bytes + ld_cbytes;
+    ld_off[n] = uint32_t(ld_row0 + W * RPI * n) * kv_row_bytes + ld_cbytes;
+    ld_off_last[n] = uint32_t(min(ld_row0 + W * RPI * n, last_key_in_tile)) * kv_row_bytes + ld_cbytes;
   }
   const char *kg = reinterpret_cast<const char *>(K + (size_t(u.kv_row0) * Hkv + hk) * D);
   const char *vg = reinterpret_cast<const char *>(V + (size_t(u.kv_row0) * Hkv + hk) * D);
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
     const char *base = src + size_t(last ? last_tile : tile) * tile_bytes;
     const uint32_t dst = lds0 + uint32_t(area + (tile % NST) * S::STAGE + 1024 * wave);
 #pragma unroll
-    for (int n = 0; n < NLD; ++n) load_lds16_sbase(base, last ? ld_off_last[n] : ld_off[n], dst + 8192 * n);
+    for (int n = 0; n < NLD; ++n) load_lds16_sbase(base, last ? ld_off_last[n] : ld_off[n], dst + 1024 * W * n);
   };
   issue_kv(kg, S::K_OFF, 0);
   issue_kv(vg, S::V_OFF, 0);
@@ -202,13 +204,21 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
   // inside the loop (they would drain the direct-load queue every iteration).
   wait_vmcnt<0>();
 #pragma unroll
-  for (int s = 0; s < NS; ++s) pin(qf[s]), pin(dof[s]);
+  for (int s = 0; s < NS; ++s) {
+    if (W == 8) pin(qf[s]), pin(dof[s]);
+    else pin_acc(qf[s]), pin_acc(dof[s]);
+  }
   pin(l2), pin(dl);
   // -Delta enters dP through the matrix pipe: one more k-step whose A fragment is 1 in two k-slots of every key row
   // and whose B fragment holds -Delta of the lane's query row split in two bf16 (hi + lo, 16 bits of mantissa) in
   // the same two slots.  One MFMA per 32 keys instead of 16 vector additions: this kernel is bound by its vector
   // ALU work (the exponentials run at quarter rate), not by the matrix pipe.
+  // (Workgroups of four waves share a register file with the dK/dV units of their launch and need its accumulation half:
+  // there the score tiles are assembly MFMAs with architectural results, and the dP chain starts from -Delta.)
   bf16x8 ones_f, dl_f;
+  f32x16 nd;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) nd[i] = dl;
   {
     const bf16_t hi = bf16_t(dl), lo = bf16_t(dl - float(hi));
 #pragma unroll
@@ -231,14 +241,24 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
         f32x16 sa, pa;
+        if constexpr (W == 8) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sa[i] = 0.f, pa[i] = 0.f;
+          for (int i = 0; i < 16; ++i) sa[i] = 0.f, pa[i] = 0.f;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          sa = mfma32(lds_read8_at(kt + koff[s] + 32 * kb * ROWB), qf[s], sa);
-          pa = mfma32(lds_read8_at(vt + koff[s] + 32 * kb * ROWB), dof[s], pa);
+          for (int s = 0; s < NS; ++s) {
+            sa = mfma32(lds_read8_at(kt + koff[s] + 32 * kb * ROWB), qf[s], sa);
+            pa = mfma32(lds_read8_at(vt + koff[s] + 32 * kb * ROWB), dof[s], pa);
+          }
+          pa = mfma32(ones_f, dl_f, pa);  // dP - Delta
+        } else {
+#pragma unroll
+          for (int s = 0; s < NS; ++s) {
+            const bf16x8 ka = lds_read8_at(kt + koff[s] + 32 * kb * ROWB), va = lds_read8_at(vt + koff[s] + 32 * kb * ROWB);
+            if (s == 0) mfma32_v_first(sa, ka, qf[0]), mfma32_v_first(pa, va, dof[0], nd);
+            else mfma32_v(sa, ka, qf[s]), mfma32_v(pa, va, dof[s]);
+          }
+          mfma_settle(sa, pa, nd);
         }
-        pa = mfma32(ones_f, dl_f, pa);  // dP - Delta
         uint32_t dw[8];
         // register i holds key j0 + 32 kb + 4 g + 8 (i / 4) + i % 4: visible iff 8 (i / 4) + i % 4 <= vis
         const int vis = pos - (j0 + 32 * kb + 4 * g);
@@ -277,7 +297,7 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
   }
   wait_vmcnt<0>();
   if (u.part >= 0) {  // a piece: the accumulators as they stand
-    float *dst = parts + size_t(u.part) * (FWD_BM * D) + wave * (32 * D) + 4 * lane;
+    float *dst = parts + size_t(u.part) * (FWD_BM * D) + pair * (32 * D) + 4 * lane;
 #pragma unroll
     for (int b = 0; b < NDB; ++b)
 #pragma unroll
@@ -296,10 +316,25 @@ __global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__rest
   });
 }
 
+template <int D>
+__global__ __launch_bounds__(512, 2) void ca_bwd_dq_kernel(const FwdUnit *__restrict__ units,
+                                                           const int32_t *__restrict__ slot_row,
+                                                           const int32_t *__restrict__ slot_pos,
+                                                           const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+                                                           const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
+                                                           const float *__restrict__ l2_slot,
+                                                           const float *__restrict__ delta_slot,
+                                                           bf16_t *__restrict__ dQ, float *__restrict__ parts, int Hq,
+                                                           int Hkv, int64_t padded, float scale) {
+  dq_workgroup<D, 8>(units[blockIdx.x], 0, slot_row, slot_pos, Q, K, V, dO, l2_slot, delta_slot, dQ, parts, Hq, Hkv, padded,
+                     scale);
+}
+
 // ------------------------------------------------------------------------------------------------ dK, dV
 template <int D>
 struct DkvSmem {
-  static constexpr int NST = 4;
+  static constexpr bool PIPE = D == 128;  // pipelined body, one workgroup per CU; plain body, two (see dkv_workgroup)
+  static constexpr int NST = PIPE ? 4 : 3;  // (without the pipeline two workgroups share a CU's LDS)
   static constexpr int TILE = BWD_BQ * 2 * D;       // one Q or dO tile of 64 slots
   static constexpr int Q_OFF = 0;
   static constexpr int DO_OFF = TILE;
@@ -324,6 +359,7 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
                                               bf16_t *__restrict__ dV, float *__restrict__ parts, int32_t *progress,
                                               int peer_stride, int Hq, int Hkv, int64_t padded, float scale) {
   using S = DkvSmem<D>;
+  constexpr bool PIPE = S::PIPE;
   constexpr int NS = D / 16, NDB = D / 32, CH = D / 8, RPI = 64 / CH, NST = S::NST;
   constexpr int NLD = BWD_BQ / (4 * RPI);  // direct loads per wave per Q (or dO) tile
   constexpr int RPW = BWD_BQ / 4;          // tile rows fetched by one wave (contiguous)
@@ -375,7 +411,8 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   const int n_it = n_blocks * Gu;
   // Query blocks are walked from the last one backwards (below), so the blocks that lie entirely below the
   // diagonal of this KV tile come first: they take the pipelined path without mask.
-  const int n_fast = ((u.slot_end - u.slot_full) / BWD_BQ) * Gu;
+  const int n_full = ((u.slot_end - u.slot_full) / BWD_BQ) * Gu;
+  const int n_fast = PIPE ? n_full : 0;  // ... where there is one
   // the stream goes on into the next unit / the next unit's K and V are fetched ahead (the loads go out before the
   // pipelined loop and are waited for, by the compiler, where the fragments change hands at the unit's end; the
   // loop's own waits count loads issued after them, so they can only wait longer.  Issued inside the loop, after its
@@ -497,9 +534,11 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   if (n_it > 0 && !cont) {
     issue_next();  // blocks 0 .. 3: four ahead; the last one is completed further down
     issue_next();
-    issue_next();
+    if (PIPE) {
+      issue_next();
 #pragma unroll
-    for (int i = 0; i < LP1; ++i) issue_piece(i);
+      for (int i = 0; i < LP1; ++i) issue_piece(i);
+    }
   }
 
   // resident K, V fragments of the wave's 32 keys (B operands of S = Q K^T and dP = dO V^T).  Keys past the
@@ -520,7 +559,10 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
     }
     wait_vmcnt<0>();
 #pragma unroll
-    for (int s = 0; s < NS; ++s) pin_acc(kf[s]), pin_acc(vf[s]);
+    for (int s = 0; s < NS; ++s) {
+      if (PIPE) pin_acc(kf[s]), pin_acc(vf[s]);
+      else pin(kf[s]), pin(vf[s]);
+    }
   }
   if (!cont) {
 #pragma unroll
@@ -581,7 +623,7 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   };
   constexpr int SUB = 32 * ROWB, HALF = 16 * ROWB;
   int it = 0;
-  if (n_fast > 0) {
+  if constexpr (PIPE) if (n_fast > 0) {
     f32x16 sc[2], dp[2];  // score tiles S and dP - Delta of sub-blocks k (even: [0], odd: [1])
     f32x16 ndt;           // -Delta of the 16 query rows of this lane (C operand layout), for the next dP chain
     f32x4 l2v[4];         // log2e*LSE of the 16 query rows of this lane, sub-block k
@@ -773,14 +815,95 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
     }
   }
 
-  if (n_it > 0 && !wrap) {  // complete the block whose first pieces were issued last
+  if (PIPE && n_it > 0 && !wrap) {  // complete the block whose first pieces were issued last
 #pragma unroll
     for (int i = LP1; i < LPI; ++i) issue_piece(i);
   }
   // ------------------------------------------------------------------------------------------------
-  // General path: blocks that straddle the diagonal (mask, skip of invisible sub-blocks).  One barrier before
+  // Plain path (head_dim 64).  A sub-block there is 16 MFMAs for the same vector work, and a lone wave per SIMD kept the
+  // matrix pipe busy 46 % of the time however its stream was pipelined.  The plain body needs half the registers (175) and,
+  // with three stages, half the LDS, so two workgroups share a CU and fill each other's waits.  Pipelined body against this
+  // one, dK/dV kernel: 2.42 -> 2.19 ms (16K-token document, 32/8 heads), 2.07 -> 1.68 ms (lone 64-row shards with contexts,
+  // 8/2 heads), 0.68 -> 0.48 ms (32K tokens of 600-token documents, 32/8 heads).  The loop over whole blocks and the one over
+  // the diagonal are apart on purpose: with both in one loop the accumulators were copied between the register files in
+  // every step.
+  if constexpr (!PIPE) {
+    // one sub-block of 32 rows; MASK: some row of the block does not see some key of the tile
+    auto sub_block = [&](int qb, const bool MASK) __attribute__((always_inline)) {
+      const int QT = S::Q_OFF + qb * SUB, DOT = S::DO_OFF + qb * SUB;
+      if (MASK) {  // entirely above the diagonal for this wave's keys? (slot positions are sorted)
+        const int sub_max_pos = lds_ld<int>(lds0 + stage * S::STAGE + S::POS_OFF + (32 * qb + 31) * 4);
+        if (sub_max_pos < u.key_pos0 + kw0) return;
+      }
+      f32x16 sa, pa;  // S, and dP - Delta: its chain starts from -Delta
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const f32x4 x = lds_ld<f32x4>(S::DL_OFF + (32 * qb + 8 * i4) * 4 + auxo);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pa[4 * i4 + e] = x[e];
+      }
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const bf16x8 qf = lds_read8_at(QT + qoff[s]), df = lds_read8_at(DOT + qoff[s]);
+        if (s == 0) mfma32_vv_first(sa, qf, kf[0]);
+        else mfma32_vv(sa, qf, kf[s]);
+        mfma32_vv(pa, df, vf[s]);
+      }
+      mfma_chain_end(sa, pa);
+      __builtin_amdgcn_sched_barrier(0);
+      f32x4 l2v[4];
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) l2v[i4] = lds_ld<f32x4>(S::L2_OFF + (32 * qb + 8 * i4) * 4 + auxo);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_settle(sa, pa);
+      uint32_t pw[8], dw[8];
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = fast_exp2(fmaf(sa[4 * i4 + e], c, -l2v[i4][e]));
+        if (MASK) {
+          const u32x4 pv = lds_ld<u32x4>(S::POS_OFF + (32 * qb + 8 * i4) * 4 + auxo);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[e] = key_pos <= int(pv[e]) ? p[e] : 0.f;
+        }
+        pw[2 * i4] = pack_bf16(p[0], p[1]);
+        pw[2 * i4 + 1] = pack_bf16(p[2], p[3]);
+        dw[2 * i4] = pack_bf16(p[0] * pa[4 * i4], p[1] * pa[4 * i4 + 1]);
+        dw[2 * i4 + 1] = pack_bf16(p[2] * pa[4 * i4 + 2], p[3] * pa[4 * i4 + 3]);
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const bf16x8 pb = __builtin_bit_cast(bf16x8, u32x4{pw[4 * t], pw[4 * t + 1], pw[4 * t + 2], pw[4 * t + 3]});
+        const bf16x8 db = __builtin_bit_cast(bf16x8, u32x4{dw[4 * t], dw[4 * t + 1], dw[4 * t + 2], dw[4 * t + 3]});
+        const int ro = t * HALF;
+#pragma unroll
+        for (int b = 0; b < NDB; ++b) {
+          const bf16x8 dot_t = join(lds_read_tr4_at(DOT + ro + toff[0][b]), lds_read_tr4_at(DOT + ro + toff[1][b]));
+          acc_dv[b] = mfma32(dot_t, pb, acc_dv[b]);
+          const bf16x8 q_t = join(lds_read_tr4_at(QT + ro + toff[0][b]), lds_read_tr4_at(QT + ro + toff[1][b]));
+          acc_dk[b] = mfma32(q_t, db, acc_dk[b]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto step = [&](const bool MASK) __attribute__((always_inline)) {
+      wait_vmcnt<(NST - 2) * LPI>();  // block `it` has landed (this wave's part); block it+1 may be in flight
+      barrier_nofence();              // ... and everybody else's; everybody is done with block it-1
+      issue_next();                   // block it+2 into its stage
+      sub_block(0, MASK);
+      __builtin_amdgcn_sched_barrier(0);
+      sub_block(1, MASK);
+      advance_q();
+      advance_t();
+    };
+    for (; it < n_full; ++it) step(false);
+    for (; it < n_it; ++it) step(true);
+  }
+  // ------------------------------------------------------------------------------------------------
+  // General path (head_dim 128): blocks that straddle the diagonal (mask, skip of invisible sub-blocks).  One barrier before
   // and one after the compute, then the refill of this stage.
-  for (; it < n_it; ++it) {
+  if constexpr (PIPE) for (; it < n_it; ++it) {
     wait_vmcnt<3 * LPI>();  // block `it` has landed (this wave's part); blocks it+1 .. it+3 may be in flight
     barrier_nofence();
 #pragma unroll
@@ -908,7 +1031,24 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
 // Units that run alone and chains of short units in one launch, so that the dispatcher hands them out longest first
 // whatever they are.
 template <int D>
-__global__ __launch_bounds__(256, 1) void ca_bwd_dkv_kernel(const BwdUnit *__restrict__ units, int n_single,
+__device__ __forceinline__ void dkv_unit_or_chain(const BwdUnit *__restrict__ units, int n_single,
+                                                  const int32_t *__restrict__ slot_pos, const bf16_t *__restrict__ Qs,
+                                                  const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
+                                                  const bf16_t *__restrict__ dOs, const float *__restrict__ l2_slot,
+                                                  const float *__restrict__ delta_slot, bf16_t *__restrict__ dK,
+                                                  bf16_t *__restrict__ dV, float *__restrict__ parts, int32_t *progress,
+                                                  int peer_stride, int Hq, int Hkv, int64_t padded, float scale) {
+  const int me = int(blockIdx.x);  // index of the workgroup = index of its first unit
+  const BwdUnit first = units[me];
+  if (first.count <= 1)
+    dkv_workgroup<D, false>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
+                                  progress, peer_stride, Hq, Hkv, padded, scale);
+  else
+    dkv_workgroup<D, true>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
+                                 progress, peer_stride, Hq, Hkv, padded, scale);
+}
+template <int D>
+__global__ __launch_bounds__(256, D == 128 ? 1 : 2) void ca_bwd_dkv_kernel(const BwdUnit *__restrict__ units, int n_single,
                                                             const int32_t *__restrict__ slot_pos,
                                                             const bf16_t *__restrict__ Qs, const bf16_t *__restrict__ K,
                                                             const bf16_t *__restrict__ V, const bf16_t *__restrict__ dOs,
@@ -918,14 +1058,38 @@ __global__ __launch_bounds__(256, 1) void ca_bwd_dkv_kernel(const BwdUnit *__res
                                                             float *__restrict__ parts, int32_t *progress,
                                                             int peer_stride, int Hq, int Hkv, int64_t padded,
                                                             float scale) {
-  const int me = int(blockIdx.x);  // index of the workgroup = index of its first unit
-  const BwdUnit first = units[me];
-  if (first.count <= 1)
-    dkv_workgroup<D, false>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
-                            progress, peer_stride, Hq, Hkv, padded, scale);
+  dkv_unit_or_chain<D>(units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts, progress,
+                             peer_stride, Hq, Hkv, padded, scale);
+}
+
+// dK/dV units (the first n_dkv workgroups) and dQ half units (workgroups of 4 groups of 32 rows, the later halves first) in
+// one launch.  For batches too small to fill the chip with either kernel: what a launch takes there is mostly its fixed
+// part, and the dQ work finds CUs that the dK/dV units leave idle.  Measured, forward + backward, two launches against one:
+// 70 -> 51 us (384 rows, 8/1 heads, head_dim 128), 48 -> 38 us (1.5K tokens, 4/2 heads, head_dim 64), 1006 -> 806 us (12K
+// tokens of long documents, 8/2 heads, where the two kernels' last units leave CUs idle one after the other); on batches
+// that fill the chip the half units cost 8 to 10 % of the pass, so the planner decides by a simulation of both.
+struct JointArgs {
+  const BwdUnit *units;
+  const FwdUnit *dq_units;
+  const int32_t *slot_row, *slot_pos, *pos_kv;
+  const bf16_t *q, *k, *v, *d_o, *q_sorted, *do_sorted;
+  const float *l2_slot, *delta_slot, *l2_kv, *delta_kv;
+  bf16_t *dq, *dk, *dv;
+  float *parts_dq, *parts_kv;
+  int32_t *progress;
+  int n_dkv, n_single, n_dq, peer_stride, hq, hkv;
+  int64_t padded;
+  float scale;
+};
+template <int D>
+__global__ __launch_bounds__(256, D == 128 ? 1 : 2) void ca_bwd_joint_kernel(const JointArgs a) {
+  const int b = int(blockIdx.x) - a.n_dkv;
+  if (b < 0)
+    dkv_unit_or_chain<D>(a.units, a.n_single, a.pos_kv, a.q_sorted, a.k, a.v, a.do_sorted, a.l2_kv, a.delta_kv,
+                                   a.dk, a.dv, a.parts_kv, a.progress, a.peer_stride, a.hq, a.hkv, a.padded, a.scale);
   else
-    dkv_workgroup<D, true>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
-                           progress, peer_stride, Hq, Hkv, padded, scale);
+    dq_workgroup<D, 4>(a.dq_units[b < a.n_dq ? b : b - a.n_dq], b < a.n_dq ? 1 : 0, a.slot_row, a.slot_pos, a.q, a.k, a.v,
+                       a.d_o, a.l2_slot, a.delta_slot, a.dq, a.parts_dq, a.hq, a.hkv, a.padded, a.scale);
 }
 
 // Adds up the pieces of the cut units: dQ of the forward / dQ units (from parts_dq; 8 groups of 32 rows), then dK and dV of
@@ -1024,12 +1188,30 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
                        progress, n_progress, padded, p->total_q, p->hq, p->hq / p->hkv, D);
   }
   if (ev) (void)hipEventRecord(ev[1], st);
-  if (!p->bwd_units.empty()) {
-    auto kern = ca_bwd_dkv_kernel<D>;
+  const FwdUnit *const dq_list = parts_dq ? p->d_fwd_pieces : p->d_fwd_units;
+  const int n_dq = int(parts_dq ? p->fwd_pieces.size() : p->fwd_units.size());
+  // (with timing enabled the two kernels are launched one by one, so that each has a time)
+  const bool joint = p->joint && !ev && (split || p->n_fwd_parts + p->n_bwd_parts == 0);
+  if (joint) {
+    auto kern = ca_bwd_joint_kernel<D>;
+    constexpr int SMEM = std::max(DkvSmem<D>::TOTAL, DqSmem<D>::TOTAL);
     static std::atomic<bool> done[16];
-    hipError_t e = set_smem(kern, DkvSmem<D>::TOTAL, p->device, done);
+    hipError_t e = set_smem(kern, SMEM, p->device, done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(unsigned(n_dkv)), dim3(256), DkvSmem<D>::TOTAL, st,
+    const JointArgs args = {parts_kv ? p->d_bwd_pieces : p->d_bwd_units, dq_list, p->d_slot_row, p->d_slot_pos, p->d_pos_kv,
+                            static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v),
+                            static_cast<const bf16_t *>(d_o), q_sorted, do_sorted, l2_slot, delta_slot, l2_kv, delta_kv,
+                            static_cast<bf16_t *>(dq), static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_dq,
+                            parts_kv, progress, n_dkv, parts_kv ? p->bwd_piece_single : p->bwd_single, n_dq,
+                            p->peer_stride, p->hq, p->hkv, padded, p->scale};
+    hipLaunchKernelGGL(kern, dim3(unsigned(n_dkv + 2 * n_dq)), dim3(256), SMEM, st, args);
+  } else if (!p->bwd_units.empty()) {
+    auto kern = ca_bwd_dkv_kernel<D>;
+    constexpr int SMEM = DkvSmem<D>::TOTAL;
+    static std::atomic<bool> done[16];
+    hipError_t e = set_smem(kern, SMEM, p->device, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(unsigned(n_dkv)), dim3(256), SMEM, st,
                        parts_kv ? p->d_bwd_pieces : p->d_bwd_units, parts_kv ? p->bwd_piece_single : p->bwd_single,
                        p->d_pos_kv, q_sorted, static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), do_sorted,
                        l2_kv, delta_kv, static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_kv, progress,
@@ -1037,13 +1219,12 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
   }
   if (p->shared_parts) combine(false, true);  // before the dQ pieces write over them
   if (ev) (void)hipEventRecord(ev[2], st);
-  if (!p->fwd_units.empty()) {
+  if (n_dq > 0 && !joint) {
     auto kern = ca_bwd_dq_kernel<D>;
     static std::atomic<bool> done[16];
     hipError_t e = set_smem(kern, DqSmem<D>::TOTAL, p->device, done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(unsigned(parts_dq ? p->fwd_pieces.size() : p->fwd_units.size())), dim3(512),
-                       DqSmem<D>::TOTAL, st, parts_dq ? p->d_fwd_pieces : p->d_fwd_units, p->d_slot_row, p->d_slot_pos,
+    hipLaunchKernelGGL(kern, dim3(unsigned(n_dq)), dim3(512), DqSmem<D>::TOTAL, st, dq_list, p->d_slot_row, p->d_slot_pos,
                        static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v),
                        static_cast<const bf16_t *>(d_o), l2_slot, delta_slot, static_cast<bf16_t *>(dq), parts_dq, p->hq,
                        p->hkv, padded, p->scale);

@@ -207,6 +207,17 @@ __device__ __forceinline__ void mfma32_v(f32x16 &d, bf16x8 a, bf16x8 b_acc) {
                : "+v"(d)
                : "v"(__builtin_bit_cast(u32x4, a)), "a"(__builtin_bit_cast(u32x4, b_acc)));
 }
+// the same with the B operand in architectural registers too
+__device__ __forceinline__ void mfma32_vv_first(f32x16 &d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0"
+               : "=&v"(d)
+               : "v"(__builtin_bit_cast(u32x4, a)), "v"(__builtin_bit_cast(u32x4, b)));
+}
+__device__ __forceinline__ void mfma32_vv(f32x16 &d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+               : "+v"(d)
+               : "v"(__builtin_bit_cast(u32x4, a)), "v"(__builtin_bit_cast(u32x4, b)));
+}
 __device__ __forceinline__ void mfma_settle(f32x16 &x, f32x16 &y) { asm volatile("s_nop 11" : "+v"(x), "+v"(y)); }
 // same; `c` was the C operand of the chain's first MFMA: keeping it an operand here keeps its registers from being
 // reused (and overwritten by an LDS read in flight) while that MFMA may still be reading them
@@ -237,6 +248,8 @@ __device__ __forceinline__ void scale_acc(f32x16 &d, float f) {
   }
   asm volatile("s_nop 4" : "+a"(d));
 }
+// same, where the wait states (mfma_settle) follow after a few other instructions
+__device__ __forceinline__ void mfma_chain_end(f32x16 &x, f32x16 &y) { asm volatile("; chain end" : "+v"(x), "+v"(y)); }
 __device__ __forceinline__ void pin(float &v) { asm volatile("" : "+v"(v)); }
 // exp2(x * c - g) as one volatile asm statement: like pin() it stays where it is written in the instruction stream
 // (between the MFMAs of its slot), but without the wait state the compiler puts between an empty asm that "defines"

@@ -102,6 +102,7 @@ struct ca_plan {
   int32_t n_fwd_parts = 0, n_bwd_parts = 0;
   // workspace with which the piece lists are used: forward, and backward, where the parts lie behind ws_bwd
   size_t ws_fwd_split = 0, ws_bwd_split = 0, ws_off_parts_kv = 0, ws_off_parts_dq = 0;
+  bool joint = false;      // backward runs dK/dV and dQ units in one launch
   bool shared_parts = false;  // the dQ parts take the place of the dK/dV parts once those have been added up
   // workspace layout for backward: [Delta fp32 hq*padded_slots][log2e*LSE fp32 hq*padded_slots]
   int slot_align = ca::SLOT_ALIGN, heads_packed = 1;  // padding of a document's slots; hp of the packed units

@@ -103,45 +103,49 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // read once more to be added up) and another launch.  The T with the shortest total is taken, if it gains a tenth: at
 // 4K tokens of 1K-token documents (32/8 heads) the simulation gives 362 us for the dK/dV kernel's 256 whole units (measured
 // 325) and 210 us for 504 pieces of at most 60 steps.
-// The figures are microseconds measured on MI355X: per step 1.7 (forward), 2.6 (dQ) and 1.75 (dK/dV) at head_dim 128, 1.2,
-// 1.3 and 0.9 at 64; the fixed part is what a unit spends around its steps (descriptor, row indices, fragments, first
-// tiles, drain, results); partial results move at about 4 TB/s.
+// The figures are microseconds measured on MI355X: per step 1.7 (forward), 2.6 (dQ) and 1.75 (dK/dV) at head_dim 128, 1.0,
+// 1.5 and 1.1 at 64; the fixed part is what a unit spends around its steps (descriptor, row indices, fragments, first
+// tiles, drain, results); partial results move at about 4 TB/s.  Two dK/dV workgroups share a CU at head_dim 64, each at
+// half the pace.
 constexpr int N_CU = 256;
+constexpr double JOINT_MAX_US = 1000;  // batches beyond this fill the chip with either kernel
 struct CutCost {
+  int slots;  // workgroups that run at a time
   double per_step, fixed, launch;
   int min_steps;
 };
+
+// When the last of `units` ((microseconds, how many), handed out in this order) ends on n_cu CUs, or a time of at least
+// at_most.
+double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_cu, double at_most) {
+  std::vector<double> busy(size_t(n_cu), 0.0);  // a heap, the least loaded CU first
+  double end = 0;
+  for (const auto &[us, n] : units)
+    for (int64_t i = 0; i < n; ++i) {
+      std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+      busy.back() += us;
+      end = std::max(end, busy.back());
+      if (end >= at_most) return end;
+      std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+    }
+  return end;
+}
 
 // units: (steps, how many of that size), longest first.  Returns the longest piece in steps, 0 to cut nothing.
 int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const CutCost &c, size_t bytes_per_part,
                    size_t max_bytes) {
   constexpr double BYTES_PER_US = 4e6;
   double total = 0, steps_per_cu = 0;
-  int64_t longest = 0, same = N_CU;  // `same`: every size comes a multiple of this many times
+  int64_t longest = 0, same = c.slots;  // `same`: every size comes a multiple of this many times
   for (const auto &[steps, count] : units) {
     total += double(count) * (c.fixed + c.per_step * double(steps));
-    steps_per_cu += double(count) * double(steps) / N_CU;
+    steps_per_cu += double(count) * double(steps) / c.slots;
     longest = std::max(longest, steps);
     same = std::gcd(same, count);
   }
   // no list of pieces can beat the mean load: most batches end here
-  if (c.fixed + c.per_step * double(longest) < 1.2 * total / N_CU) return 0;
+  if (c.fixed + c.per_step * double(longest) < 1.2 * total / c.slots) return 0;
   std::vector<std::pair<double, int64_t>> sizes;  // (microseconds, how many / same)
-  std::vector<double> busy;
-  auto makespan = [&](double at_most) {  // of `sizes`; gives up beyond at_most
-    std::sort(sizes.begin(), sizes.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
-    busy.assign(size_t(N_CU / same), 0.0);  // a heap, the least loaded CU first
-    double end = 0;
-    for (const auto &[us, n] : sizes)
-      for (int64_t i = 0; i < n; ++i) {
-        std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
-        busy.back() += us;
-        end = std::max(end, busy.back());
-        if (end >= at_most) return end;
-        std::push_heap(busy.begin(), busy.end(), std::greater<double>());
-      }
-    return end;
-  };
   double best = 0;
   int64_t best_t = 0;
   int worse = 0;
@@ -160,8 +164,9 @@ int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const 
     }
     const size_t bytes = size_t(parts) * bytes_per_part;
     const double extra = parts ? c.launch + double(bytes) / BYTES_PER_US : 0.0;
-    if (parts && (bytes > max_bytes || sum / N_CU + extra >= best)) break;  // more and smaller pieces only cost more
-    const double us = makespan(parts ? best - extra : 1e30) + extra;
+    if (parts && (bytes > max_bytes || sum / c.slots + extra >= best)) break;  // more and smaller pieces only cost more
+    std::sort(sizes.begin(), sizes.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+    const double us = makespan(sizes, c.slots / same, parts ? best - extra : 1e30) + extra;
     if (!parts) best = 0.9 * us;
     else if (us < best) best = us, best_t = t, worse = 0;
     else if (++worse == 3) break;
@@ -314,6 +319,9 @@ void schedule(ca_plan_t *p) {
   // needs at most this much more.
   constexpr size_t MAX_CUT_BYTES = size_t(256) << 20;
   size_t cut_budget = 0;
+  const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.75, 12.0, 5.0, 4} : CutCost{2 * N_CU, 2.0, 14.0, 5.0, 4};
+  const CutCost cost_fwd = {N_CU, p->d == 128 ? 2.1 : 1.25, 9.0, 5.0, 4};
+  std::vector<int64_t> wg_steps;  // of the dK/dV kernel's workgroups of one KV head, as they are launched
   p->bwd_steps = 0;
   for (auto &t : btiles) p->bwd_steps += int64_t(t.slot_end - t.slot_begin) / BWD_BQ * t.heads * hkv;
   {
@@ -357,6 +365,8 @@ void schedule(ca_plan_t *p) {
       units.reserve(tiles.size() * hkv);
       units.resize(size_t(workgroups));
       single = int32_t(first_chain * hkv);
+      wg_steps.clear();
+      for (auto &c : list) wg_steps.push_back(c.steps);
       for (size_t ci = 0; ci < list.size(); ++ci) {
         const size_t a = list[ci].a, b = list[ci].b;
         for (int h = 0; h < hkv; ++h) {
@@ -383,7 +393,6 @@ void schedule(ca_plan_t *p) {
       if (!sizes.empty() && sizes.back().first == c.steps) sizes.back().second += hkv;
       else sizes.push_back({c.steps, hkv});
     }
-    const CutCost cost_dkv = {p->d == 128 ? 1.75 : 0.9, 12.0, 5.0, 4};
     const int64_t T = best_piece(sizes, cost_dkv, part_bytes(p->d), cut_budget - std::min<size_t>(cut_budget, 1 << 16));
     if (T > 0) {
       std::vector<BwdUnit> tiles;
@@ -423,7 +432,6 @@ void schedule(ca_plan_t *p) {
       if (!sizes.empty() && sizes.back().first == t.cost) sizes.back().second += hq / t.u.hp;
       else sizes.push_back({t.cost, hq / t.u.hp});
     }
-    const CutCost cost_fwd = {p->d == 128 ? 2.1 : 1.25, 9.0, 5.0, 4};
     const int64_t T = best_piece(sizes, cost_fwd, part_bytes(p->d) + FWD_STAT_BYTES, cut_budget - std::min<size_t>(cut_budget, 1 << 16));
     if (T > 0) {
       std::vector<TileRef> pieces;
@@ -456,6 +464,33 @@ void schedule(ca_plan_t *p) {
         }
     }
   }
+  {
+    // One launch or two for the backward.  The dQ kernel proper runs 256 rows per workgroup, two waves per SIMD; in the
+    // joint launch a workgroup is four waves of 32 rows, which costs more per row (1.6 us per tile of 128 rows against 2.6 of
+    // 256 at head_dim 128, where they have a SIMD each) but fills the CUs that too few dK/dV units leave idle, and saves a launch.
+    const int slots = cost_dkv.slots;
+    double mean = 0;
+    for (int64_t s : wg_steps) mean += (cost_dkv.fixed + cost_dkv.per_step * double(s)) * hkv / slots;
+    if (!wg_steps.empty() && !p->fwd_units.empty() && mean < JOINT_MAX_US) {
+      std::vector<std::pair<double, int64_t>> all, dq;
+      const int64_t same = std::gcd<int64_t>(N_CU, std::gcd(hkv, hq / hp));
+      for (int64_t s : wg_steps) all.push_back({cost_dkv.fixed + cost_dkv.per_step * double(s), hkv / same});
+      const double per = p->d == 128 ? 2.6 : 1.5, per_half = p->d == 128 ? 1.6 : 1.7;
+      const double dkv_us = makespan(all, slots / same, 1e30);
+      size_t first_half = all.size();
+      for (const FwdUnit &u : p->fwd_pieces.empty() ? p->fwd_units : p->fwd_pieces) {
+        const double tiles = double((u.n_keys + FWD_BN - 1) / FWD_BN);
+        if (!dq.empty() && dq.back().first == cost_fwd.fixed + per * tiles) ++dq.back().second, ++all.back().second;
+        else dq.push_back({cost_fwd.fixed + per * tiles, 1}), all.push_back({cost_fwd.fixed + per_half * tiles, 1});
+      }
+      for (auto &x : dq) x.second = (x.second + same - 1) / same;
+      for (size_t i = first_half; i < all.size(); ++i) all[i].second = (all[i].second + same - 1) / same;
+      const double apart = dkv_us + makespan(dq, N_CU / same, 1e30) + cost_dkv.launch;
+      const size_t n = all.size();
+      for (size_t i = first_half; i < n; ++i) all.push_back(all[i]);
+      p->joint = makespan(all, slots / same, apart) < apart;
+    }
+  }
   // workspace with which the piece lists are used
   if (p->n_fwd_parts > 0) p->ws_fwd_split = size_t(p->n_fwd_parts) * (part_bytes(p->d) + FWD_STAT_BYTES);
   p->ws_bwd_split = p->ws_bwd;
@@ -468,7 +503,8 @@ void schedule(ca_plan_t *p) {
     p->ws_off_parts_kv = p->ws_off_parts_dq = at;
     const size_t kv = size_t(p->n_bwd_parts) * part_bytes(p->d), dq = size_t(p->n_fwd_parts) * part_bytes(p->d);
     p->shared_parts = kv > 0 && dq > 0 && at - p->ws_bwd + kv + dq > cut_budget;
-    if (!p->shared_parts) p->ws_off_parts_dq += kv;
+    if (p->shared_parts) p->joint = false;
+    else p->ws_off_parts_dq += kv;
     p->ws_bwd_split = std::max(p->ws_off_parts_kv + kv, p->ws_off_parts_dq + dq);
   }
   p->q_covered = covered_q == p->total_q;
@@ -557,11 +593,12 @@ int ca_plan_info(const ca_plan_t *p, int64_t *out, int n) {
   if (!p) return 0;
   int64_t full_tiles = 0;
   for (auto &u : p->fwd_units) full_tiles += u.hp == 1 && u.head == 0;
-  const int64_t v[13] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
+  const int64_t v[14] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
                          ca::BWD_BN, int64_t(p->bwd_units.size()), ca::FWD_BN, int64_t(p->slot_row.size()),
-                         p->fwd_steps, p->bwd_steps, ca::BWD_BQ, p->slot_align, p->heads_packed, p->bwd_workgroups};
-  for (int i = 0; i < n && i < 13 && out; ++i) out[i] = v[i];
-  return 13;
+                         p->fwd_steps, p->bwd_steps, ca::BWD_BQ, p->slot_align, p->heads_packed, p->bwd_workgroups,
+                         p->joint};
+  for (int i = 0; i < n && i < 14 && out; ++i) out[i] = v[i];
+  return 14;
 }
 
 int64_t ca_plan_rows(const ca_plan_t *p, int32_t *rows, int32_t *pos) {

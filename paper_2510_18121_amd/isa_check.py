@@ -13,6 +13,10 @@ and verifies, instruction by instruction:
 2. Transcendentals (`check_trans_use`): the instruction directly after a `v_exp_f32` (and its kin) does not read its
    result unless it is itself a transcendental or an `s_nop` (one wait state is required on this architecture).
 
+3. Operands of assembly MFMAs (`check_mfma_operands`): no vector instruction within two wait states before one writes a
+   register it reads.  Between VALU writes and builtin MFMAs the compiler places those wait states itself; where it has to
+   copy an operand between the register files in front of an assembly MFMA it does not.
+
     python -m paper_2510_18121_amd.isa_check            # compiles csrc/ca_bwd.hip and csrc/ca_fwd.hip, prints findings
 """
 from __future__ import annotations
@@ -123,6 +127,42 @@ def check_mfma_chains(asm: str):
     return n, marks, bad
 
 
+def check_mfma_operands(asm: str):
+    """Returns (number of MFMAs in inline assembly, list of findings)."""
+    def regs(text):
+        out = set()
+        for m in re.finditer(r"\b([va])\[(\d+):(\d+)\]|\b([va])(\d+)\b", text):
+            if m.group(1):
+                out.update((m.group(1), i) for i in range(int(m.group(2)), int(m.group(3)) + 1))
+            else:
+                out.add((m.group(4), int(m.group(5))))
+        return out
+
+    ins, inside = [], False
+    for line in asm.split("\n"):
+        t = line.strip()
+        if t.startswith((";;#ASMSTART", ";;#ASMEND")):
+            inside = t.startswith(";;#ASMSTART")
+            continue
+        t = t.split(";")[0].strip()
+        if t and not t.endswith(":") and not t.startswith("."):
+            ins.append((t, inside))
+    n, bad = 0, []
+    for i, (t, in_asm) in enumerate(ins):
+        if not in_asm or not t.startswith("v_mfma"):
+            continue
+        n += 1
+        reads, waited = regs(t.split(",", 1)[1]), 0
+        for p, _ in reversed(ins[max(0, i - 2):i]):
+            if waited >= 2:
+                break
+            if p.startswith("v_") and not p.startswith("v_mfma") and regs(p.split(None, 1)[1].split(",")[0]) & reads:
+                bad.append((p, t))
+            m = re.match(r"s_nop (\d+)", p)
+            waited += int(m.group(1)) + 1 if m else 1
+    return n, bad
+
+
 def check_trans_use(asm: str):
     """Returns (number of transcendental instructions, list of findings)."""
     ins = []
@@ -155,7 +195,12 @@ def main():
     status = 0
     for src in ("ca_bwd.hip", "ca_fwd.hip"):
         asm = compile_to_asm(src)
-        for body in kernel_bodies(asm, "ca_bwd_dkv_kernel") + kernel_bodies(asm, "ca_fwd_kernel"):
+        no, bado = check_mfma_operands(asm)
+        print(f"{src}: {no} assembly MFMAs, {len(bado)} findings on their operands")
+        for f in bado:
+            print("  ", *f)
+        status |= bool(bado)
+        for body in sum((kernel_bodies(asm, k) for k in ("ca_bwd_dkv_kernel", "ca_bwd_joint_kernel", "ca_fwd_kernel")), []):
             n, marks, bad = check_mfma_chains(body)
             print(f"{src}: {body.split(':')[0]}: {n} hand-written MFMA chains, {marks} chain-end markers, "
                   f"{len(bad)} findings")

@@ -68,6 +68,28 @@ def test_pieces_match_the_oracle_and_whole_units(name):
         assert torch.equal(more[n], cut[n]), n
 
 
+@pytest.mark.parametrize("hq,hkv,d,shards", [(4, 2, 128, [(0, 300)]), (3, 1, 64, [(0, 65), (100, 31)]), (8, 1, 128, [(40, 1)]),
+                                             (16, 2, 64, [(0, 200), (37, 500)]), (6, 2, 128, [(500, 16), (3, 129)]),
+                                             (4, 1, 64, [(1000, 20)])])
+def test_joint_backward_matches_separate_launches(hq, hkv, d, shards):
+    """Small batches run dK/dV and dQ units in one launch (dQ units in halves of 128 rows: all head packings, halves that
+    see fewer keys than their unit, rows that fill no half); with timing enabled the two kernels are launched one by one."""
+    b = W.custom([a + n for a, n in shards], [(i, a, n) for i, (a, n) in enumerate(shards)], hq, hkv, d, seed=92)
+    t = W.make_tensors(b, DEV)
+    plan = B.ca_plan(b)
+    assert plan.info()["joint_backward"] == 1
+    joint = P.run_hip(b, *t, plan=plan)
+    plan.profile_enable(True)
+    apart = P.run_hip(b, *t, plan=plan)
+    plan.profile_enable(False)
+    ref = P.run_oracle(b, *t)
+    for r, tag in ((joint, "joint"), (apart, "apart")):
+        e = P.errors(r, ref)
+        print(hq, hkv, d, tag, e, flush=True)
+        P.assert_parity(e, tag)
+    assert torch.equal(joint["dk"], apart["dk"]) and torch.equal(joint["dv"], apart["dv"])
+
+
 def test_pieces_at_scores_that_outgrow_the_reference():
     """A piece whose scores leave the finite range is repeated by the general path; its weight dominates the others'."""
     b = W.custom([4000], [(0, 3800, 200)], 2, 1, 128, seed=91, scale=1.0)

@@ -1,0 +1,32 @@
+"""Static checks of the generated assembly: operands of assembly MFMAs in all kernels, and the MFMA chains of the kernel that
+runs dK/dV and dQ units in one launch (no GPU)."""
+import os
+
+import pytest
+
+from paper_2510_18121_amd import isa_check as C
+
+pytestmark = pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")),
+                                reason="hipcc is needed to produce the assembly")
+
+
+@pytest.mark.parametrize("source", ["ca_bwd.hip", "ca_fwd.hip"])
+def test_operands_of_assembly_mfmas_are_settled(source):
+    asm = C.compile_to_asm(source)
+    n, bad = C.check_mfma_operands(asm)
+    assert n > 100 and not bad, bad
+    for body in C.kernel_bodies(asm, "ca_bwd_joint_kernel"):
+        chains, _, found = C.check_mfma_chains(body)
+        assert chains >= 10 and not found, found  # dK/dV bodies and the dQ body
+        assert "scratch_" not in body
+
+
+def test_planted_copies_in_front_of_an_mfma_are_found():
+    mfma = "\t;;#ASMSTART\n\tv_mfma_f32_32x32x16_bf16 v[0:15], v[40:43], a[64:67], v[0:15]\n\t;;#ASMEND\n"
+    far = "\tv_accvgpr_write_b32 a67, v9\n\ts_nop 1\n" + mfma
+    assert C.check_mfma_operands(far) == (1, [])
+    assert len(C.check_mfma_operands("\tv_accvgpr_write_b32 a67, v9\n" + mfma)[1]) == 1
+    assert len(C.check_mfma_operands("\tv_accvgpr_write_b32 a67, v9\n\ts_nop 0\n" + mfma)[1]) == 1
+    assert len(C.check_mfma_operands("\tv_mov_b32_e32 v3, v9\n" + mfma)[1]) == 1
+    assert C.check_mfma_operands("\tv_mov_b32_e32 v33, v9\n" + mfma) == (1, [])
+    assert C.check_mfma_operands("\tv_mov_b32_e32 v3, v9\n" + mfma.replace(";;#ASMSTART", "").replace(";;#ASMEND", "")) == (0, [])
