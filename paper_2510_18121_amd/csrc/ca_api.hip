@@ -63,6 +63,7 @@ static void free_device(ca_plan_t *p) {
   if (p->d_blob) (void)hipFree(p->d_blob);
   p->d_blob = nullptr;
   p->d_slot_row = p->d_slot_pos = p->d_block_rpk = p->d_pos_kv = nullptr;
+  p->d_joint_order = nullptr;
   p->d_fwd_units = p->d_fwd_pieces = nullptr;
   p->d_bwd_units = p->d_bwd_pieces = nullptr;
   p->d_fwd_combine = p->d_bwd_combine = nullptr;
@@ -122,9 +123,9 @@ int ca_plan_upload(ca_plan_t *p, void *hip_stream) {
     bytes = (bytes + src.size() * sizeof(src[0]) + 255) / 256 * 256;
     return at;
   };
-  const size_t at[10] = {place(p->slot_row),    place(p->slot_pos),   place(p->block_rpk),   place(p->pos_kv),
+  const size_t at[11] = {place(p->slot_row),    place(p->slot_pos),   place(p->block_rpk),   place(p->pos_kv),
                          place(p->fwd_units),   place(p->bwd_units),  place(p->fwd_pieces),  place(p->bwd_pieces),
-                         place(p->fwd_combine), place(p->bwd_combine)};
+                         place(p->fwd_combine), place(p->bwd_combine), place(p->joint_order)};
   if (bytes == 0) return CA_OK;
   try {
     p->blob.assign(bytes, 0);
@@ -149,6 +150,7 @@ int ca_plan_upload(ca_plan_t *p, void *hip_stream) {
   put(p->fwd_units, p->d_fwd_units, at[4]), put(p->bwd_units, p->d_bwd_units, at[5]);
   put(p->fwd_pieces, p->d_fwd_pieces, at[6]), put(p->bwd_pieces, p->d_bwd_pieces, at[7]);
   put(p->fwd_combine, p->d_fwd_combine, at[8]), put(p->bwd_combine, p->d_bwd_combine, at[9]);
+  put(p->joint_order, p->d_joint_order, at[10]);
   if ((e = hipMemcpyAsync(p->d_blob, p->blob.data(), bytes, hipMemcpyHostToDevice, st)) != hipSuccess) {
     free_device(p);
     return hip_fail("plan upload", e);

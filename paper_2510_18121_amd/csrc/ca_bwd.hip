@@ -1037,8 +1037,8 @@ __device__ __forceinline__ void dkv_unit_or_chain(const BwdUnit *__restrict__ un
                                                   const bf16_t *__restrict__ dOs, const float *__restrict__ l2_slot,
                                                   const float *__restrict__ delta_slot, bf16_t *__restrict__ dK,
                                                   bf16_t *__restrict__ dV, float *__restrict__ parts, int32_t *progress,
-                                                  int peer_stride, int Hq, int Hkv, int64_t padded, float scale) {
-  const int me = int(blockIdx.x);  // index of the workgroup = index of its first unit
+                                                  int peer_stride, int Hq, int Hkv, int64_t padded, float scale,
+                                                  const int me /* index of the workgroup = index of its first unit */) {
   const BwdUnit first = units[me];
   if (first.count <= 1)
     dkv_workgroup<D, false>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
@@ -1059,16 +1059,16 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void ca_bwd_dkv_kernel(const
                                                             int peer_stride, int Hq, int Hkv, int64_t padded,
                                                             float scale) {
   dkv_unit_or_chain<D>(units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts, progress,
-                             peer_stride, Hq, Hkv, padded, scale);
+                       peer_stride, Hq, Hkv, padded, scale, int(blockIdx.x));
 }
 
-// dK/dV units (the first n_dkv workgroups) and dQ half units (workgroups of 4 groups of 32 rows, the later halves first) in
-// one launch.  For batches too small to fill the chip with either kernel: what a launch takes there is mostly its fixed
+// dK/dV units and dQ half units (workgroups of 4 groups of 32 rows) in one launch, longest first.  For batches too small to fill the chip with either kernel: what a launch takes there is mostly its fixed
 // part, and the dQ work finds CUs that the dK/dV units leave idle.  Measured, forward + backward, two launches against one:
 // 70 -> 51 us (384 rows, 8/1 heads, head_dim 128), 48 -> 38 us (1.5K tokens, 4/2 heads, head_dim 64), 1006 -> 806 us (12K
 // tokens of long documents, 8/2 heads, where the two kernels' last units leave CUs idle one after the other); on batches
 // that fill the chip the half units cost 8 to 10 % of the pass, so the planner decides by a simulation of both.
 struct JointArgs {
+  const int32_t *order;  // what each workgroup does (ca_plan::joint_order), or nullptr
   const BwdUnit *units;
   const FwdUnit *dq_units;
   const int32_t *slot_row, *slot_pos, *pos_kv;
@@ -1083,13 +1083,16 @@ struct JointArgs {
 };
 template <int D>
 __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void ca_bwd_joint_kernel(const JointArgs a) {
-  const int b = int(blockIdx.x) - a.n_dkv;
-  if (b < 0)
-    dkv_unit_or_chain<D>(a.units, a.n_single, a.pos_kv, a.q_sorted, a.k, a.v, a.do_sorted, a.l2_kv, a.delta_kv,
-                                   a.dk, a.dv, a.parts_kv, a.progress, a.peer_stride, a.hq, a.hkv, a.padded, a.scale);
-  else
-    dq_workgroup<D, 4>(a.dq_units[b < a.n_dq ? b : b - a.n_dq], b < a.n_dq ? 1 : 0, a.slot_row, a.slot_pos, a.q, a.k, a.v,
-                       a.d_o, a.l2_slot, a.delta_slot, a.dq, a.parts_dq, a.hq, a.hkv, a.padded, a.scale);
+  const int i = int(blockIdx.x) - a.n_dkv;
+  const int w = a.order ? a.order[blockIdx.x] : i < 0 ? int(blockIdx.x) : i < a.n_dq ? -1 - (a.n_dq + i) : -1 - (i - a.n_dq);
+  if (w >= 0) {
+    dkv_unit_or_chain<D>(a.units, a.n_single, a.pos_kv, a.q_sorted, a.k, a.v, a.do_sorted, a.l2_kv, a.delta_kv, a.dk, a.dv,
+                         a.parts_kv, a.progress, a.peer_stride, a.hq, a.hkv, a.padded, a.scale, w);
+  } else {
+    const int half = -1 - w >= a.n_dq ? 1 : 0;
+    dq_workgroup<D, 4>(a.dq_units[-1 - w - half * a.n_dq], half, a.slot_row, a.slot_pos, a.q, a.k, a.v, a.d_o, a.l2_slot,
+                       a.delta_slot, a.dq, a.parts_dq, a.hq, a.hkv, a.padded, a.scale);
+  }
 }
 
 // Adds up the pieces of the cut units: dQ of the forward / dQ units (from parts_dq; 8 groups of 32 rows), then dK and dV of
@@ -1198,7 +1201,7 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
     static std::atomic<bool> done[16];
     hipError_t e = set_smem(kern, SMEM, p->device, done);
     if (e != hipSuccess) return e;
-    const JointArgs args = {parts_kv ? p->d_bwd_pieces : p->d_bwd_units, dq_list, p->d_slot_row, p->d_slot_pos, p->d_pos_kv,
+    const JointArgs args = {p->joint_order.empty() ? nullptr : p->d_joint_order, parts_kv ? p->d_bwd_pieces : p->d_bwd_units, dq_list, p->d_slot_row, p->d_slot_pos, p->d_pos_kv,
                             static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v),
                             static_cast<const bf16_t *>(d_o), q_sorted, do_sorted, l2_slot, delta_slot, l2_kv, delta_kv,
                             static_cast<bf16_t *>(dq), static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_dq,

@@ -102,7 +102,9 @@ struct ca_plan {
   int32_t n_fwd_parts = 0, n_bwd_parts = 0;
   // workspace with which the piece lists are used: forward, and backward, where the parts lie behind ws_bwd
   size_t ws_fwd_split = 0, ws_bwd_split = 0, ws_off_parts_kv = 0, ws_off_parts_dq = 0;
-  bool joint = false;      // backward runs dK/dV and dQ units in one launch
+  bool joint = false;  // backward runs dK/dV and dQ units in one launch: dK/dV workgroups, then dQ halves 1, then 0, or,
+  // if not empty, in this order: i >= 0: dK/dV workgroup i; below: -1 - (half * dQ units + unit)
+  std::vector<int32_t> joint_order;
   bool shared_parts = false;  // the dQ parts take the place of the dK/dV parts once those have been added up
   // workspace layout for backward: [Delta fp32 hq*padded_slots][log2e*LSE fp32 hq*padded_slots]
   int slot_align = ca::SLOT_ALIGN, heads_packed = 1;  // padding of a document's slots; hp of the packed units
@@ -115,6 +117,7 @@ struct ca_plan {
   void *d_blob = nullptr;  // one allocation that holds all of the arrays below, copied from `blob`
   std::vector<char> blob;
   const int32_t *d_slot_row = nullptr, *d_slot_pos = nullptr, *d_block_rpk = nullptr, *d_pos_kv = nullptr;
+  const int32_t *d_joint_order = nullptr;
   const ca::FwdUnit *d_fwd_units = nullptr, *d_fwd_pieces = nullptr;
   const ca::BwdUnit *d_bwd_units = nullptr, *d_bwd_pieces = nullptr;
   const ca::CombineUnit *d_fwd_combine = nullptr, *d_bwd_combine = nullptr;

@@ -9,7 +9,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <functional>
 #include <numeric>
 #include <sstream>
 
@@ -118,15 +117,24 @@ struct CutCost {
 // When the last of `units` ((microseconds, how many), handed out in this order) ends on n_cu CUs, or a time of at least
 // at_most.
 double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_cu, double at_most) {
-  std::vector<double> busy(size_t(n_cu), 0.0);  // a heap, the least loaded CU first
+  std::vector<double> busy(size_t(n_cu), 0.0);  // a heap, the least loaded CU on top
   double end = 0;
+  const size_t n_busy = busy.size();
   for (const auto &[us, n] : units)
     for (int64_t i = 0; i < n; ++i) {
-      std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
-      busy.back() += us;
-      end = std::max(end, busy.back());
-      if (end >= at_most) return end;
-      std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+      const double t = busy[0] + us;
+      if (t > end) {
+        end = t;
+        if (end >= at_most) return end;
+      }
+      size_t at = 0;  // the top takes the unit and sinks
+      for (size_t c = 1; c < n_busy; c = 2 * at + 1) {
+        if (c + 1 < n_busy && busy[c + 1] < busy[c]) ++c;
+        if (busy[c] >= t) break;
+        busy[at] = busy[c];
+        at = c;
+      }
+      busy[at] = t;
     }
   return end;
 }
@@ -472,23 +480,55 @@ void schedule(ca_plan_t *p) {
     double mean = 0;
     for (int64_t s : wg_steps) mean += (cost_dkv.fixed + cost_dkv.per_step * double(s)) * hkv / slots;
     if (!wg_steps.empty() && !p->fwd_units.empty() && mean < JOINT_MAX_US) {
-      std::vector<std::pair<double, int64_t>> all, dq;
+      // groups of equal workgroups that follow each other in their list: (microseconds, how many, first entry of joint_order,
+      // step from entry to entry)
+      struct Group {
+        double us;
+        int32_t n, entry, step;
+      };
+      std::vector<Group> groups;
+      const std::vector<FwdUnit> &units = p->fwd_pieces.empty() ? p->fwd_units : p->fwd_pieces;
+      const int32_t n_dq = int32_t(units.size());
       const int64_t same = std::gcd<int64_t>(N_CU, std::gcd(hkv, hq / hp));
-      for (int64_t s : wg_steps) all.push_back({cost_dkv.fixed + cost_dkv.per_step * double(s), hkv / same});
-      const double per = p->d == 128 ? 2.6 : 1.5, per_half = p->d == 128 ? 1.6 : 1.7;
-      const double dkv_us = makespan(all, slots / same, 1e30);
-      size_t first_half = all.size();
-      for (const FwdUnit &u : p->fwd_pieces.empty() ? p->fwd_units : p->fwd_pieces) {
-        const double tiles = double((u.n_keys + FWD_BN - 1) / FWD_BN);
-        if (!dq.empty() && dq.back().first == cost_fwd.fixed + per * tiles) ++dq.back().second, ++all.back().second;
-        else dq.push_back({cost_fwd.fixed + per * tiles, 1}), all.push_back({cost_fwd.fixed + per_half * tiles, 1});
+      std::vector<std::pair<double, int64_t>> dkv, dq;
+      double sum = 0;
+      for (size_t i = 0; i < wg_steps.size(); ++i) {
+        const double us = cost_dkv.fixed + cost_dkv.per_step * double(wg_steps[i]);
+        dkv.push_back({us, hkv / same});
+        groups.push_back({us, hkv, int32_t(i) * hkv, 1});
+        sum += us * hkv;
       }
-      for (auto &x : dq) x.second = (x.second + same - 1) / same;
-      for (size_t i = first_half; i < all.size(); ++i) all[i].second = (all[i].second + same - 1) / same;
-      const double apart = dkv_us + makespan(dq, N_CU / same, 1e30) + cost_dkv.launch;
-      const size_t n = all.size();
-      for (size_t i = first_half; i < n; ++i) all.push_back(all[i]);
-      p->joint = makespan(all, slots / same, apart) < apart;
+      const double per = p->d == 128 ? 2.6 : 1.5, per_half = p->d == 128 ? 1.6 : 1.7;
+      for (int32_t half = 1; half >= 0; --half)
+        for (int32_t i = 0; i < n_dq;) {
+          const FwdUnit &u = units[size_t(i)];
+          const int32_t n = hq / u.hp, tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
+          if (half == 1) dq.push_back({cost_fwd.fixed + per * tiles, n / same});
+          // the tiles the half's rows see (its last slot has its highest position)
+          const int32_t last = p->slot_pos[size_t(u.slot0 + ((4 * half + 3) / u.hp) * 32 + 31)] - u.key0;
+          const double us = cost_fwd.fixed + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1));
+          groups.push_back({us, n, -1 - (half * n_dq + i), -1});
+          sum += us * n;
+          i += n;
+        }
+      const double apart = makespan(dkv, slots / same, 1e30) + makespan(dq, N_CU / same, 1e30) + cost_dkv.launch;
+      if (sum / slots < apart) {
+        std::vector<std::pair<double, int64_t>> all;
+        auto span_of = [&](double at_most) {
+          all.clear();
+          for (const Group &x : groups) all.push_back({x.us, x.n / same});
+          return makespan(all, slots / same, at_most);
+        };
+        // dK/dV units, then dQ halves, or, where that is shorter by more than the look-up it takes, all by their length
+        const double listed = span_of(1e30);
+        std::stable_sort(groups.begin(), groups.end(), [](const Group &x, const Group &y) { return x.us > y.us; });
+        const double sorted = span_of(listed);
+        const bool order = sorted < listed - 2.0;
+        p->joint = (order ? sorted : listed) < apart;
+        if (p->joint && order)
+          for (const Group &x : groups)
+            for (int32_t i = 0; i < x.n; ++i) p->joint_order.push_back(x.entry + i * x.step);
+      }
     }
   }
   // workspace with which the piece lists are used
