@@ -213,47 +213,56 @@ def ca_plan(batch) -> Plan:
 
 
 def _stream_ptr(stream):
+    """The hipStream_t as an integer (or None): torch's current stream unless one is given."""
     if stream is None:
         import torch
-        if torch.cuda.is_available():
-            return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-        return ctypes.c_void_p(None)
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        if torch.cuda.is_initialized():  # the raw handle, without a Stream object around it: 0.4 us instead of 3.7 per call
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+        return torch.cuda.current_stream().cuda_stream or None if torch.cuda.is_available() else None
+    return (stream if isinstance(stream, int) else stream.cuda_stream) or None
 
 
 def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None and t.numel() > 0 else ctypes.c_void_p(None)
+    return t.data_ptr() if t is not None and t.numel() > 0 else None
 
 
 def _expect(t, shape, dtype, name):
-    if tuple(t.shape) != tuple(shape) or t.dtype != dtype or not t.is_contiguous() or not t.is_cuda:
+    if t.shape != shape or t.dtype != dtype or not t.is_contiguous() or not t.is_cuda:
         raise ValueError(f"{name}: expected contiguous device tensor {tuple(shape)} {dtype}, got {tuple(t.shape)} {t.dtype}")
 
 
 def ca_forward(plan: Plan, q, k, v, o, lse, ws=None, stream=None):
     """Launch the fused forward on torch's current stream (or `stream`).  Writes o (bf16) and lse (fp32)."""
     import torch
-    b = plan.batch
-    _expect(q, (b.total_q, b.n_q_heads, b.head_dim), torch.bfloat16, "q")
-    _expect(k, (b.total_kv, b.n_kv_heads, b.head_dim), torch.bfloat16, "k")
-    _expect(v, (b.total_kv, b.n_kv_heads, b.head_dim), torch.bfloat16, "v")
-    _expect(o, (b.total_q, b.n_q_heads, b.head_dim), torch.bfloat16, "o")
+    b, bf16 = plan.batch, torch.bfloat16
+    qs, ks = (b.total_q, b.n_q_heads, b.head_dim), (b.total_kv, b.n_kv_heads, b.head_dim)
+    _expect(q, qs, bf16, "q")
+    _expect(k, ks, bf16, "k")
+    _expect(v, ks, bf16, "v")
+    _expect(o, qs, bf16, "o")
     _expect(lse, (b.n_q_heads, b.total_q), torch.float32, "lse")
     wsb = ws.numel() * ws.element_size() if ws is not None else 0
     _check(lib().ca_forward(plan.handle, _p(q), _p(k), _p(v), _p(o), _p(lse), _p(ws), wsb, _stream_ptr(stream)))
 
 
+def _expect_backward(b, q, k, v, o, d_o, lse, dq, dk, dv):
+    import torch
+    bf16 = torch.bfloat16
+    qs, ks = (b.total_q, b.n_q_heads, b.head_dim), (b.total_kv, b.n_kv_heads, b.head_dim)
+    _expect(q, qs, bf16, "q")
+    _expect(o, qs, bf16, "o")
+    _expect(d_o, qs, bf16, "d_o")
+    _expect(dq, qs, bf16, "dq")
+    _expect(k, ks, bf16, "k")
+    _expect(v, ks, bf16, "v")
+    _expect(dk, ks, bf16, "dk")
+    _expect(dv, ks, bf16, "dv")
+    _expect(lse, (b.n_q_heads, b.total_q), torch.float32, "lse")
+
+
 def ca_backward(plan: Plan, q, k, v, o, d_o, lse, dq, dk, dv, ws, stream=None):
     """Launch the backward on torch's current stream (or `stream`).  Writes dq, dk, dv (bf16)."""
-    import torch
-    b = plan.batch
-    qs, ks = (b.total_q, b.n_q_heads, b.head_dim), (b.total_kv, b.n_kv_heads, b.head_dim)
-    for t, s, n in ((q, qs, "q"), (o, qs, "o"), (d_o, qs, "d_o"), (dq, qs, "dq"), (k, ks, "k"), (v, ks, "v"),
-                    (dk, ks, "dk"), (dv, ks, "dv")):
-        _expect(t, s, torch.bfloat16, n)
-    _expect(lse, (b.n_q_heads, b.total_q), torch.float32, "lse")
+    _expect_backward(plan.batch, q, k, v, o, d_o, lse, dq, dk, dv)
     wsb = ws.numel() * ws.element_size() if ws is not None else 0
     _check(lib().ca_backward(plan.handle, _p(q), _p(k), _p(v), _p(o), _p(d_o), _p(lse), _p(dq), _p(dk), _p(dv),
                              _p(ws), wsb, _stream_ptr(stream)))
@@ -261,13 +270,7 @@ def ca_backward(plan: Plan, q, k, v, o, d_o, lse, dq, dk, dv, ws, stream=None):
 
 def ca_backward_static_ws(plan: Plan, q, k, v, o, d_o, lse, dq, dk, dv, stream=None):
     """ca_backward on the library's own device-resident workspace (for callers that may not allocate)."""
-    import torch
-    b = plan.batch
-    qs, ks = (b.total_q, b.n_q_heads, b.head_dim), (b.total_kv, b.n_kv_heads, b.head_dim)
-    for t, s, n in ((q, qs, "q"), (o, qs, "o"), (d_o, qs, "d_o"), (dq, qs, "dq"), (k, ks, "k"), (v, ks, "v"),
-                    (dk, ks, "dk"), (dv, ks, "dv")):
-        _expect(t, s, torch.bfloat16, n)
-    _expect(lse, (b.n_q_heads, b.total_q), torch.float32, "lse")
+    _expect_backward(plan.batch, q, k, v, o, d_o, lse, dq, dk, dv)
     _check(lib().ca_backward_static_ws(plan.handle, _p(q), _p(k), _p(v), _p(o), _p(d_o), _p(lse), _p(dq), _p(dk),
                                        _p(dv), _stream_ptr(stream)))
 
