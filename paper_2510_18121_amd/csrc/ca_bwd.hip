@@ -15,7 +15,9 @@
 //          dK and dV are written once, already summed over the group's heads and all tasks of the document.
 //          Workgroups of one KV head that run on one XCD walk the same Q/dO tiles and pace each other through
 //          published step counts, so that the tiles are fetched into that XCD's L2 once ("convoy", see the kernel).
-// No atomics and no fp32 dQ buffer: the price is that S and dP are computed in both kernels (7 contractions
+//   joint: both kinds of workgroup in one launch, for batches that fill the chip with neither.
+//   combine: adds up the fp32 partial results of units that the planner cut into pieces, in order, and stores them.
+// No atomics and no fp32 dQ accumulation: the price is that S and dP are computed in both kernels (7 contractions
 // instead of the minimal 5).  Results are deterministic.
 #include <algorithm>
 #include <atomic>
@@ -1039,14 +1041,20 @@ __device__ __forceinline__ void dkv_unit_or_chain(const BwdUnit *__restrict__ un
                                                   bf16_t *__restrict__ dV, float *__restrict__ parts, int32_t *progress,
                                                   int peer_stride, int Hq, int Hkv, int64_t padded, float scale,
                                                   const int me /* index of the workgroup = index of its first unit */) {
-  const BwdUnit first = units[me];
-  if (first.count <= 1)
-    dkv_workgroup<D, false>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
-                                  progress, peer_stride, Hq, Hkv, padded, scale);
+  // Each body loads the descriptor itself: loaded once for both, its fields are kept in lanes of vector registers across the
+  // branch and, in a chain, moved back for every unit (206 lane moves in the kernel against 94; forward + backward of 64-row
+  // lone shards with contexts, 8/2 heads: 6032 -> 6005 us, other batches 0 to 0.7 % faster).
+  int first = me;
+  const int count = units[me].count;
+  asm volatile("" : "+s"(first));
+  if (count <= 1)
+    dkv_workgroup<D, false>(me, units[first], units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
+                            progress, peer_stride, Hq, Hkv, padded, scale);
   else
-    dkv_workgroup<D, true>(me, first, units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
-                                 progress, peer_stride, Hq, Hkv, padded, scale);
+    dkv_workgroup<D, true>(me, units[first], units, n_single, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts,
+                           progress, peer_stride, Hq, Hkv, padded, scale);
 }
+
 template <int D>
 __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void ca_bwd_dkv_kernel(const BwdUnit *__restrict__ units, int n_single,
                                                             const int32_t *__restrict__ slot_pos,
@@ -1062,11 +1070,12 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void ca_bwd_dkv_kernel(const
                        peer_stride, Hq, Hkv, padded, scale, int(blockIdx.x));
 }
 
-// dK/dV units and dQ half units (workgroups of 4 groups of 32 rows) in one launch, longest first.  For batches too small to fill the chip with either kernel: what a launch takes there is mostly its fixed
-// part, and the dQ work finds CUs that the dK/dV units leave idle.  Measured, forward + backward, two launches against one:
-// 70 -> 51 us (384 rows, 8/1 heads, head_dim 128), 48 -> 38 us (1.5K tokens, 4/2 heads, head_dim 64), 1006 -> 806 us (12K
-// tokens of long documents, 8/2 heads, where the two kernels' last units leave CUs idle one after the other); on batches
-// that fill the chip the half units cost 8 to 10 % of the pass, so the planner decides by a simulation of both.
+// dK/dV units and dQ half units (workgroups of 4 groups of 32 rows) in one launch, longest first.  For batches too small to
+// fill the chip with either kernel: what a launch takes there is mostly its fixed part, and the dQ work finds CUs that the
+// dK/dV units leave idle.  Measured, forward + backward, two launches against one: 70 -> 51 us (384 rows, 8/1 heads,
+// head_dim 128), 48 -> 38 us (1.5K tokens, 4/2 heads, head_dim 64), 1006 -> 806 us (12K tokens of long documents, 8/2
+// heads, where the two kernels' last units leave CUs idle one after the other); on batches that fill the chip the half
+// units cost 8 to 10 % of the pass, so the planner decides by a simulation of both.
 struct JointArgs {
   const int32_t *order;  // what each workgroup does (ca_plan::joint_order), or nullptr
   const BwdUnit *units;

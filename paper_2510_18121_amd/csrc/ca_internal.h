@@ -12,15 +12,16 @@ namespace ca {
 // Tile geometry.  Every document's sorted query rows occupy a run of "slots" padded to the plan's slot alignment
 // (at most SLOT_ALIGN), so that forward tiles and backward q blocks (BWD_BQ slots) both tile the same arrays.
 constexpr int SLOT_ALIGN = 256;
-constexpr int FWD_BM = 256;  // query rows per forward work unit (8 waves x 32)
+constexpr int FWD_BM = 256;  // query rows per forward work unit (8 row groups x 32)
 constexpr int FWD_BN = 64;   // keys per forward inner step
 constexpr int BWD_BN = 128;  // keys owned by one backward work unit (4 waves x 32)
 constexpr int BWD_BQ = 64;   // query rows per backward inner step
 
-// One workgroup of the forward / dQ kernels: 8 waves of 32 slots each.  A full tile of a document is 256 slots of
-// one query head (hp = 1).  The slots a document has left over after its full tiles are covered by head-packed units
-// instead: 256 / hp slots of hp consecutive query heads of one KV group (they read the same K/V), wave w taking
-// slots slot0 + 32 (w / hp) .. of head  head + w % hp  - so that short documents keep all 8 waves busy too.
+// One workgroup of the forward / dQ kernels (half of it in the joint backward launch): 8 row groups of 32 slots, one or
+// two to a wave.  A full tile of a document is 256 slots of one query head (hp = 1).  The slots a document has left over
+// after its full tiles are covered by head-packed units instead: 256 / hp slots of hp consecutive query heads of one KV
+// group (they read the same K/V), row group w taking slots slot0 + 32 (w / hp) .. of head  head + w % hp  - so that
+// short documents keep all waves busy too.
 struct FwdUnit {
   int32_t slot0;    // first slot of the unit
   int32_t kv_row0;  // packed KV row of the document's token 0
