@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <numeric>
 #include <sstream>
 
@@ -117,11 +118,19 @@ struct CutCost {
 // When the last of `units` ((microseconds, how many), handed out in this order) ends on n_cu CUs, or a time of at least
 // at_most.
 double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_cu, double at_most) {
-  std::vector<double> busy(size_t(n_cu), 0.0);  // a heap, the least loaded CU on top
+  std::vector<double> busy;  // once every CU has a unit: a heap, the least loaded CU on top
+  const size_t n_busy = size_t(n_cu);
+  busy.reserve(n_busy);
   double end = 0;
-  const size_t n_busy = busy.size();
-  for (const auto &[us, n] : units)
-    for (int64_t i = 0; i < n; ++i) {
+  for (const auto &[us, n] : units) {
+    int64_t i = 0;
+    for (; i < n && busy.size() < n_busy; ++i) {  // the first units find idle CUs
+      busy.push_back(us);
+      end = std::max(end, us);
+      if (busy.size() == n_busy) std::make_heap(busy.begin(), busy.end(), std::greater<double>());
+    }
+    if (end >= at_most) return end;
+    for (; i < n; ++i) {
       const double t = busy[0] + us;
       if (t > end) {
         end = t;
@@ -136,6 +145,7 @@ double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_
       }
       busy[at] = t;
     }
+  }
   return end;
 }
 
