@@ -174,7 +174,7 @@ int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const 
     double sum = 0;
     sizes.clear();
     for (const auto &[steps, count] : units) {
-      const int64_t k = (steps + t - 1) / t;
+      const int64_t k = std::max<int64_t>(1, (steps + t - 1) / t);  // (units without steps, which write zeros, stay whole)
       const double us = c.fixed + c.per_step * double(steps) / double(k);
       sizes.push_back({us, count / same * k});
       sum += us * double(count * k);
