@@ -442,8 +442,8 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   // the wave's auxiliary array: log2e*LSE (wave 0), -Delta (wave 1), slot positions (wave 2); wave 3's load goes to
   // a spare area, so that every wave issues the same number of loads, and brings the peers' progress counters (below)
   const int64_t aux_hstride = wave < 2 ? padded : 0;
-  const int aux_bstep = wave == 3 ? 0 : BWD_BQ;
-  // Convoy.  The workgroups of one KV head that run on one XCD (units peer_stride apart) walk the same Q/dO tiles
+  const int aux_bstep = PIPE && wave == 3 ? 0 : BWD_BQ;
+  // Convoy (head_dim 128).  The workgroups of one KV head that run on one XCD (units peer_stride apart) walk the same Q/dO tiles
   // from the same last block; as long as they are within an L2's worth of steps of each other only the first
   // of them fetches a tile from beyond the L2.  Each workgroup publishes the number of steps it has taken; wave 3's
   // auxiliary load (a filler otherwise) fetches the counters of up to 32 such peers along with every stage, and a
@@ -454,6 +454,9 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   // Only units that stream at least 64 MB of Q/dO tiles wait for peers: on shorter ones (documents below about 32K
   // rows at four heads per group) the tiles missed in L2 are cheap and the waiting for later-started peers is not
   // (measured: -13 % on batches of 16K-token documents with every unit waiting, nothing gained there).
+  // At head_dim 64 nothing is paced and wave 3's filler fetches the positions once more: a tile is half the bytes, and
+  // without pacing the kernel takes the same time per pair on a 32K-token document as on a 128K-token one (32/8 heads:
+  // 7.84, 30.8 and 123.1 ms at 32K, 64K and 128K tokens; 4 and 16 times the first is 31.4 and 125.4), so nothing is lost.
   constexpr int CONVOY = (1 << 20) / (2 * BWD_BQ * ROWB);  // 1 MB of Q/dO tiles (a quarter of an L2), in steps
   constexpr int CONVOY_REACH = 3 * CONVOY;                 // peers further behind than this are left alone
   constexpr int CONVOY_MIN_STEPS = (64 << 20) / (2 * BWD_BQ * ROWB);
@@ -467,7 +470,7 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
                            : reinterpret_cast<const float *>(slot_pos)) +
               u.slot_begin + int64_t(pblk) * BWD_BQ + lane;
     // Only workgroups of a single unit have peers: those come first in the list, and their index is their unit's.
-    if (wave == 3) {
+    if (PIPE && wave == 3) {
       const int grp = 32 * peer_stride;
       const int pu = me - me % grp + me % peer_stride + peer_stride * lane;
       const int32_t *pp = progress + n_single;  // a counter that stays 0: "not running"
@@ -481,7 +484,7 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   }
   int32_t *const my_progress = progress + me;
   auto publish = [&](int steps) __attribute__((always_inline)) {  // call from wave 3 only; chains have no peers
-    if (!CHAIN && lane == 0) __hip_atomic_store(my_progress, steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (PIPE && !CHAIN && lane == 0) __hip_atomic_store(my_progress, steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   const uint32_t aux_lds = wave == 0 ? S::L2_OFF : wave == 1 ? S::DL_OFF : wave == 2 ? S::POS_OFF : S::SPARE_OFF;
   constexpr int LPI = 2 * NLD + 1;  // loads per wave per iteration
@@ -520,18 +523,13 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   // that the four waves' pieces do not pile up in the memory pipeline (one 1 KB load per 16 cycles per CU): by MFMA
   // slot of the phase, after the barrier in B(2 it + 1), then in B(2 it + 2), then in B(2 it + 3) before its
   // barrier (the cursor piece last).  slot -> piece index, or -1.
-  constexpr int NPOST = D == 128 ? 2 : 1, NMID = D == 128 ? 5 : 3, NPRE = LPI - NPOST - NMID;
-  static_assert(NPRE >= 1 && NPRE <= 2, "piece schedule");
+  constexpr int NPOST = 2, NMID = 5;
+  static_assert(!PIPE || LPI == NPOST + NMID + 2, "piece schedule");
   auto piece_of = [](int qb, int m) constexpr -> int {
-    if (D == 128) {
-      if (qb == 1) return m == 10 ? 0 : m == 13 ? 1 : m == 4 ? NPOST + NMID : m == 6 ? NPOST + NMID + 1 : -1;
-      return m == 4 ? NPOST : m == 6 ? NPOST + 1 : m == 10 ? NPOST + 2 : m == 12 ? NPOST + 3 : m == 14 ? NPOST + 4 : -1;
-    }
-    if (qb == 1) return m == 6 ? 0 : m == 2 ? NPOST + NMID : -1;
-    return m == 2 ? NPOST : m == 3 ? NPOST + 1 : m == 6 ? NPOST + 2 : -1;
+    if (qb == 1) return m == 10 ? 0 : m == 13 ? 1 : m == 4 ? NPOST + NMID : m == 6 ? NPOST + NMID + 1 : -1;
+    return m == 4 ? NPOST : m == 6 ? NPOST + 1 : m == 10 ? NPOST + 2 : m == 12 ? NPOST + 3 : m == 14 ? NPOST + 4 : -1;
   };
-  constexpr int NB1 = NPOST;
-  constexpr int LP1 = NB1;  // pieces of the newest block that are issued before the pipelined path takes over
+  constexpr int LP1 = NPOST;  // pieces of the newest block that are issued before the pipelined path takes over
 
   if (n_it > 0 && !cont) {
     issue_next();  // blocks 0 .. 3: four ahead; the last one is completed further down
@@ -673,13 +671,9 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
         if (s + PA < NS) opq[s % PA] = lds_read8_at(S::Q_OFF + nat + qoff[s + PA]);
         if (vec) {
           tlo = lds_read_tr4_at(X + toff[0][s >> 1]);
-          if constexpr (NS == 8) {  // pair s in step s (one exponential per MFMA), packed in step s + 1
-            if (s >= 1 && s < 7) pack_p(s - 1);
-            if (s < 6) vec_p1(sr, s >> 1, 2 * (s & 1));
-          } else {  // pairs 2s and 2s+1 in step s (two exponentials per MFMA), each packed one MFMA later
-            if (s >= 1) pack_p(2 * s - 1);
-            if (s < 3) vec_p1(sr, s, 0), vec_p1(sr, s, 1);
-          }
+          // pair s in step s (one exponential per MFMA), packed in step s + 1
+          if (s >= 1 && s < 7) pack_p(s - 1);
+          if (s < 6) vec_p1(sr, s >> 1, 2 * (s & 1));
         }
         __builtin_amdgcn_sched_barrier(0);
         if (s == 0) mfma32_v_first(dpw, opd[0], vf[0], ndt);
@@ -688,11 +682,7 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
         if (vec) {
           thi = lds_read_tr4_at(X + toff[1][s >> 1]);
           opb[s] = join(tlo, thi);
-          if constexpr (NS == 8) {
-            if (s < 6) vec_p1(sr, s >> 1, 2 * (s & 1) + 1);
-          } else {
-            if (s < 3) pack_p(2 * s), vec_p1(sr, s, 2), vec_p1(sr, s, 3);
-          }
+          if (s < 6) vec_p1(sr, s >> 1, 2 * (s & 1) + 1);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -773,21 +763,13 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
               }
               // the vector ALU's share of this phase: dS of rows 0..7 before the first dK group, the last quarter
               // of P before the second dV group, dS of rows 8..15 before the second dK group
-              if constexpr (NDB == 4) {
-                if (m == 0) vec_ds(dp[qb], 0);
-                if (m == 1) vec_ds(dp[qb], 1);
-                if (m == 2) vec_p1(sc[qb], 3, 0), vec_p1(sc[qb], 3, 1);
-                if (m == 3) vec_p1(sc[qb], 3, 2), vec_p1(sc[qb], 3, 3), pack_p(6);  // a pack never directly follows
-                if (m == 4) pack_p(7);                                              // the exponentials it reads
-                if (m == 8) vec_ds(dp[qb], 2);
-                if (m == 9) vec_ds(dp[qb], 3);
-              } else {
-                if (m == 0) vec_ds(dp[qb], 0), vec_ds(dp[qb], 1);
-                if (m == 1) vec_p1(sc[qb], 3, 0), vec_p1(sc[qb], 3, 1);
-                if (m == 2) vec_p1(sc[qb], 3, 2), vec_p1(sc[qb], 3, 3), pack_p(6);
-                if (m == 3) pack_p(7);
-                if (m == 4) vec_ds(dp[qb], 2), vec_ds(dp[qb], 3);
-              }
+              if (m == 0) vec_ds(dp[qb], 0);
+              if (m == 1) vec_ds(dp[qb], 1);
+              if (m == 2) vec_p1(sc[qb], 3, 0), vec_p1(sc[qb], 3, 1);
+              if (m == 3) vec_p1(sc[qb], 3, 2), vec_p1(sc[qb], 3, 3), pack_p(6);  // a pack never directly follows
+              if (m == 4) pack_p(7);                                              // the exponentials it reads
+              if (m == 8) vec_ds(dp[qb], 2);
+              if (m == 9) vec_ds(dp[qb], 3);
               // first natural fragments of sub-block k+2 (block it+1: first half for qb == 0, second for qb == 1)
 #pragma unroll
               for (int o = (2 * PA * m) / (4 * NDB); o < (2 * PA * (m + 1)) / (4 * NDB); ++o) {
@@ -823,12 +805,12 @@ __device__ __forceinline__ void dkv_workgroup(const int me, const BwdUnit &first
   }
   // ------------------------------------------------------------------------------------------------
   // Plain path (head_dim 64).  A sub-block there is 16 MFMAs for the same vector work, and a lone wave per SIMD kept the
-  // matrix pipe busy 46 % of the time however its stream was pipelined.  The plain body needs half the registers (175) and,
-  // with three stages, half the LDS, so two workgroups share a CU and fill each other's waits.  Pipelined body against this
-  // one, dK/dV kernel: 2.42 -> 2.19 ms (16K-token document, 32/8 heads), 2.07 -> 1.68 ms (lone 64-row shards with contexts,
-  // 8/2 heads), 0.68 -> 0.48 ms (32K tokens of 600-token documents, 32/8 heads).  The loop over whole blocks and the one over
-  // the diagonal are apart on purpose: with both in one loop the accumulators were copied between the register files in
-  // every step.
+  // matrix pipe busy 46 % of the time however its stream was pipelined.  The plain body needs half the registers (172) and,
+  // with three stages, half the LDS, so two workgroups share a CU and fill each other's waits.  Pipelined body, one workgroup
+  // per CU, against this one, dK/dV kernel, 32/8 heads: 0.39 -> 0.28 ms (8 documents of 2K tokens), 2.30 -> 2.10 (one of 16K),
+  // 9.14 -> 7.84 (32K), 35.3 -> 30.8 (64K), 137 -> 123 (128K), 2.40 -> 1.96 (the last 1000 rows of 128K); 16/16 and 8/1 heads
+  // alike: the plain body is the faster one at every length.  The loop over whole blocks and the one over the diagonal are
+  // apart on purpose: with both in one loop the accumulators were copied between the register files in every step.
   if constexpr (!PIPE) {
     // one sub-block of 32 rows; MASK: some row of the block does not see some key of the tile
     auto sub_block = [&](int qb, const bool MASK) __attribute__((always_inline)) {
