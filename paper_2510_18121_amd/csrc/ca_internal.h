@@ -115,8 +115,8 @@ struct ca_plan {
   bool q_covered = false, kv_covered = false;  // every packed Q row / KV row belongs to some unit
   // device copies
   int device = -1;
-  void *d_blob = nullptr;  // one allocation that holds all of the arrays below, copied from `blob`
-  std::vector<char> blob;
+  void *d_blob = nullptr;  // one allocation that holds all of the arrays below
+  std::vector<char> blob;  // host copies of the small ones, which go up together
   const int32_t *d_slot_row = nullptr, *d_slot_pos = nullptr, *d_block_rpk = nullptr, *d_pos_kv = nullptr;
   const int32_t *d_joint_order = nullptr;
   const ca::FwdUnit *d_fwd_units = nullptr, *d_fwd_pieces = nullptr;
