@@ -109,6 +109,11 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // half the pace.
 constexpr int N_CU = 256;
 constexpr double JOINT_MAX_US = 1000;  // batches beyond this fill the chip with either kernel
+// The choice between one backward launch and two simulates lists of thousands of units, at 20 to 40 ns each more than the rest
+// of planning takes: ca_plan_host for 37K tokens in lone 860-row shards (8/1 heads) 65 us without it, 192 with all units
+// simulated, 106 so; of 1600 batches none gets another launch.  (Cut lengths are searched with all units: simulated so, one of
+// 1600 batches got a cut that cost 2 %.)
+constexpr int64_t JOINT_UNITS = 512;
 struct CutCost {
   int slots;  // workgroups that run at a time
   double per_step, fixed, launch;
@@ -116,21 +121,28 @@ struct CutCost {
 };
 
 // When the last of `units` ((microseconds, how many), handed out in this order) ends on n_cu CUs, or a time of at least
-// at_most.
-double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_cu, double at_most) {
-  std::vector<double> busy;  // once every CU has a unit: a heap, the least loaded CU on top
-  const size_t n_busy = size_t(n_cu);
-  busy.reserve(n_busy);
+// at_most.  A list of more than max_units is simulated with 2, 4, .. neighbours of it as one unit (of their mean length) on as
+// many times fewer CUs: neighbours are of nearly equal length.
+double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_cu, double at_most, int64_t max_units = INT64_MAX) {
+  int64_t total = 0, q = 1;
   double end = 0;
-  for (const auto &[us, n] : units) {
+  for (const auto &[us, n] : units) total += n, end = std::max(end, us);
+  while (total / q > max_units && n_cu % (2 * q) == 0 && n_cu > 16 * q) q *= 2;
+  std::vector<double> busy;  // once every CU has a unit: a heap, the least loaded CU on top
+  const size_t n_busy = size_t(n_cu / q);
+  busy.reserve(n_busy);
+  int64_t held = 0;  // units that do not make up a group yet, and the sum of their lengths
+  double held_us = 0;
+  for (const auto &[unit_us, count] : units) {
+    const int64_t n = (held + count) / q;  // groups that are complete now; the first takes in the units held
+    double us = held > 0 ? (held_us + double(q - held) * unit_us) / double(q) : unit_us;
     int64_t i = 0;
-    for (; i < n && busy.size() < n_busy; ++i) {  // the first units find idle CUs
+    for (; i < n && busy.size() < n_busy; ++i, us = unit_us) {  // the first units find idle CUs
       busy.push_back(us);
-      end = std::max(end, us);
       if (busy.size() == n_busy) std::make_heap(busy.begin(), busy.end(), std::greater<double>());
     }
     if (end >= at_most) return end;
-    for (; i < n; ++i) {
+    for (; i < n; ++i, us = unit_us) {
       const double t = busy[0] + us;
       if (t > end) {
         end = t;
@@ -145,7 +157,10 @@ double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_
       }
       busy[at] = t;
     }
+    held = held + count - n * q;
+    held_us = n > 0 ? double(held) * unit_us : held_us + double(count) * unit_us;
   }
+  if (held > 0) end = std::max(end, (busy.size() < n_busy ? 0.0 : busy[0]) + held_us / double(held));
   return end;
 }
 
@@ -171,20 +186,24 @@ int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const 
   for (double T = double(longest); T >= c.min_steps; T = std::min(T / 1.2, std::max(1.3 * steps_per_cu, 4.0 * c.min_steps))) {
     const int64_t t = int64_t(T);
     int64_t parts = 0;
-    double sum = 0;
+    size_t n_cut = 0;  // the leading units are the long ones
+    double sum = 0, piece = 0;
     sizes.clear();
     for (const auto &[steps, count] : units) {
       const int64_t k = std::max<int64_t>(1, (steps + t - 1) / t);  // (units without steps, which write zeros, stay whole)
       const double us = c.fixed + c.per_step * double(steps) / double(k);
       sizes.push_back({us, count / same * k});
       sum += us * double(count * k);
-      if (k > 1) parts += count * k;
+      if (k > 1) parts += count * k, ++n_cut;
+      piece = std::max(piece, us);
     }
     const size_t bytes = size_t(parts) * bytes_per_part;
     const double extra = parts ? c.launch + double(bytes) / BYTES_PER_US : 0.0;
     if (parts && (bytes > max_bytes || sum / c.slots + extra >= best)) break;  // more and smaller pieces only cost more
-    std::sort(sizes.begin(), sizes.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
-    const double us = makespan(sizes, c.slots / same, parts ? best - extra : 1e30) + extra;
+    auto longer = [](const auto &x, const auto &y) { return x.first > y.first; };
+    std::sort(sizes.begin(), sizes.begin() + n_cut, longer);
+    std::inplace_merge(sizes.begin(), sizes.begin() + n_cut, sizes.end(), longer);
+    const double us = parts && piece + extra >= best ? best : makespan(sizes, c.slots / same, parts ? best - extra : 1e30) + extra;
     if (!parts) best = 0.9 * us;
     else if (us < best) best = us, best_t = t, worse = 0;
     else if (++worse == 3) break;
@@ -501,12 +520,13 @@ void schedule(ca_plan_t *p) {
       const int32_t n_dq = int32_t(units.size());
       const int64_t same = std::gcd<int64_t>(N_CU, std::gcd(hkv, hq / hp));
       std::vector<std::pair<double, int64_t>> dkv, dq;
-      double sum = 0;
+      double sum = 0, longest = 0;
       for (size_t i = 0; i < wg_steps.size(); ++i) {
         const double us = cost_dkv.fixed + cost_dkv.per_step * double(wg_steps[i]);
         dkv.push_back({us, hkv / same});
         groups.push_back({us, hkv, int32_t(i) * hkv, 1});
         sum += us * hkv;
+        longest = std::max(longest, us);
       }
       const double per = p->d == 128 ? 2.6 : 1.5, per_half = p->d == 128 ? 1.6 : 1.7;
       for (int32_t half = 1; half >= 0; --half)
@@ -519,22 +539,27 @@ void schedule(ca_plan_t *p) {
           const double us = cost_fwd.fixed + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1));
           groups.push_back({us, n, -1 - (half * n_dq + i), -1});
           sum += us * n;
+          longest = std::max(longest, us);
           i += n;
         }
-      const double apart = makespan(dkv, slots / same, 1e30) + makespan(dq, N_CU / same, 1e30) + cost_dkv.launch;
+      const double apart = makespan(dkv, slots / same, 1e30, JOINT_UNITS) + makespan(dq, N_CU / same, 1e30, JOINT_UNITS) + cost_dkv.launch;
       if (sum / slots < apart) {
         std::vector<std::pair<double, int64_t>> all;
         auto span_of = [&](double at_most) {
           all.clear();
           for (const Group &x : groups) all.push_back({x.us, x.n / same});
-          return makespan(all, slots / same, at_most);
+          return makespan(all, slots / same, at_most, JOINT_UNITS);
         };
         // dK/dV units, then dQ halves, or, where that is shorter by more than the look-up it takes, all by their length
-        const double listed = span_of(1e30);
-        std::stable_sort(groups.begin(), groups.end(), [](const Group &x, const Group &y) { return x.us > y.us; });
-        const double sorted = span_of(listed);
-        const bool order = sorted < listed - 2.0;
-        p->joint = (order ? sorted : listed) < apart;
+        const double listed = span_of(apart + 2.0);
+        const double goal = std::min(listed - 2.0, apart);  // what the order by length has to beat; no order beats the mean load
+        double sorted = goal;
+        if (sum / slots < goal && longest < goal) {
+          std::stable_sort(groups.begin(), groups.end(), [](const Group &x, const Group &y) { return x.us > y.us; });
+          sorted = span_of(goal);
+        }
+        const bool order = sorted < goal;
+        p->joint = order || listed < apart;
         if (p->joint && order)
           for (const Group &x : groups)
             for (int32_t i = 0; i < x.n; ++i) p->joint_order.push_back(x.entry + i * x.step);
