@@ -19,9 +19,7 @@ class _CoreAttention(torch.autograd.Function):
         lse = torch.empty((b.n_q_heads, b.total_q), dtype=torch.float32, device=q.device)
         # partial results of the forward have memory of the call's own: forwards of one server may overlap in time (other
         # streams, or another call's backward, which uses the server's workspace)
-        n = server.fwd_ws_bytes
-        ws = torch.empty(n, dtype=torch.uint8, device=q.device) if n else None
-        B.ca_forward(server.plan, q, k, v, o, lse, ws)
+        B.ca_forward(server.plan, q, k, v, o, lse, B._scratch(server.fwd_ws_bytes, 0, q.device))
         ctx.save_for_backward(q, k, v, o, lse)
         ctx.server = server
         return o

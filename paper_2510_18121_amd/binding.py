@@ -275,12 +275,23 @@ def ca_backward_static_ws(plan: Plan, q, k, v, o, d_o, lse, dq, dk, dv, stream=N
                                        _p(dv), _stream_ptr(stream)))
 
 
-def alloc_workspace(plan: Plan, device="cuda"):
-    """A torch uint8 buffer big enough for both calls, with room for the partial results of units cut into pieces
-    (torch's allocator returns 256-byte aligned blocks)."""
+def _scratch(preferred, needed, device):
+    """A uint8 buffer of `preferred` bytes, or of `needed` (None for 0) where the device has no room for that: partial results
+    of cut units may take 256 MiB, and a batch that fits without them must go on fitting."""
     import torch
-    f, b = plan.workspace_bytes_split()
-    return torch.empty(max(f, b, 256), dtype=torch.uint8, device=device)
+    if preferred > needed:
+        try:
+            return torch.empty(preferred, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    return torch.empty(needed, dtype=torch.uint8, device=device) if needed else None
+
+
+def alloc_workspace(plan: Plan, device="cuda"):
+    """A torch uint8 buffer big enough for both calls, with room for the partial results of units cut into pieces where the
+    device has it (torch's allocator returns 256-byte aligned blocks).  Both calls write to it: calls that may overlap in time
+    need one each."""
+    return _scratch(max(*plan.workspace_bytes_split(), 256), max(*plan.workspace_bytes(), 256), device)
 
 
 def ca_merge_partials(part_rows, o_part, lse_part, o, lse, o_back=None, lse_back=None, stream=None):
