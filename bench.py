@@ -173,7 +173,6 @@ def main():
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    plan.profile_enable(True)
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     clocks = EngineClockSampler()
     wall0 = time.perf_counter()
@@ -185,7 +184,9 @@ def main():
         torch.cuda.synchronize()
     wall = time.perf_counter() - wall0
     ms_per_step = e0.elapsed_time(e1) / args.steps
-    # per-kernel durations: HIP events recorded by the library on the launch stream, one more pass
+    # per-kernel durations: HIP events recorded by the library on the launch stream, in passes of their own (with timing on,
+    # small batches run their one backward launch as two)
+    plan.profile_enable(True)
     kern = {"fwd_kernel_ms": [], "bwd_prep_ms": [], "bwd_dkv_ms": [], "bwd_dq_ms": []}
     for _ in range(max(1, min(args.steps, 3))):
         step()

@@ -184,8 +184,12 @@ int ca_sum_partial_dq(const int32_t *part_rows, int64_t n_rows, int32_t n_parts,
  * ca_backward on that plan records HIP events on the caller's stream around its kernels.
  * ca_profile_read blocks until the last recorded events have completed and writes milliseconds to
  * out[0..4): {forward kernel, backward preparation (Delta and log-sum-exp in slot order, zero fills
- * when some rows belong to no task), backward dK/dV kernel, backward dQ kernel}; entries of calls not made since enabling are 0.  Enabling creates events
- * (the only allocation); disabling destroys them.
+ * when some rows belong to no task), backward dK/dV kernel, backward dQ kernel}; entries of calls not made since enabling are 0.
+ * A launch that adds up partial results counts with the kernel before it: in ca_forward with the forward kernel, in
+ * ca_backward with the dQ kernel (dK/dV partial results that dQ's take the place of: with the dK/dV kernel).  Where ca_backward
+ * runs dK/dV and dQ units in one launch (joint_backward of ca_plan_info), it runs the same workgroups as two launches while
+ * timing is enabled, so that each kind has a time: results are the same bit for bit, the two times together are more than
+ * the one launch takes.  Enabling creates events (the only allocation); disabling destroys them.
  */
 int ca_profile_enable(ca_plan_t *plan, int on);
 int ca_profile_read(ca_plan_t *plan, float *out_ms);
@@ -247,7 +251,7 @@ const char *ca_last_error(void); /* thread-local detail of the last failing call
  * (q blocks x heads) steps, bwd_q_block_rows, slot_align (a document's rows are padded to this many slots),
  * heads_packed (query heads per head-packed forward unit), n_bwd_workgroups (workgroups of the dK/dV kernel: short
  * backward units are chained, see below), joint_backward (1: the backward runs its dK/dV and dQ units in one launch, given
- * the workspace of ca_plan_workspace_bytes_split and no timing).  n_q_tiles counts the full 256-slot tiles.
+ * the workspace of ca_plan_workspace_bytes_split; in two while timing is enabled).  n_q_tiles counts the full 256-slot tiles.
  * Returns the number of values available.
  */
 int ca_plan_info(const ca_plan_t *plan, int64_t *out, int n);

@@ -1184,21 +1184,26 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
   if (ev) (void)hipEventRecord(ev[1], st);
   const FwdUnit *const dq_list = parts_dq ? p->d_fwd_pieces : p->d_fwd_units;
   const int n_dq = int(parts_dq ? p->fwd_pieces.size() : p->fwd_units.size());
-  // (with timing enabled the two kernels are launched one by one, so that each has a time)
-  const bool joint = p->joint && !ev && (split || p->n_fwd_parts + p->n_bwd_parts == 0);
+  const bool joint = p->joint && (split || p->n_fwd_parts + p->n_bwd_parts == 0);
+  JointArgs args = {};
+  auto launch_joint = [&](int32_t workgroups) {
+    hipLaunchKernelGGL(ca_bwd_joint_kernel<D>, dim3(unsigned(workgroups)), dim3(256),
+                       std::max(DkvSmem<D>::TOTAL, DqSmem<D>::TOTAL), st, args);
+  };
   if (joint) {
     auto kern = ca_bwd_joint_kernel<D>;
     constexpr int SMEM = std::max(DkvSmem<D>::TOTAL, DqSmem<D>::TOTAL);
     static std::atomic<bool> done[16];
     hipError_t e = set_smem(kern, SMEM, p->device, done);
     if (e != hipSuccess) return e;
-    const JointArgs args = {p->joint_order.empty() ? nullptr : p->d_joint_order, parts_kv ? p->d_bwd_pieces : p->d_bwd_units, dq_list, p->d_slot_row, p->d_slot_pos, p->d_pos_kv,
-                            static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v),
-                            static_cast<const bf16_t *>(d_o), q_sorted, do_sorted, l2_slot, delta_slot, l2_kv, delta_kv,
-                            static_cast<bf16_t *>(dq), static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_dq,
-                            parts_kv, progress, n_dkv, parts_kv ? p->bwd_piece_single : p->bwd_single, n_dq,
-                            p->peer_stride, p->hq, p->hkv, padded, p->scale};
-    hipLaunchKernelGGL(kern, dim3(unsigned(n_dkv + 2 * n_dq)), dim3(256), SMEM, st, args);
+    args = {p->joint_order.empty() || ev ? nullptr : p->d_joint_order, parts_kv ? p->d_bwd_pieces : p->d_bwd_units, dq_list,
+            p->d_slot_row, p->d_slot_pos, p->d_pos_kv, static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k),
+            static_cast<const bf16_t *>(v), static_cast<const bf16_t *>(d_o), q_sorted, do_sorted, l2_slot, delta_slot, l2_kv,
+            delta_kv, static_cast<bf16_t *>(dq), static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_dq, parts_kv,
+            progress, n_dkv, parts_kv ? p->bwd_piece_single : p->bwd_single, n_dq, p->peer_stride, p->hq, p->hkv, padded,
+            p->scale};
+    // (with timing enabled the same workgroups run as two launches, so that each kind has a time)
+    launch_joint(ev ? n_dkv : n_dkv + 2 * n_dq);
   } else if (!p->bwd_units.empty()) {
     auto kern = ca_bwd_dkv_kernel<D>;
     constexpr int SMEM = DkvSmem<D>::TOTAL;
@@ -1213,7 +1218,10 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
   }
   if (p->shared_parts) combine(false, true);  // before the dQ pieces write over them
   if (ev) (void)hipEventRecord(ev[2], st);
-  if (n_dq > 0 && !joint) {
+  if (joint) {
+    args.n_dkv = 0;  // dQ halves only
+    if (ev) launch_joint(2 * n_dq);
+  } else if (n_dq > 0) {
     auto kern = ca_bwd_dq_kernel<D>;
     static std::atomic<bool> done[16];
     hipError_t e = set_smem(kern, DqSmem<D>::TOTAL, p->device, done);

@@ -73,7 +73,7 @@ def test_pieces_match_the_oracle_and_whole_units(name):
                                              (4, 1, 64, [(1000, 20)])])
 def test_joint_backward_matches_separate_launches(hq, hkv, d, shards):
     """Small batches run dK/dV and dQ units in one launch (dQ units in halves of 128 rows: all head packings, halves that
-    see fewer keys than their unit, rows that fill no half); with timing enabled the two kernels are launched one by one."""
+    see fewer keys than their unit, rows that fill no half); with timing enabled their workgroups run as two launches."""
     b = W.custom([a + n for a, n in shards], [(i, a, n) for i, (a, n) in enumerate(shards)], hq, hkv, d, seed=92)
     t = W.make_tensors(b, DEV)
     plan = B.ca_plan(b)
@@ -131,3 +131,22 @@ def test_pieces_replay_from_a_graph():
         torch.cuda.synchronize()
         for t, w in zip(outs, want):
             assert torch.equal(t, w)
+
+
+@pytest.mark.parametrize("hq,hkv,d,shards", [(4, 2, 128, [(0, 300)]), (6, 2, 128, [(500, 16), (3, 129)]), (8, 1, 64, [(40, 700)]),
+                                             (8, 2, 128, [(0, 1024), (100, 411)])])
+def test_timing_does_not_change_results(hq, hkv, d, shards):
+    """Joint batches, with and without cut units: all results bit for bit the same with timing enabled, which reports a time for
+    each kind of unit."""
+    b = W.custom([a + n for a, n in shards], [(i, a, n) for i, (a, n) in enumerate(shards)], hq, hkv, d, seed=93)
+    t = W.make_tensors(b, DEV)
+    plan = B.ca_plan(b)
+    assert plan.info()["joint_backward"] == 1
+    want = P.run_hip(b, *t, plan=plan)
+    plan.profile_enable(True)
+    got = P.run_hip(b, *t, plan=plan)
+    times = plan.profile_read()
+    plan.profile_enable(False)
+    for n in ("o", "lse", "dq", "dk", "dv"):
+        assert torch.equal(got[n], want[n]), n
+    assert times["bwd_dkv_ms"] > 0 and times["bwd_dq_ms"] > 0, times
