@@ -298,8 +298,9 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
     }
   }
   wait_vmcnt<0>();
+  const int out_lane = lane_id();  // (derived again: `lane` does not stay in a register across the loop, it is spilled)
   if (u.part >= 0) {  // a piece: the accumulators as they stand
-    float *dst = parts + size_t(u.part) * (FWD_BM * D) + pair * (32 * D) + 4 * lane;
+    float *dst = parts + size_t(u.part) * (FWD_BM * D) + pair * (32 * D) + 4 * out_lane;
 #pragma unroll
     for (int b = 0; b < NDB; ++b)
 #pragma unroll
@@ -312,7 +313,7 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
   // last tile)
   __syncthreads();
   static_assert(8 * PATCH_BYTES <= S::TOTAL, "patches fit in the stages");
-  store_tile_as_lines<NDB>(lds0 + wave * PATCH_BYTES, acc, scale, lane, [&](int p) __attribute__((always_inline)) -> bf16_t * {
+  store_tile_as_lines<NDB>(lds0 + wave * PATCH_BYTES, acc, scale, out_lane, [&](int p) __attribute__((always_inline)) -> bf16_t * {
     const int rw = __shfl(row, p);
     return rw >= 0 ? dQ + (size_t(rw) * Hq + head) * D : nullptr;
   });

@@ -30,3 +30,11 @@ def test_planted_copies_in_front_of_an_mfma_are_found():
     assert len(C.check_mfma_operands("\tv_mov_b32_e32 v3, v9\n" + mfma)[1]) == 1
     assert C.check_mfma_operands("\tv_mov_b32_e32 v33, v9\n" + mfma) == (1, [])
     assert C.check_mfma_operands("\tv_mov_b32_e32 v3, v9\n" + mfma.replace(";;#ASMSTART", "").replace(";;#ASMEND", "")) == (0, [])
+
+
+def test_dq_kernel_keeps_everything_in_registers():
+    asm = C.compile_to_asm("ca_bwd.hip")
+    bodies = C.kernel_bodies(asm, "ca_bwd_dq_kernel")
+    assert len(bodies) == 2  # head_dim 128 and 64
+    for body in bodies:
+        assert "scratch_" not in body
