@@ -65,8 +65,8 @@ def test_overflow_inside_a_masked_tile_repeats_the_unit(d):
 @pytest.mark.parametrize("kind", [float("inf"), float("nan")])
 @pytest.mark.parametrize("d,key,rows", [(64, 100, 64), (128, 100, 64), (64, 170, 128), (128, 170, 128)])
 def test_values_beyond_a_waves_last_block_do_not_reach_its_rows(d, key, rows, kind):
-    """Probabilities of masked keys are 0, but 0 times a non-finite value is not: a wave multiplies no 32-key block that none
-    of its rows sees.  Waves hold positions 10..73 and 74..137 here; their last tiles hold blocks from key 96 and from key 160
+    """Probabilities of masked keys are 0, but 0 times a non-finite value is not: a wave multiplies no values of a 32-key block
+    that none of its rows sees.  Waves hold positions 10..73 and 74..137 here; their last tiles hold blocks from key 96 and from key 160
     on that they do not see."""
     b = W.custom([300], [(0, 10, 290)], 2, 2, d, seed=85)
     q, k, v, _ = W.make_tensors(b, DEV)
