@@ -50,7 +50,8 @@ def compile_to_asm(source: str) -> str:
 
 
 def kernel_bodies(asm: str, name_part: str):
-    """The instruction streams (label to s_endpgm) of the kernels whose mangled name contains name_part."""
+    """The instruction streams (label to the function's end: a kernel that returns early has several s_endpgm) of the kernels
+    whose mangled name contains name_part."""
     out, cur = [], None
     for line in asm.split("\n"):
         if cur is None:
@@ -58,7 +59,7 @@ def kernel_bodies(asm: str, name_part: str):
                 cur = [line]
         else:
             cur.append(line)
-            if line.strip().startswith("s_endpgm"):
+            if line.startswith(".Lfunc_end"):
                 out.append("\n".join(cur))
                 cur = None
     return out

@@ -38,3 +38,9 @@ def test_dq_kernel_keeps_everything_in_registers():
     assert len(bodies) == 2  # head_dim 128 and 64
     for body in bodies:
         assert "scratch_" not in body
+
+
+def test_kernels_that_return_early_are_seen_to_their_end():
+    asm = "_Z1kv:\n\ts_endpgm\n.LBB0_1:\n\tscratch_store_dword off, v0, off\n\ts_endpgm\n.Lfunc_end0:\n\tv_nop\n"
+    (body,) = C.kernel_bodies(asm, "1kv")
+    assert "scratch_" in body and body.count("s_endpgm") == 2 and "v_nop" not in body
