@@ -211,12 +211,16 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
     else pin_acc(qf[s]), pin_acc(dof[s]);
   }
   pin(l2), pin(dl);
-  // -Delta enters dP through the matrix pipe: one more k-step whose A fragment is 1 in two k-slots of every key row
-  // and whose B fragment holds -Delta of the lane's query row split in two bf16 (hi + lo, 16 bits of mantissa) in
-  // the same two slots.  One MFMA per 32 keys instead of 16 vector additions: this kernel is bound by its vector
-  // ALU work (the exponentials run at quarter rate), not by the matrix pipe.
-  // (Workgroups of four waves share a register file with the dK/dV units of their launch and need its accumulation half:
-  // there the score tiles are assembly MFMAs with architectural results, and the dP chain starts from -Delta.)
+  // -Delta enters dP through the matrix pipe.  At head_dim 64 the dP chain starts from it: 16 registers hold it as the C
+  // operand (dQ kernel against the extra k-step: 1.53 -> 1.43 ms on a 16K-token document, 0.668 -> 0.631 on 64 of 1024, 32/8
+  // heads; 1.01 -> 0.91 on lone 120-row shards, 8/2).  At 128, where the kernel has no 16 registers left, one more k-step adds it: an A fragment that is 1 in two
+  // k-slots of every key row, and a B fragment that holds -Delta of the lane's query row split in two bf16 (hi + lo, 16 bits of
+  // mantissa) in the same two slots; one MFMA per 32 keys instead of 16 vector additions (this kernel is bound by its vector
+  // ALU work - the exponentials run at quarter rate - not by the matrix pipe).
+  // Workgroups of four waves share a register file with the dK/dV units of their launch and need its accumulation half: there
+  // the score tiles are assembly MFMAs with architectural results.  Both sizes do the same arithmetic in the same order, so
+  // that dQ does not depend on which of them computes it.
+  constexpr bool FROM_DELTA = D == 64;
   bf16x8 ones_f, dl_f;
   f32x16 nd;
 #pragma unroll
@@ -227,7 +231,11 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
     for (int i = 0; i < 8; ++i) ones_f[i] = bf16_t(0.f), dl_f[i] = bf16_t(0.f);
     if (g == 0) ones_f[0] = bf16_t(1.f), ones_f[1] = bf16_t(1.f), dl_f[0] = hi, dl_f[1] = lo;
   }
-  pin(ones_f), pin(dl_f);
+  if constexpr (!FROM_DELTA) {
+    pin(ones_f);
+    if (W == 8) pin(dl_f);
+    else pin_acc(dl_f);
+  }
 
   for (int j = 0; j < n_tiles; ++j) {
     const int j0 = j * FWD_BN;
@@ -245,21 +253,27 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
         f32x16 sa, pa;
         if constexpr (W == 8) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) sa[i] = 0.f, pa[i] = 0.f;
+          for (int i = 0; i < 16; ++i) sa[i] = 0.f, pa[i] = FROM_DELTA ? nd[i] : 0.f;
 #pragma unroll
           for (int s = 0; s < NS; ++s) {
             sa = mfma32(lds_read8_at(kt + koff[s] + 32 * kb * ROWB), qf[s], sa);
             pa = mfma32(lds_read8_at(vt + koff[s] + 32 * kb * ROWB), dof[s], pa);
           }
-          pa = mfma32(ones_f, dl_f, pa);  // dP - Delta
+          if constexpr (!FROM_DELTA) pa = mfma32(ones_f, dl_f, pa);  // dP - Delta
         } else {
 #pragma unroll
           for (int s = 0; s < NS; ++s) {
             const bf16x8 ka = lds_read8_at(kt + koff[s] + 32 * kb * ROWB), va = lds_read8_at(vt + koff[s] + 32 * kb * ROWB);
-            if (s == 0) mfma32_v_first(sa, ka, qf[0]), mfma32_v_first(pa, va, dof[0], nd);
-            else mfma32_v(sa, ka, qf[s]), mfma32_v(pa, va, dof[s]);
+            if (s > 0) mfma32_v(sa, ka, qf[s]), mfma32_v(pa, va, dof[s]);
+            else if constexpr (FROM_DELTA) mfma32_v_first(sa, ka, qf[0]), mfma32_v_first(pa, va, dof[0], nd);
+            else mfma32_v_first(sa, ka, qf[0]), mfma32_v_first(pa, va, dof[0]);
           }
-          mfma_settle(sa, pa, nd);
+          if constexpr (FROM_DELTA) {
+            mfma_settle(sa, pa, nd);
+          } else {
+            mfma32_v(pa, ones_f, dl_f);
+            mfma_settle(sa, pa);
+          }
         }
         uint32_t dw[8];
         // register i holds key j0 + 32 kb + 4 g + 8 (i / 4) + i % 4: visible iff 8 (i / 4) + i % 4 <= vis

@@ -150,3 +150,24 @@ def test_timing_does_not_change_results(hq, hkv, d, shards):
     for n in ("o", "lse", "dq", "dk", "dv"):
         assert torch.equal(got[n], want[n]), n
     assert times["bwd_dkv_ms"] > 0 and times["bwd_dq_ms"] > 0, times
+
+
+@pytest.mark.parametrize("hq,hkv,d,n,length", [(32, 8, 128, 4, 800), (16, 16, 64, 2, 500)])
+def test_whole_units_do_not_depend_on_the_batch(hq, hkv, d, n, length):
+    """With the workspace of whole units, a document's results are the same bit for bit whatever else is in the batch: on its
+    own, where dK/dV and dQ units share a launch, and next to long documents, where they do not."""
+    long = [16384, 9001]
+    small = W.custom([length] * n, [(i, 0, length) for i in range(n)], hq, hkv, d, seed=94)
+    large = W.custom([length] * n + long, [(i, 0, length) for i in range(n)] + [(n + i, 0, m) for i, m in enumerate(long)],
+                     hq, hkv, d, seed=94)
+    t = W.make_tensors(large, DEV)
+    rows, results = n * length, []
+    for b, joint in ((large, 0), (small, 1)):
+        plan = B.ca_plan(b)
+        assert plan.info()["joint_backward"] == joint
+        tb = t if b is large else tuple(x[:rows].contiguous() for x in t)
+        results.append(run(b, tb, 0, plan.workspace_bytes()[1], plan))
+    assert plan.workspace_bytes()[1] == plan.workspace_bytes_split()[1], "nothing is cut: the small batch runs its one launch"
+    for name in ("o", "dq", "dk", "dv"):
+        assert torch.equal(results[0][name][:rows], results[1][name]), name
+    assert torch.equal(results[0]["lse"][:, :rows], results[1]["lse"])
