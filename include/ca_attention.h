@@ -102,9 +102,12 @@ int ca_plan_workspace_bytes(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bw
  * ca_plan_workspace_bytes_split: workspace with which the calls also cut long work units into pieces.  A batch with few
  * long units (a lone shard with a long context, a small batch) leaves most of the GPU idle; given this much workspace
  * ca_forward and ca_backward run such units as several workgroups, whose fp32 partial results (at most 256 MiB more than
- * ca_plan_workspace_bytes, and never beyond CA_STATIC_WS_BYTES where that holds the batch otherwise) are added up by one
- * more launch, in a fixed order.  With less, but at least ca_plan_workspace_bytes, the calls compute the same with whole
- * units; the two differ in the order of fp32 sums.  Equal to ca_plan_workspace_bytes where nothing is cut.
+ * ca_plan_workspace_bytes) are added up by one more launch, in a fixed order.  Equal to ca_plan_workspace_bytes where nothing is
+ * cut.  With less, but at least ca_plan_workspace_bytes, the calls compute the same with whole units, or, where the partial
+ * results go beyond CA_STATIC_WS_BYTES and whole units do not, with pieces that stay within that, if so much is given.
+ * What differs is the order of fp32 sums and the rounding of probabilities (each piece has a reference of its own): which units
+ * are cut depends on the whole batch, so with this workspace the last bits of a document's results depend on what else is in the
+ * batch.  With the workspace of ca_plan_workspace_bytes and not more they follow from the document alone.
  */
 int ca_plan_workspace_bytes_split(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bwd_bytes);
 

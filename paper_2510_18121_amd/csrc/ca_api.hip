@@ -63,6 +63,7 @@ static int static_ws_on_device(int device, void **out) {
 constexpr size_t SMALL_ARRAY = 256 << 10;
 
 static void free_device(ca_plan_t *p) {
+  if (p->within_static) free_device(p->within_static.get());
   if (p->device < 0) return;
   int cur = -1;
   if (hipGetDevice(&cur) == hipSuccess && cur != p->device) (void)hipSetDevice(p->device);
@@ -119,6 +120,10 @@ int ca_plan_upload(ca_plan_t *p, void *hip_stream) {
   }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   free_device(p);
+  if (p->within_static) {
+    const int rc = ca_plan_upload(p->within_static.get(), hip_stream);
+    if (rc != CA_OK) return rc;
+  }
   int dev = -1;
   CA_HIP(hipGetDevice(&dev));
   p->device = dev;
@@ -261,8 +266,11 @@ int ca_forward(const ca_plan_t *p, const void *q, const void *k, const void *v, 
   ca_plan_t *mp = const_cast<ca_plan_t *>(p);  // timing state only
   if (p->profile) (void)hipEventRecord(static_cast<hipEvent_t>(mp->ev[0]), st);
   // with room for partial results (and only then) long units are cut into pieces
-  const bool split = p->ws_fwd_split > 0 && ws && ws_bytes >= p->ws_fwd_split && reinterpret_cast<uintptr_t>(ws) % 256 == 0;
-  hipError_t e = launch_fwd(p, q, k, v, o, lse, split ? ws : nullptr, st);
+  auto fits = [&](const ca_plan_t *x) {
+    return x->ws_fwd_split > 0 && ws && ws_bytes >= x->ws_fwd_split && reinterpret_cast<uintptr_t>(ws) % 256 == 0;
+  };
+  const ca_plan_t *const use = p->within_static && !fits(p) ? p->within_static.get() : p;
+  hipError_t e = launch_fwd(use, q, k, v, o, lse, fits(use) ? ws : nullptr, st);
   if (e != hipSuccess) return hip_fail("forward launch", e);
   if (p->profile) {
     (void)hipEventRecord(static_cast<hipEvent_t>(mp->ev[1]), st);
@@ -285,8 +293,9 @@ int ca_backward(const ca_plan_t *p, const void *q, const void *k, const void *v,
     return CA_ERR_INVALID_ARG;
   }
   ca_plan_t *mp = const_cast<ca_plan_t *>(p);  // timing state only
-  const bool split = p->ws_bwd_split > p->ws_bwd && ws_bytes >= p->ws_bwd_split;
-  hipError_t e = launch_bwd(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, static_cast<hipStream_t>(hip_stream),
+  const ca_plan_t *const use = p->within_static && ws_bytes < p->ws_bwd_split ? p->within_static.get() : p;
+  const bool split = use->ws_bwd_split > use->ws_bwd && ws_bytes >= use->ws_bwd_split;
+  hipError_t e = launch_bwd(use, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, static_cast<hipStream_t>(hip_stream),
                             p->profile ? reinterpret_cast<hipEvent_t *>(&mp->ev[2]) : nullptr);
   if (e != hipSuccess) return hip_fail("backward launch", e);
   if (p->profile) mp->ev_bwd = true;

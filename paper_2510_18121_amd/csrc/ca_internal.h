@@ -2,6 +2,7 @@
 #pragma once
 #include <cstddef>
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -107,6 +108,11 @@ struct ca_plan {
   // if not empty, in this order: i >= 0: dK/dV workgroup i; below: -1 - (half * dQ units + unit)
   std::vector<int32_t> joint_order;
   bool shared_parts = false;  // the dQ parts take the place of the dK/dV parts once those have been added up
+  // simulated time of the cut forward units (0: nothing to cut) and of the backward units and their partial results (0: not simulated)
+  double us_fwd = 0, us_bwd = 0;
+  // where the partial results take the backward workspace beyond the static one, which whole units fit: the plan of the same batch
+  // that stays within it, for calls with less workspace than this plan's lists need
+  std::unique_ptr<ca_plan> within_static;
   // workspace layout for backward: [Delta fp32 hq*padded_slots][log2e*LSE fp32 hq*padded_slots]
   int slot_align = ca::SLOT_ALIGN, heads_packed = 1;  // padding of a document's slots; hp of the packed units
   size_t ws_fwd = 0, ws_bwd = 0, ws_off_l2 = 0, ws_off_qs = 0, ws_off_dos = 0, ws_off_prog = 0;

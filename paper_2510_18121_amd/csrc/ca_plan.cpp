@@ -7,9 +7,11 @@
 // composability observation (Section 3.2: throughput depends on the aggregate tokens of a fused call,
 // not on their document of origin) carried below its 128-token shard granularity.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <numeric>
 #include <sstream>
 
@@ -114,6 +116,7 @@ constexpr double JOINT_MAX_US = 1000;  // batches beyond this fill the chip with
 // simulated, 106 so; of 1600 batches none gets another launch.  (Cut lengths are searched with all units: simulated so, one of
 // 1600 batches got a cut that cost 2 %.)
 constexpr int64_t JOINT_UNITS = 512;
+constexpr double BYTES_PER_US = 4e6;  // partial results, written and read
 struct CutCost {
   int slots;  // workgroups that run at a time
   double per_step, fixed, launch;
@@ -164,10 +167,14 @@ double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_
   return end;
 }
 
-// units: (steps, how many of that size), longest first.  Returns the longest piece in steps, 0 to cut nothing.
-int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const CutCost &c, size_t bytes_per_part,
-                   size_t max_bytes) {
-  constexpr double BYTES_PER_US = 4e6;
+// The longest piece in steps (0: cut nothing) and the launch time that gives, under each of two limits of the partial results.
+struct Cut {
+  int64_t piece = 0;
+  double us = 0;
+};
+// units: (steps, how many of that size), longest first.
+std::array<Cut, 2> best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const CutCost &c, size_t bytes_per_part,
+                              const std::array<size_t, 2> &max_bytes) {
   double total = 0, steps_per_cu = 0;
   int64_t longest = 0, same = c.slots;  // `same`: every size comes a multiple of this many times
   for (const auto &[steps, count] : units) {
@@ -176,12 +183,15 @@ int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const 
     longest = std::max(longest, steps);
     same = std::gcd(same, count);
   }
+  std::array<Cut, 2> cut;
   // no list of pieces can beat the mean load: most batches end here
-  if (c.fixed + c.per_step * double(longest) < 1.2 * total / c.slots) return 0;
+  if (c.fixed + c.per_step * double(longest) < 1.2 * total / c.slots) return cut;
   std::vector<std::pair<double, int64_t>> sizes;  // (microseconds, how many / same)
-  double best = 0;
-  int64_t best_t = 0;
-  int worse = 0;
+  struct Search {
+    double best = 0;
+    int worse = 0;
+    bool done = false;
+  } search[2];
   // whole units first, then pieces from a little over the mean load downwards
   for (double T = double(longest); T >= c.min_steps; T = std::min(T / 1.2, std::max(1.3 * steps_per_cu, 4.0 * c.min_steps))) {
     const int64_t t = int64_t(T);
@@ -199,19 +209,31 @@ int64_t best_piece(const std::vector<std::pair<int64_t, int64_t>> &units, const 
     }
     const size_t bytes = size_t(parts) * bytes_per_part;
     const double extra = parts ? c.launch + double(bytes) / BYTES_PER_US : 0.0;
-    if (parts && (bytes > max_bytes || sum / c.slots + extra >= best)) break;  // more and smaller pieces only cost more
+    for (int i = 0; i < 2; ++i)  // more and smaller pieces only cost more
+      if (parts && (bytes > max_bytes[size_t(i)] || sum / c.slots + extra >= search[i].best)) search[i].done = true;
+    if (search[0].done && search[1].done) break;
     auto longer = [](const auto &x, const auto &y) { return x.first > y.first; };
     std::sort(sizes.begin(), sizes.begin() + n_cut, longer);
     std::inplace_merge(sizes.begin(), sizes.begin() + n_cut, sizes.end(), longer);
-    const double us = parts && piece + extra >= best ? best : makespan(sizes, c.slots / same, parts ? best - extra : 1e30) + extra;
-    if (!parts) best = 0.9 * us;
-    else if (us < best) best = us, best_t = t, worse = 0;
-    else if (++worse == 3) break;
+    double at_most = 0;
+    for (const Search &x : search)
+      if (!x.done) at_most = std::max(at_most, x.best - extra);
+    if (!parts) at_most = 1e30;
+    const double us = piece >= at_most ? piece + extra : makespan(sizes, c.slots / same, at_most) + extra;
+    for (int i = 0; i < 2; ++i) {
+      Search &x = search[i];
+      if (x.done) continue;
+      if (!parts) x.best = 0.9 * us, cut[size_t(i)].us = us;
+      else if (us < x.best) x.best = us, cut[size_t(i)] = {t, us}, x.worse = 0;
+      else if (++x.worse == 3) x.done = true;
+    }
   }
-  return best_t;
+  return cut;
 }
 
-void schedule(ca_plan_t *p) {
+// beyond_static: cut units may take the backward workspace beyond the library's static one where whole units would not.
+// Returns whether the search for cuts saw a tenth less time there.
+bool schedule(ca_plan_t *p, bool beyond_static) {
   const int hq = p->hq, hkv = p->hkv, g = hq / hkv;
   // tasks of each document, by position
   std::vector<std::vector<int32_t>> by_doc(p->n_docs);
@@ -352,10 +374,13 @@ void schedule(ca_plan_t *p) {
     p->peer_stride = int(std::lcm<int64_t>(8, hkv));
     return (p->ws_off_prog + (size_t(p->bwd_workgroups) + 64) * sizeof(int32_t) + 255) / 256 * 256;
   };
-  // Partial results are bounded: a batch that fits the library's static workspace still does with them, a larger one
-  // needs at most this much more.
-  constexpr size_t MAX_CUT_BYTES = size_t(256) << 20;
+  // Partial results are bounded: at most this much more than whole units need, and, unless beyond_static, no more than what the
+  // library's static workspace has left over (at 8 query heads of 128 it holds 15.8K rows, so from 8K rows on too little to cut
+  // with: forward + backward of 9K rows, 8/1 heads, 1.75 ms with what is left and 0.85 ms with 256 MiB).
+  constexpr size_t MAX_CUT_BYTES = size_t(256) << 20, SPARE = 1 << 16;  // SPARE: progress counters
   size_t cut_budget = 0;
+  std::array<size_t, 2> limits{};
+  bool more = false;
   const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.75, 12.0, 5.0, 4} : CutCost{2 * N_CU, 2.0, 14.0, 5.0, 4};
   const CutCost cost_fwd = {N_CU, p->d == 128 ? 2.1 : 1.25, 9.0, 5.0, 4};
   std::vector<int64_t> wg_steps;  // of the dK/dV kernel's workgroups of one KV head, as they are launched
@@ -424,13 +449,16 @@ void schedule(ca_plan_t *p) {
     lay_out(chains, btiles, p->bwd_units, {}, p->bwd_workgroups, p->bwd_single);
     p->ws_bwd = base_workspace();
     // the list in which long units that run alone are cut along their query blocks
-    cut_budget = p->ws_bwd <= CA_STATIC_WS_BYTES ? CA_STATIC_WS_BYTES - p->ws_bwd : MAX_CUT_BYTES;
+    cut_budget = p->ws_bwd <= CA_STATIC_WS_BYTES && !beyond_static ? CA_STATIC_WS_BYTES - p->ws_bwd : MAX_CUT_BYTES;
+    limits = {cut_budget - std::min(cut_budget, SPARE), MAX_CUT_BYTES - SPARE};
     std::vector<std::pair<int64_t, int64_t>> sizes;
     for (auto &c : chains) {
       if (!sizes.empty() && sizes.back().first == c.steps) sizes.back().second += hkv;
       else sizes.push_back({c.steps, hkv});
     }
-    const int64_t T = best_piece(sizes, cost_dkv, part_bytes(p->d), cut_budget - std::min<size_t>(cut_budget, 1 << 16));
+    const auto [cut, free_cut] = best_piece(sizes, cost_dkv, part_bytes(p->d), limits);
+    more = more || free_cut.us < 0.9 * cut.us;
+    const int64_t T = cut.piece;
     if (T > 0) {
       std::vector<BwdUnit> tiles;
       std::vector<int32_t> pieces;
@@ -469,7 +497,10 @@ void schedule(ca_plan_t *p) {
       if (!sizes.empty() && sizes.back().first == t.cost) sizes.back().second += hq / t.u.hp;
       else sizes.push_back({t.cost, hq / t.u.hp});
     }
-    const int64_t T = best_piece(sizes, cost_fwd, part_bytes(p->d) + FWD_STAT_BYTES, cut_budget - std::min<size_t>(cut_budget, 1 << 16));
+    const auto [cut, free_cut] = best_piece(sizes, cost_fwd, part_bytes(p->d) + FWD_STAT_BYTES, limits);
+    more = more || free_cut.us < 0.9 * cut.us;
+    p->us_fwd = cut.us;
+    const int64_t T = cut.piece;
     if (T > 0) {
       std::vector<TileRef> pieces;
       for (auto &t : ftiles) {
@@ -542,7 +573,11 @@ void schedule(ca_plan_t *p) {
           longest = std::max(longest, us);
           i += n;
         }
+      const double parts_us = p->n_fwd_parts + p->n_bwd_parts > 0
+                                  ? cost_dkv.launch + double(size_t(p->n_fwd_parts + p->n_bwd_parts) * part_bytes(p->d)) / BYTES_PER_US
+                                  : 0.0;
       const double apart = makespan(dkv, slots / same, 1e30, JOINT_UNITS) + makespan(dq, N_CU / same, 1e30, JOINT_UNITS) + cost_dkv.launch;
+      p->us_bwd = apart + parts_us;
       if (sum / slots < apart) {
         std::vector<std::pair<double, int64_t>> all;
         auto span_of = [&](double at_most) {
@@ -560,6 +595,7 @@ void schedule(ca_plan_t *p) {
         }
         const bool order = sorted < goal;
         p->joint = order || listed < apart;
+        if (p->joint) p->us_bwd = (order ? sorted : listed) + parts_us;
         if (p->joint && order)
           for (const Group &x : groups)
             for (int32_t i = 0; i < x.n; ++i) p->joint_order.push_back(x.entry + i * x.step);
@@ -578,12 +614,33 @@ void schedule(ca_plan_t *p) {
     p->ws_off_parts_kv = p->ws_off_parts_dq = at;
     const size_t kv = size_t(p->n_bwd_parts) * part_bytes(p->d), dq = size_t(p->n_fwd_parts) * part_bytes(p->d);
     p->shared_parts = kv > 0 && dq > 0 && at - p->ws_bwd + kv + dq > cut_budget;
-    if (p->shared_parts) p->joint = false;
+    if (p->shared_parts) p->joint = false;  // (its time stays estimated as if it were not shared: a launch of a few us)
     else p->ws_off_parts_dq += kv;
     p->ws_bwd_split = std::max(p->ws_off_parts_kv + kv, p->ws_off_parts_dq + dq);
   }
   p->q_covered = covered_q == p->total_q;
   p->kv_covered = covered_kv == p->total_kv;
+  return more;
+}
+
+std::unique_ptr<ca_plan_t> described(const ca_batch_desc *desc) {
+  auto p = std::make_unique<ca_plan_t>();
+  p->n_docs = desc->n_docs, p->n_tasks = desc->n_tasks;
+  p->hq = desc->n_q_heads, p->hkv = desc->n_kv_heads, p->d = desc->head_dim;
+  p->total_q = desc->total_q, p->total_kv = desc->total_kv;
+  p->scale = desc->softmax_scale > 0.f ? desc->softmax_scale : 1.0f / std::sqrt(float(desc->head_dim));
+  if (desc->n_docs > 0) {
+    p->doc_kv_start.assign(desc->doc_kv_start, desc->doc_kv_start + desc->n_docs);
+    p->doc_kv_len.assign(desc->doc_kv_len, desc->doc_kv_len + desc->n_docs);
+  }
+  if (desc->n_tasks > 0) {
+    p->task_doc.assign(desc->task_doc, desc->task_doc + desc->n_tasks);
+    p->task_q_start.assign(desc->task_q_start, desc->task_q_start + desc->n_tasks);
+    p->task_q_len.assign(desc->task_q_len, desc->task_q_len + desc->n_tasks);
+    p->task_q_pos.assign(desc->task_q_pos, desc->task_q_pos + desc->n_tasks);
+    p->task_kv_len.assign(desc->task_kv_len, desc->task_kv_len + desc->n_tasks);
+  }
+  return p;
 }
 }  // namespace
 
@@ -593,36 +650,27 @@ int build_plan(const ca_batch_desc *desc, ca_plan_t **out) {
     return CA_ERR_INVALID_ARG;
   }
   *out = nullptr;
-  ca_plan_t *p = nullptr;
   try {
     validate(desc);
-    p = new ca_plan_t();
-    p->n_docs = desc->n_docs, p->n_tasks = desc->n_tasks;
-    p->hq = desc->n_q_heads, p->hkv = desc->n_kv_heads, p->d = desc->head_dim;
-    p->total_q = desc->total_q, p->total_kv = desc->total_kv;
-    p->scale = desc->softmax_scale > 0.f ? desc->softmax_scale : 1.0f / std::sqrt(float(desc->head_dim));
-    if (desc->n_docs > 0) {
-      p->doc_kv_start.assign(desc->doc_kv_start, desc->doc_kv_start + desc->n_docs);
-      p->doc_kv_len.assign(desc->doc_kv_len, desc->doc_kv_len + desc->n_docs);
+    auto p = described(desc);
+    // Where cutting units beyond the static workspace looks better by a tenth, both plans are made, and kept if the whole pass
+    // is: the larger for callers that bring the workspace, the smaller inside it for all others.
+    if (schedule(p.get(), false)) {
+      auto large = described(desc);
+      schedule(large.get(), true);
+      if (p->us_bwd > 0 && large->us_bwd > 0 && large->us_fwd + large->us_bwd < 0.9 * (p->us_fwd + p->us_bwd)) {
+        large->within_static = std::move(p);
+        p = std::move(large);
+      }
     }
-    if (desc->n_tasks > 0) {
-      p->task_doc.assign(desc->task_doc, desc->task_doc + desc->n_tasks);
-      p->task_q_start.assign(desc->task_q_start, desc->task_q_start + desc->n_tasks);
-      p->task_q_len.assign(desc->task_q_len, desc->task_q_len + desc->n_tasks);
-      p->task_q_pos.assign(desc->task_q_pos, desc->task_q_pos + desc->n_tasks);
-      p->task_kv_len.assign(desc->task_kv_len, desc->task_kv_len + desc->n_tasks);
-    }
-    schedule(p);
+    *out = p.release();
   } catch (const Fail &f) {
-    delete p;
     set_error(f.msg);
     return f.code;
   } catch (const std::bad_alloc &) {
-    delete p;
     set_error("out of host memory while planning");
     return CA_ERR_INVALID_ARG;
   }
-  *out = p;
   return CA_OK;
 }
 

@@ -171,3 +171,29 @@ def test_whole_units_do_not_depend_on_the_batch(hq, hkv, d, n, length):
     for name in ("o", "dq", "dk", "dv"):
         assert torch.equal(results[0][name][:rows], results[1][name]), name
     assert torch.equal(results[0]["lse"][:, :rows], results[1]["lse"])
+
+
+@pytest.mark.parametrize("hq,hkv,d,shard", [(8, 1, 128, (0, 9000)), (32, 4, 64, (50, 5000))])
+def test_pieces_beyond_and_inside_the_static_workspace(hq, hkv, d, shard):
+    """Partial results that go beyond the static workspace, which whole units fit: with room for them, with the static
+    workspace's size (pieces that stay inside it), through the static workspace itself, and as whole units."""
+    a, n = shard
+    b = W.custom([a + n], [(0, a, n)], hq, hkv, d, seed=96)
+    t = W.make_tensors(b, DEV)
+    plan, static = B.ca_plan(b), B.lib().ca_static_workspace_bytes()
+    (_, b0), (f1, b1) = plan.workspace_bytes(), plan.workspace_bytes_split()
+    assert b0 <= static < b1
+    ref = P.run_oracle(b, *t)
+    results = {}
+    for ws_f, ws_b in ((f1, b1), (0, b1 - 1), (0, static), (0, b0)):
+        r = results[ws_b] = run(b, t, ws_f, ws_b, plan)
+        e = P.errors(r, ref)
+        print(hq, hkv, d, ws_f, ws_b, e, flush=True)
+        P.assert_parity(e, (ws_f, ws_b))
+    q, k, v, d_o = t
+    r = results[static]
+    dq, dk, dv = (torch.full_like(x, float("nan")) for x in (q, k, v))
+    B.ca_backward_static_ws(plan, q, k, v, r["o"], d_o, r["lse"], dq, dk, dv)
+    torch.cuda.synchronize()
+    for name, got in (("dq", dq), ("dk", dk), ("dv", dv)):
+        assert torch.equal(got, r[name]) and torch.equal(results[b1 - 1][name], r[name]), name

@@ -44,7 +44,12 @@ def planner(tmp_path_factory):
     main.write_text('#include "ca_plan.cpp"\nextern "C" void ca_plan_destroy_host(ca_plan_t *p) { delete p; }\n'
                     'extern "C" double simulate(const double *us, const int64_t *n, int64_t k, int64_t cus, double at_most) {\n'
                     "  std::vector<std::pair<double, int64_t>> u;\n  for (int64_t i = 0; i < k; ++i) u.push_back({us[i], n[i]});\n"
-                    "  return ca::makespan(u, cus, at_most, 512);\n}\n")
+                    "  return ca::makespan(u, cus, at_most, 512);\n}\n"
+                    'extern "C" int64_t within(const ca_plan_t *p, int64_t *out) {\n'
+                    "  const ca_plan_t *s = p->within_static.get();\n  if (!s) return 0;\n"
+                    "  const int64_t v[6] = {int64_t(s->ws_bwd), int64_t(s->ws_bwd_split), int64_t(p->ws_bwd_split), s->n_fwd_parts, s->n_bwd_parts,\n"
+                    "                        int64_t(s->bwd_units.size()) - int64_t(p->bwd_units.size())};\n"
+                    "  for (int i = 0; i < 6; ++i) out[i] = v[i];\n  return 1;\n}\n")
     csrc = os.path.join(ROOT, "paper_2510_18121_amd", "csrc")
     subprocess.run([CXX, "-O1", "-std=c++17", "-shared", "-fPIC", "-fsanitize=float-divide-by-zero", "-fno-sanitize-recover=all",
                     "-I", csrc, "-I", os.path.join(ROOT, "include"), "-o", out, str(main)], check=True)
@@ -90,3 +95,26 @@ def test_simulated_list_schedule(planner, seed):
             mean = float((us * n).sum()) / cus
             assert max(0.99 * mean, us[0]) <= got and abs(got - want) <= 0.03 * want, (seed, total, cus, got, want)
         assert lib.simulate(us.ctypes.data, n.ctypes.data, len(us), cus, 0.5 * got) >= 0.5 * got
+
+
+def test_plan_inside_the_static_workspace(planner):
+    """Where partial results go beyond the static workspace, which whole units fit, the plan holds another one that stays inside."""
+    from paper_2510_18121_amd import binding as B
+    from paper_2510_18121_amd import workloads as W
+
+    lib, static = ctypes.CDLL(planner), B.lib().ca_static_workspace_bytes()
+    lib.ca_plan_host.argtypes = B.lib().ca_plan_host.argtypes
+    lib.within.restype, lib.within.argtypes = ctypes.c_int64, [ctypes.c_void_p, ctypes.c_void_p]
+    lib.ca_plan_destroy_host.argtypes = [ctypes.c_void_p]
+    seen = 0
+    for n, hq, hkv, d in ((6000, 8, 1, 128), (9000, 8, 1, 128), (15800, 8, 1, 128), (16500, 8, 1, 128), (1900, 64, 8, 128), (26000, 8, 1, 64)):
+        keep, h = [], ctypes.c_void_p()
+        desc = B.make_desc(W.custom([n], [(0, 0, n)], hq, hkv, d), keep)
+        assert lib.ca_plan_host(ctypes.byref(desc), ctypes.byref(h)) == 0
+        out = np.zeros(6, np.int64)
+        if lib.within(h, out.ctypes.data):
+            seen += 1
+            base, inside, beyond, _, _, units = out.tolist()
+            assert base <= inside <= static < beyond <= base + (256 << 20) and units == 0
+        lib.ca_plan_destroy_host(h)
+    assert seen >= 3
