@@ -112,11 +112,13 @@ int ca_plan_workspace_bytes(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bw
 int ca_plan_workspace_bytes_split(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bwd_bytes);
 
 /*
- * ca_forward: O and LSE for every query row of every task, one fused launch on `hip_stream`.
+ * ca_forward: O and LSE for every query row of every task, one fused launch on `hip_stream`, or two where units are cut (the
+ * second adds up the partial results that the first has left in ws).
  * q,k,v: device bf16 inputs; o: device bf16 output; lse: device fp32 output [n_q_heads][total_q].
- * ws: device workspace of at least fwd_bytes (may be NULL when fwd_bytes is 0), 256-byte aligned; used, if it is given, for
- * partial results when it has the size ca_plan_workspace_bytes_split states.
- * Allocates nothing, never synchronises.
+ * ws: device workspace of at least fwd_bytes (may be NULL when fwd_bytes is 0), 256-byte aligned.  It is WRITTEN if it has room
+ * for the partial results of cut units (ca_plan_workspace_bytes_split), and not touched otherwise.
+ * Allocates nothing, never synchronises.  Two calls, forward or backward, whose workspaces overlap must not overlap in time on
+ * the device: a forward on one stream next to a forward or backward on another needs a workspace of its own, or none.
  */
 int ca_forward(const ca_plan_t *plan, const void *q, const void *k, const void *v, void *o, float *lse,
                void *ws, size_t ws_bytes, void *hip_stream);
@@ -129,8 +131,11 @@ int ca_forward(const ca_plan_t *plan, const void *q, const void *k, const void *
  * position-sorted bf16 copies of Q and dO
  * (bwd_bytes is about 4 * n_q_heads * padded_rows * (4 + head_dim) bytes: a little over the size of Q plus dO),
  * and one 4-byte progress counter per workgroup of the dK/dV kernel, through which at head_dim 128 workgroups that read the
- * same Q/dO tiles pace each other (timing only).  No arithmetic uses atomics: results are bit-reproducible from run to run.  Allocates
- * nothing, never synchronises.  Two calls whose workspaces overlap must not overlap in time on the device.
+ * same Q/dO tiles pace each other (timing only); and the partial results of cut units, if it has room for them
+ * (ca_plan_workspace_bytes_split).  Launches the preparation, the kernels of dK/dV and dQ (one launch where both are small), one
+ * or two that add up partial results where units are cut, and fills for rows that belong to no task or document.  No arithmetic
+ * uses atomics: results are bit-reproducible from run to run.  Allocates nothing, never synchronises.  Two calls, forward or
+ * backward, whose workspaces overlap must not overlap in time on the device.
  */
 int ca_backward(const ca_plan_t *plan, const void *q, const void *k, const void *v, const void *o,
                 const void *d_o, const float *lse, void *dq, void *dk, void *dv,
@@ -139,7 +144,7 @@ int ca_backward(const ca_plan_t *plan, const void *q, const void *k, const void 
 /*
  * ca_backward_static_ws: ca_backward for callers that can neither allocate device memory nor hold a workspace of
  * their own: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * results and kernels as ca_backward, minus `ws`: the workspace is a device-resident array of
+ * results and kernels as ca_backward with a workspace of that size, minus `ws`: the workspace is a device-resident array of
  * CA_STATIC_WS_BYTES inside the library (every GPU the library runs on holds its own copy until the process
  * ends; its address on the current device is looked up on the first call there, with no allocation).
  * A batch whose ca_plan_workspace_bytes() backward figure exceeds CA_STATIC_WS_BYTES is refused with

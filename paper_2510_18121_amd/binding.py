@@ -232,7 +232,8 @@ def _expect(t, shape, dtype, name):
 
 
 def ca_forward(plan: Plan, q, k, v, o, lse, ws=None, stream=None):
-    """Launch the fused forward on torch's current stream (or `stream`).  Writes o (bf16) and lse (fp32)."""
+    """Launch the fused forward on torch's current stream (or `stream`).  Writes o (bf16) and lse (fp32), and, if it has room
+    for the partial results of cut units, ws: calls that may overlap in time need one each, or none."""
     import torch
     b, bf16 = plan.batch, torch.bfloat16
     qs, ks = (b.total_q, b.n_q_heads, b.head_dim), (b.total_kv, b.n_kv_heads, b.head_dim)
