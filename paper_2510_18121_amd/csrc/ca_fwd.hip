@@ -26,7 +26,7 @@
 // softmax runs in base 2 with scale*log2(e) folded into one FMA.
 //
 // At head_dim 64 a tile has half the MFMAs for the same exponentials: the kernel is bound by its vector work and, with
-// one wave per SIMD, by its latencies.  Its 254 registers and 64 KB of LDS let two workgroups share a CU there, so that
+// one wave per SIMD, by its latencies.  Its 248 registers and 64 KB of LDS let two workgroups share a CU there, so that
 // one computes while the other waits: 190 -> 139 us on 16K tokens of 2K-token documents (16/16 heads), 855 -> 765 us
 // on 32K tokens of lone 120-row shards with contexts of up to 16K (8/2 heads).
 #include <atomic>
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
   auto read_v = [&](uint32_t vb, int t, int b) __attribute__((always_inline)) {
     return join(lds_read_tr4_at(voff[0][b] + vb + 16 * t * ROWB), lds_read_tr4_at(voff[1][b] + vb + 16 * t * ROWB));
   };
-  // scores of both groups for one block, not interleaved with anything (prologue and diagonal tiles)
+  // scores of both groups for one block, not interleaved with anything (prologue and general path)
   auto scores_plain = [&](uint32_t kb, f32x16 &s0, f32x16 &s1) __attribute__((always_inline)) {
     bf16x8 ka[NS];
     read_k(kb, ka);
@@ -239,16 +239,15 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
   auto p_operand = [&](const uint32_t (&pw)[8], int t) __attribute__((always_inline)) {
     return __builtin_bit_cast(bf16x8, u32x4{pw[4 * t], pw[4 * t + 1], pw[4 * t + 2], pw[4 * t + 3]});
   };
-  // P V of one block for both groups (or one), not interleaved with anything
-  auto pv_plain = [&](uint32_t vb, const uint32_t (&p0)[8], const uint32_t (&p1)[8], bool do0, bool do1)
-                      __attribute__((always_inline)) {
+  // P V of one block for both groups, not interleaved with anything
+  auto pv_plain = [&](uint32_t vb, const uint32_t (&p0)[8], const uint32_t (&p1)[8]) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int b = 0; b < NDB; ++b) {
         const bf16x8 a = read_v(vb, t, b);
-        if (do0) acc[0][b] = mfma32(a, p_operand(p0, t), acc[0][b]);
-        if (do1) acc[1][b] = mfma32(a, p_operand(p1, t), acc[1][b]);
+        acc[0][b] = mfma32(a, p_operand(p0, t), acc[0][b]);
+        acc[1][b] = mfma32(a, p_operand(p1, t), acc[1][b]);
       }
   };
 
@@ -291,7 +290,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
       exp_pack(gx, x[gx], pw[gx]);
     }
     const uint32_t vb = uint32_t(kb * BLK);
-    pv_plain(vb, pw[0], pw[1], true, true);
+    pv_plain(vb, pw[0], pw[1]);
     // The first rows of a document see a handful of keys, their output is as large as a single V row, and
     // the 2^-9 relative rounding of P to bf16 then shows up at the 1e-2 level next to the output's own bf16
     // rounding.  For the waves that hold such rows, the rounding residue of P is fed through the matrix pipe
@@ -306,7 +305,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, D == 64 ? 2 : 1) void ca_fwd_kernel
           const uint32_t h = pw[gx][e];
           pl[gx][e] = pack_bf16(x[gx][2 * e] - __uint_as_float(h << 16), x[gx][2 * e + 1] - __uint_as_float(h & 0xffff0000u));
         }
-      pv_plain(vb, pl[0], pl[1], true, true);
+      pv_plain(vb, pl[0], pl[1]);
     }
   };
 

@@ -104,7 +104,8 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // steps into equal pieces evens the load out and costs a `fixed` per piece, the partial results (written by the pieces,
 // read once more to be added up) and another launch.  The T with the shortest total is taken, if it gains a tenth: at
 // 4K tokens of 1K-token documents (32/8 heads) the simulation gives 362 us for the dK/dV kernel's 256 whole units (measured
-// 325) and 210 us for 504 pieces of at most 60 steps.
+// 332) and 199 us for 472 units and pieces of at most 64 steps (measured 232, and 10 to add the pieces up): good enough to rank
+// cuts by, not to predict what one gains.
 // The figures are microseconds measured on MI355X: per step 1.7 (forward), 2.6 (dQ) and 1.75 (dK/dV) at head_dim 128, 1.0,
 // 1.5 and 1.1 at 64; the fixed part is what a unit spends around its steps (descriptor, row indices, fragments, first
 // tiles, drain, results); partial results move at about 4 TB/s.  Two dK/dV workgroups share a CU at head_dim 64, each at
