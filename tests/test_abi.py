@@ -70,3 +70,19 @@ def test_mfma_stream_rejects_bad_arguments_on_the_host():
     assert lib.ca_mfma_stream(None, 64, 4, 0, None, None) == B.CA_ERR_INVALID_ARG
     assert b"null" in lib.ca_last_error()
     assert lib.ca_mfma_stream(None, 64, 0, 0, None, None) == B.CA_OK
+
+
+def test_current_stream_without_torchs_raw_handle(monkeypatch):
+    """The stream comes from torch's raw handle, which is not part of its public interface, or else from the stream object."""
+    import types
+
+    import torch
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 55 + device, raising=False)
+    assert B._stream_ptr(None) == 55
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert B._stream_ptr(None) == 77 and B._stream_ptr(5) == 5
