@@ -114,8 +114,8 @@ constexpr int N_CU = 256;
 constexpr double JOINT_MAX_US = 1000;  // batches beyond this fill the chip with either kernel
 // The choice between one backward launch and two simulates lists of thousands of units, at 20 to 40 ns each more than the rest
 // of planning takes: ca_plan_host for 37K tokens in lone 860-row shards (8/1 heads) 65 us without it, 192 with all units
-// simulated, 106 so; of 1600 batches none gets another launch.  (Cut lengths are searched with all units: simulated so, one of
-// 1600 batches got a cut that cost 2 %.)
+// simulated, 106 so; of 1600 batches none gets another launch, two of 600 another order in it (backward 0.7 % slower, 0.3 %
+// faster).  (Cut lengths are searched with all units: simulated so, one of 1600 batches got a cut that cost 2 %.)
 constexpr int64_t JOINT_UNITS = 512;
 constexpr double BYTES_PER_US = 4e6;  // partial results, written and read
 struct CutCost {
