@@ -219,7 +219,9 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
   // ALU work - the exponentials run at quarter rate - not by the matrix pipe).
   // Workgroups of four waves share a register file with the dK/dV units of their launch and need its accumulation half: there
   // the score tiles are assembly MFMAs with architectural results.  Both sizes do the same arithmetic in the same order, so
-  // that dQ does not depend on which of them computes it.
+  // that dQ does not depend on which of them computes it.  (At 128 the extra k-step is an MFMA of 25 for workgroups of four,
+  // which could start from -Delta: 0 to 0.8 % of the passes that use them.  Starting from -Delta in workgroups of eight, 16
+  // registers set anew for every block, makes the dQ kernel 1 % slower; kept in registers it spills, 30 % slower.)
   constexpr bool FROM_DELTA = D == 64;
   bf16x8 ones_f, dl_f;
   f32x16 nd;
