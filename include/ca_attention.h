@@ -130,8 +130,7 @@ int ca_forward(const ca_plan_t *plan, const void *q, const void *k, const void *
  * slot), fp32 -<dO, O> and log2(e)*LSE (twice: by head and slot, and in the row order of the dK/dV kernel's tiles), and
  * position-sorted bf16 copies of Q and dO
  * (bwd_bytes is about 4 * n_q_heads * padded_rows * (4 + head_dim) bytes: a little over the size of Q plus dO),
- * and one 4-byte progress counter per workgroup of the dK/dV kernel, through which at head_dim 128 workgroups that read the
- * same Q/dO tiles pace each other (timing only); and the partial results of cut units, if it has room for them
+ * and the partial results of cut units, if it has room for them
  * (ca_plan_workspace_bytes_split).  Launches the preparation, the kernels of dK/dV and dQ (one launch where both are small), one
  * or two that add up partial results where units are cut, and fills for rows that belong to no task or document.  No arithmetic
  * uses atomics: results are bit-reproducible from run to run.  Allocates nothing, never synchronises.  Two calls, forward or

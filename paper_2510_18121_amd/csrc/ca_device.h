@@ -25,6 +25,13 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// v_mfma_f32_16x16x32_bf16: C[16x16] += A[16x32] * B[32x16].
+//   A: lane l holds A[l%16][8*(l/16) .. +7];  B: lane l holds B[8*(l/16) .. +7][l%16];
+//   C: lane l, register i holds C[4*(l/16) + i][l%16].
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // 16-byte LDS read of 8 consecutive bf16.
 __device__ __forceinline__ bf16x8 lds_read8(const char *p) { return *reinterpret_cast<const bf16x8 *>(p); }
 
@@ -69,6 +76,20 @@ __device__ __forceinline__ float xor32_max(float x) {
 
 __device__ __forceinline__ int lane_id() { return int(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))); }
 
+// A constant that the compiler cannot see through: what is computed from it is computed where it stands, not kept in a register
+// (or spilled) across a long loop.  The vector instruction itself stays the compiler's, which places the wait states that
+// MFMAs in flight need around it.
+__device__ __forceinline__ int opaque(int k) {
+  asm volatile("" : "+s"(k));
+  return k;
+}
+__device__ __forceinline__ int lane_id_here() {
+  const uint32_t all = opaque(-1);
+  return int(__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u)));
+}
+// a ^ b: of a loop-carried LDS address and the distance to one of its fragments
+__device__ __forceinline__ int xor_here(int a, const int b) { return a ^ opaque(b); }
+
 __device__ __forceinline__ int wave_max(int v) {
   for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
   return v;
@@ -97,6 +118,19 @@ namespace ca {
 template <int D>
 __device__ __forceinline__ int tile_sw(int r) {
   return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
+}
+
+// The same for tiles that feed 16x16 MFMAs:
+//   * A natural read is 16 rows x 64 bytes: lane l reads chunk 4 s + l / 16 of row l % 16, and the 16 lanes served together are 0-3,
+//     12-15 of one run of 16 lanes and 4-11 of the next one's (a swizzle without conflicts inside each run has them in every
+//     second read: 30 to 40 % of the LDS cycles of the backward kernels).  So with q = r / 4 % 4 the low bits f(q) of sw are
+//     0, 2, 3, 1: f(1) = f(2) ^ 1 and f(0) = f(3) ^ 1 keep those apart; bits 2..3 follow the row's low bits.
+//   * An 8-byte transposing read is served 8 consecutive rows x one 32-byte piece at a time: f(0), f(1) as well as f(2), f(3)
+//     differ in bit 1.
+template <int D>
+__device__ __forceinline__ int tile_sw16(int r) {
+  const int q0 = (r >> 2) & 1, q1 = (r >> 3) & 1;
+  return (D == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2) | (q0 ^ q1) << 1 | q1;
 }
 
 // byte offset of logical 16-byte chunk c of row r
@@ -129,6 +163,17 @@ __device__ __forceinline__ void load_lds16_sbase(const void *base_uniform, uint3
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
   const uint64_t sb = ((uint64_t)hi << 32) | lo;
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :
+               : "v"(lane_off), "s"(sb), "s"(m0v)
+               : "memory", "m0");
+}
+// the 4-byte form
+__device__ __forceinline__ void load_lds4_sbase(const void *base_uniform, uint32_t lane_off, uint32_t lds_off_uniform) {
+  const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_off_uniform);
+  const uint64_t b = (uint64_t)(uintptr_t)base_uniform;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  const uint64_t sb = ((uint64_t)hi << 32) | lo;
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :
                : "v"(lane_off), "s"(sb), "s"(m0v)
                : "memory", "m0");
@@ -304,6 +349,14 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 
+// Workgroups that are halves of n units: which unit and which half workgroup i of 2 n is.  The halves of a unit are 8 workgroups
+// apart, on one XCD: they read the same K and V.
+__device__ __forceinline__ void half_of_unit(int &i, int n, int &half) {
+  const int n8 = n & ~7, rest = n - n8, t = i - 2 * n8;  // (the last units have fewer than 8 neighbours)
+  half = t < 0 ? !((i >> 3) & 1) : t < rest;
+  i = t < 0 ? (i >> 4) * 8 + (i & 7) : n8 + t - (half ? 0 : rest);
+}
+
 // ---- a wave's 32 x D result tile, stored as whole lines.
 // In the accumulator layout of Xt = A B (32x32 MFMAs, 32-row blocks b of the D values) lane (r, g) holds, of row r
 // (a key, or a query row), the values 32 b + 8 q4 + 4 g .. + 3 in acc[b][4 q4 ..]: 4 values out of every 8.  Stored
@@ -339,6 +392,45 @@ __device__ __forceinline__ void store_tile_as_lines(uint32_t patch, const f32x16
       if (dst[i]) *reinterpret_cast<u32x4 *>(dst[i] + 64 * h + 8 * ocol) = x;
     }
   }
+}
+
+// The same for a tile computed by 16x16 MFMAs: of row 16 t + lane % 16, acc[b][t] holds the values 16 b + 4 (lane / 16) .. + 3.
+// (tiles T0 and T0 + 1 of acc; f0 and f1 scale their values.)
+template <int T0, int ND, int NT, class F>
+__device__ __forceinline__ void store_tile16_as_lines(uint32_t patch, const f32x4 (&acc)[ND][NT], float f0, float f1, int lane,
+                                                      F dst_of_row) {
+  const int orow = lane >> 3, ocol = lane & 7;
+  const uint32_t wr = patch + (lane & 15) * PATCH_ROW_BYTES + 8 * (lane >> 4);  // + 16 rows t + 32 b
+  const uint32_t rd = patch + orow * PATCH_ROW_BYTES + 16 * ocol;               // the lane's row (+ 8 i) and 16-byte piece
+  bf16_t *dst[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) dst[i] = dst_of_row(orow + 8 * i);
+#pragma unroll
+  for (int h = 0; h < ND / 4; ++h) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const f32x4 a = acc[4 * h + b][T0 + t];
+        const float f = t == 0 ? f0 : f1;
+        *(CA_LDS u32x2 *)(wr + 16 * t * PATCH_ROW_BYTES + 32 * b) = u32x2{pack_bf16(a[0] * f, a[1] * f), pack_bf16(a[2] * f, a[3] * f)};
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u32x4 x = *(const CA_LDS u32x4 *)(rd + 8 * i * PATCH_ROW_BYTES);
+      if (dst[i]) *reinterpret_cast<u32x4 *>(dst[i] + 64 * h + 8 * ocol) = x;
+    }
+  }
+}
+// ... and as a partial result, in the order of 32x32 accumulators that the combine kernels read: quad k of lane (r, g) is
+// columns 8 k + 4 g .. + 3 of row r (256-byte runs per 16 lanes)
+template <int T0, int ND, int NT>
+__device__ __forceinline__ void store_tile16_as_part(float *dst, const f32x4 (&acc)[ND][NT], int lane) {
+  dst += 256 * (lane >> 5) + 128 * ((lane >> 4) & 1) + 4 * (lane & 15);
+#pragma unroll
+  for (int b = 0; b < ND; ++b)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4 *>(dst + 512 * b + 64 * t) = acc[b][T0 + t];
 }
 
 // ---- sums of partial results (the combine kernels).  One workgroup of four waves adds up the n_parts blocks of 32 rows x

@@ -18,7 +18,7 @@ constexpr int FWD_BN = 64;   // keys per forward inner step
 constexpr int BWD_BN = 128;  // keys owned by one backward work unit (4 waves x 32)
 constexpr int BWD_BQ = 64;   // query rows per backward inner step
 
-// One workgroup of the forward / dQ kernels (half of it in the joint backward launch): 8 row groups of 32 slots, one or
+// One workgroup of the forward / dQ kernels, or two (halves, in the joint backward launch): 8 row groups of 32 slots, one or
 // two to a wave.  A full tile of a document is 256 slots of one query head (hp = 1).  The slots a document has left over
 // after its full tiles are covered by head-packed units instead: 256 / hp slots of hp consecutive query heads of one KV
 // group (they read the same K/V), row group w taking slots slot0 + 32 (w / hp) .. of head  head + w % hp  - so that
@@ -94,19 +94,19 @@ struct ca_plan {
   std::vector<ca::FwdUnit> fwd_units;
   std::vector<ca::BwdUnit> bwd_units;
   int32_t bwd_workgroups = 0;  // workgroups of the dK/dV kernel: the leading units of bwd_units
-  int32_t bwd_single = 0;      // so many leading workgroups are units that run alone (only those pace each other)
   int64_t fwd_steps = 0, bwd_steps = 0;
   // the lists with long units cut into pieces; empty where that gains nothing
   std::vector<ca::FwdUnit> fwd_pieces;
   std::vector<ca::BwdUnit> bwd_pieces;
   std::vector<ca::CombineUnit> fwd_combine, bwd_combine;
-  int32_t bwd_piece_workgroups = 0, bwd_piece_single = 0;
+  int32_t bwd_piece_workgroups = 0;
   int32_t n_fwd_parts = 0, n_bwd_parts = 0;
   // workspace with which the piece lists are used: forward, and backward, where the parts lie behind ws_bwd
   size_t ws_fwd_split = 0, ws_bwd_split = 0, ws_off_parts_kv = 0, ws_off_parts_dq = 0;
   bool joint = false;  // backward runs dK/dV and dQ units in one launch: dK/dV workgroups, then dQ halves 1, then 0, or,
   // if not empty, in this order: i >= 0: dK/dV workgroup i; below: -1 - (half * dQ units + unit)
   std::vector<int32_t> joint_order;
+  bool joint_lost = false;  // one launch looked better, but the parts are shared
   bool shared_parts = false;  // the dQ parts take the place of the dK/dV parts once those have been added up
   // simulated time of the cut forward units (0: nothing to cut) and of the backward units and their partial results (0: not simulated)
   double us_fwd = 0, us_bwd = 0;
@@ -115,9 +115,8 @@ struct ca_plan {
   std::unique_ptr<ca_plan> within_static;
   // workspace layout for backward: [Delta fp32 hq*padded_slots][log2e*LSE fp32 hq*padded_slots]
   int slot_align = ca::SLOT_ALIGN, heads_packed = 1;  // padding of a document's slots; hp of the packed units
-  size_t ws_fwd = 0, ws_bwd = 0, ws_off_l2 = 0, ws_off_qs = 0, ws_off_dos = 0, ws_off_prog = 0;
+  size_t ws_fwd = 0, ws_bwd = 0, ws_off_l2 = 0, ws_off_qs = 0, ws_off_dos = 0;
   size_t ws_off_delta_kv = 0, ws_off_l2_kv = 0;  // the row statistics once more, in the row order of the dK/dV tiles
-  int peer_stride = 8;  // distance, in backward units, between units of one KV head that run on one XCD
   bool q_covered = false, kv_covered = false;  // every packed Q row / KV row belongs to some unit
   // device copies
   int device = -1;

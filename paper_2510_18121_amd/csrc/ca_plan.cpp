@@ -106,12 +106,17 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // 4K tokens of 1K-token documents (32/8 heads) the simulation gives 362 us for the dK/dV kernel's 256 whole units (measured
 // 332) and 199 us for 472 units and pieces of at most 64 steps (measured 232, and 10 to add the pieces up): good enough to rank
 // cuts by, not to predict what one gains.
-// The figures are microseconds measured on MI355X: per step 1.7 (forward), 2.6 (dQ) and 1.75 (dK/dV) at head_dim 128, 1.0,
-// 1.5 and 1.1 at 64; the fixed part is what a unit spends around its steps (descriptor, row indices, fragments, first
-// tiles, drain, results); partial results move at about 4 TB/s.  Two dK/dV workgroups share a CU at head_dim 64, each at
-// half the pace.
+// The figures are microseconds measured on MI355X.  Two or three workgroups share a CU and its throughput: a step takes a forward
+// or dK/dV workgroup about as long alone on a CU as the CU takes per step of several, so a CU counts as one server at that pace
+// (head_dim 128, per step alone / of two: forward 1.8 / 1.8, dK/dV 1.75 / 1.6; at 64 of three: 1.0 and 0.85).  The fixed part is what
+// a unit spends around its steps (descriptor, row indices, fragments, first tiles, drain, results) and another workgroup does not
+// hide; partial results move at about 4 TB/s.
 constexpr int N_CU = 256;
-constexpr double JOINT_MAX_US = 1000;  // batches beyond this fill the chip with either kernel
+// Batches with more dK/dV work than this per CU run two launches.  One launch against two, forward + backward at head_dim 128: 499 ->
+// 459 us (4K tokens of documents of about 1K, 0.2 ms of dK/dV work), 2250 -> 2200 (256 rows in 16 windows of 8K keys, 1.0 ms); beyond,
+// lone shards lose (1000 rows with a 130K context, 3.2 ms: 7.72 -> 8.0 ms; 64-row shards with contexts, 2.8 ms: 5.33 -> 5.40: half units
+// read K and V twice as often) and packed documents gain 2 % (64K tokens, 4.4 ms).  At 64 the 16K-token batch of 0.2 ms loses 1 %.
+constexpr double JOINT_MAX_US = 1500, JOINT_MAX_US_64 = 1000;
 // The choice between one backward launch and two simulates lists of thousands of units, at 20 to 40 ns each more than the rest
 // of planning takes: ca_plan_host for 37K tokens in lone 860-row shards (8/1 heads) 65 us without it, 192 with all units
 // simulated, 106 so; of 1600 batches none gets another launch, two of 600 another order in it (backward 0.7 % slower, 0.3 %
@@ -365,24 +370,19 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     p->ws_off_l2 = per;
     p->ws_off_qs = 2 * per;
     p->ws_off_dos = 2 * per + copy;
-    // ... and one progress counter per backward workgroup (plus a block of zeros), by which the dK/dV workgroups that walk
-    // the same Q/dO tiles keep within an L2 window of each other.  Workgroups go to the 8 XCDs round robin in index
-    // order (workgroup i to XCD (i + c) mod 8) and unit i has KV head i mod n_kv_heads, so units lcm(8, n_kv_heads)
-    // apart share both.
     p->ws_off_delta_kv = 2 * per + 2 * copy;
     p->ws_off_l2_kv = 3 * per + 2 * copy;
-    p->ws_off_prog = 4 * per + 2 * copy;
-    p->peer_stride = int(std::lcm<int64_t>(8, hkv));
-    return (p->ws_off_prog + (size_t(p->bwd_workgroups) + 64) * sizeof(int32_t) + 255) / 256 * 256;
+    return 4 * per + 2 * copy;
   };
   // Partial results are bounded: at most this much more than whole units need, and, unless beyond_static, no more than what the
   // library's static workspace has left over (at 8 query heads of 128 it holds 15.8K rows, so from 8K rows on too little to cut
   // with: forward + backward of 9K rows, 8/1 heads, 1.75 ms with what is left and 0.85 ms with 256 MiB).
-  constexpr size_t MAX_CUT_BYTES = size_t(256) << 20, SPARE = 1 << 16;  // SPARE: progress counters
+  constexpr size_t MAX_CUT_BYTES = size_t(256) << 20;
   size_t cut_budget = 0;
   std::array<size_t, 2> limits{};
   bool more = false;
-  const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.75, 12.0, 5.0, 4} : CutCost{2 * N_CU, 2.0, 14.0, 5.0, 4};
+  double us_apart = 0;  // simulated time of the backward in two launches
+  const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.65, 10.0, 5.0, 4} : CutCost{2 * N_CU, 1.75, 12.0, 5.0, 4};
   const CutCost cost_fwd = {N_CU, p->d == 128 ? 2.1 : 1.25, 9.0, 5.0, 4};
   std::vector<int64_t> wg_steps;  // of the dK/dV kernel's workgroups of one KV head, as they are launched
   p->bwd_steps = 0;
@@ -418,16 +418,12 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     }
     // workgroups are handed out in index order: longest first, a chain counting with all its steps
     auto lay_out = [&](std::vector<Chain> &list, const std::vector<BwdUnit> &tiles, std::vector<BwdUnit> &units,
-                       const std::vector<int32_t> &pieces, int32_t &workgroups, int32_t &single) {
+                       const std::vector<int32_t> &pieces, int32_t &workgroups) {
       // (pieces: 0, or how many pieces the unit is cut into; those have their first head's part in `follow`)
       std::stable_sort(list.begin(), list.end(), [](const Chain &x, const Chain &y) { return x.steps > y.steps; });
-      size_t first_chain = list.size();
-      for (size_t ci = list.size(); ci-- > 0;)
-        if (list[ci].b - list[ci].a > 1) first_chain = ci;
       workgroups = int32_t(list.size() * hkv);
       units.reserve(tiles.size() * hkv);
       units.resize(size_t(workgroups));
-      single = int32_t(first_chain * hkv);
       wg_steps.clear();
       for (auto &c : list) wg_steps.push_back(c.steps);
       for (size_t ci = 0; ci < list.size(); ++ci) {
@@ -447,11 +443,11 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
         }
       }
     };
-    lay_out(chains, btiles, p->bwd_units, {}, p->bwd_workgroups, p->bwd_single);
+    lay_out(chains, btiles, p->bwd_units, {}, p->bwd_workgroups);
     p->ws_bwd = base_workspace();
     // the list in which long units that run alone are cut along their query blocks
     cut_budget = p->ws_bwd <= CA_STATIC_WS_BYTES && !beyond_static ? CA_STATIC_WS_BYTES - p->ws_bwd : MAX_CUT_BYTES;
-    limits = {cut_budget - std::min(cut_budget, SPARE), MAX_CUT_BYTES - SPARE};
+    limits = {cut_budget, MAX_CUT_BYTES};
     std::vector<std::pair<int64_t, int64_t>> sizes;
     for (auto &c : chains) {
       if (!sizes.empty() && sizes.back().first == c.steps) sizes.back().second += hkv;
@@ -487,7 +483,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
         for (int h = 0; h < hkv; ++h, p->n_bwd_parts += int32_t(k))
           p->bwd_combine.push_back({p->n_bwd_parts, int32_t(k), u.kv_row, u.n_valid, h, 0});
       }
-      if (!p->bwd_combine.empty()) lay_out(list, tiles, p->bwd_pieces, pieces, p->bwd_piece_workgroups, p->bwd_piece_single);
+      if (!p->bwd_combine.empty()) lay_out(list, tiles, p->bwd_pieces, pieces, p->bwd_piece_workgroups);
     }
   }
   {
@@ -523,7 +519,10 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
         for (int i = 0; i < hq / t.u.hp; ++i, p->n_fwd_parts += int32_t(k))
           p->fwd_combine.push_back({p->n_fwd_parts, int32_t(k), t.u.slot0, (i % hkv) * g + (i / hkv) * t.u.hp, t.u.hp, 0});
       }
-      std::stable_sort(pieces.begin(), pieces.end(), [](const TileRef &a, const TileRef &b) { return a.cost > b.cost; });
+      // (pieces of one length by the window they attend: the pieces that read the same keys run side by side)
+      std::stable_sort(pieces.begin(), pieces.end(), [](const TileRef &a, const TileRef &b) {
+        return a.cost != b.cost ? a.cost > b.cost : a.u.kv_row0 < b.u.kv_row0;
+      });
       for (auto &t : pieces)
         for (int i = 0; i < hq / t.u.hp; ++i) {
           FwdUnit u = t.u;
@@ -534,13 +533,13 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     }
   }
   {
-    // One launch or two for the backward.  The dQ kernel proper runs 256 rows per workgroup, two waves per SIMD; in the
-    // joint launch a workgroup is four waves of 32 rows, which costs more per row (1.6 us per tile of 128 rows against 2.6 of
-    // 256 at head_dim 128, where they have a SIMD each) but fills the CUs that too few dK/dV units leave idle, and saves a launch.
+    // One launch or two for the backward.  The dQ kernel proper runs 256 rows per workgroup; in the joint launch a workgroup is
+    // half of that, two to a CU at the same pace per row (2.4 us per tile of 256 rows at head_dim 128, 1.4 at 64), which fills
+    // the CUs that too few dK/dV units leave idle, and saves a launch.
     const int slots = cost_dkv.slots;
     double mean = 0;
     for (int64_t s : wg_steps) mean += (cost_dkv.fixed + cost_dkv.per_step * double(s)) * hkv / slots;
-    if (!wg_steps.empty() && !p->fwd_units.empty() && mean < JOINT_MAX_US) {
+    if (!wg_steps.empty() && !p->fwd_units.empty() && mean < (p->d == 128 ? JOINT_MAX_US : JOINT_MAX_US_64)) {
       // groups of equal workgroups that follow each other in their list: (microseconds, how many, first entry of joint_order,
       // step from entry to entry)
       struct Group {
@@ -560,7 +559,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
         sum += us * hkv;
         longest = std::max(longest, us);
       }
-      const double per = p->d == 128 ? 2.6 : 1.5, per_half = p->d == 128 ? 1.6 : 1.7;
+      const double per = p->d == 128 ? 2.4 : 1.4, per_half = p->d == 128 ? 1.2 : 1.4, fixed_half = p->d == 128 ? 4.0 : 7.0;
       for (int32_t half = 1; half >= 0; --half)
         for (int32_t i = 0; i < n_dq;) {
           const FwdUnit &u = units[size_t(i)];
@@ -568,7 +567,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
           if (half == 1) dq.push_back({cost_fwd.fixed + per * tiles, n / same});
           // the tiles the half's rows see (its last slot has its highest position)
           const int32_t last = p->slot_pos[size_t(u.slot0 + ((4 * half + 3) / u.hp) * 32 + 31)] - u.key0;
-          const double us = cost_fwd.fixed + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1));
+          const double us = fixed_half + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1));
           groups.push_back({us, n, -1 - (half * n_dq + i), -1});
           sum += us * n;
           longest = std::max(longest, us);
@@ -578,7 +577,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
                                   ? cost_dkv.launch + double(size_t(p->n_fwd_parts + p->n_bwd_parts) * part_bytes(p->d)) / BYTES_PER_US
                                   : 0.0;
       const double apart = makespan(dkv, slots / same, 1e30, JOINT_UNITS) + makespan(dq, N_CU / same, 1e30, JOINT_UNITS) + cost_dkv.launch;
-      p->us_bwd = apart + parts_us;
+      p->us_bwd = us_apart = apart + parts_us;
       if (sum / slots < apart) {
         std::vector<std::pair<double, int64_t>> all;
         auto span_of = [&](double at_most) {
@@ -607,16 +606,15 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   if (p->n_fwd_parts > 0) p->ws_fwd_split = size_t(p->n_fwd_parts) * (part_bytes(p->d) + FWD_STAT_BYTES);
   p->ws_bwd_split = p->ws_bwd;
   if (p->n_fwd_parts + p->n_bwd_parts > 0) {
-    // [progress counters of the dK/dV pieces][dK/dV parts][dQ parts], or, where that is beyond the budget, one region that
-    // the dQ parts use after the dK/dV parts have been added up (one launch more)
-    size_t at = p->ws_bwd;
-    if (p->n_bwd_parts > 0) at += (size_t(p->bwd_piece_workgroups) + 64) * sizeof(int32_t);
-    at = (at + 255) / 256 * 256;
-    p->ws_off_parts_kv = p->ws_off_parts_dq = at;
+    // [dK/dV parts][dQ parts], or, where that is beyond the budget, one region that the dQ parts use after the dK/dV parts have been added up (one launch more)
+    p->ws_off_parts_kv = p->ws_off_parts_dq = p->ws_bwd;
     const size_t kv = size_t(p->n_bwd_parts) * part_bytes(p->d), dq = size_t(p->n_fwd_parts) * part_bytes(p->d);
-    p->shared_parts = kv > 0 && dq > 0 && at - p->ws_bwd + kv + dq > cut_budget;
-    if (p->shared_parts) p->joint = false;  // (its time stays estimated as if it were not shared: a launch of a few us)
-    else p->ws_off_parts_dq += kv;
+    p->shared_parts = kv > 0 && dq > 0 && kv + dq > cut_budget;
+    if (p->shared_parts) {
+      p->joint_lost = p->joint;
+      p->joint = false, p->joint_order.clear(), p->us_bwd = us_apart;
+    }
+    if (!p->shared_parts) p->ws_off_parts_dq += kv;
     p->ws_bwd_split = std::max(p->ws_off_parts_kv + kv, p->ws_off_parts_dq + dq);
   }
   p->q_covered = covered_q == p->total_q;
@@ -654,12 +652,17 @@ int build_plan(const ca_batch_desc *desc, ca_plan_t **out) {
   try {
     validate(desc);
     auto p = described(desc);
-    // Where cutting units beyond the static workspace looks better by a tenth, both plans are made, and kept if the whole pass
-    // is: the larger for callers that bring the workspace, the smaller inside it for all others.
-    if (schedule(p.get(), false)) {
+    // Where cutting units beyond the static workspace looks better by a tenth, or would save a backward launch worth it (the dQ parts
+    // take the place of the dK/dV parts inside, which needs two), both plans are made, and kept if the whole pass
+    // is: the larger for callers that bring the workspace, the smaller inside it for all others.  (Forward + backward, 8/2 heads,
+    // without and with the second case: 2048 rows with an 8K context 318 -> 266 us, 3072 rows 404 -> 356 us; simulated to gain 34 and
+    // 38 us.  Below 25 us the larger workspace is not taken for it.)
+    const bool more = schedule(p.get(), false);
+    if (more || p->joint_lost) {
       auto large = described(desc);
       schedule(large.get(), true);
-      if (p->us_bwd > 0 && large->us_bwd > 0 && large->us_fwd + large->us_bwd < 0.9 * (p->us_fwd + p->us_bwd)) {
+      const double inside = p->us_fwd + p->us_bwd, beyond = large->us_fwd + large->us_bwd;
+      if (p->us_bwd > 0 && large->us_bwd > 0 && ((more && beyond < 0.9 * inside) || (p->joint_lost && inside - beyond > 25))) {
         large->within_static = std::move(p);
         p = std::move(large);
       }
