@@ -162,7 +162,7 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
   // and with more than two stages tiles past the end as the last tile (the wait at the top of a tile counts loads)
   const uint32_t kv_row_bytes = uint32_t(Hkv) * D * 2;
   const int ld_row0 = RPI * wave + lane / CH;  // + W*RPI*n
-  const uint32_t ld_cbytes = uint32_t((lane % CH) ^ tile_sw16<D>(ld_row0)) * 16;
+  const uint32_t ld_cbytes = uint32_t((lane % CH) ^ tile_sw<D>(ld_row0)) * 16;
   const int last_tile = n_tiles - 1, last_key_in_tile = min(FWD_BN, u.n_keys - last_tile * FWD_BN) - 1;
   const uint32_t ld_off = uint32_t(ld_row0) * kv_row_bytes + ld_cbytes;  // + W*RPI*n rows (the swizzle repeats every 16)
   static_assert(W * RPI % 16 == 0);
@@ -202,8 +202,8 @@ __device__ __forceinline__ void dq_workgroup(const FwdUnit &u, const int half, c
       dof[s][rg] = *reinterpret_cast<const bf16x8 *>(dO + off + 32 * s);
     }
   }
-  int koff = lds0 + li * ROWB + 16 * (j4 ^ tile_sw16<D>(li));
-  int toff = lds0 + (4 * j4 + (li >> 2)) * ROWB + 16 * (((li >> 1) & 1) ^ tile_sw16<D>(4 * j4 + (li >> 2))) + 8 * (li & 1);
+  int koff = lds0 + li * ROWB + 16 * (j4 ^ tile_sw<D>(li));
+  int toff = lds0 + (4 * j4 + (li >> 2)) * ROWB + 16 * (((li >> 1) & 1) ^ tile_sw<D>(4 * j4 + (li >> 2))) + 8 * (li & 1);
 
   f32x4 acc[ND][2];
 #pragma unroll
@@ -409,7 +409,7 @@ __device__ __forceinline__ void dkv_workgroup(const int me /* index of the first
     // every wave issues the same number of loads).  Q and dO come from their slot-ordered copies [block][head][64][D], in which
     // the tile of a (block, head) is one contiguous run: a load is (wave-uniform tile address) + (per-lane constant).
     const int trow = RPW * wave + lane / CH;
-    const uint32_t ld_off = uint32_t(trow * ROWB + 16 * ((lane % CH) ^ tile_sw16<D>(trow)));
+    const uint32_t ld_off = uint32_t(trow * ROWB + 16 * ((lane % CH) ^ tile_sw<D>(trow)));
     int left = n_it;  // tiles still to be fetched
     int ph = 0, pst = 0;
     const int64_t tile0 = (int64_t(u.slot_begin / BWD_BQ + n_blocks - 1) * Hq + hk * G) * head_stride;
@@ -465,8 +465,8 @@ __device__ __forceinline__ void dkv_workgroup(const int me /* index of the first
 #pragma unroll
     for (int s = 0; s < NK; ++s) pin(kf[s][0]), pin(kf[s][1]), pin(vf[s][0]), pin(vf[s][1]);
     // natural reads, transposing reads and row statistics in the current stage
-    int nb = lds0 + li * ROWB + 16 * (j ^ tile_sw16<D>(li));
-    int tb = lds0 + (4 * j + (li >> 2)) * ROWB + 16 * (((li >> 1) & 1) ^ tile_sw16<D>(4 * j + (li >> 2))) + 8 * (li & 1);
+    int nb = lds0 + li * ROWB + 16 * (j ^ tile_sw<D>(li));
+    int tb = lds0 + (4 * j + (li >> 2)) * ROWB + 16 * (((li >> 1) & 1) ^ tile_sw<D>(4 * j + (li >> 2))) + 8 * (li & 1);
     int auxo = lds0 + 16 * j, stage = 0;
 
     f32x4 acc_dk[ND][2], acc_dv[ND][2];

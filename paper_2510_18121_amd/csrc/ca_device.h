@@ -18,13 +18,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 #define CA_LDS __attribute__((address_space(3)))
 
-// v_mfma_f32_32x32x16_bf16: C[32x32] += A[32x16] * B[16x32].
-//   A: lane l holds A[l%32][8*(l/32) .. +7];  B: lane l holds B[8*(l/32) .. +7][l%32];
-//   C: lane l, register i holds C[(i/4)*8 + (l/32)*4 + i%4][l%32].
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
 // v_mfma_f32_16x16x32_bf16: C[16x16] += A[16x32] * B[32x16].
 //   A: lane l holds A[l%16][8*(l/16) .. +7];  B: lane l holds B[8*(l/16) .. +7][l%16];
 //   C: lane l, register i holds C[4*(l/16) + i][l%16].
@@ -32,22 +25,16 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// 16-byte LDS read of 8 consecutive bf16.
-__device__ __forceinline__ bf16x8 lds_read8(const char *p) { return *reinterpret_cast<const bf16x8 *>(p); }
-
 // ds_read_b64_tr_b16: inside each group of 16 lanes, lane i points at 4 consecutive bf16 and receives
 // element (i%4) of the 4 values read by lanes 4j + i/4, j = 0..3.  With lane i pointing at
 // tile[r0 + i/4][c0 + 4*(i%4)] the lane gets tile[r0 .. r0+3][c0 + i]: a 4x16 block, transposed.
-__device__ __forceinline__ bf16x4 lds_read_tr4(const char *p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((CA_LDS bf16x4 *)(p));
-}
-
-// the same reads, addressed by a 32-bit LDS byte address (no generic-pointer arithmetic, and constant parts of
-// the address fold into the instruction's offset field)
-__device__ __forceinline__ bf16x8 lds_read8_at(uint32_t a) { return *(const CA_LDS bf16x8 *)a; }
+// (LDS reads are addressed by a 32-bit LDS byte address: no generic-pointer arithmetic, and constant parts of the address fold
+// into the instruction's offset field.)
 __device__ __forceinline__ bf16x4 lds_read_tr4_at(uint32_t a) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((CA_LDS bf16x4 *)a);
 }
+// 16-byte LDS read of 8 consecutive bf16
+__device__ __forceinline__ bf16x8 lds_read8_at(uint32_t a) { return *(const CA_LDS bf16x8 *)a; }
 template <class T>
 __device__ __forceinline__ T lds_ld(uint32_t a) {
   return *(const CA_LDS T *)a;
@@ -74,7 +61,16 @@ __device__ __forceinline__ float xor32_max(float x) {
   return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
 
-__device__ __forceinline__ int lane_id() { return int(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))); }
+// max of, and sum with, the values held by the lanes that differ in bits 4 and 5 of their index
+__device__ __forceinline__ float quad_max(float x) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return xor32_max(fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
+}
 
 // A constant that the compiler cannot see through: what is computed from it is computed where it stands, not kept in a register
 // (or spilled) across a long loop.  The vector instruction itself stays the compiler's, which places the wait states that
@@ -104,12 +100,13 @@ __device__ __forceinline__ int wave_min(int v) {
 // ---------------------------------------------------------------------------------------------
 // LDS tiles of R rows x D bf16 in natural (row-major) layout, rows unpadded, with the 16-byte chunks of
 // each row XOR-swizzled by a function of the row.  gfx950's LDS has 64 banks of 4 bytes (256 B/clk).
-//   * a 16-byte read (lane <-> row, all lanes the same logical chunk) is served 16 consecutive rows
-//     at a time, so sw(r) must take 16 (D=128) distinct values over 16 consecutive rows
-//     (for D=64, where two rows share a 256-byte line, 8 distinct values over rows of equal parity);
-//   * an 8-byte transposing read is served 4 consecutive rows x two adjacent 32-byte pieces at a time, so
-//     bits 2..3 of sw must follow the row's low bits.
-// sw(r) below satisfies both, so one tile can feed natural and transposed MFMA operands.
+//   * A natural read is 16 rows x 64 bytes: lane l reads chunk 4 s + l / 16 of row l % 16, and the 16 lanes served together are 0-3,
+//     12-15 of one run of 16 lanes and 4-11 of the next one's (a swizzle without conflicts inside each run has them in every
+//     second read: 30 to 40 % of the LDS cycles of the backward kernels).  So with q = r / 4 % 4 the low bits f(q) of sw are
+//     0, 2, 3, 1: f(1) = f(2) ^ 1 and f(0) = f(3) ^ 1 keep those apart; bits 2..3 follow the row's low bits.
+//   * An 8-byte transposing read is served 8 consecutive rows x one 32-byte piece at a time: f(0), f(1) as well as f(2), f(3)
+//     differ in bit 1.
+// (At head_dim 64 two rows share a 256-byte line.)  So one tile can feed natural and transposed MFMA operands.
 // Because rows are unpadded, a tile can be filled by global_load_lds_dwordx4, which writes
 // lane i's 16 bytes at (wave-uniform LDS base) + 16 i: the swizzle is applied by choosing which global
 // chunk each lane fetches.
@@ -117,30 +114,9 @@ namespace ca {
 
 template <int D>
 __device__ __forceinline__ int tile_sw(int r) {
-  return D == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
-}
-
-// The same for tiles that feed 16x16 MFMAs:
-//   * A natural read is 16 rows x 64 bytes: lane l reads chunk 4 s + l / 16 of row l % 16, and the 16 lanes served together are 0-3,
-//     12-15 of one run of 16 lanes and 4-11 of the next one's (a swizzle without conflicts inside each run has them in every
-//     second read: 30 to 40 % of the LDS cycles of the backward kernels).  So with q = r / 4 % 4 the low bits f(q) of sw are
-//     0, 2, 3, 1: f(1) = f(2) ^ 1 and f(0) = f(3) ^ 1 keep those apart; bits 2..3 follow the row's low bits.
-//   * An 8-byte transposing read is served 8 consecutive rows x one 32-byte piece at a time: f(0), f(1) as well as f(2), f(3)
-//     differ in bit 1.
-template <int D>
-__device__ __forceinline__ int tile_sw16(int r) {
   const int q0 = (r >> 2) & 1, q1 = (r >> 3) & 1;
   return (D == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2) | (q0 ^ q1) << 1 | q1;
 }
-
-// byte offset of logical 16-byte chunk c of row r
-template <int D>
-__device__ __forceinline__ int tile_off(int r, int c) {
-  return r * (2 * D) + ((c ^ tile_sw<D>(r)) << 4);
-}
-
-#define CA_GLOBAL __attribute__((address_space(1)))
-#define CA_CONST __attribute__((address_space(4)))
 
 // One wave-wide direct load global -> LDS: lane i's 16 (or 4) bytes from `src` land at
 // lds_base + 16 i (or 4 i); lds_base must be wave-uniform.  Written as inline assembly on purpose: the
@@ -148,15 +124,8 @@ __device__ __forceinline__ int tile_off(int r, int c) {
 // and would drain the whole prefetch queue (s_waitcnt vmcnt(0)) before it.  Here the kernels pace
 // the queue themselves with wait_vmcnt<N>() and a barrier.  Loads the compiler does not know about can
 // only make its own vmcnt waits stricter than needed, never weaker: vector loads retire in order.
-__device__ __forceinline__ void load_lds16(const void *src, char *lds_base_uniform) {
-  const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(CA_LDS char *)lds_base_uniform);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(src), "s"(base)
-               : "memory", "m0");
-}
-// same, addressed as (wave-uniform 64-bit base in SGPRs) + (per-lane unsigned 32-bit byte offset); the LDS
-// destination is a byte offset from the start of LDS
+// The address is (wave-uniform 64-bit base in SGPRs) + (per-lane unsigned 32-bit byte offset); the LDS destination is a
+// wave-uniform LDS byte address.
 __device__ __forceinline__ void load_lds16_sbase(const void *base_uniform, uint32_t lane_off, uint32_t lds_off_uniform) {
   const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_off_uniform);
   const uint64_t b = (uint64_t)(uintptr_t)base_uniform;
@@ -178,34 +147,6 @@ __device__ __forceinline__ void load_lds4_sbase(const void *base_uniform, uint32
                : "v"(lane_off), "s"(sb), "s"(m0v)
                : "memory", "m0");
 }
-// same, with the LDS destination given as a wave-uniform 32-bit LDS byte address
-__device__ __forceinline__ void load_lds16_at(const void *src, uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(src), "s"(lds_addr_uniform)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void load_lds4_at(const void *src, uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-               :
-               : "v"(src), "s"(lds_addr_uniform)
-               : "memory", "m0");
-}
-// the same, read at device scope (past this CU's vector L1): for values other workgroups keep writing
-__device__ __forceinline__ void load_lds4_at_fresh(const void *src, uint32_t lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off sc1"
-               :
-               : "v"(src), "s"(lds_addr_uniform)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void load_lds4(const void *src, char *lds_base_uniform) {
-  const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(CA_LDS char *)lds_base_uniform);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-               :
-               : "v"(src), "s"(base)
-               : "memory", "m0");
-}
-
 // workgroup barrier without the memory fence of __syncthreads() (which would also drain the direct loads):
 // the caller has waited for its own LDS reads (lgkmcnt) and for the direct loads that must be visible
 __device__ __forceinline__ void barrier_nofence() {
@@ -220,124 +161,7 @@ __device__ __forceinline__ void pin(bf16x8 &v) {
   asm volatile("" : "+v"(w));
   v = __builtin_bit_cast(bf16x8, w);
 }
-// same, but leaves the value in an accumulation register (MFMA A/B operands can be read from either file;
-// values only ever consumed by MFMAs need not occupy architectural VGPRs)
-__device__ __forceinline__ void pin_acc(bf16x8 &v) {
-  u32x4 w = __builtin_bit_cast(u32x4, v);
-  asm volatile("" : "+a"(w));
-  v = __builtin_bit_cast(bf16x8, w);
-}
-
-// MFMA whose result tuple lives in ARCHITECTURAL registers and whose B operand lives in the accumulation file.
-// A kernel that runs one wave per SIMD has 256 registers of each kind; once it needs both, the compiler gives
-// every MFMA an accumulation-file result, and a result the vector ALU needs next then costs one v_accvgpr_read per
-// register.  These forms are for short-lived score tiles that go straight to the vector ALU, with B operands that
-// stay resident for the whole kernel and are read by MFMAs only.
-// The compiler does not see an MFMA in them, so it inserts none of the wait states the hardware requires between an
-// MFMA and a non-MFMA instruction that reads its result: mfma_settle() supplies them (the result of this 8-pass
-// MFMA may be read 11 issue slots after it; 12 are waited) and takes the tuples as operands, so no reader can be
-// scheduled ahead of it.  Between the first MFMA of a chain and the settle nothing else may touch the tuple.
-// Dependent MFMAs on one tuple need no wait.
-__device__ __forceinline__ void mfma32_v_first(f32x16 &d, bf16x8 a, bf16x8 b_acc) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0"
-               : "=&v"(d)
-               : "v"(__builtin_bit_cast(u32x4, a)), "a"(__builtin_bit_cast(u32x4, b_acc)));
-}
-// d = a b + c, with c another architectural tuple
-__device__ __forceinline__ void mfma32_v_first(f32x16 &d, bf16x8 a, bf16x8 b_acc, const f32x16 &c) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3"
-               : "=&v"(d)
-               : "v"(__builtin_bit_cast(u32x4, a)), "a"(__builtin_bit_cast(u32x4, b_acc)), "v"(c));
-}
-__device__ __forceinline__ void mfma32_v(f32x16 &d, bf16x8 a, bf16x8 b_acc) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
-               : "+v"(d)
-               : "v"(__builtin_bit_cast(u32x4, a)), "a"(__builtin_bit_cast(u32x4, b_acc)));
-}
-// the same with the B operand in architectural registers too
-__device__ __forceinline__ void mfma32_vv_first(f32x16 &d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0"
-               : "=&v"(d)
-               : "v"(__builtin_bit_cast(u32x4, a)), "v"(__builtin_bit_cast(u32x4, b)));
-}
-__device__ __forceinline__ void mfma32_vv(f32x16 &d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
-               : "+v"(d)
-               : "v"(__builtin_bit_cast(u32x4, a)), "v"(__builtin_bit_cast(u32x4, b)));
-}
-__device__ __forceinline__ void mfma_settle(f32x16 &x, f32x16 &y) { asm volatile("s_nop 11" : "+v"(x), "+v"(y)); }
-// same; `c` was the C operand of the chain's first MFMA: keeping it an operand here keeps its registers from being
-// reused (and overwritten by an LDS read in flight) while that MFMA may still be reading them
-__device__ __forceinline__ void mfma_settle(f32x16 &x, f32x16 &y, const f32x16 &c) {
-  asm volatile("s_nop 11" : "+v"(x), "+v"(y) : "v"(c));
-}
-// End of a chain whose first non-MFMA reader is known to be at least a whole phase of MFMAs away (the pipelined loop of
-// the dK/dV kernel): no wait states are needed, only the ordering of mfma_settle().  The assembly comment is what
-// the static check of the generated instruction stream (isa_check.py, run by the CPU tests) looks for: it verifies that
-// nothing but MFMAs touches the tuples for the next 16 issue cycles.
-__device__ __forceinline__ void mfma_chain_end(f32x16 &x, f32x16 &y, const f32x16 &c) {
-  asm volatile("; chain end" : "+v"(x), "+v"(y) : "v"(c));
-}
-// d *= f for a result tuple that lives in the accumulation file, one element at a time through one architectural
-// register (left to the compiler, every tuple of the wave is copied over at once, which at two waves per SIMD spills).
-// The wait states stand for those between the MFMA that wrote the tuple and the first read, and between the last write and
-// an MFMA that reads it, which the compiler does not place around assembly.
-__device__ __forceinline__ void scale_acc(f32x16 &d, float f) {
-  float t;
-  asm volatile("s_nop 15" : "+a"(d));
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    float e = d[i];
-    asm volatile("v_accvgpr_read_b32 %1, %0\n\ts_nop 0\n\tv_mul_f32 %1, %1, %2\n\ts_nop 0\n\tv_accvgpr_write_b32 %0, %1"
-                 : "+a"(e), "=&v"(t)
-                 : "v"(f));
-    d[i] = e;
-  }
-  asm volatile("s_nop 4" : "+a"(d));
-}
-// same, where the wait states (mfma_settle) follow after a few other instructions
-__device__ __forceinline__ void mfma_chain_end(f32x16 &x, f32x16 &y) { asm volatile("; chain end" : "+v"(x), "+v"(y)); }
 __device__ __forceinline__ void pin(float &v) { asm volatile("" : "+v"(v)); }
-// exp2(x * c - g) as one volatile asm statement: like pin() it stays where it is written in the instruction stream
-// (between the MFMAs of its slot), but without the wait state the compiler puts between an empty asm that "defines"
-// a register and the first instruction that reads it.  (A multiply-add feeding a transcendental needs no wait state.)
-__device__ __forceinline__ uint32_t pack_bf16_pinned(float a, float b) {
-  uint32_t r;
-  asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-// {bf16(p0 * d0), bf16(p1 * d1)} and {bf16(p2 * d2), bf16(p3 * d3)}, pinned likewise
-__device__ __forceinline__ void mul_pack_bf16_pinned(float p0, float p1, float p2, float p3, float d0, float d1,
-                                                     float d2, float d3, uint32_t &lo, uint32_t &hi) {
-  float t0, t1, t2, t3;
-  asm volatile(
-      "v_mul_f32 %2, %6, %10\n\tv_mul_f32 %3, %7, %11\n\tv_mul_f32 %4, %8, %12\n\tv_mul_f32 %5, %9, %13\n\t"
-      "v_cvt_pk_bf16_f32 %0, %2, %3\n\tv_cvt_pk_bf16_f32 %1, %4, %5"
-      : "=&v"(lo), "=&v"(hi), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-      : "v"(p0), "v"(p1), "v"(p2), "v"(p3), "v"(d0), "v"(d1), "v"(d2), "v"(d3));
-}
-__device__ __forceinline__ float exp2_fma_pinned(float x, float c, float g) {
-  float r;
-  asm volatile("v_fma_f32 %0, %1, %2, -%3\n\tv_exp_f32 %0, %0" : "=v"(r) : "v"(x), "v"(c), "v"(g));
-  return r;
-}
-// x = exp2(x * c - g) in place (the register of x is reused, so a register tuple exponentiated element by element
-// stays where it is), pinned likewise
-__device__ __forceinline__ void exp2_fma_inplace_pinned(float &x, float c, float g) {
-  asm volatile("v_fma_f32 %0, %0, %1, -%2\n\tv_exp_f32 %0, %0" : "+v"(x) : "v"(c), "v"(g));
-}
-// the same with sum += prev in between.  prev may be the result of the transcendental issued directly before this
-// statement: the multiply-add stands between the two.
-__device__ __forceinline__ void exp2_fma_add_inplace_pinned(float &x, float c, float g, float &sum, float prev) {
-  asm volatile("v_fma_f32 %0, %0, %2, -%3\n\tv_add_f32 %1, %1, %4\n\tv_exp_f32 %0, %0"
-               : "+v"(x), "+v"(sum)
-               : "v"(c), "v"(g), "v"(prev));
-}
-// sum += prev where prev may be the result of a transcendental issued directly before (one wait state supplied)
-__device__ __forceinline__ void add_after_trans_pinned(float &sum, float prev) {
-  asm volatile("s_nop 0\n\tv_add_f32 %0, %0, %1" : "+v"(sum) : "v"(prev));
-}
-__device__ __forceinline__ void pin(int &v) { asm volatile("" : "+v"(v)); }
 
 // wait until at most n of this wave's vector-memory loads are outstanding (n <= 63)
 template <int N>
@@ -358,43 +182,14 @@ __device__ __forceinline__ void half_of_unit(int &i, int n, int &half) {
 }
 
 // ---- a wave's 32 x D result tile, stored as whole lines.
-// In the accumulator layout of Xt = A B (32x32 MFMAs, 32-row blocks b of the D values) lane (r, g) holds, of row r
-// (a key, or a query row), the values 32 b + 8 q4 + 4 g .. + 3 in acc[b][4 q4 ..]: 4 values out of every 8.  Stored
-// from there, one instruction touches 32 rows with 16 bytes each, and the 16 D / 32 of them per tile keep a CU's address
-// unit busy for microseconds.  Instead the wave passes 64 values per row at a time through an LDS patch of its own
-// (PATCH_BYTES at `patch`, an LDS byte address; a wave's LDS instructions execute in order, so nothing synchronises)
-// and stores 8 rows x 128 bytes per instruction.  f scales the values (per lane, i.e. per row r); dst_of_row(p)
+// In the accumulator layout of Xt = A B (16x16 MFMAs, 16-row blocks b of the D values, tiles t of 16 rows of X) lane l holds, of row
+// 16 t + l % 16 (a key, or a query row), the values 16 b + 4 (l / 16) .. + 3 in acc[b][t].  Stored from there, one instruction
+// touches 16 rows with 32 bytes each, and a CU's address unit is busy with a tile's stores for microseconds.  Instead the wave
+// passes 64 values per row at a time through an LDS patch of its own (PATCH_BYTES at `patch`, an LDS byte address; a wave's LDS
+// instructions execute in order, so nothing synchronises) and stores 8 rows x 128 bytes per instruction.  dst_of_row(p)
 // returns where row p (0..31) of the tile begins in memory, or nullptr for a row that is not stored.
 constexpr int PATCH_ROW_BYTES = 128 + 16;  // 16 bytes off a power of two
 constexpr int PATCH_BYTES = 32 * PATCH_ROW_BYTES;
-template <int NDB, class F>
-__device__ __forceinline__ void store_tile_as_lines(uint32_t patch, const f32x16 (&acc)[NDB], float f, int lane,
-                                                    F dst_of_row) {
-  const int r = lane & 31, g = lane >> 5, orow = lane >> 3, ocol = lane & 7;
-  const uint32_t wr = patch + r * PATCH_ROW_BYTES + 8 * g;  // + 64 (b & 1) + 16 q4
-  const uint32_t rd = patch + orow * PATCH_ROW_BYTES + 16 * ocol;  // the lane's row (+ 8 i) and 16-byte piece
-  bf16_t *dst[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) dst[i] = dst_of_row(orow + 8 * i);
-#pragma unroll
-  for (int h = 0; h < NDB / 2; ++h) {
-#pragma unroll
-    for (int bb = 0; bb < 2; ++bb)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x16 &a = acc[2 * h + bb];
-        const u32x2 w = {pack_bf16(a[4 * q4] * f, a[4 * q4 + 1] * f), pack_bf16(a[4 * q4 + 2] * f, a[4 * q4 + 3] * f)};
-        *(CA_LDS u32x2 *)(wr + 64 * bb + 16 * q4) = w;
-      }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const u32x4 x = *(const CA_LDS u32x4 *)(rd + 8 * i * PATCH_ROW_BYTES);
-      if (dst[i]) *reinterpret_cast<u32x4 *>(dst[i] + 64 * h + 8 * ocol) = x;
-    }
-  }
-}
-
-// The same for a tile computed by 16x16 MFMAs: of row 16 t + lane % 16, acc[b][t] holds the values 16 b + 4 (lane / 16) .. + 3.
 // (tiles T0 and T0 + 1 of acc; f0 and f1 scale their values.)
 template <int T0, int ND, int NT, class F>
 __device__ __forceinline__ void store_tile16_as_lines(uint32_t patch, const f32x4 (&acc)[ND][NT], float f0, float f1, int lane,

@@ -18,7 +18,7 @@ constexpr int FWD_BN = 64;   // keys per forward inner step
 constexpr int BWD_BN = 128;  // keys owned by one backward work unit (4 waves x 32)
 constexpr int BWD_BQ = 64;   // query rows per backward inner step
 
-// One workgroup of the forward / dQ kernels, or two (halves, in the joint backward launch): 8 row groups of 32 slots, one or
+// One workgroup of the forward / dQ kernels, or two (halves; always in the joint backward launch): 8 row groups of 32 slots, one or
 // two to a wave.  A full tile of a document is 256 slots of one query head (hp = 1).  The slots a document has left over
 // after its full tiles are covered by head-packed units instead: 256 / hp slots of hp consecutive query heads of one KV
 // group (they read the same K/V), row group w taking slots slot0 + 32 (w / hp) .. of head  head + w % hp  - so that
@@ -101,6 +101,7 @@ struct ca_plan {
   std::vector<ca::CombineUnit> fwd_combine, bwd_combine;
   int32_t bwd_piece_workgroups = 0;
   int32_t n_fwd_parts = 0, n_bwd_parts = 0;
+  bool fwd_halves = false, fwd_piece_halves = false;  // forward workgroups are halves of units (of 128 rows): of each list
   // workspace with which the piece lists are used: forward, and backward, where the parts lie behind ws_bwd
   size_t ws_fwd_split = 0, ws_bwd_split = 0, ws_off_parts_kv = 0, ws_off_parts_dq = 0;
   bool joint = false;  // backward runs dK/dV and dQ units in one launch: dK/dV workgroups, then dQ halves 1, then 0, or,

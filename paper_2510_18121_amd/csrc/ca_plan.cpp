@@ -383,7 +383,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   bool more = false;
   double us_apart = 0;  // simulated time of the backward in two launches
   const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.65, 10.0, 5.0, 4} : CutCost{2 * N_CU, 1.75, 12.0, 5.0, 4};
-  const CutCost cost_fwd = {N_CU, p->d == 128 ? 2.1 : 1.25, 9.0, 5.0, 4};
+  const CutCost cost_fwd = {N_CU, p->d == 128 ? 1.9 : 1.1, 8.0, 5.0, 4};
   std::vector<int64_t> wg_steps;  // of the dK/dV kernel's workgroups of one KV head, as they are launched
   p->bwd_steps = 0;
   for (auto &t : btiles) p->bwd_steps += int64_t(t.slot_end - t.slot_begin) / BWD_BQ * t.heads * hkv;
@@ -531,6 +531,34 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
           p->fwd_pieces.push_back(u);
         }
     }
+  }
+  {
+    // Forward workgroups: whole units, or their halves of 128 rows.  Halves are a finer schedule, and two of them run a unit that is
+    // alone on its CU in 60 % of the time; where both fill the chip a tile costs two halves 7 % more (K and V fragments feed half
+    // the MFMAs).  Microseconds, start + per tile: a unit 8 + 1.78 (2.05 where no CU has two) at head_dim 128, 5 + 1.0 (1.15) at 64; a
+    // half 4 + 0.96 and 2.5 + 0.53.  Measured, units against halves, head_dim 128: 45 -> 24 us (32 units of 16 tiles), 196 -> 182
+    // (384 of 64), 135 -> 110 (4K tokens of documents of about 1K: 512 units of 1 to 50 tiles), 229 -> 250 (512 of 64), 480 -> 534
+    // (512 of 128).
+    auto halves = [&](const std::vector<FwdUnit> &units) {
+      if (units.size() > size_t(4 * N_CU)) return false;
+      const bool d128 = p->d == 128, lone = units.size() <= size_t(N_CU);
+      const double fixed = d128 ? 8.0 : 5.0, per = d128 ? (lone ? 2.05 : 1.78) : lone ? 1.15 : 1.0;
+      const double fixed_half = d128 ? 4.0 : 2.5, per_half = d128 ? 0.96 : 0.53;
+      std::vector<std::pair<double, int64_t>> whole, half;
+      for (size_t i = 0, n; i < units.size(); i += n) {
+        const FwdUnit &u = units[i];
+        n = size_t(hq / u.hp);
+        const int32_t tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
+        // the tiles the first half's rows see (its last slot has its highest position)
+        const int32_t last = p->slot_pos[size_t(u.slot0 + (3 / u.hp) * 32 + 31)] - u.key0;
+        whole.push_back({fixed + per * tiles, int64_t(n)});
+        half.push_back({fixed_half + per_half * tiles, int64_t(n)});
+        half.push_back({fixed_half + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1)), int64_t(n)});
+      }
+      return makespan(half, N_CU, 1e30, JOINT_UNITS) < makespan(whole, N_CU, 1e30, JOINT_UNITS);
+    };
+    p->fwd_halves = halves(p->fwd_units);
+    p->fwd_piece_halves = halves(p->fwd_pieces);
   }
   {
     // One launch or two for the backward.  The dQ kernel proper runs 256 rows per workgroup; in the joint launch a workgroup is

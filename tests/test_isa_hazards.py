@@ -39,14 +39,11 @@ def test_forward_kernel_transcendentals_and_chains():
     n, bad = C.check_trans_use(asm)
     assert n > 50 and not bad, bad
     bodies = C.kernel_bodies(asm, "ca_fwd_kernel")
-    assert len(bodies) == 2  # head_dim 128 and 64
+    assert len(bodies) == 4  # head_dim 128 and 64, units and halves of units
     for body in bodies:
-        # score chains of the pipelined steps, of the prologue and of the diagonal path, every one ended by wait states
-        n, marks, bad = C.check_mfma_chains(body)
-        assert n >= 6 and marks == 0
-        assert not bad, bad
-        # the pipelined loop keeps everything in registers
+        # the loops keep everything in registers
         assert "scratch_" not in body
+    assert C.assembly_vector_instructions(asm) == []
 
 
 M = "v_mfma_f32_32x32x16_bf16"

@@ -13,8 +13,7 @@ pytestmark = pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt
 @pytest.mark.parametrize("source", ["ca_bwd.hip", "ca_fwd.hip"])
 def test_operands_of_assembly_mfmas_are_settled(source):
     asm = C.compile_to_asm(source)
-    n, bad = C.check_mfma_operands(asm)
-    assert (n > 100) == (source == "ca_fwd.hip") and not bad, bad  # the backward kernels have none
+    assert C.check_mfma_operands(asm) == (0, [])  # none is left to settle by hand
     for body in C.kernel_bodies(asm, "ca_bwd_joint_kernel"):
         assert "scratch_" not in body
 
