@@ -196,7 +196,7 @@ def main():
     kavg = {kk: sum(vv) / len(vv) for kk, vv in kern.items()}
     plan.profile_enable(False)
     # what the matrix pipes sustain on this device, right after the timed work (chip warm): the library's MFMA-only
-    # kernel on N(0,1) bf16 operands, one wave per SIMD like the dK/dV kernel, three launches of about a quarter second
+    # kernel (32x32x16 MFMAs) on N(0,1) bf16 operands, one wave per SIMD, three launches of about a quarter second
     # each, the last one reported; then the same with an attention kernel's other per-MFMA work issued alongside
     sustained = sustained_side = None
     if not args.no_sustained_probe:
@@ -205,8 +205,8 @@ def main():
         with probe_clocks:
             sustained = mfma_rate.sustained_tflops("normal", 0, 1, device=dev)[-1]
         sustained_side = mfma_rate.sustained_tflops("normal", 1, 1, device=dev)[-1]
-        # the dQ kernel runs two waves per SIMD with side work of about level 1; the forward kernel one wave per SIMD
-        # with side work of about level 2 (an exponential per MFMA)
+        # yardsticks: two waves per SIMD with side work of about level 1 (the dQ kernel's), one wave per SIMD with side work of
+        # about level 2 (the forward kernel's: an exponential per MFMA)
         sustained_dq = mfma_rate.sustained_tflops("normal", 1, 2, device=dev)[-1]
         sustained_fwd = mfma_rate.sustained_tflops("normal", 2, 1, device=dev)[-1]
     if args.calibration_copy_mib > 0:

@@ -48,8 +48,8 @@ struct BwdUnit {  // one (KV tile, KV head)
   int32_t kv_head;
   // Chains.  The first n_bwd_workgroups units of the list are one workgroup each; a workgroup goes on with the
   // `count - 1` units stored from index `follow` on (behind the workgroups' own units; same KV head, no longer than
-  // its first).  Long units run alone (count 1); short ones are chained, because what a unit costs beyond its steps
-  // (filling the pipeline, fetching K and V, draining) can then overlap with the steps of its neighbours.
+  // its first).  Long units run alone (count 1); short ones are chained: fewer workgroups to hand out, of more nearly
+  // equal length.
   int32_t follow;
   int32_t count;  // units of this workgroup including this one; 0 in a unit that follows another
   // (block, head) tiles per query block: the heads of the KV group, or fewer where a document of at most 32 rows has

@@ -390,7 +390,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   {
     // Chains of the dK/dV kernel: consecutive KV tiles of the sorted list (equal or similar cost; the tiles of one
     // document under the same query rows are neighbours in it) whose units are short - at most CHAIN_UNIT_STEPS
-    // steps each: what chaining saves per unit is a few steps' worth - go to one workgroup per KV head.  A chain
+    // steps each - go to one workgroup per KV head.  A chain
     // takes at most CHAIN_STEPS_MAX steps and CHAIN_UNITS_MAX units, and at most 1/(2 N_CU) of the short units' steps
     // still to be handed out: chains shrink towards the end of the list, so that the last workgroups of the launch
     // are small ones and the CUs finish together.
