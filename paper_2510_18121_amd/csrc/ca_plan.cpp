@@ -748,12 +748,12 @@ int ca_plan_info(const ca_plan_t *p, int64_t *out, int n) {
   if (!p) return 0;
   int64_t full_tiles = 0;
   for (auto &u : p->fwd_units) full_tiles += u.hp == 1 && u.head == 0;
-  const int64_t v[14] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
+  const int64_t v[16] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
                          ca::BWD_BN, int64_t(p->bwd_units.size()), ca::FWD_BN, int64_t(p->slot_row.size()),
                          p->fwd_steps, p->bwd_steps, ca::BWD_BQ, p->slot_align, p->heads_packed, p->bwd_workgroups,
-                         p->joint};
-  for (int i = 0; i < n && i < 14 && out; ++i) out[i] = v[i];
-  return 14;
+                         p->joint, p->fwd_halves, p->fwd_piece_halves};
+  for (int i = 0; i < n && i < 16 && out; ++i) out[i] = v[i];
+  return 16;
 }
 
 int64_t ca_plan_rows(const ca_plan_t *p, int32_t *rows, int32_t *pos) {

@@ -1,5 +1,6 @@
 """The forward kernel runs whole units of 256 rows, or, where a list has few of them, their halves: the same results bit for bit,
-on shards that begin and end anywhere and in units that hold several heads."""
+on shards that begin and end anywhere and in units that hold several heads.  Both forms repeat what leaves the finite range."""
+import numpy as np
 import pytest
 import torch
 
@@ -11,27 +12,52 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+def batches(docs, tasks, hq, hkv, d, **kw):
+    """The batch alone, and in front of as many more documents, of a unit per head each, as make its list run whole units (lists
+    of more than 1024 units)."""
+    fill = -(-1100 // hq)
+    small = W.custom(docs, tasks, hq, hkv, d, seed=97, **kw)
+    large = W.custom(docs + [300] * fill, tasks + [(len(docs) + i, 44, 256) for i in range(fill)], hq, hkv, d, seed=97, **kw)
+    return small, large
+
+
+def both_forms(small, large, q, k, v):
+    """Results of the small batch's rows from whole units (as part of the large one) and from halves."""
+    nq, nk, results = small.total_q, small.total_kv, []
+    for b, (qq, kk, vv) in ((large, (q, k, v)), (small, (q[:nq].contiguous(), k[:nk].contiguous(), v[:nk].contiguous()))):
+        plan = B.ca_plan(b)
+        assert plan.info()["forward_halves"] == (b is small)
+        o, lse = torch.full_like(qq, float("nan")), torch.full((b.n_q_heads, b.total_q), float("nan"), device=DEV)
+        B.ca_forward(plan, qq, kk, vv, o, lse)  # no workspace: whole units or halves of them, no pieces
+        torch.cuda.synchronize()
+        results.append({"o": o[:nq], "lse": lse[:, :nq]})
+    return results
+
+
 @pytest.mark.parametrize("d,hq,hkv", [(64, 8, 1), (128, 8, 8), (128, 8, 2)])
 def test_halves_equal_whole_units(d, hq, hkv):
     # (first position, rows): around the edges of keys tiles (64), waves (32, 64 rows), halves (128) and units (256)
     shards = [(0, 1), (0, 129), (17, 300), (40, 64), (63, 130), (64, 257), (100, 513), (200, 31), (1000, 256)]
-    few = [a + n for a, n in shards]
-    tasks = [(i, a, n) for i, (a, n) in enumerate(shards)]
-    fill = -(-1100 // hq)  # documents of one unit per head: beyond 1024 units every list runs whole ones
-    small = W.custom(few, tasks, hq, hkv, d, seed=97)
-    large = W.custom(few + [300] * fill, tasks + [(len(few) + i, 44, 256) for i in range(fill)], hq, hkv, d, seed=97)
-    q, k, v, d_o = W.make_tensors(large, DEV)
-    nq, nk = small.total_q, small.total_kv
-    results = []
-    for b, (qq, kk, vv) in ((large, (q, k, v)), (small, (q[:nq].contiguous(), k[:nk].contiguous(), v[:nk].contiguous()))):
-        plan = B.ca_plan(b)
-        assert (len(plan.fwd_units()) > 1024) == (b is large)
-        o, lse = torch.full_like(qq, float("nan")), torch.full((hq, b.total_q), float("nan"), device=DEV)
-        B.ca_forward(plan, qq, kk, vv, o, lse)  # no workspace: whole units or halves of them, no pieces
-        torch.cuda.synchronize()
-        results.append((o[:nq], lse[:, :nq]))
-    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
-    t = (q[:nq].contiguous(), k[:nk].contiguous(), v[:nk].contiguous())
-    e = P.errors({"o": results[1][0], "lse": results[1][1]}, P.run_oracle(small, *t))
+    small, large = batches([a + n for a, n in shards], [(i, a, n) for i, (a, n) in enumerate(shards)], hq, hkv, d)
+    q, k, v, _ = W.make_tensors(large, DEV)
+    whole, halves = both_forms(small, large, q, k, v)
+    assert torch.equal(whole["o"], halves["o"]) and torch.equal(whole["lse"], halves["lse"])
+    e = P.errors(halves, P.run_oracle(small, q[:small.total_q], k[:small.total_kv], v[:small.total_kv]))
     print(d, hq, hkv, e, flush=True)
     assert e["o_err_over_bound"] <= 1.0 and e["lse_max_abs"] <= P.LSE_MAX_ABS, e
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_both_forms_repeat_after_an_overflow(d):
+    """The last 20 keys of a document score about 2^200 above everything before (in probability)."""
+    n = 300
+    small, large = batches([n], [(0, 0, n)], 2, 1, d, scale=1.0)
+    q, k, v, _ = W.make_tensors(large, DEV)
+    q = torch.full_like(q, 1.0)
+    k = (k.float() * 0.01).to(torch.bfloat16)
+    k[n - 20:n] = (200.0 * np.log(2.0)) / d
+    ref = P.run_oracle(small, q[:n], k[:n], v[:n])
+    for got, form in zip(both_forms(small, large, q, k, v), ("whole units", "halves")):
+        e = P.errors(got, ref)
+        print(d, form, e, flush=True)
+        assert e["o_err_over_bound"] <= 1.0 and e["lse_max_abs"] <= P.LSE_MAX_ABS, (form, e)

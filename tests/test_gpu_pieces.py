@@ -98,9 +98,20 @@ def test_pieces_at_scores_that_outgrow_the_reference():
     k = (k.float() * 0.01).to(torch.bfloat16)
     k[2100:2110] = (200.0 * np.log(2.0)) / 128
     plan = B.ca_plan(b)
-    assert plan.workspace_bytes_split()[0] > 0
+    assert plan.workspace_bytes_split()[0] > 0 and plan.info()["forward_piece_halves"] == 1
     hip = P.run_hip(b, q, k, v, plan=plan)
     e = P.errors(hip, P.run_oracle(b, q, k, v))
+    print(e, flush=True)
+    assert e["o_err_over_bound"] <= 1.0 and e["lse_max_abs"] <= P.LSE_MAX_ABS, e
+
+
+def test_pieces_that_are_whole_units_at_head_dim_64():
+    """The batches above run their pieces as halves of units; this one's are whole."""
+    b = W.custom([5000], [(0, 0, 5000)], 8, 1, 64, seed=95)
+    q, k, v, _ = W.make_tensors(b, DEV)
+    plan = B.ca_plan(b)
+    assert len(plan.pieces()["fwd"]) > 0 and plan.info()["forward_piece_halves"] == 0
+    e = P.errors(P.run_hip(b, q, k, v, plan=plan), P.run_oracle(b, q, k, v))
     print(e, flush=True)
     assert e["o_err_over_bound"] <= 1.0 and e["lse_max_abs"] <= P.LSE_MAX_ABS, e
 
