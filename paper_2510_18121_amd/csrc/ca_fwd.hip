@@ -208,36 +208,39 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
     return join(lds_read_tr4_at(a), lds_read_tr4_at(a + HALF));
   };
   // scores beyond a row's position become -infinity: register e holds key key0 + 4 (lane / 16) + e
-  auto mask = [&](f32x4 (&s)[NR], int key0) __attribute__((always_inline)) {
+  auto mask = [&](int r0, auto &s, int key0) __attribute__((always_inline)) {  // (s: of row groups r0 ..)
     const int lane = lane_id_here();
 #pragma unroll
-    for (int rg = 0; rg < NR; ++rg) {
-      const int vis = lds_ld<int>(lds0 + S::POS_OFF + 64 * (NR * wave + rg) + 4 * (lane & 15)) - key0 - 4 * (lane >> 4);
+    for (int i = 0; i < int(sizeof(s) / sizeof(s[0])); ++i) {
+      const int vis = lds_ld<int>(lds0 + S::POS_OFF + 64 * (NR * wave + r0 + i) + 4 * (lane & 15)) - key0 - 4 * (lane >> 4);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s[rg][e] = e <= vis ? s[rg][e] : -INFINITY;
+      for (int e = 0; e < 4; ++e) s[i][e] = e <= vis ? s[i][e] : -INFINITY;
     }
   };
-  // scores of the 16 keys h of the tile in the current stage, not interleaved with anything, and their maximum per row
-  auto scores_plain = [&](int h, f32x4 (&s)[NR]) __attribute__((always_inline)) {
+  // scores of the 32 keys at koff and row groups r0 .. (as x has), not interleaved with anything
+  auto scores_plain = [&](int r0, auto &x) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < NK; ++k) {
-      const bf16x8 a = read_k(h >> 1, h & 1, k);
+    for (int s = 0; s < NK; ++s) {
 #pragma unroll
-      for (int rg = 0; rg < NR; ++rg) s[rg] = mfma16(a, qf[k][rg], k == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[rg]);
+      for (int kt = 0; kt < 2; ++kt) {
+        const bf16x8 a = read_k(0, kt, s);
+#pragma unroll
+        for (int i = 0; i < int(sizeof(x[0]) / sizeof(x[0][0])); ++i) x[kt][i] = mfma16(a, qf[s][r0 + i], s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : x[kt][i]);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto row_max = [&](const f32x4 &a) __attribute__((always_inline)) { return quad_max(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]))); };
+  auto largest = [&](const f32x4 &a, const f32x4 &b) __attribute__((always_inline)) {
+    return fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(b[0], b[1]), fmaxf(b[2], b[3])));
+  };
 
   // ------------------------------------------------------------------------------------------ general path
-  // the first tile of a document's first rows (below) and, after an overflow, whole units, 16 keys at a time: mask, row
-  // maximum, lazy rescaling, nothing interleaved
-  auto general_keys = [&](int jt, int h) __attribute__((always_inline)) {
-    const int k0 = jt * FWD_BN + 16 * h;
+  // the first tile of a document's first rows (below) and, after an overflow, whole units, 32 keys at a time (at
+  // koff and voff): mask, row maximum, lazy rescaling, nothing interleaved
+  auto general_block = [&](int k0, auto residue) __attribute__((always_inline)) {
+    constexpr bool RESIDUE = decltype(residue)::value;
+    constexpr int GS = D == 64 && !RESIDUE ? NR : 2;  // row groups at a time: with more the registers do not hold all of it
     if (k0 > wmax) return;
-    f32x4 x[NR];
-    scores_plain(h, x);
-    if (k0 + 15 > wmin) mask(x, k0);  // some (row, key) may be above the diagonal
     // Lazy rescaling: the running reference m only moves when some row's maximum has grown by more than
     // 2^RESCALE_LOG2; until then probabilities are taken relative to the stale m (they stay below
     // 2^RESCALE_LOG2, harmless in fp32 and bf16) and the accumulators need no multiply.
@@ -245,48 +248,68 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
     // m = M_NONE and gets probabilities 0)
     // The first rows of a document see a handful of keys, their output is as large as a single V row, and the 2^-9 relative
     // rounding of P to bf16 would show up at the 1e-2 level next to the output's own bf16 rounding.  So the rounding residue of
-    // P goes through the matrix pipe too: of the 32 k-slots of an MFMA 16 take P and 16 its residue, against the same V rows
-    // (P = hi + lo), which makes P V as good as fp32.
-    bf16x8 pb[NR];
+    // P goes through the matrix pipe too (P = hi + lo), which makes P V as good as fp32.  Later tiles go without: with it, and 16 keys
+    // at a time, a forward that repeats all of its 16K tokens took 700 us instead of 493 (16/16 heads, head_dim 64) and 1600
+    // instead of 1310 (32/8, 128).
 #pragma unroll
-    for (int rg = 0; rg < NR; ++rg) {
-      const float m_cand = fmaxf(m[rg], row_max(x[rg]) * c);
-      if (__any(m_cand > m[rg] + RESCALE_LOG2)) {
-        const float alpha = m[rg] == M_NONE ? 0.f : fast_exp2(m[rg] - m_cand);
-        m[rg] = m_cand;
-        lsum[rg] *= alpha;
+    for (int r0 = 0; r0 < NR; r0 += GS) {
+      f32x4 x[2][GS];
+      scores_plain(r0, x);
+      if (k0 + 31 > wmin) mask(r0, x[0], k0), mask(r0, x[1], k0 + 16);  // some (row, key) may be above the diagonal
+      bf16x8 hi[GS], lo[GS];
 #pragma unroll
-        for (int b = 0; b < ND; ++b) acc[b][rg] *= alpha;
+      for (int i = 0; i < GS; ++i) {
+        const int rg = r0 + i;
+        const float top = largest(x[0][i], x[1][i]);
+        if (__any(top * c > m[rg] + RESCALE_LOG2)) {
+          const float m_cand = fmaxf(m[rg], quad_max(top) * c);
+          const float alpha = m[rg] == M_NONE ? 0.f : fast_exp2(m[rg] - m_cand);
+          m[rg] = m_cand;
+          lsum[rg] *= alpha;
+#pragma unroll
+          for (int b = 0; b < ND; ++b) acc[b][rg] *= alpha;
+        }
+        uint32_t h[4], l[4];
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+          float v[4], r[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = fast_exp2(fmaf(x[kt][i][e], c, -m[rg])), r[e] = v[e] - float(bf16_t(v[e]));
+          lsum[rg] += (v[0] + v[1]) + (v[2] + v[3]);
+          h[2 * kt] = pack_bf16(v[0], v[1]), h[2 * kt + 1] = pack_bf16(v[2], v[3]);
+          l[2 * kt] = pack_bf16(r[0], r[1]), l[2 * kt + 1] = pack_bf16(r[2], r[3]);
+        }
+        hi[i] = __builtin_bit_cast(bf16x8, u32x4{h[0], h[1], h[2], h[3]});
+        lo[i] = __builtin_bit_cast(bf16x8, u32x4{l[0], l[1], l[2], l[3]});
+        __builtin_amdgcn_sched_barrier(0);
       }
-      float lo[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[rg][e] = fast_exp2(fmaf(x[rg][e], c, -m[rg]));
-        lsum[rg] += x[rg][e];
-        lo[e] = x[rg][e] - float(bf16_t(x[rg][e]));
+      for (int b = 0; b < ND; ++b) {
+        const bf16x8 a = read_v(0, b);
+#pragma unroll
+        for (int i = 0; i < GS; ++i) acc[b][r0 + i] = mfma16(a, hi[i], acc[b][r0 + i]);
+        if (RESIDUE) {
+#pragma unroll
+          for (int i = 0; i < GS; ++i) acc[b][r0 + i] = mfma16(a, lo[i], acc[b][r0 + i]);
+        }
+        if (b & 1) __builtin_amdgcn_sched_barrier(0);
       }
-      pb[rg] = __builtin_bit_cast(bf16x8, u32x4{pack_bf16(x[rg][0], x[rg][1]), pack_bf16(x[rg][2], x[rg][3]), pack_bf16(lo[0], lo[1]),
-                                                pack_bf16(lo[2], lo[3])});
-    }
-#pragma unroll
-    for (int b = 0; b < ND; ++b) {
-      const bf16x4 a = lds_read_tr4_at((b == 0 ? voff : xor_here(voff, 32 * b)) + 16 * h * ROWB);
-#pragma unroll
-      for (int rg = 0; rg < NR; ++rg) acc[b][rg] = mfma16(join(a, a), pb[rg], acc[b][rg]);
-      __builtin_amdgcn_sched_barrier(0);
     }
   };
-
-  auto general_tile = [&](int jt) __attribute__((always_inline)) {
-    top(jt);
-#pragma unroll
-    for (int h = 0; h < FWD_BN / 16; ++h) general_keys(jt, h);
+  auto general_tile = [&](int jt, auto residue) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int kb = 0; kb < 2; ++kb) {
+      general_block(jt * FWD_BN + 32 * kb, residue);
+      koff += 32 * ROWB, voff += 32 * ROWB;
+    }
+    koff -= FWD_BN * ROWB, voff -= FWD_BN * ROWB;
     advance(jt);
   };
 
   int j = 0;
   if (wmin64 < FWD_BN) {  // rows that see less than a tile: hi + lo P on tile 0
-    general_tile(0);
+    top(0);
+    general_tile(0, std::true_type{});
     j = 1;
   }
   // ------------------------------------------------------------------------------------------ fast path
@@ -343,7 +366,7 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
           next();
         }
         if (MASK) {
-          mask(s[0], key0), mask(s[1], key0 + 16);
+          mask(0, s[0], key0), mask(0, s[1], key0 + 16);
 #pragma unroll
           for (int rg = 0; rg < NR; ++rg) expo(0, rg);
         }
@@ -366,10 +389,13 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
     const int entry = j;
     top(j);
     if (j == 0) {  // the maximum over the first keys, which every row sees, becomes the reference
-      f32x4 s[NR];
-      scores_plain(0, s);
 #pragma unroll
-      for (int rg = 0; rg < NR; ++rg) m[rg] = row_max(s[rg]) * c;
+      for (int r0 = 0; r0 < NR; r0 += 2) {
+        f32x4 x[2][2];
+        scores_plain(r0, x);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) m[r0 + i] = quad_max(largest(x[0][i], x[0][i])) * c;
+      }
     }
     for (; j < n_fast; ++j) {
       if (j > entry) top(j);
@@ -405,7 +431,12 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
     clear();
     first_stage();
     issue_first();
-    for (j = 0; j < n_tiles; ++j) general_tile(j);
+    top(0);
+    general_tile(0, std::true_type{});
+    for (j = 1; j < n_tiles; ++j) {
+      top(j);
+      general_tile(j, std::false_type{});
+    }
     wait_vmcnt<0>();
     __syncthreads();  // the epilogue writes into the stages
   }
