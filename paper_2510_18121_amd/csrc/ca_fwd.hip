@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
     // and ND of V transposed.  The exponentials of the first 16 keys go between the score MFMAs of the other 16; fences keep that
     // order.  (Whole units have no registers for more than 2 ahead without spilling, and gain nothing from 3.)
     constexpr int NF = 2 * NK + ND, AHEAD = HALVES ? 4 : 2;
-    auto blocks = [&](const int KB0, const int KB1, const bool MASK, int key0) __attribute__((always_inline)) {
+    auto blocks = [&](const int KB0, const int KB1, const bool MASK, int key0, const bool FIRST = false) __attribute__((always_inline)) {
       bf16x8 fr[AHEAD];
       auto fetch = [&](int i) __attribute__((always_inline)) -> bf16x8 {
         const int kb = KB0 + i / NF, f = i % NF;
@@ -359,14 +359,18 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
           const int kt = f / NK;
 #pragma unroll
           for (int rg = 0; rg < NR; ++rg) s[kt][rg] = mfma16(fr[at % AHEAD], qf[f % NK][rg], f % NK == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[kt][rg]);
-          if (!MASK && kt == 1) {
+          if (!MASK && !(FIRST && kb == 0) && kt == 1) {
 #pragma unroll
             for (int rg = NR * (f - NK) / NK; rg < NR * (f - NK + 1) / NK; ++rg) expo(0, rg);
           }
           next();
         }
-        if (MASK) {
-          mask(0, s[0], key0), mask(0, s[1], key0 + 16);
+        if (FIRST && kb == 0) {
+#pragma unroll
+          for (int rg = 0; rg < NR; ++rg) m[rg] = quad_max(largest(s[0][rg], s[1][rg])) * c;
+        }
+        if (MASK) mask(0, s[0], key0), mask(0, s[1], key0 + 16);
+        if (MASK || (FIRST && kb == 0)) {
 #pragma unroll
           for (int rg = 0; rg < NR; ++rg) expo(0, rg);
         }
@@ -388,14 +392,10 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
     };
     const int entry = j;
     top(j);
-    if (j == 0) {  // the maximum over the first keys, which every row sees, becomes the reference
-#pragma unroll
-      for (int r0 = 0; r0 < NR; r0 += 2) {
-        f32x4 x[2][2];
-        scores_plain(r0, x);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) m[r0 + i] = quad_max(largest(x[0][i], x[0][i])) * c;
-      }
+    if (j == 0) {  // the maximum over the first 32 keys, which every row sees, becomes the reference
+      blocks(0, 2, false, 0, true);
+      advance(0);
+      j = 1;
     }
     for (; j < n_fast; ++j) {
       if (j > entry) top(j);

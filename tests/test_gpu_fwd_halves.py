@@ -61,3 +61,22 @@ def test_both_forms_repeat_after_an_overflow(d):
         e = P.errors(got, ref)
         print(d, form, e, flush=True)
         assert e["o_err_over_bound"] <= 1.0 and e["lse_max_abs"] <= P.LSE_MAX_ABS, (form, e)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_the_reference_is_the_maximum_of_the_first_32_keys(d):
+    """Keys 20 and 21 share the weight (what the others have, 2^-60 each, is lost in fp32).  Referred to their own score their
+    probabilities are 1, which bf16 holds, so that O is the mean of their V rows, rounded once; referred to a smaller score
+    they are 2^60.37, and O carries their rounding."""
+    n = 300
+    small, large = batches([n], [(0, 0, n)], 2, 1, d, scale=1.0)
+    q, k, v, _ = W.make_tensors(large, DEV)
+    q, k = torch.full_like(q, 1.0), torch.zeros_like(k)
+    k[20:22] = 60.37 * np.log(2.0) / d
+    mean = (v[20].float() + v[21].float()) / 2
+    # (a score times log2(e) and its fp32 rounding, which is subtracted, are 2^-19 apart: where that decides how O is rounded, skip)
+    sure = (mean * (1 + 1e-5)).to(torch.bfloat16) == (mean * (1 - 1e-5)).to(torch.bfloat16)
+    sure = (sure & (mean.abs() > 1e-3)).expand(n - 21, 2, d)  # (where the two cancel, the others show)
+    assert sure.float().mean() > 0.4
+    for got in both_forms(small, large, q, k, v):
+        assert torch.equal(got["o"][21:][sure], mean.to(torch.bfloat16).expand(n - 21, 2, d)[sure])
