@@ -132,9 +132,11 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
 
   // Q fragments: B operand of S^T = K Q^T; lane holds Q[row][32 s + 8 (lane / 16) .. +7]
   bf16x8 qf[NK][NR];
-  int wmax, wmin;  // the last key that any row, that every row of the wave sees
-  // the same as wmin over the 64 rows that a wave has in whole units: what a row's results depend on must not be which of the two it is in
+  // The last key that every row of the wave sees (positions are sorted), and that every row, that any row of the 64 sees that share a
+  // wave in whole units: which blocks are multiplied, so whom a non-finite value of V reaches, does not depend on the form either.
+  const int wmin = slot_pos[u.slot0 + (pair0 >> hp_lg) * 32] - u.key0;
   const int wmin64 = slot_pos[u.slot0 + ((pair0 & ~1) >> hp_lg) * 32] - u.key0;
+  const int wmax64 = slot_pos[u.slot0 + ((pair0 | 1) >> hp_lg) * 32 + 31] - u.key0;
   uint32_t koff, voff;  // per-lane LDS read addresses into the current stage: natural reads of K, transposing reads of V
   {
     const int lane = lane_id_here(), j4 = lane >> 4, li = lane & 15;
@@ -147,10 +149,6 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
 #pragma unroll
       for (int s = 0; s < NK; ++s) qf[s][rg] = *reinterpret_cast<const bf16x8 *>(qp + 32 * s);
     }
-    wmax = pos[0], wmin = pos[0];
-#pragma unroll
-    for (int rg = 1; rg < NR; ++rg) wmax = max(wmax, pos[rg]), wmin = min(wmin, pos[rg]);
-    wmax = wave_max(wmax), wmin = wave_min(wmin);
     // (only masked blocks need the positions: they wait in LDS)
     if (lane < 16) {
 #pragma unroll
@@ -163,11 +161,10 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
     voff = lds0 + S::V_OFF + (4 * j4 + (li >> 2)) * ROWB + 16 * (((li >> 1) & 1) ^ tile_sw<D>(4 * j4 + (li >> 2))) + 8 * (li & 1);
   };
   first_stage();
-  wmax = __builtin_amdgcn_readfirstlane(wmax), wmin = __builtin_amdgcn_readfirstlane(wmin);
-  // tiles j < n_fast are entirely visible to every row of this wave, tiles from n_seen on are seen by none of its rows
+  // tiles j < n_fast are entirely visible to every row of this wave, tiles from n_seen on are seen by none of the 64
   // (rows may see past the window of a piece; one that is not the unit's last has whole tiles only)
   const int n_fast = min(wmin + 1, u.n_keys) / FWD_BN;
-  const int n_seen = wmax < 0 ? 0 : min(wmax / FWD_BN + 1, n_tiles);
+  const int n_seen = wmax64 < 0 ? 0 : min(wmax64 / FWD_BN + 1, n_tiles);
 
   f32x4 acc[ND][NR];
   float m[NR], lsum[NR];
@@ -235,12 +232,12 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
   };
 
   // ------------------------------------------------------------------------------------------ general path
-  // the first tile of a document's first rows (below) and, after an overflow, whole units, 32 keys at a time (at
+  // the first tile of a document's first rows (below) and, after an overflow, all tiles of the rows concerned, 32 keys at a time (at
   // koff and voff): mask, row maximum, lazy rescaling, nothing interleaved
   auto general_block = [&](int k0, auto residue) __attribute__((always_inline)) {
     constexpr bool RESIDUE = decltype(residue)::value;
     constexpr int GS = D == 64 && !RESIDUE ? NR : 2;  // row groups at a time: with more the registers do not hold all of it
-    if (k0 > wmax) return;
+    if (k0 > wmax64) return;
     // Lazy rescaling: the running reference m only moves when some row's maximum has grown by more than
     // 2^RESCALE_LOG2; until then probabilities are taken relative to the stale m (they stay below
     // 2^RESCALE_LOG2, harmless in fp32 and bf16) and the accumulators need no multiply.
@@ -406,7 +403,7 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
       if (j > entry) top(j);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
-        if (FWD_BN * j + 32 * kb <= wmax) blocks(kb, kb + 1, true, FWD_BN * j + 32 * kb);
+        if (FWD_BN * j + 32 * kb <= wmax64) blocks(kb, kb + 1, true, FWD_BN * j + 32 * kb);
       advance(j);
     }
     bool inside = true;  // (false for NaN)
@@ -416,26 +413,31 @@ __global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(
   }
   for (; j < n_tiles; ++j) top(j);  // tiles only other waves see: this wave's part of the loads
   wait_vmcnt<0>();  // nothing may still be writing LDS
-  // Did the fast path of any wave of the workgroup meet a maximum beyond its window?  (The tiles are shared, so
-  // the workgroup repeats the unit together or not at all.)  Flags go through the first bytes of LDS: every tile read
-  // and every direct load of the workgroup is complete after the first barrier.
+  // Did the fast path of any wave meet a maximum beyond its window?  Then the rows of its half of the unit (128 rows) are computed
+  // again.  The tiles are shared, so all waves of the workgroup go along; those of the other half of a whole unit only fetch.
+  // Flags go through the first bytes of LDS: every tile read and every direct load of the workgroup is complete after the
+  // first barrier.
   barrier_nofence();
   if (lane_id_here() == 0) *reinterpret_cast<volatile int *>(smem + 4 * wave) = outgrown ? 1 : 0;
   __syncthreads();
-  int flags = 0;
+  int flags = 0, mine = 0;
 #pragma unroll
-  for (int w = 0; w < W; ++w) flags |= *reinterpret_cast<volatile int *>(smem + 4 * w);
+  for (int w = 0; w < W; ++w) {
+    const int f = *reinterpret_cast<volatile int *>(smem + 4 * w);
+    flags |= f;
+    if (HALVES || w / 2 == wave / 2) mine |= f;
+  }
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(flags) != 0) {
-    // the whole unit again, every tile through the general path
-    clear();
+    const bool again = __builtin_amdgcn_readfirstlane(mine) != 0;
+    if (again) clear();
     first_stage();
     issue_first();
-    top(0);
-    general_tile(0, std::true_type{});
+    top(0);  // every tile through the general path
+    if (again) general_tile(0, std::true_type{});
     for (j = 1; j < n_tiles; ++j) {
       top(j);
-      general_tile(j, std::false_type{});
+      if (again) general_tile(j, std::false_type{});
     }
     wait_vmcnt<0>();
     __syncthreads();  // the epilogue writes into the stages

@@ -80,3 +80,36 @@ def test_the_reference_is_the_maximum_of_the_first_32_keys(d):
     assert sure.float().mean() > 0.4
     for got in both_forms(small, large, q, k, v):
         assert torch.equal(got["o"][21:][sure], mean.to(torch.bfloat16).expand(n - 21, 2, d)[sure])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_an_overflow_in_one_half_leaves_the_other_alone(d):
+    """Rows 200 and up of a unit leave the finite range and are computed again with the rest of their half; the other half is not,
+    in either form."""
+    n = 256
+    small, large = batches([n], [(0, 0, n)], 2, 1, d, scale=1.0)
+    q, k, v, _ = W.make_tensors(large, DEV)
+    q = torch.full_like(q, 1.0)
+    k = (k.float() * 0.05).to(torch.bfloat16)
+    k[200:204] = (200.0 * np.log(2.0)) / d
+    whole, halves = both_forms(small, large, q, k, v)
+    assert torch.isfinite(whole["o"]).all() and float(whole["lse"][:, 200:].min()) > 130
+    assert torch.equal(whole["o"], halves["o"]) and torch.equal(whole["lse"], halves["lse"])
+
+
+@pytest.mark.parametrize("kind", [float("inf"), float("nan")])
+@pytest.mark.parametrize("d", [64, 128])
+def test_whom_a_non_finite_value_reaches_does_not_depend_on_the_form(d, kind):
+    """A masked key multiplies its value by 0, so a non-finite one reaches the rows that are multiplied with its 32 keys: those of
+    the 64 that share a wave in whole units."""
+    shards = [(10, 290), (0, 256), (100, 40)]
+    small, large = batches([a + n for a, n in shards], [(i, a, n) for i, (a, n) in enumerate(shards)], 2, 2, d)
+    q, k, v, _ = W.make_tensors(large, DEV)
+    for key in (20, 40, 57, 100, 130, 170, 210):
+        bad = v.clone()
+        for i, (a, n) in enumerate(shards):
+            if key < a + n:
+                bad[sum(x + y for x, y in shards[:i]) + key] = kind
+        whole, halves = both_forms(small, large, q, k, bad)
+        assert torch.equal(whole["o"].isnan(), halves["o"].isnan()) and not torch.isfinite(whole["o"]).all()
+        assert torch.equal(whole["o"].nan_to_num(0.0), halves["o"].nan_to_num(0.0)) and torch.equal(whole["lse"], halves["lse"])
