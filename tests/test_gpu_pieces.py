@@ -17,6 +17,9 @@ BATCHES = {
     "lone ragged shard": ([5000], [(0, 4711, 289)], 8, 2, 128),
     "lone ragged shard d64": ([5000], [(0, 4711, 289)], 8, 2, 64),
     "one row": ([4099], [(0, 4098, 1)], 4, 1, 128),
+    # units of 256 slots whose rows are in one wave of one half
+    "few rows, no GQA": ([6000], [(0, 5990, 5)], 3, 3, 128),
+    "few rows, no GQA d64": ([6000], [(0, 5950, 34)], 3, 3, 64),
     "one document": ([2111], [(0, 0, 2111)], 4, 2, 128),
     "one document d64, no GQA": ([1900], [(0, 0, 1900)], 3, 3, 64),
     "GQA 8, two documents": ([1500, 700], [(0, 0, 811), (0, 811, 689), (1, 100, 600)], 8, 1, 128),
