@@ -45,7 +45,7 @@ struct FwdSmem {
 };
 
 template <int D, bool HALVES>
-__global__ __launch_bounds__(256, D == 64 || HALVES ? 3 : 2) void ca_fwd_kernel(const FwdUnit *__restrict__ units, int n_units,
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void ca_fwd_kernel(const FwdUnit *__restrict__ units, int n_units,
                                                                    const int32_t *__restrict__ slot_row,
                                                                    const int32_t *__restrict__ slot_pos,
                                                                    const bf16_t *__restrict__ Q,
