@@ -259,7 +259,8 @@ const char *ca_last_error(void); /* thread-local detail of the last failing call
  * heads_packed (query heads per head-packed forward unit), n_bwd_workgroups (workgroups of the dK/dV kernel: short
  * backward units are chained, see below), joint_backward (1: the backward runs its dK/dV and dQ units in one launch, given
  * the workspace of ca_plan_workspace_bytes_split; in two while timing is enabled), forward_halves and forward_piece_halves (1:
- * the workgroups of ca_forward are halves, of 128 rows, of the units in the list of whole units, in the list of pieces).
+ * the workgroups of ca_forward are halves, of 128 rows, of the units in the list of whole units, in the list of pieces), forward_turns and
+ * forward_piece_turns (1: workgroups of that list that share a CU take turns at having priority).
  * n_q_tiles counts the full 256-slot tiles.
  * Returns the number of values available.
  */

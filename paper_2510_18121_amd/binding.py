@@ -117,7 +117,8 @@ class Plan:
 
     INFO_KEYS = ("q_tile_rows", "n_q_tiles", "n_fwd_units", "kv_tile_rows", "n_bwd_units", "fwd_kv_step",
                  "padded_rows", "fwd_steps", "bwd_steps", "bwd_q_block_rows", "slot_align", "heads_packed",
-                 "n_bwd_workgroups", "joint_backward", "forward_halves", "forward_piece_halves")
+                 "n_bwd_workgroups", "joint_backward", "forward_halves", "forward_piece_halves",
+                 "forward_turns", "forward_piece_turns")
 
     def __init__(self, handle, batch):
         self.handle = ctypes.c_void_p(handle)

@@ -45,7 +45,7 @@ struct FwdSmem {
 };
 
 template <int D, bool HALVES>
-__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void ca_fwd_kernel(const FwdUnit *__restrict__ units, int n_units,
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void ca_fwd_kernel(const FwdUnit *__restrict__ units, int n_units, int turns,
                                                                    const int32_t *__restrict__ slot_row,
                                                                    const int32_t *__restrict__ slot_pos,
                                                                    const bf16_t *__restrict__ Q,
@@ -66,6 +66,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void ca_fwd_kernel(const FwdU
   constexpr float RESCALE_LOG2 = 8.0f;
   constexpr float M_NONE = -3.402823466e38f;  // running maximum of a row that has seen no key: finite, so that -inf - m is -inf
   constexpr int NR = HALVES ? 2 : 4;  // groups of 16 rows per wave
+  constexpr int TURN_LG = 13;         // a turn in clock cycles: two to three tiles
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(CA_LDS char *)smem;  // LDS byte address of the dynamic segment
 
@@ -195,6 +196,13 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void ca_fwd_kernel(const FwdU
   auto top = [&](int j) __attribute__((always_inline)) {
     wait_vmcnt<2 * (NST - 2) * NLD>();
     barrier_nofence();  // ... and everybody else's; everybody is done with tile j-1
+    // Two workgroups of equal length that share a CU take turns at having priority (workgroups i and i + 256 share one).  Left to
+    // itself the hardware serves the older one first: it runs nearly as fast as alone, and its neighbour ends up alone on the CU
+    // (cycles per tile of the faster and the slower one, 4512 and 6701 of 506 tiles each; taking turns 5714 and 6263).
+    if (D == 128 && turns) {
+      if ((uint32_t(__builtin_amdgcn_s_memtime() >> TURN_LG) ^ (blockIdx.x / N_CU)) & 1) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(0);
+    }
     if (NST > 2 || j < last_tile) issue_kv(j + NST - 1);  // (with three stages always: the wait counts loads)
   };
   auto advance = [&](int j) __attribute__((always_inline)) {
@@ -516,6 +524,7 @@ static hipError_t launch_fwd_t(const ca_plan_t *p, const void *q, const void *k,
   float *const pp = static_cast<float *>(parts);
   float *const stats = pp ? pp + size_t(p->n_fwd_parts) * (FWD_BM * D) : nullptr;
   const size_t n = pp ? p->fwd_pieces.size() : p->fwd_units.size();
+  const FwdForm form = pp ? p->fwd_piece_form : p->fwd_form;
   auto launch = [&](auto halves) {
     constexpr bool HALVES = decltype(halves)::value;
     auto kern = ca_fwd_kernel<D, HALVES>;
@@ -527,11 +536,11 @@ static hipError_t launch_fwd_t(const ca_plan_t *p, const void *q, const void *k,
       attr_done[p->device & 15].store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL(kern, dim3(unsigned(HALVES ? 2 * n : n)), dim3(256), SMEM, st, pp ? p->d_fwd_pieces : p->d_fwd_units, int(n),
-                       p->d_slot_row, p->d_slot_pos, static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k),
+                       int(form.turns), p->d_slot_row, p->d_slot_pos, static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k),
                        static_cast<const bf16_t *>(v), static_cast<bf16_t *>(o), lse, pp, stats, p->hq, p->hkv, p->total_q, c);
     return hipSuccess;
   };
-  const hipError_t launched = (pp ? p->fwd_piece_halves : p->fwd_halves) ? launch(std::true_type{}) : launch(std::false_type{});
+  const hipError_t launched = form.halves ? launch(std::true_type{}) : launch(std::false_type{});
   if (launched != hipSuccess) return launched;
   if (pp) {
     hipLaunchKernelGGL(ca_combine_fwd_kernel<D>, dim3(unsigned(p->fwd_combine.size() * 8 * (D / 64))), dim3(256), 0, st,

@@ -77,6 +77,13 @@ struct CombineUnit {
 inline size_t part_bytes(int d) { return size_t(FWD_BM) * d * 4; }
 constexpr size_t FWD_STAT_BYTES = 8 * 64 * 2 * 4;
 
+constexpr int N_CU = 256;
+// How the forward kernel runs a list of units (the planner chooses, see there)
+struct FwdForm {
+  bool halves = false;  // workgroups are halves of units (of 128 rows)
+  bool turns = false;   // workgroups that share a CU take turns at having priority
+};
+
 }  // namespace ca
 
 struct ca_plan {
@@ -101,7 +108,7 @@ struct ca_plan {
   std::vector<ca::CombineUnit> fwd_combine, bwd_combine;
   int32_t bwd_piece_workgroups = 0;
   int32_t n_fwd_parts = 0, n_bwd_parts = 0;
-  bool fwd_halves = false, fwd_piece_halves = false;  // forward workgroups are halves of units (of 128 rows): of each list
+  ca::FwdForm fwd_form, fwd_piece_form;
   // workspace with which the piece lists are used: forward, and backward, where the parts lie behind ws_bwd
   size_t ws_fwd_split = 0, ws_bwd_split = 0, ws_off_parts_kv = 0, ws_off_parts_dq = 0;
   bool joint = false;  // backward runs dK/dV and dQ units in one launch: dK/dV workgroups, then dQ halves 1, then 0, or,

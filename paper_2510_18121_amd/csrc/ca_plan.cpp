@@ -111,7 +111,6 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // (head_dim 128, per step alone / of two: forward 1.8 / 1.8, dK/dV 1.75 / 1.6; at 64 of three: 1.0 and 0.85).  The fixed part is what
 // a unit spends around its steps (descriptor, row indices, fragments, first tiles, drain, results) and another workgroup does not
 // hide; partial results move at about 4 TB/s.
-constexpr int N_CU = 256;
 // Batches with more dK/dV work than this per CU run two launches.  One launch against two, forward + backward at head_dim 128: 499 ->
 // 459 us (4K tokens of documents of about 1K, 0.2 ms of dK/dV work), 2250 -> 2200 (256 rows in 16 windows of 8K keys, 1.0 ms); beyond,
 // lone shards lose (1000 rows with a 130K context, 3.2 ms: 7.72 -> 8.0 ms; 64-row shards with contexts, 2.8 ms: 5.33 -> 5.40: half units
@@ -171,6 +170,44 @@ double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_
   }
   if (held > 0) end = std::max(end, (busy.size() < n_busy ? 0.0 : busy[0]) + held_us / double(held));
   return end;
+}
+
+// Forward workgroups: whole units, or their halves of 128 rows.  Halves are a finer schedule, and two of them run a unit that is
+// alone on its CU in 60 % of the time; where both fill the chip a tile costs two halves 7 % more (K and V fragments feed half
+// the MFMAs).  Measured, units against halves, head_dim 128: 45 -> 24 us (32 units of 16 tiles), 196 -> 182 (384 of 64), 135 -> 110
+// (4K tokens of documents of about 1K: 512 units of 1 to 50 tiles), 229 -> 250 (512 of 64), 480 -> 534 (512 of 128).
+// Workgroups of equal length of which a CU gets two share it evenly only if they take turns at having priority (see the kernel).
+// Without and with that: 1705 -> 1630 us (512 pieces of 508 tiles), 1900 -> 1858 (halves of 256 pieces of 1016), 74.1 -> 72.2 (halves of
+// 256 pieces of 32).  In a list of unequal ones the longest are the oldest, and better off served first; with more than two per CU
+// there is no tail to even out (halves of 384 pieces of 22 tiles: 79 -> 89 us).
+struct FwdUnits {
+  double tiles, tiles_half;  // of a unit, and of its first half
+  int64_t n;
+};
+struct FwdRun {
+  FwdForm form;
+  double us;
+};
+// The better form of a list, longest first, and its time.  Microseconds, start + per tile, fitted to the figures above.
+FwdRun fwd_run(const std::vector<FwdUnits> &list, int d) {
+  if (list.empty()) return {{}, 0.0};
+  int64_t units = 0;
+  for (const FwdUnits &u : list) units += u.n;
+  const bool d128 = d == 128, lone = units <= N_CU, equal = list.back().tiles >= 0.9 * list.front().tiles;
+  auto turns = [&](int64_t workgroups) { return d128 && equal && workgroups > N_CU && workgroups <= 2 * N_CU; };
+  const bool whole_turns = turns(units), half_turns = turns(2 * units);
+  const double fixed = d128 ? 8.0 : 5.0, per = whole_turns ? 1.5 : d128 ? (lone ? 2.05 : 1.78) : lone ? 1.15 : 1.0;
+  const double fixed_half = d128 ? 4.0 : 2.5, per_half = half_turns ? 0.87 : d128 ? 0.96 : 0.53;
+  std::vector<std::pair<double, int64_t>> whole, half;
+  for (const FwdUnits &u : list) whole.push_back({fixed + per * u.tiles, u.n});
+  const FwdRun run{{false, whole_turns}, makespan(whole, N_CU, 1e30, JOINT_UNITS)};
+  if (units > 4 * N_CU) return run;
+  for (const FwdUnits &u : list) {
+    half.push_back({fixed_half + per_half * u.tiles, u.n});
+    half.push_back({fixed_half + per_half * u.tiles_half, u.n});
+  }
+  const double us = makespan(half, N_CU, run.us, JOINT_UNITS);
+  return us < run.us ? FwdRun{{true, half_turns}, us} : run;
 }
 
 // The longest piece in steps (0: cut nothing) and the launch time that gives, under each of two limits of the partial results.
@@ -383,6 +420,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   bool more = false;
   double us_apart = 0;  // simulated time of the backward in two launches
   const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.65, 10.0, 5.0, 4} : CutCost{2 * N_CU, 1.75, 12.0, 5.0, 4};
+  const double dq_per_tile = p->d == 128 ? 2.4 : 1.4, dq_fixed = 8.0;  // of the dQ kernel
   const CutCost cost_fwd = {N_CU, p->d == 128 ? 1.9 : 1.1, 8.0, 5.0, 4};
   std::vector<int64_t> wg_steps;  // of the dK/dV kernel's workgroups of one KV head, as they are launched
   p->bwd_steps = 0;
@@ -394,7 +432,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     // takes at most CHAIN_STEPS_MAX steps and CHAIN_UNITS_MAX units, and at most 1/(2 N_CU) of the short units' steps
     // still to be handed out: chains shrink towards the end of the list, so that the last workgroups of the launch
     // are small ones and the CUs finish together.
-    constexpr int64_t N_CU = 256, CHAIN_UNIT_STEPS = 16, CHAIN_STEPS_MAX = 256, CHAIN_UNITS_MAX = 32;
+    constexpr int64_t CHAIN_UNIT_STEPS = 16, CHAIN_STEPS_MAX = 256, CHAIN_UNITS_MAX = 32;
     auto cost = [&](const BwdUnit &u) { return int64_t(u.slot_end - u.slot_begin) / BWD_BQ * u.heads; };
     int64_t remaining = 0;  // steps of short units, all KV heads
     for (auto &t : btiles)
@@ -533,32 +571,21 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     }
   }
   {
-    // Forward workgroups: whole units, or their halves of 128 rows.  Halves are a finer schedule, and two of them run a unit that is
-    // alone on its CU in 60 % of the time; where both fill the chip a tile costs two halves 7 % more (K and V fragments feed half
-    // the MFMAs).  Microseconds, start + per tile: a unit 8 + 1.78 (2.05 where no CU has two) at head_dim 128, 5 + 1.0 (1.15) at 64; a
-    // half 4 + 0.96 and 2.5 + 0.53.  Measured, units against halves, head_dim 128: 45 -> 24 us (32 units of 16 tiles), 196 -> 182
-    // (384 of 64), 135 -> 110 (4K tokens of documents of about 1K: 512 units of 1 to 50 tiles), 229 -> 250 (512 of 64), 480 -> 534
-    // (512 of 128).
-    auto halves = [&](const std::vector<FwdUnit> &units) {
-      if (units.size() > size_t(4 * N_CU)) return false;
-      const bool d128 = p->d == 128, lone = units.size() <= size_t(N_CU);
-      const double fixed = d128 ? 8.0 : 5.0, per = d128 ? (lone ? 2.05 : 1.78) : lone ? 1.15 : 1.0;
-      const double fixed_half = d128 ? 4.0 : 2.5, per_half = d128 ? 0.96 : 0.53;
-      std::vector<std::pair<double, int64_t>> whole, half;
+    auto form = [&](const std::vector<FwdUnit> &units) {
+      std::vector<FwdUnits> list;
+      if (units.size() > size_t(4 * N_CU)) return FwdForm{};
       for (size_t i = 0, n; i < units.size(); i += n) {
         const FwdUnit &u = units[i];
         n = size_t(hq / u.hp);
         const int32_t tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
         // the tiles the first half's rows see (its last slot has its highest position)
         const int32_t last = p->slot_pos[size_t(u.slot0 + (3 / u.hp) * 32 + 31)] - u.key0;
-        whole.push_back({fixed + per * tiles, int64_t(n)});
-        half.push_back({fixed_half + per_half * tiles, int64_t(n)});
-        half.push_back({fixed_half + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1)), int64_t(n)});
+        list.push_back({double(tiles), double(std::max(1, std::min(tiles, last / FWD_BN + 1))), int64_t(n)});
       }
-      return makespan(half, N_CU, 1e30, JOINT_UNITS) < makespan(whole, N_CU, 1e30, JOINT_UNITS);
+      return fwd_run(list, p->d).form;
     };
-    p->fwd_halves = halves(p->fwd_units);
-    p->fwd_piece_halves = halves(p->fwd_pieces);
+    p->fwd_form = form(p->fwd_units);
+    p->fwd_piece_form = form(p->fwd_pieces);
   }
   {
     // One launch or two for the backward.  The dQ kernel proper runs 256 rows per workgroup; in the joint launch a workgroup is
@@ -587,12 +614,12 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
         sum += us * hkv;
         longest = std::max(longest, us);
       }
-      const double per = p->d == 128 ? 2.4 : 1.4, per_half = p->d == 128 ? 1.2 : 1.4, fixed_half = p->d == 128 ? 4.0 : 7.0;
+      const double per_half = p->d == 128 ? 1.2 : 1.4, fixed_half = p->d == 128 ? 4.0 : 7.0;
       for (int32_t half = 1; half >= 0; --half)
         for (int32_t i = 0; i < n_dq;) {
           const FwdUnit &u = units[size_t(i)];
           const int32_t n = hq / u.hp, tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
-          if (half == 1) dq.push_back({cost_fwd.fixed + per * tiles, n / same});
+          if (half == 1) dq.push_back({dq_fixed + dq_per_tile * tiles, n / same});
           // the tiles the half's rows see (its last slot has its highest position)
           const int32_t last = p->slot_pos[size_t(u.slot0 + ((4 * half + 3) / u.hp) * 32 + 31)] - u.key0;
           const double us = fixed_half + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1));
@@ -681,9 +708,9 @@ int build_plan(const ca_batch_desc *desc, ca_plan_t **out) {
     validate(desc);
     auto p = described(desc);
     // Where cutting units beyond the static workspace looks better by a tenth, or would save a backward launch worth it (the dQ parts
-    // take the place of the dK/dV parts inside, which needs two), both plans are made, and kept if the whole pass
-    // is: the larger for callers that bring the workspace, the smaller inside it for all others.  (Forward + backward, 8/2 heads,
-    // without and with the second case: 2048 rows with an 8K context 318 -> 266 us, 3072 rows 404 -> 356 us; simulated to gain 34 and
+    // take the place of the dK/dV parts inside, which needs two), both plans are
+    // made, and kept if the whole pass is better: the larger for callers that bring the workspace, the smaller inside it for all others.  (Forward + backward, 8/2 heads,
+    // without and with the launch saved: 2048 rows with an 8K context 318 -> 266 us, 3072 rows 404 -> 356 us; simulated to gain 34 and
     // 38 us.  Below 25 us the larger workspace is not taken for it.)
     const bool more = schedule(p.get(), false);
     if (more || p->joint_lost) {
@@ -748,12 +775,12 @@ int ca_plan_info(const ca_plan_t *p, int64_t *out, int n) {
   if (!p) return 0;
   int64_t full_tiles = 0;
   for (auto &u : p->fwd_units) full_tiles += u.hp == 1 && u.head == 0;
-  const int64_t v[16] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
+  const int64_t v[18] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
                          ca::BWD_BN, int64_t(p->bwd_units.size()), ca::FWD_BN, int64_t(p->slot_row.size()),
                          p->fwd_steps, p->bwd_steps, ca::BWD_BQ, p->slot_align, p->heads_packed, p->bwd_workgroups,
-                         p->joint, p->fwd_halves, p->fwd_piece_halves};
-  for (int i = 0; i < n && i < 16 && out; ++i) out[i] = v[i];
-  return 16;
+                         p->joint, p->fwd_form.halves, p->fwd_piece_form.halves, p->fwd_form.turns, p->fwd_piece_form.turns};
+  for (int i = 0; i < n && i < 18 && out; ++i) out[i] = v[i];
+  return 18;
 }
 
 int64_t ca_plan_rows(const ca_plan_t *p, int32_t *rows, int32_t *pos) {

@@ -113,3 +113,15 @@ def test_whom_a_non_finite_value_reaches_does_not_depend_on_the_form(d, kind):
         whole, halves = both_forms(small, large, q, k, bad)
         assert torch.equal(whole["o"].isnan(), halves["o"].isnan()) and not torch.isfinite(whole["o"]).all()
         assert torch.equal(whole["o"].nan_to_num(0.0), halves["o"].nan_to_num(0.0)) and torch.equal(whole["lse"], halves["lse"])
+
+
+def test_taking_turns_does_not_change_results():
+    """512 units of equal length, two per CU, which take turns at having priority, against the same among 1632 that do not."""
+    small, large = batches([500] * 16, [(i, 244, 256) for i in range(16)], 32, 8, 128)
+    q, k, v, _ = W.make_tensors(large, DEV)
+    nq, nk, results = small.total_q, small.total_kv, []
+    for b, (qq, kk, vv) in ((large, (q, k, v)), (small, (q[:nq].contiguous(), k[:nk].contiguous(), v[:nk].contiguous()))):
+        plan = B.ca_plan(b)
+        assert plan.info()["forward_turns"] == (b is small) and plan.info()["forward_halves"] == 0
+        results.append(P.run_hip(b, qq, kk, vv, plan=plan))
+    assert torch.equal(results[0]["o"][:nq], results[1]["o"]) and torch.equal(results[0]["lse"][:, :nq], results[1]["lse"])
