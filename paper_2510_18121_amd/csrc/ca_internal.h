@@ -115,6 +115,7 @@ struct ca_plan {
   // if not empty, in this order: i >= 0: dK/dV workgroup i; below: -1 - (half * dQ units + unit)
   std::vector<int32_t> joint_order;
   bool joint_lost = false;  // one launch looked better, but the parts are shared
+  bool pieces_lost = false;  // shorter forward pieces looked better, but their parts are beyond the static workspace
   bool shared_parts = false;  // the dQ parts take the place of the dK/dV parts once those have been added up
   // simulated time of the cut forward units (0: nothing to cut) and of the backward units and their partial results (0: not simulated)
   double us_fwd = 0, us_bwd = 0;

@@ -121,6 +121,7 @@ constexpr double JOINT_MAX_US = 1500, JOINT_MAX_US_64 = 1000;
 // simulated, 106 so; of 1600 batches none gets another launch, two of 600 another order in it (backward 0.7 % slower, 0.3 %
 // faster).  (Cut lengths are searched with all units: simulated so, one of 1600 batches got a cut that cost 2 %.)
 constexpr int64_t JOINT_UNITS = 512;
+constexpr double BEYOND_STATIC_US = 25;  // what a pass has to gain for partial results beyond the static workspace, if not a tenth
 constexpr double BYTES_PER_US = 4e6;  // partial results, written and read
 struct CutCost {
   int slots;  // workgroups that run at a time
@@ -535,7 +536,49 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     const auto [cut, free_cut] = best_piece(sizes, cost_fwd, part_bytes(p->d) + FWD_STAT_BYTES, limits);
     more = more || free_cut.us < 0.9 * cut.us;
     p->us_fwd = cut.us;
-    const int64_t T = cut.piece;
+    int64_t T = cut.piece;
+    // That search takes a CU for one server.  Long pieces are worth a look at both forms of a workgroup, in both kernels.  By the
+    // search 128 units of 2032 tiles are 256 pieces, and 176 of 938 stay whole; 512 pieces, of which two whole ones share a CU, and
+    // 704 take 1.64 ms instead of 1.85 and 1.15 instead of 1.41 in the forward, and no longer in the backward.  (Not where units hold
+    // a few rows: four rows of each of five documents, 16/16 heads, gained 200 us of 1130 and lost 150 of 3900 in the backward, whose
+    // halves of padding read all keys.)
+    constexpr int64_t LONG_PIECE = 128;
+    const int64_t longest = ftiles.empty() ? 0 : ftiles[0].cost, units = int64_t(p->fwd_units.size());
+    const bool filled = std::all_of(ftiles.begin(), ftiles.end(), [&](const TileRef &t) { return p->slot_row[size_t(t.u.slot0 + 4 / t.u.hp * 32)] >= 0; });
+    if (filled && longest >= 2 * LONG_PIECE && 2 * units <= 4 * N_CU) {
+      struct Run {
+        double fwd, both;
+        size_t bytes;
+      };
+      auto run_of = [&](int64_t t) {
+        std::vector<FwdUnits> list;
+        std::vector<std::pair<double, int64_t>> dq;
+        int64_t parts = 0;
+        for (const auto &[tiles, n] : sizes) {
+          const int64_t k = t > 0 ? std::max<int64_t>(1, (tiles + t - 1) / t) : 1;
+          const double of_piece = double(tiles) / double(k);
+          list.push_back({of_piece, of_piece, n * k});
+          if (k > 1) parts += n * k;
+        }
+        std::stable_sort(list.begin(), list.end(), [](const FwdUnits &a, const FwdUnits &b) { return a.tiles > b.tiles; });
+        for (const FwdUnits &x : list) dq.push_back({dq_fixed + dq_per_tile * x.tiles, x.n});
+        Run r{fwd_run(list, p->d).us, 0.0, size_t(parts) * (part_bytes(p->d) + FWD_STAT_BYTES)};
+        if (parts > 0) r.fwd += cost_fwd.launch + double(r.bytes) / BYTES_PER_US;
+        r.both = r.fwd + makespan(dq, N_CU, 1e30, JOINT_UNITS);
+        if (parts > 0) r.both += cost_fwd.launch + double(r.bytes) / BYTES_PER_US;
+        return r;
+      };
+      Run best = run_of(T), beyond = best;
+      for (int64_t k = 2; k * units <= 4 * N_CU && longest >= k * LONG_PIECE; ++k) {
+        const int64_t t = (longest + k - 1) / k;
+        const Run r = run_of(t);
+        if (r.bytes <= limits[0] && r.both + BEYOND_STATIC_US < best.both) best = r, T = t;
+        if (r.bytes <= limits[1] && r.both < beyond.both) beyond = r;
+      }
+      p->pieces_lost = best.both - beyond.both > BEYOND_STATIC_US;
+      more = more || p->pieces_lost;
+      p->us_fwd = best.fwd;
+    }
     if (T > 0) {
       std::vector<TileRef> pieces;
       for (auto &t : ftiles) {
@@ -594,7 +637,8 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     const int slots = cost_dkv.slots;
     double mean = 0;
     for (int64_t s : wg_steps) mean += (cost_dkv.fixed + cost_dkv.per_step * double(s)) * hkv / slots;
-    if (!wg_steps.empty() && !p->fwd_units.empty() && mean < (p->d == 128 ? JOINT_MAX_US : JOINT_MAX_US_64)) {
+    const bool may_join = mean < (p->d == 128 ? JOINT_MAX_US : JOINT_MAX_US_64);
+    if (!wg_steps.empty() && !p->fwd_units.empty() && (may_join || p->pieces_lost || beyond_static)) {
       // groups of equal workgroups that follow each other in their list: (microseconds, how many, first entry of joint_order,
       // step from entry to entry)
       struct Group {
@@ -633,7 +677,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
                                   : 0.0;
       const double apart = makespan(dkv, slots / same, 1e30, JOINT_UNITS) + makespan(dq, N_CU / same, 1e30, JOINT_UNITS) + cost_dkv.launch;
       p->us_bwd = us_apart = apart + parts_us;
-      if (sum / slots < apart) {
+      if (may_join && sum / slots < apart) {
         std::vector<std::pair<double, int64_t>> all;
         auto span_of = [&](double at_most) {
           all.clear();
@@ -708,7 +752,7 @@ int build_plan(const ca_batch_desc *desc, ca_plan_t **out) {
     validate(desc);
     auto p = described(desc);
     // Where cutting units beyond the static workspace looks better by a tenth, or would save a backward launch worth it (the dQ parts
-    // take the place of the dK/dV parts inside, which needs two), both plans are
+    // take the place of the dK/dV parts inside, which needs two), or leaves room for two long forward pieces per CU, both plans are
     // made, and kept if the whole pass is better: the larger for callers that bring the workspace, the smaller inside it for all others.  (Forward + backward, 8/2 heads,
     // without and with the launch saved: 2048 rows with an 8K context 318 -> 266 us, 3072 rows 404 -> 356 us; simulated to gain 34 and
     // 38 us.  Below 25 us the larger workspace is not taken for it.)
@@ -717,7 +761,7 @@ int build_plan(const ca_batch_desc *desc, ca_plan_t **out) {
       auto large = described(desc);
       schedule(large.get(), true);
       const double inside = p->us_fwd + p->us_bwd, beyond = large->us_fwd + large->us_bwd;
-      if (p->us_bwd > 0 && large->us_bwd > 0 && ((more && beyond < 0.9 * inside) || (p->joint_lost && inside - beyond > 25))) {
+      if (p->us_bwd > 0 && large->us_bwd > 0 && ((more && beyond < 0.9 * inside) || ((p->joint_lost || p->pieces_lost) && inside - beyond > BEYOND_STATIC_US))) {
         large->within_static = std::move(p);
         p = std::move(large);
       }

@@ -8,6 +8,10 @@ from paper_2510_18121_amd import workloads as W
 @pytest.mark.parametrize("n,rows,keys,hq,hkv,d,pieces,halves,turns", [
     # 32 units of 256 tiles: 256 pieces, whose 512 halves share the CUs evenly
     (1, 256, 16384, 32, 8, 128, 256, 1, 1),
+    # 128 units of 2032 tiles: two whole pieces per CU beat two halves of one twice as long by more than their parts cost
+    (1, 1000, 130001, 32, 8, 128, 512, 0, 1),
+    # 176 of 938: fewer units than CUs, but too many to ignore that two share one
+    (2, 700, 60000, 32, 8, 128, 704, 0, 0),
     # head_dim 64 has three workgroups per CU and takes no turns
     (1, 256, 16384, 32, 8, 64, 256, 1, 0),
 ])
@@ -16,6 +20,14 @@ def test_lone_shards(n, rows, keys, hq, hkv, d, pieces, halves, turns):
     info = p.info()
     got = len(p.pieces()["fwd"]), info["forward_piece_halves"], info["forward_piece_turns"]
     assert got == (pieces, halves, turns)
+
+
+def test_parts_beyond_the_static_workspace_leave_a_plan_inside_it():
+    """Callers with the static workspace run the pieces that fit it."""
+    b = W.custom([130001], [(0, 129001, 1000)], 32, 8, 128)
+    p = B.ca_plan_host(b)
+    static = B.lib().ca_static_workspace_bytes()
+    assert p.workspace_bytes()[1] < static < p.workspace_bytes_split()[1]
 
 
 def test_units_of_unlike_length_take_no_turns():
