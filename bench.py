@@ -196,19 +196,17 @@ def main():
     kavg = {kk: sum(vv) / len(vv) for kk, vv in kern.items()}
     plan.profile_enable(False)
     # what the matrix pipes sustain on this device, right after the timed work (chip warm): the library's MFMA-only
-    # kernel (32x32x16 MFMAs) on N(0,1) bf16 operands, one wave per SIMD, three launches of about a quarter second
-    # each, the last one reported; then the same with an attention kernel's other per-MFMA work issued alongside
+    # kernel on N(0,1) bf16 operands, in the attention kernels' shape (16x16x32) and at their two waves per SIMD, three launches
+    # of about a quarter second each, the last one reported; then the same with the other work per MFMA issued alongside that the
+    # backward kernels and the forward kernel have
     sustained = sustained_side = None
     if not args.no_sustained_probe:
         from paper_2510_18121_amd import mfma_rate
         probe_clocks = EngineClockSampler()
         with probe_clocks:
-            sustained = mfma_rate.sustained_tflops("normal", 0, 1, device=dev)[-1]
-        sustained_side = mfma_rate.sustained_tflops("normal", 1, 1, device=dev)[-1]
-        # yardsticks: two waves per SIMD with side work of about level 1 (the dQ kernel's), one wave per SIMD with side work of
-        # about level 2 (the forward kernel's: an exponential per MFMA)
-        sustained_dq = mfma_rate.sustained_tflops("normal", 1, 2, device=dev)[-1]
-        sustained_fwd = mfma_rate.sustained_tflops("normal", 2, 1, device=dev)[-1]
+            sustained = mfma_rate.sustained_tflops("normal", 0, 2, device=dev, shape=16)[-1]
+        sustained_side = mfma_rate.sustained_tflops("normal", 1, 2, device=dev, shape=16)[-1]
+        sustained_fwd = mfma_rate.sustained_tflops("normal", 2, 2, device=dev, shape=16)[-1]
     if args.calibration_copy_mib > 0:
         src = torch.empty(args.calibration_copy_mib << 20, dtype=torch.uint8, device=dev).fill_(3)
         dst = torch.empty_like(src)
@@ -260,13 +258,14 @@ def main():
             "during_probe": probe_clocks.summary(), "with_side_work_tflops": sustained_side,
             "frac_with_side_work": bwd_main_tflops / sustained_side,
             "other_kernels": {
-                "ca_fwd_kernel": {"executed_tflops": fwd_tflops, "stream_one_wave_side_work_2_tflops": sustained_fwd,
+                "ca_fwd_kernel": {"executed_tflops": fwd_tflops, "stream_side_work_2_tflops": sustained_fwd,
                                   "frac": fwd_tflops / sustained_fwd},
-                "ca_bwd_dq_kernel": {"executed_tflops": dq_tflops, "stream_two_waves_side_work_1_tflops": sustained_dq,
-                                     "frac": dq_tflops / sustained_dq}},
-            "what": "ca_mfma_stream in this run after the timed steps: v_mfma_f32_32x32x16_bf16 back to back from "
-                    "registers, N(0,1) bf16 operands, one wave per SIMD on all CUs; with_side_work adds one 16-byte "
-                    "LDS read per lane and two multiply-adds per MFMA and one exponential per two MFMAs"}
+                "ca_bwd_dq_kernel": {"executed_tflops": dq_tflops, "stream_side_work_1_tflops": sustained_side,
+                                     "frac": dq_tflops / sustained_side}},
+            "what": "ca_mfma_stream16 in this run after the timed steps: v_mfma_f32_16x16x32_bf16 back to back from registers, "
+                    "N(0,1) bf16 operands, two waves per SIMD on all CUs; with_side_work and side_work_1 add one 16-byte LDS "
+                    "read per lane and two multiply-adds per two MFMAs and an exponential per four, side_work_2 four "
+                    "multiply-adds and an exponential per two and a read per four"}
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(args.workload)
     print(json.dumps(out), flush=True)

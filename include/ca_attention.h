@@ -203,8 +203,7 @@ int ca_profile_read(ca_plan_t *plan, float *out_ms);
 
 /*
  * ca_mfma_stream: calibration aid for the matrix-pipe roofline, not a step of the method.  Launches n_workgroups
- * workgroups of four waves; every wave issues n_mfma_per_wave v_mfma_f32_32x32x16_bf16 (the instruction the three
- * attention kernels are built on) back to back from registers, with no memory access in the loop.  Timed by the
+ * workgroups of four waves; every wave issues n_mfma_per_wave v_mfma_f32_32x32x16_bf16 back to back from registers, with no memory access in the loop.  Timed by the
  * caller over enough workgroups to fill the chip (HIP events on hip_stream around the call), it gives the rate the
  * matrix pipes sustain on this device for this kind of operand data and this many waves per SIMD:
  * n_workgroups * 4 * n_mfma_per_wave * 32768 flops per launch.
@@ -214,7 +213,7 @@ int ca_profile_read(ca_plan_t *plan, float *out_ms);
  *   n_mfma_per_wave : a non-negative multiple of 64.
  *   side_work : 0 = MFMAs only.  1 or 2 = every MFMA is followed by the other work an attention kernel issues per
  *              MFMA, results unused: one 16-byte LDS read per lane and 2 (4) fp32 multiply-adds, plus one
- *              exponential per two MFMAs (per MFMA): about the dK/dV (forward) kernel's ratio.  Uses 16 KiB of LDS.
+ *              exponential per two MFMAs (per MFMA).  Uses 16 KiB of LDS.
  *   sums     : device, fp32 [n_workgroups][256], written: per thread the sum of its 64 accumulator values (with
  *              all-ones operands exactly 256 * n_mfma_per_wave as long as that is below 2^24), so a caller can
  *              check that the instructions ran.
@@ -222,6 +221,14 @@ int ca_profile_read(ca_plan_t *plan, float *out_ms);
  */
 int ca_mfma_stream(const void *operands, int64_t n_mfma_per_wave, int32_t n_workgroups, int32_t side_work, float *sums,
                    void *hip_stream);
+/*
+ * ca_mfma_stream16: the same with v_mfma_f32_16x16x32_bf16, the instruction the three attention kernels are built on: 16384 flops
+ * per MFMA, and with all-ones operands sums of 128 * n_mfma_per_wave.  side_work 1: per two MFMAs one LDS read and 2
+ * multiply-adds, per four an exponential (about the dK/dV and dQ kernels' ratio at head_dim 128); 2: per two MFMAs 4 multiply-adds
+ * and an exponential, per four one LDS read (the forward kernel's).
+ */
+int ca_mfma_stream16(const void *operands, int64_t n_mfma_per_wave, int32_t n_workgroups, int32_t side_work, float *sums,
+                     void *hip_stream);
 
 /*
  * ca_xcd_map: which XCD (each of the 8 has an L2 of its own) every workgroup of a launch of n_workgroups workgroups of

@@ -79,7 +79,7 @@ def lib() -> ctypes.CDLL:
         i32, i64 = ctypes.c_int32, ctypes.c_int64
         L.ca_merge_partials.argtypes = [vp, i64, i32, vp, vp, i64, vp, vp, vp, vp, i32, i32, vp]
         L.ca_sum_partial_dq.argtypes = [vp, i64, i32, vp, i64, vp, i32, i32, vp]
-        L.ca_mfma_stream.argtypes = [vp, i64, i32, i32, vp, vp]
+        L.ca_mfma_stream.argtypes = L.ca_mfma_stream16.argtypes = [vp, i64, i32, i32, vp, vp]
         L.ca_xcd_map.argtypes = [i32, i32, vp, vp]
         L.ca_atomic_stream.argtypes = [vp, vp, i32, i32, i32, i32, i32, vp, vp]
         _lib = L
@@ -328,14 +328,17 @@ def ca_sum_partial_dq(part_rows, dq_part, dq, stream=None):
     _check(lib().ca_sum_partial_dq(_p(part_rows), n_rows, n_parts, _p(dq_part), tq, _p(dq), hq, d, _stream_ptr(stream)))
 
 
-def ca_mfma_stream(operands, n_mfma_per_wave, sums, side_work=0, stream=None):
-    """Back-to-back bf16 MFMAs from registers in sums.shape[0] workgroups (a calibration aid; see the header)."""
+def ca_mfma_stream(operands, n_mfma_per_wave, sums, side_work=0, stream=None, shape=32):
+    """Back-to-back bf16 MFMAs from registers in sums.shape[0] workgroups (a calibration aid; see the header); shape 32: 32x32x16,
+    16: 16x16x32 (ca_mfma_stream16)."""
     import torch
     _expect(operands, (16, 256, 8), torch.bfloat16, "operands")
     n_wg = sums.shape[0]
     _expect(sums, (n_wg, 256), torch.float32, "sums")
-    _check(lib().ca_mfma_stream(_p(operands), int(n_mfma_per_wave), n_wg, int(side_work), _p(sums),
-                                _stream_ptr(stream)))
+    if shape not in (16, 32):
+        raise ValueError(f"shape {shape}: 16 or 32")
+    stream_of = lib().ca_mfma_stream if shape == 32 else lib().ca_mfma_stream16
+    _check(stream_of(_p(operands), int(n_mfma_per_wave), n_wg, int(side_work), _p(sums), _stream_ptr(stream)))
 
 
 def ca_xcd_map(n_workgroups, threads_per_workgroup=256, device="cuda", stream=None):

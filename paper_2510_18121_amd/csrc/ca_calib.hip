@@ -1,6 +1,6 @@
-// Calibration aid for the matrix-pipe roofline (not a step of the method): a kernel that does nothing but issue
-// v_mfma_f32_32x32x16_bf16 back to back from registers, the instruction all three attention kernels are built on.
-// Timed over the whole chip it gives the rate the matrix pipes sustain on a given kind of operand data (the chip
+// Calibration aid for the matrix-pipe roofline (not a step of the method): kernels that do nothing but issue
+// v_mfma_f32_32x32x16_bf16, or v_mfma_f32_16x16x32_bf16, the instruction all three attention kernels are built on, back to back
+// from registers.  Timed over the whole chip it gives the rate the matrix pipes sustain on a given kind of operand data (the chip
 // lowers its clock under such load, by an amount that depends on the data), which is what the attention kernels'
 // executed flop rates can be held against besides the published peak.
 #include <hip/hip_runtime.h>
@@ -74,6 +74,65 @@ __global__ __launch_bounds__(256) void ca_mfma_stream_kernel(const u32x4 *__rest
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < 16; ++i) s += (c[0][i] + c[1][i]) + (c[2][i] + c[3][i]);
+  sums[size_t(blockIdx.x) * 256 + threadIdx.x] = s;
+}
+
+// The same with v_mfma_f32_16x16x32_bf16, half the flops: MFMA (r, j) is chain[j & 3] += A[j] x B[(j + r) & 7].  The other work
+// per flop is an attention kernel's (head_dim 128).  SIDE = 1: per two MFMAs one 16-byte LDS read per lane and 2 multiply-adds, per
+// four an exponential (dK/dV and dQ, whose fragments feed two MFMAs).  SIDE = 2: per two MFMAs 4 multiply-adds and an exponential,
+// per four one LDS read (forward, whose fragments feed four).
+template <int SIDE>
+__global__ __launch_bounds__(256) void ca_mfma_stream16_kernel(const u32x4 *__restrict__ operands, int n_rounds,
+                                                               float *__restrict__ sums) {
+  extern __shared__ u32x4 calib_lds[];
+  bf16x8 a[CALIB_FRAGS], b[CALIB_FRAGS];
+#pragma unroll
+  for (int i = 0; i < CALIB_FRAGS; ++i) {
+    a[i] = __builtin_bit_cast(bf16x8, operands[(2 * i) * 256 + threadIdx.x]);
+    b[i] = __builtin_bit_cast(bf16x8, operands[(2 * i + 1) * 256 + threadIdx.x]);
+    pin(a[i]), pin(b[i]);
+  }
+  uint32_t lds_addr = 0;
+  float v[8], e[4];
+  u32x4 t[4];
+  if (SIDE > 0) {
+#pragma unroll
+    for (int i = 0; i < CALIB_LDS_BYTES / 16 / 256; ++i) calib_lds[i * 256 + threadIdx.x] = __builtin_bit_cast(u32x4, a[i]);
+    __syncthreads();
+    lds_addr = uint32_t(size_t(&calib_lds[0])) + 16 * threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = float(a[i][0]);
+  }
+  f32x4 c[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) c[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int it = 0; it < n_rounds; ++it) {
+#pragma unroll
+    for (int r = 0; r < CALIB_FRAGS; ++r)
+#pragma unroll
+      for (int j = 0; j < CALIB_FRAGS; ++j) {
+        c[j & 3] = mfma16(a[j], b[(j + r) & 7], c[j & 3]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (SIDE > 0 && (j & 1)) {
+          constexpr int READS = SIDE == 1 ? 4 : 2;  // per 8 MFMAs, all waited for behind the last
+          if (SIDE == 1 || (j & 3) == 3)
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(t[j * READS / 8]) : "v"(lds_addr), "n"(j * READS / 8 * 4096));
+#pragma unroll
+          for (int l = 0; l < 2 * SIDE; ++l)
+            asm volatile("v_fma_f32 %0, %0, %1, %2" : "+v"(v[(j + l) & 7]) : "v"(0.75f), "v"(0.25f));
+          // its result is not read by the vector instructions that follow it directly
+          if (SIDE == 2 || (j & 3) == 3) asm volatile("v_exp_f32 %0, %1" : "=v"(e[j >> 1]) : "v"(v[(j + 4) & 7]));
+          if (j == 7) {
+            if (SIDE == 1) asm volatile("s_waitcnt lgkmcnt(0)" ::"v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]));
+            else asm volatile("s_waitcnt lgkmcnt(0)" ::"v"(t[0]), "v"(t[1]));
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+  }
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s += (c[0][i] + c[1][i]) + (c[2][i] + c[3][i]);
   sums[size_t(blockIdx.x) * 256 + threadIdx.x] = s;
 }
 
@@ -177,9 +236,10 @@ extern "C" int ca_atomic_stream(const void *operands, float *tiles, int32_t n_ti
   return CA_OK;
 }
 
-extern "C" int ca_mfma_stream(const void *operands, int64_t n_mfma_per_wave, int32_t n_workgroups, int32_t side_work,
-                              float *sums, void *hip_stream) {
-  using namespace ca;
+namespace ca {
+// shape: 32 (32x32x16 MFMAs) or 16 (16x16x32)
+static int mfma_stream(int shape, const void *operands, int64_t n_mfma_per_wave, int32_t n_workgroups, int32_t side_work,
+                       float *sums, void *hip_stream) {
   std::ostringstream os;
   if (n_mfma_per_wave < 0 || n_mfma_per_wave % CALIB_ROUND != 0 || n_mfma_per_wave / CALIB_ROUND > 0x7fffffff) {
     os << "n_mfma_per_wave " << n_mfma_per_wave << ": must be a non-negative multiple of " << CALIB_ROUND
@@ -201,9 +261,13 @@ extern "C" int ca_mfma_stream(const void *operands, int64_t n_mfma_per_wave, int
   const hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const auto *ops = static_cast<const u32x4 *>(operands);
   const int n_rounds = int(n_mfma_per_wave / CALIB_ROUND);
-  if (side_work == 0) ca_mfma_stream_kernel<0><<<grid, 256, 0, st>>>(ops, n_rounds, sums);
-  else if (side_work == 1) ca_mfma_stream_kernel<1><<<grid, 256, CALIB_LDS_BYTES, st>>>(ops, n_rounds, sums);
-  else ca_mfma_stream_kernel<2><<<grid, 256, CALIB_LDS_BYTES, st>>>(ops, n_rounds, sums);
+  auto *const kernel = shape == 32 ? (side_work == 0   ? ca_mfma_stream_kernel<0>
+                                      : side_work == 1 ? ca_mfma_stream_kernel<1>
+                                                       : ca_mfma_stream_kernel<2>)
+                                   : (side_work == 0   ? ca_mfma_stream16_kernel<0>
+                                      : side_work == 1 ? ca_mfma_stream16_kernel<1>
+                                                       : ca_mfma_stream16_kernel<2>);
+  kernel<<<grid, 256, side_work == 0 ? 0 : CALIB_LDS_BYTES, st>>>(ops, n_rounds, sums);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     os << "mfma stream launch: " << hipGetErrorName(e) << " (" << hipGetErrorString(e) << ")";
@@ -211,4 +275,15 @@ extern "C" int ca_mfma_stream(const void *operands, int64_t n_mfma_per_wave, int
     return CA_ERR_HIP;
   }
   return CA_OK;
+}
+}  // namespace ca
+
+extern "C" int ca_mfma_stream(const void *operands, int64_t n_mfma_per_wave, int32_t n_workgroups, int32_t side_work,
+                              float *sums, void *hip_stream) {
+  return ca::mfma_stream(32, operands, n_mfma_per_wave, n_workgroups, side_work, sums, hip_stream);
+}
+
+extern "C" int ca_mfma_stream16(const void *operands, int64_t n_mfma_per_wave, int32_t n_workgroups, int32_t side_work,
+                                float *sums, void *hip_stream) {
+  return ca::mfma_stream(16, operands, n_mfma_per_wave, n_workgroups, side_work, sums, hip_stream);
 }

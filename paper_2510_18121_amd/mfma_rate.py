@@ -14,7 +14,7 @@ import math
 
 from . import binding as B
 
-FLOPS_PER_MFMA = 2 * 32 * 32 * 16
+FLOPS_PER_MFMA = 2 * 32 * 32 * 16  # of a 32x32x16 MFMA, which takes 32 cycles; a 16x16x32 one has and takes half
 KINDS = ("zeros", "ones", "normal", "softmax")
 
 
@@ -40,27 +40,28 @@ def make_operands(kind: str, device="cuda", seed: int = 5):
 
 
 def sustained_tflops(kind: str = "normal", side_work: int = 0, workgroups_per_cu: int = 1, launch_ms: float = 250.0,
-                     launches: int = 3, device="cuda"):
+                     launches: int = 3, device="cuda", shape: int = 32):
     """TFLOP/s of each of `launches` back-to-back launches of about launch_ms each (the first ones run while the
     clock is still settling; take the last as the sustained figure).  workgroups_per_cu = 1 puts one wave on every
-    SIMD (the dK/dV kernel's occupancy), 2 two (the forward and dQ kernels'); side_work as in `ca_mfma_stream`."""
+    SIMD, 2 two (the occupancy of all three attention kernels at head_dim 128); shape 32 issues 32x32x16 MFMAs, 16 the attention
+    kernels' 16x16x32; side_work as in `ca_mfma_stream` and `ca_mfma_stream16`."""
     import torch
     ops = make_operands(kind, device)
     n_cu = torch.cuda.get_device_properties(device).multi_processor_count
     n_wg = workgroups_per_cu * n_cu
     sums = torch.empty((n_wg, 256), dtype=torch.float32, device=device)
-    # a SIMD issues an MFMA every 32 cycles at best; assume 1.5 GHz to size the launch, rounded to whole rounds
-    n_mfma = max(64, int(launch_ms * 1e-3 * 1.5e9 / 32 / workgroups_per_cu) // 64 * 64)
-    B.ca_mfma_stream(ops, 64, sums, side_work)  # code object loaded, clocks woken
+    # a SIMD issues an MFMA every 32 (16) cycles at best; assume 1.5 GHz to size the launch, rounded to whole rounds
+    n_mfma = max(64, int(launch_ms * 1e-3 * 1.5e9 / shape / workgroups_per_cu) // 64 * 64)
+    B.ca_mfma_stream(ops, 64, sums, side_work, shape=shape)  # code object loaded, clocks woken
     torch.cuda.synchronize(device)
     out = []
     for _ in range(launches):
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
-        B.ca_mfma_stream(ops, n_mfma, sums, side_work)
+        B.ca_mfma_stream(ops, n_mfma, sums, side_work, shape=shape)
         e1.record()
         e1.synchronize()
-        out.append(n_wg * 4 * n_mfma * FLOPS_PER_MFMA / (e0.elapsed_time(e1) * 1e-3) / 1e12)
+        out.append(n_wg * 4 * n_mfma * FLOPS_PER_MFMA * shape / 32 / (e0.elapsed_time(e1) * 1e-3) / 1e12)
     return out
 
 
@@ -71,6 +72,7 @@ def main():
     ap.add_argument("--side-work", type=int, default=0, choices=(0, 1, 2))
     ap.add_argument("--workgroups-per-cu", type=int, default=1)
     ap.add_argument("--launches", type=int, default=5)
+    ap.add_argument("--shape", type=int, default=32, choices=(16, 32), help="32: 32x32x16 MFMAs, 16: 16x16x32")
     args = ap.parse_args()
     table = (("normal", 0, 1), ("normal", 0, 2), ("normal", 0, 8), ("normal", 1, 1), ("normal", 1, 2), ("normal", 2, 1),
              ("normal", 2, 2), ("zeros", 0, 1), ("ones", 0, 1), ("softmax", 0, 1), ("normal", 0, 1))
@@ -78,7 +80,7 @@ def main():
         table = ((args.kind, args.side_work, args.workgroups_per_cu),)
     print(f"operands  side_work  workgroups/CU   TFLOP/s of {args.launches} back-to-back launches of about 0.25 s")
     for kind, side, wpc in table:
-        r = sustained_tflops(kind, side, wpc, launches=args.launches)
+        r = sustained_tflops(kind, side, wpc, launches=args.launches, shape=args.shape)
         print(f"{kind:8s}  {side:9d}  {wpc:13d}   " + "  ".join(f"{x:7.1f}" for x in r), flush=True)
 
 

@@ -17,6 +17,18 @@ def test_all_ones_operands_give_the_exact_count():
         assert torch.equal(sums, torch.full_like(sums, 256.0 * n_mfma))
 
 
+def test_16x16_stream_gives_the_exact_count():
+    ops = M.make_operands("ones")
+    for n_mfma, n_wg, side in ((64, 3, 0), (640, 17, 0), (128, 5, 1), (192, 4, 2)):
+        sums = torch.full((n_wg, 256), -1.0, dtype=torch.float32, device="cuda")
+        B.ca_mfma_stream(ops, n_mfma, sums, side, shape=16)
+        torch.cuda.synchronize()
+        # every MFMA adds 32 to each of the 4 values a lane holds of its chain
+        assert torch.equal(sums, torch.full_like(sums, 128.0 * n_mfma))
+    with pytest.raises(ValueError):
+        B.ca_mfma_stream(ops, 64, sums, shape=8)
+
+
 def test_products_follow_the_documented_pairing():
     # A fragments all ones, B fragment i filled with i+1: MFMA (r, j) adds 16 (i+1) with i = (j + r) mod 8, and over
     # the 64 MFMAs of a round every chain meets every B fragment twice
@@ -45,6 +57,6 @@ def test_zero_work_and_bad_arguments():
 
 
 def test_sustained_rate_is_plausible():
-    for side, wpc in ((0, 1), (1, 2)):
-        r = M.sustained_tflops("normal", side, wpc, launch_ms=40.0, launches=2)
+    for side, wpc, shape in ((0, 1, 32), (1, 2, 32), (0, 2, 16), (1, 2, 16), (2, 2, 16)):
+        r = M.sustained_tflops("normal", side, wpc, launch_ms=40.0, launches=2, shape=shape)
         assert all(200.0 < x < 2600.0 for x in r), r
