@@ -624,10 +624,10 @@ __global__ __launch_bounds__(256, 2) void ca_bwd_dkv_kernel(const BwdUnit *__res
 
 // dK/dV units and dQ half units (workgroups of 4 groups of 32 rows) in one launch, longest first.  For batches too small to
 // fill the chip with either kernel: what a launch takes there is mostly its fixed part, and the dQ work finds CUs that the
-// dK/dV units leave idle.  Measured, forward + backward, two launches against one: 70 -> 51 us (384 rows, 8/1 heads,
-// head_dim 128), 48 -> 38 us (1.5K tokens, 4/2 heads, head_dim 64), 1006 -> 806 us (12K tokens of long documents, 8/2
-// heads, where the two kernels' last units leave CUs idle one after the other); on batches that fill the chip the half
-// units cost 8 to 10 % of the pass, so the planner decides by a simulation of both.
+// dK/dV units leave idle.  Measured, backward, two launches against one: 49 -> 30 us (384 rows, 8/1 heads, head_dim 128), 31 -> 22 us
+// (1.5K tokens, 4/2 heads, head_dim 64), 356 -> 315 us (16K tokens of documents of about 2K, 8/2 heads, where the two kernels' last
+// units leave CUs idle one after the other).  Batches that fill the chip gain 1 or 2 % or lose as much, 4 % at head_dim 64: the
+// planner decides by a simulation of both and a limit (JOINT_MAX_US).
 struct JointArgs {
   const int32_t *order;  // what each workgroup does (ca_plan::joint_order), or nullptr
   const BwdUnit *units;

@@ -19,8 +19,9 @@
 // One wave per SIMD with 384 registers, 32x32 MFMAs and a software pipeline across blocks written out slot by slot, against this
 // (32/8 heads, head_dim 128): 52.0 -> 47.9 ms (128K tokens of long and short documents), 2.55 -> 2.29 ms (64K tokens of documents
 // of about 2K), 9.54 -> 8.78 ms (64/8 heads); with halves 45 -> 24 us (32 units of 16 tiles), 16.2 -> 10.9 us (1.5K tokens, 4/2
-// heads, head_dim 64).  Slower: 256 pieces of 32 tiles 66 -> 69 us, 256 of 1016 1.64 -> 1.93 ms, where the matrix pipe is neither
-// short of power nor of waves.
+// heads, head_dim 64).  Slower, by up to 4 %: lists short enough that the clock stays up (256 pieces of 32 tiles, 66 -> 67 to 69 us at
+// 2.2 GHz).  It is not the fetches, for which a wave waits 1 % of a tile: units of eight waves with four stages took the same time, as
+// did fragments further ahead and the exponentials spread over both blocks' MFMAs; K and V prefetched to L2 cost 9 %.
 //
 // The fast path exponentiates against the maximum of the first keys (see there) and masks on the diagonal; tile 0 of a document's
 // first rows and units in which that maximum was outgrown take a general path with lazy rescaling of the accumulators.  The

@@ -63,9 +63,9 @@ struct BwdUnit {  // one (KV tile, KV head)
 // planner makes a second list of units, in which long ones are cut into pieces along the loop they run (the keys of a
 // forward / dQ unit, the query blocks of a dK/dV unit).  A piece writes its fp32 accumulators to the workspace, and
 // ca_combine_* add the pieces of a unit up, in order (no atomics: bit-reproducible), and store the results.  Measured,
-// whole units against pieces: forward of that lone shard (32/8 heads, head_dim 128) 333 -> 75 us; forward + backward of
-// 1000 rows with a 130K context 10.4 -> 8.1 ms; of the 4K-token batch 592 -> 500 us; of documents of 512 and 1024 tokens
-// (4/2 heads, head_dim 64) 92 -> 48 us.
+// whole units against pieces: forward of that lone shard (32/8 heads, head_dim 128) 271 -> 81 us; forward + backward of
+// 1000 rows with a 130K context 9.8 -> 7.3 ms; of the 4K-token batch 597 -> 395 us; of documents of 512 and 1024 tokens
+// (4/2 heads, head_dim 64) 85 -> 34 us.
 struct CombineUnit {
   int32_t part0, n_parts;  // blocks of partial results of the unit
   // forward / dQ unit: first slot, first query head, hp.   dK/dV unit: first packed KV row, valid keys, KV head.

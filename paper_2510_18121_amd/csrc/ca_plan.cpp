@@ -103,18 +103,21 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // simulated here (32 CUs stand for 256 where every unit comes once for each of 8 heads).  Cutting every unit longer than T
 // steps into equal pieces evens the load out and costs a `fixed` per piece, the partial results (written by the pieces,
 // read once more to be added up) and another launch.  The T with the shortest total is taken, if it gains a tenth: at
-// 4K tokens of 1K-token documents (32/8 heads) the simulation gives 362 us for the dK/dV kernel's 256 whole units (measured
-// 332) and 199 us for 472 units and pieces of at most 64 steps (measured 232, and 10 to add the pieces up): good enough to rank
-// cuts by, not to predict what one gains.
+// 4K tokens of 1K-token documents (32/8 heads) the simulation gives 340 us for the dK/dV kernel's 256 whole units (measured
+// 353) and 201 us for 472 units and pieces of at most 66 steps and their sums (measured 164 and 10): good enough to rank cuts by, not
+// to predict what one gains.
 // The figures are microseconds measured on MI355X.  Two or three workgroups share a CU and its throughput: a step takes a forward
 // or dK/dV workgroup about as long alone on a CU as the CU takes per step of several, so a CU counts as one server at that pace
-// (head_dim 128, per step alone / of two: forward 1.8 / 1.8, dK/dV 1.75 / 1.6; at 64 of three: 1.0 and 0.85).  The fixed part is what
-// a unit spends around its steps (descriptor, row indices, fragments, first tiles, drain, results) and another workgroup does not
-// hide; partial results move at about 4 TB/s.
-// Batches with more dK/dV work than this per CU run two launches.  One launch against two, forward + backward at head_dim 128: 499 ->
-// 459 us (4K tokens of documents of about 1K, 0.2 ms of dK/dV work), 2250 -> 2200 (256 rows in 16 windows of 8K keys, 1.0 ms); beyond,
-// lone shards lose (1000 rows with a 130K context, 3.2 ms: 7.72 -> 8.0 ms; 64-row shards with contexts, 2.8 ms: 5.33 -> 5.40: half units
-// read K and V twice as often) and packed documents gain 2 % (64K tokens, 4.4 ms).  At 64 the 16K-token batch of 0.2 ms loses 1 %.
+// (head_dim 128, per step alone / of two: forward 1.8 / 1.8, dK/dV 1.75 / 1.6; at 64 of three: 1.0 and 0.85).  (The dK/dV kernel at
+// 64 counts as two servers per CU, each at half that pace: 1.75 per step.)  The fixed part is what a unit spends around its steps
+// (descriptor, row indices, fragments, first tiles, drain, results) and another workgroup does not hide; partial results move at
+// about 4 TB/s.
+// Batches with more dK/dV work than this per CU run two launches.  Backward in two launches against one, documents of 1K to 4K on
+// average (dK/dV work per CU), head_dim 128: 215 -> 165 us (4K tokens, 32/8 heads; 0.08 ms), 637 -> 503 (8K; 0.27), 1345 -> 1204 (16K;
+// 0.65), 2281 -> 2235 (32K; 1.15), 4322 -> 4250 (64K, 16/16; 2.4).  Lone shards, whose half units read K and V twice as often, lose:
+// 710 -> 719 us (1000 rows with a 32K context, 16/4; 0.45), 5.33 -> 5.40 ms (64-row shards with contexts; 2.8), 7.72 -> 8.0 ms (1000
+// rows with 130K; 3.2).  The line lies where the one's gain is down to the other's loss.  Head_dim 64: 83 -> 60 us (4K, 16/16; 0.03
+// ms), 412 -> 399 (16K; 0.21), 1350 -> 1335 (32K, 32/8; 0.62), 1236 -> 1205 (64K, 8/2; 0.58), 2504 -> 2605 (64K, 16/16; 1.3).
 constexpr double JOINT_MAX_US = 1500, JOINT_MAX_US_64 = 1000;
 // The choice between one backward launch and two simulates lists of thousands of units, at 20 to 40 ns each more than the rest
 // of planning takes: ca_plan_host for 37K tokens in lone 860-row shards (8/1 heads) 65 us without it, 192 with all units
