@@ -16,7 +16,7 @@
 //   joint: both kinds of workgroup in one launch, for batches that fill the chip with neither.
 //   combine: adds up the fp32 partial results of units that the planner cut into pieces, in order, and stores them.
 // All products are v_mfma_f32_16x16x32_bf16.  On N(0,1) operands the chip's power limit, not the matrix pipe, sets the rate, and
-// this shape costs less energy per flop than 32x32x16 (alone 2066 against 1763 TFLOP/s).  Its price is twice the MFMA
+// this shape costs less energy per flop than 32x32x16 (alone 1928 against 1741 TFLOP/s).  Its price is twice the MFMA
 // instructions, each about 9 cycles of the vector issue port (probe; an exponential 9, other vector instructions 4): 870 port
 // cycles per 1024 matrix cycles in the dK/dV kernel, 726 per 768 in the dQ kernel.  32x32x16 -> 16x16x32 with everything else
 // alike, 128K tokens of long and short documents in shuffled shards (32/8 heads, head_dim 128): dK/dV kernel 108.0 -> 104.2 ms,

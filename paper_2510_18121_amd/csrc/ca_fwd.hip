@@ -15,7 +15,7 @@
 // K and V tiles of 64 keys go from global memory straight into swizzled LDS tiles (global_load_lds).  Q fragments (64 registers at
 // head_dim 128, 64 rows) and accumulators (128) stay in registers, one block of scores takes 32 more: within 256 two workgroups
 // share a CU (three at head_dim 64), drift apart and fill each other's waits.  What bounds the kernel is the power limit: on N(0,1)
-// data the 16x16 shape costs less energy per flop than 32x32 (alone 2066 against 1763 TFLOP/s), at twice the issue slots.
+// data the 16x16 shape costs less energy per flop than 32x32 (alone 1928 against 1741 TFLOP/s), at twice the issue slots.
 // One wave per SIMD with 384 registers, 32x32 MFMAs and a software pipeline across blocks written out slot by slot, against this
 // (32/8 heads, head_dim 128): 52.0 -> 47.9 ms (128K tokens of long and short documents), 2.55 -> 2.29 ms (64K tokens of documents
 // of about 2K), 9.54 -> 8.78 ms (64/8 heads); with halves 45 -> 24 us (32 units of 16 tiles), 16.2 -> 10.9 us (1.5K tokens, 4/2

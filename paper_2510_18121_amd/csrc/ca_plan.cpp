@@ -529,8 +529,8 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     }
   }
   {
-    // the list in which long forward / dQ units are cut along their keys (one list for both kernels: per step 1.7 and 2.6
-    // us at head_dim 128, the mean stands for both)
+    // the list in which long forward / dQ units are cut along their keys (one list for both kernels: per step 1.5 to
+    // 2.05 and 2.4 us at head_dim 128, for which 1.9 stands)
     std::vector<std::pair<int64_t, int64_t>> sizes;
     for (auto &t : ftiles) {
       if (!sizes.empty() && sizes.back().first == t.cost) sizes.back().second += hq / t.u.hp;
