@@ -293,7 +293,7 @@ int64_t ca_plan_fwd_units(const ca_plan_t *plan, int32_t *units);
 int64_t ca_plan_bwd_units(const ca_plan_t *plan, int32_t *units);
 /* The lists the calls run when they cut units into pieces (ca_plan_workspace_bytes_split); empty where nothing is cut.
  *  fwd_pieces : [n][8]  = the 5 fields above (kv row and keys of the piece's window), document position of the window's
- *                         first key, block of partial results (-1: a whole unit), 0
+ *                         first key, block of partial results (-1: a whole unit), slots of the unit that hold rows
  *  bwd_pieces : [n][10] = the 10 fields above (slots of the piece's query blocks; follow = -1 - block of partial results,
  *                         not negative in a whole unit); *n_workgroups (may be NULL): leading units that are one
  *                         workgroup each

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void ca_fwd_kernel(const FwdU
   const FwdUnit u = units[at_unit];
   // A half of padding has nothing to store.  (Of one to a few rows per document it is every second one: 111 -> 92 us for 2 rows with 84K keys,
   // 32/8 heads, 109 -> 92 for 13 rows with 43K, 16/16, 1280 -> 918 for five times 4 rows with 126K, 16/16.)
-  if (HALVES && slot_row[u.slot0 + ((W * half) >> __builtin_ctz(u.hp)) * 32] < 0) return;
+  if (HALVES && ((W * half) >> __builtin_ctz(u.hp)) * 32 >= u.rows) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hk = __builtin_amdgcn_readfirstlane(u.head / (Hq / Hkv));  // (uniform, for scalar K/V addresses)
   // (wave, group of 32) -> 32-slot group and query head inside the unit: pair 2 wave + x takes slots 32 (pair / hp) ..
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void ca_fwd_kernel(const FwdU
   const int wmin = slot_pos[u.slot0 + (pair0 >> hp_lg) * 32] - u.key0;
   const int wmin64 = slot_pos[u.slot0 + ((pair0 & ~1) >> hp_lg) * 32] - u.key0;
   // (a wave without a row, which padding is behind all rows, multiplies nothing)
-  const bool has_rows = slot_row[u.slot0 + ((pair0 & ~1) >> hp_lg) * 32] >= 0;
+  const bool has_rows = ((pair0 & ~1) >> hp_lg) * 32 < u.rows;
   const int wmax64 = has_rows ? slot_pos[u.slot0 + ((pair0 | 1) >> hp_lg) * 32 + 31] - u.key0 : -1;
   uint32_t koff, voff;  // per-lane LDS read addresses into the current stage: natural reads of K, transposing reads of V
   {

@@ -34,7 +34,7 @@ struct FwdUnit {
   // accumulators, to block `part` of the workspace's partial results; -1 in a unit that attends all its keys.
   int32_t key0;
   int32_t part;
-  int32_t reserved;
+  int32_t rows;  // slots of the unit that hold rows (padding is behind them)
 };
 constexpr int FWD_UNIT_INTS = 5;  // leading fields reported by ca_plan_fwd_units
 

@@ -350,12 +350,12 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     for (; a + FWD_BM <= s1; a += FWD_BM) {
       if (p->slot_row[a] < 0) break;  // pure padding
       int32_t n_keys = p->slot_pos[a + FWD_BM - 1] + 1;
-      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, 1, 0, -1, 0}});
+      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, 1, 0, -1, int32_t(std::min<int64_t>(FWD_BM, s0 + n_rows - a))}});
     }
     for (; a < s1; a += sub) {
       if (p->slot_row[a] < 0) break;  // pure padding
       int32_t n_keys = p->slot_pos[a + sub - 1] + 1;
-      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, int32_t(hp), 0, -1, 0}});
+      ftiles.push_back({(n_keys + FWD_BN - 1) / FWD_BN, {int32_t(a), kv_row0, n_keys, 0, int32_t(hp), 0, -1, int32_t(std::min<int64_t>(sub, s0 + n_rows - a))}});
     }
     // backward KV tiles: every resident key of the document.  Keys beyond the last query position get a
     // unit without query blocks, which writes their zero gradient.
@@ -547,7 +547,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     // halves of padding read all keys.)
     constexpr int64_t LONG_PIECE = 128;
     const int64_t longest = ftiles.empty() ? 0 : ftiles[0].cost, units = int64_t(p->fwd_units.size());
-    const bool filled = std::all_of(ftiles.begin(), ftiles.end(), [&](const TileRef &t) { return p->slot_row[size_t(t.u.slot0 + 4 / t.u.hp * 32)] >= 0; });
+    const bool filled = std::all_of(ftiles.begin(), ftiles.end(), [&](const TileRef &t) { return t.u.rows > 4 / t.u.hp * 32; });
     if (filled && longest >= 2 * LONG_PIECE && 2 * units <= 4 * N_CU) {
       struct Run {
         double fwd, both;

@@ -37,3 +37,14 @@ def test_units_of_unlike_length_take_no_turns():
     assert info["n_fwd_units"] == 512 and info["forward_turns"] == 0
     info = B.ca_plan_host(W.custom([1280] * 16, [(i, 1024, 256) for i in range(16)], 32, 8, 128)).info()
     assert info["n_fwd_units"] == 512 and info["forward_turns"] == 1
+
+
+@pytest.mark.parametrize("hq,hkv,shards", [(3, 3, [(5990, 5)]), (4, 1, [(4000, 70), (3900, 33)]), (16, 2, [(3000, 300), (10, 290)])])
+def test_units_know_how_many_of_their_slots_hold_rows(hq, hkv, shards):
+    """The forward kernel leaves out halves and waves behind a unit's last row."""
+    p = B.ca_plan_host(W.custom([a + n for a, n in shards], [(i, a, n) for i, (a, n) in enumerate(shards)], hq, hkv, 128))
+    row, units = p.rows()[0], p.pieces()["fwd"].tolist()
+    assert units
+    for slot0, _, _, _, hp, _, _, rows in units:
+        held = row[slot0:slot0 + 256 // hp] >= 0
+        assert rows == held.sum() > 0 and held[:rows].all()
