@@ -183,7 +183,9 @@ double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_
 // Workgroups of equal length of which a CU gets two share it evenly only if they take turns at having priority (see the kernel).
 // Without and with that: 1705 -> 1630 us (512 pieces of 508 tiles), 1900 -> 1858 (halves of 256 pieces of 1016), 74.1 -> 72.2 (halves of
 // 256 pieces of 32).  In a list of unequal ones the longest are the oldest, and better off served first; with more than two per CU
-// there is no tail to even out (halves of 384 pieces of 22 tiles: 79 -> 89 us).
+// there is no tail to even out (halves of 384 pieces of 22 tiles: 79 -> 89 us).  A turn is two to three tiles: workgroups of less than a
+// few turns only pay for the clock.
+constexpr double MIN_TURN_TILES = 12;
 struct FwdUnits {
   double tiles, tiles_half;  // of a unit, and of its first half
   int64_t n;
@@ -198,7 +200,7 @@ FwdRun fwd_run(const std::vector<FwdUnits> &list, int d) {
   int64_t units = 0;
   for (const FwdUnits &u : list) units += u.n;
   const bool d128 = d == 128, lone = units <= N_CU, equal = list.back().tiles >= 0.9 * list.front().tiles;
-  auto turns = [&](int64_t workgroups) { return d128 && equal && workgroups > N_CU && workgroups <= 2 * N_CU; };
+  auto turns = [&](int64_t workgroups) { return d128 && equal && workgroups > N_CU && workgroups <= 2 * N_CU && list.back().tiles >= MIN_TURN_TILES; };
   const bool whole_turns = turns(units), half_turns = turns(2 * units);
   const double fixed = d128 ? 8.0 : 5.0, per = whole_turns ? 1.5 : d128 ? (lone ? 2.05 : 1.78) : lone ? 1.15 : 1.0;
   const double fixed_half = d128 ? 4.0 : 2.5, per_half = half_turns ? 0.87 : d128 ? 0.96 : 0.53;

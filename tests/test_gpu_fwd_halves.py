@@ -117,7 +117,7 @@ def test_whom_a_non_finite_value_reaches_does_not_depend_on_the_form(d, kind):
 
 def test_taking_turns_does_not_change_results():
     """512 units of equal length, two per CU, which take turns at having priority, against the same among 1632 that do not."""
-    small, large = batches([500] * 16, [(i, 244, 256) for i in range(16)], 32, 8, 128)
+    small, large = batches([1280] * 16, [(i, 1024, 256) for i in range(16)], 32, 8, 128)
     q, k, v, _ = W.make_tensors(large, DEV)
     nq, nk, results = small.total_q, small.total_kv, []
     for b, (qq, kk, vv) in ((large, (q, k, v)), (small, (q[:nq].contiguous(), k[:nk].contiguous(), v[:nk].contiguous()))):
