@@ -221,12 +221,14 @@ def main():
     clock_mhz = getattr(props, "clock_rate", 0) / 1e3 or clocks.max_mhz or 0.0
     # 4096 dense bf16 flops per clock per CU; None when neither source reports the engine clock
     peak_from_device = props.multi_processor_count * 4096 * clock_mhz * 1e6 / 1e12 if clock_mhz > 0 else None
-    # the dK/dV kernel executes 4 of the backward's contractions (S, dP, dV, dK): 8*D*Hq*pairs flops
-    dkv_flops = fl["bwd"] * 0.8
+    # the one-pass kernel executes the backward's 5 contractions: 10*D*Hq*pairs flops; where there are two kernels the dK/dV kernel
+    # executes 4 of them (S, dP, dV, dK)
+    one_pass = bool(plan.info()["one_pass_backward"]) and ws.numel() >= plan.workspace_bytes_one_pass()
+    dkv_flops = fl["bwd"] * (1.0 if one_pass else 0.8)
     bwd_main_tflops = dkv_flops / (kavg["bwd_dkv_ms"] * 1e-3) / 1e12 if kavg["bwd_dkv_ms"] > 0 else 0.0
     fwd_tflops = fl["fwd"] / (kavg["fwd_kernel_ms"] * 1e-3) / 1e12 if kavg["fwd_kernel_ms"] > 0 else 0.0
     # the dQ kernel executes 3 contractions (S, dP, dQ): 6*D*Hq*pairs flops
-    dq_tflops = fl["bwd"] * 0.6 / (kavg["bwd_dq_ms"] * 1e-3) / 1e12 if kavg["bwd_dq_ms"] > 0 else 0.0
+    dq_tflops = fl["bwd"] * 0.6 / (kavg["bwd_dq_ms"] * 1e-3) / 1e12 if kavg["bwd_dq_ms"] > 0 and not one_pass else 0.0
     out = {
         "metric": "core-attention fwd+bwd TFLOP/s (causal FLOPs), 1 GPU",
         "value": tflops, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -243,14 +245,14 @@ def main():
                    "peak_bf16_tflops_from_device": peak_from_device, "during_timed_steps": clocks.summary()},
         "kernels_ms": kavg, "fwd_only_tflops": fwd_tflops, "bwd_only_tflops": bwd_tflops, "plan_ms": plan_ms, "plan_first_call_ms": plan_first_ms,
         "wall_s_timed": wall,
-        "roofline": {"kernel": "ca_bwd_dkv_kernel", "bound": "mfma", "achieved": bwd_main_tflops,
+        "roofline": {"kernel": "ca_bwd_fused_kernel" if one_pass else "ca_bwd_dkv_kernel", "bound": "mfma", "achieved": bwd_main_tflops,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": bwd_main_tflops / PEAK_BF16_TFLOPS,
                      "traffic": None,
                      "traffic_profiled": DKV_TRAFFIC_PROFILED if args.workload == DKV_TRAFFIC_PROFILED["workload"] else None},
     }
-    # The metric credits 14*D flops per (pair, head); the kernels execute 18*D (the dK/dV and the dQ kernel both
-    # recompute S and dP).  Executed rate next to the rate of back-to-back MFMAs measured in this run:
-    executed = (fl["fwd"] + 1.4 * fl["bwd"]) / (ms_per_step * 1e-3) / 1e12
+    # The metric credits 14*D flops per (pair, head), which is what the one pass executes; where there are two backward kernels they
+    # execute 18*D (both recompute S and dP).  Executed rate next to the rate of back-to-back MFMAs measured in this run:
+    executed = (fl["fwd"] + (1.0 if one_pass else 1.4) * fl["bwd"]) / (ms_per_step * 1e-3) / 1e12
     out["executed_tflops"] = executed
     if sustained is not None:
         out["roofline"]["sustained_mfma"] = {
@@ -260,8 +262,8 @@ def main():
             "other_kernels": {
                 "ca_fwd_kernel": {"executed_tflops": fwd_tflops, "stream_side_work_2_tflops": sustained_fwd,
                                   "frac": fwd_tflops / sustained_fwd},
-                "ca_bwd_dq_kernel": {"executed_tflops": dq_tflops, "stream_side_work_1_tflops": sustained_side,
-                                     "frac": dq_tflops / sustained_side}},
+                **({} if one_pass else {"ca_bwd_dq_kernel": {
+                    "executed_tflops": dq_tflops, "stream_side_work_1_tflops": sustained_side, "frac": dq_tflops / sustained_side}})},
             "what": "ca_mfma_stream16 in this run after the timed steps: v_mfma_f32_16x16x32_bf16 back to back from registers, "
                     "N(0,1) bf16 operands, two waves per SIMD on all CUs; with_side_work and side_work_1 add one 16-byte LDS "
                     "read per lane and two multiply-adds per two MFMAs and an exponential per four, side_work_2 four "

@@ -112,6 +112,14 @@ int ca_plan_workspace_bytes(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bw
 int ca_plan_workspace_bytes_split(const ca_plan_t *plan, size_t *fwd_bytes, size_t *bwd_bytes);
 
 /*
+ * ca_plan_workspace_bytes_one_pass: workspace with which ca_backward computes dK, dV and dQ in one pass, with S and dP computed once
+ * instead of twice; 0 where that would not be faster (small batches).  It holds fp32 sums of dQ, 4 * n_q_heads * padded_rows *
+ * head_dim bytes and a little more behind the bwd_bytes of ca_plan_workspace_bytes.  With less the calls do what is said above.  The
+ * results are those of whole units, bit for bit.
+ */
+int ca_plan_workspace_bytes_one_pass(const ca_plan_t *plan, size_t *bwd_bytes);
+
+/*
  * ca_forward: O and LSE for every query row of every task, one fused launch on `hip_stream`, or two where units are cut (the
  * second adds up the partial results that the first has left in ws).
  * q,k,v: device bf16 inputs; o: device bf16 output; lse: device fp32 output [n_q_heads][total_q].
@@ -130,10 +138,10 @@ int ca_forward(const ca_plan_t *plan, const void *q, const void *k, const void *
  * slot), fp32 -<dO, O> and log2(e)*LSE (twice: by head and slot, and in the row order of the dK/dV kernel's tiles), and
  * position-sorted bf16 copies of Q and dO
  * (bwd_bytes is about 4 * n_q_heads * padded_rows * (4 + head_dim) bytes: a little over the size of Q plus dO),
- * and the partial results of cut units, if it has room for them
- * (ca_plan_workspace_bytes_split).  Launches the preparation, the kernels of dK/dV and dQ (one launch where both are small), one
- * or two that add up partial results where units are cut, and fills for rows that belong to no task or document.  No arithmetic
- * uses atomics: results are bit-reproducible from run to run.  Allocates nothing, never synchronises.  Two calls, forward or
+ * and, if it has room for them, the partial results of cut units
+ * (ca_plan_workspace_bytes_split) or the fp32 sums of dQ of the one pass (ca_plan_workspace_bytes_one_pass).  Launches the preparation, the kernels of dK/dV and dQ (one
+ * launch where both are small, or the one pass), one or two that add up partial results where units are cut, and fills for rows that belong to no task or document.  No arithmetic
+ * uses atomics (the one pass takes its units by an atomic count per XCD, and adds to dQ in a fixed order): results are bit-reproducible from run to run.  Allocates nothing, never synchronises.  Two calls, forward or
  * backward, whose workspaces overlap must not overlap in time on the device.
  */
 int ca_backward(const ca_plan_t *plan, const void *q, const void *k, const void *v, const void *o,
@@ -196,7 +204,7 @@ int ca_sum_partial_dq(const int32_t *part_rows, int64_t n_rows, int32_t n_parts,
  * ca_backward with the dQ kernel (dK/dV partial results that dQ's take the place of: with the dK/dV kernel).  Where ca_backward
  * runs dK/dV and dQ units in one launch (joint_backward of ca_plan_info), it runs the same workgroups as two launches while
  * timing is enabled, so that each kind has a time: results are the same bit for bit, the two times together are more than
- * the one launch takes.  Enabling creates events (the only allocation); disabling destroys them.
+ * the one launch takes.  The one pass (ca_plan_workspace_bytes_one_pass) counts as the dK/dV kernel, and dQ takes no time.  Enabling creates events (the only allocation); disabling destroys them.
  */
 int ca_profile_enable(ca_plan_t *plan, int on);
 int ca_profile_read(ca_plan_t *plan, float *out_ms);
@@ -267,7 +275,8 @@ const char *ca_last_error(void); /* thread-local detail of the last failing call
  * backward units are chained, see below), joint_backward (1: the backward runs its dK/dV and dQ units in one launch, given
  * the workspace of ca_plan_workspace_bytes_split; in two while timing is enabled), forward_halves and forward_piece_halves (1:
  * the workgroups of ca_forward are halves, of 128 rows, of the units in the list of whole units, in the list of pieces), forward_turns and
- * forward_piece_turns (1: workgroups of that list that share a CU take turns at having priority).
+ * forward_piece_turns (1: workgroups of that list that share a CU take turns at having priority), one_pass_backward (1: given the
+ * workspace of ca_plan_workspace_bytes_one_pass, the backward computes dK, dV and dQ in one pass).
  * n_q_tiles counts the full 256-slot tiles.
  * Returns the number of values available.
  */
@@ -302,6 +311,10 @@ int64_t ca_plan_bwd_units(const ca_plan_t *plan, int32_t *units);
 int64_t ca_plan_fwd_pieces(const ca_plan_t *plan, int32_t *units);
 int64_t ca_plan_bwd_pieces(const ca_plan_t *plan, int32_t *units, int32_t *n_workgroups);
 int64_t ca_plan_combine_units(const ca_plan_t *plan, int32_t backward, int32_t *units);
+/* The units of the backward in one pass (empty where it is not taken): [n][10], fields as in bwd (tiles of 256 keys at head_dim
+ * 128, of 128 at 64; from the third field on every row sees a later key too; count 1, follow 0).  queue: [9], or NULL; units
+ * queue[i] .. queue[i + 1] - 1 are those of XCD i, in the order in which its workgroups take them. */
+int64_t ca_plan_one_pass_units(const ca_plan_t *plan, int32_t *units, int32_t *queue);
 
 #ifdef __cplusplus
 }

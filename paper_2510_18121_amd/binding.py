@@ -68,10 +68,12 @@ def lib() -> ctypes.CDLL:
         L.ca_profile_read.argtypes = [vp, vp]
         L.ca_plan_info.argtypes = [vp, vp, ctypes.c_int]
         for f in (L.ca_plan_rows, L.ca_plan_fwd_units, L.ca_plan_bwd_units, L.ca_plan_fwd_pieces, L.ca_plan_bwd_pieces,
-                  L.ca_plan_combine_units):
+                  L.ca_plan_combine_units, L.ca_plan_one_pass_units):
             f.restype = ctypes.c_int64
         L.ca_plan_fwd_pieces.argtypes = [vp, vp]
         L.ca_plan_bwd_pieces.argtypes = [vp, vp, vp]
+        L.ca_plan_workspace_bytes_one_pass.argtypes = [vp, vp]
+        L.ca_plan_one_pass_units.argtypes = [vp, vp, vp]
         L.ca_plan_combine_units.argtypes = [vp, ctypes.c_int32, vp]
         L.ca_plan_rows.argtypes = [vp, vp, vp]
         L.ca_plan_fwd_units.argtypes = [vp, vp]
@@ -118,7 +120,7 @@ class Plan:
     INFO_KEYS = ("q_tile_rows", "n_q_tiles", "n_fwd_units", "kv_tile_rows", "n_bwd_units", "fwd_kv_step",
                  "padded_rows", "fwd_steps", "bwd_steps", "bwd_q_block_rows", "slot_align", "heads_packed",
                  "n_bwd_workgroups", "joint_backward", "forward_halves", "forward_piece_halves",
-                 "forward_turns", "forward_piece_turns")
+                 "forward_turns", "forward_piece_turns", "one_pass_backward")
 
     def __init__(self, handle, batch):
         self.handle = ctypes.c_void_p(handle)
@@ -138,6 +140,12 @@ class Plan:
         f, b = ctypes.c_size_t(), ctypes.c_size_t()
         _check(lib().ca_plan_workspace_bytes_split(self.handle, ctypes.byref(f), ctypes.byref(b)))
         return int(f.value), int(b.value)
+
+    def workspace_bytes_one_pass(self):
+        """Workspace with which the backward runs in one pass; 0 where that would not be faster."""
+        b = ctypes.c_size_t()
+        _check(lib().ca_plan_workspace_bytes_one_pass(self.handle, ctypes.byref(b)))
+        return int(b.value)
 
     def info(self) -> dict:
         out = np.zeros(len(self.INFO_KEYS), np.int64)
@@ -161,6 +169,13 @@ class Plan:
         u = np.zeros((n, 10), np.int32)
         lib().ca_plan_bwd_units(self.handle, u.ctypes.data)
         return u
+
+    def one_pass_units(self):
+        """Units of the backward in one pass (fields as in bwd_units), and where each XCD's queue of them begins."""
+        n = lib().ca_plan_one_pass_units(self.handle, None, None)
+        u, q = np.zeros((n, 10), np.int32), np.zeros(9, np.int32)
+        lib().ca_plan_one_pass_units(self.handle, u.ctypes.data, q.ctypes.data)
+        return u, q
 
     def pieces(self) -> dict:
         """The lists of units cut into pieces (arrays as in the header; empty where nothing is cut)."""
@@ -291,9 +306,16 @@ def _scratch(preferred, needed, device):
 
 
 def alloc_workspace(plan: Plan, device="cuda"):
-    """A torch uint8 buffer big enough for both calls, with room for the partial results of units cut into pieces where the
-    device has it (torch's allocator returns 256-byte aligned blocks).  Both calls write to it: calls that may overlap in time
-    need one each."""
+    """A torch uint8 buffer big enough for both calls, with room for the partial results of units cut into pieces, or for a
+    backward in one pass, where the device has it (torch's allocator returns 256-byte aligned blocks).  Both calls write to it:
+    calls that may overlap in time need one each."""
+    import torch
+    one_pass = plan.workspace_bytes_one_pass()
+    if one_pass:
+        try:
+            return torch.empty(max(one_pass, *plan.workspace_bytes_split()), dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            pass
     return _scratch(max(*plan.workspace_bytes_split(), 256), max(*plan.workspace_bytes(), 256), device)
 
 

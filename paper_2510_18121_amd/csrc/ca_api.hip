@@ -14,7 +14,7 @@ namespace ca {
 hipError_t launch_fwd(const ca_plan_t *p, const void *q, const void *k, const void *v, void *o, float *lse, void *parts,
                       hipStream_t st);
 hipError_t launch_bwd(const ca_plan_t *p, const void *q, const void *k, const void *v, const void *o, const void *d_o,
-                      const float *lse, void *dq, void *dk, void *dv, void *ws, bool split, hipStream_t st,
+                      const float *lse, void *dq, void *dk, void *dv, void *ws, bool split, bool fused, hipStream_t st,
                       hipEvent_t *ev);
 
 static int hip_fail(const char *what, hipError_t e) {
@@ -72,7 +72,7 @@ static void free_device(ca_plan_t *p) {
   p->d_slot_row = p->d_slot_pos = p->d_block_rpk = p->d_pos_kv = nullptr;
   p->d_joint_order = nullptr;
   p->d_fwd_units = p->d_fwd_pieces = nullptr;
-  p->d_bwd_units = p->d_bwd_pieces = nullptr;
+  p->d_bwd_units = p->d_bwd_pieces = p->d_fused_units = nullptr;
   p->d_fwd_combine = p->d_bwd_combine = nullptr;
   if (cur >= 0 && cur != p->device) (void)hipSetDevice(cur);
   p->device = -1;
@@ -138,7 +138,7 @@ int ca_plan_upload(ca_plan_t *p, void *hip_stream) {
   try {
     auto add = [&](const auto &src) { arrays.push_back({src.data(), src.size() * sizeof(src[0]), 0}); };
     add(p->slot_row), add(p->slot_pos), add(p->block_rpk), add(p->pos_kv), add(p->fwd_units), add(p->bwd_units);
-    add(p->fwd_pieces), add(p->bwd_pieces), add(p->fwd_combine), add(p->bwd_combine), add(p->joint_order);
+    add(p->fwd_pieces), add(p->bwd_pieces), add(p->fwd_combine), add(p->bwd_combine), add(p->joint_order), add(p->fused_units);
     for (const bool large : {false, true}) {
       for (Array &a : arrays)
         if ((a.bytes > SMALL_ARRAY) == large) a.at = bytes, bytes = (bytes + a.bytes + 255) / 256 * 256;
@@ -171,7 +171,7 @@ int ca_plan_upload(ca_plan_t *p, void *hip_stream) {
   auto place = [&](auto *&dst, int i) { dst = reinterpret_cast<std::remove_reference_t<decltype(dst)>>(device + arrays[size_t(i)].at); };
   place(p->d_slot_row, 0), place(p->d_slot_pos, 1), place(p->d_block_rpk, 2), place(p->d_pos_kv, 3);
   place(p->d_fwd_units, 4), place(p->d_bwd_units, 5), place(p->d_fwd_pieces, 6), place(p->d_bwd_pieces, 7);
-  place(p->d_fwd_combine, 8), place(p->d_bwd_combine, 9), place(p->d_joint_order, 10);
+  place(p->d_fwd_combine, 8), place(p->d_bwd_combine, 9), place(p->d_joint_order, 10), place(p->d_fused_units, 11);
   // the vectors and `blob` stay alive in the plan, so the asynchronous copies read valid memory
   return CA_OK;
 }
@@ -295,7 +295,8 @@ int ca_backward(const ca_plan_t *p, const void *q, const void *k, const void *v,
   ca_plan_t *mp = const_cast<ca_plan_t *>(p);  // timing state only
   const ca_plan_t *const use = p->within_static && ws_bytes < p->ws_bwd_split ? p->within_static.get() : p;
   const bool split = use->ws_bwd_split > use->ws_bwd && ws_bytes >= use->ws_bwd_split;
-  hipError_t e = launch_bwd(use, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, static_cast<hipStream_t>(hip_stream),
+  const bool fused = p->fused && ws_bytes >= p->ws_bwd_fused;
+  hipError_t e = launch_bwd(fused ? p : use, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, fused, static_cast<hipStream_t>(hip_stream),
                             p->profile ? reinterpret_cast<hipEvent_t *>(&mp->ev[2]) : nullptr);
   if (e != hipSuccess) return hip_fail("backward launch", e);
   if (p->profile) mp->ev_bwd = true;

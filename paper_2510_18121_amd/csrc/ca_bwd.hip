@@ -27,6 +27,7 @@
 #include <atomic>
 
 #include "ca_device.h"
+#include "ca_fused.h"
 #include "ca_internal.h"
 
 namespace ca {
@@ -38,9 +39,10 @@ __global__ void ca_bwd_prep_kernel(const int32_t *__restrict__ slot_row, const i
                                    const bf16_t *__restrict__ Q, const bf16_t *__restrict__ O,
                                    const bf16_t *__restrict__ dO, const float *__restrict__ LSE,
                                    float *__restrict__ delta_slot, float *__restrict__ l2_slot,
-                                   float *__restrict__ delta_kv, float *__restrict__ l2_kv,
+                                   float *__restrict__ stats_kv,
                                    bf16_t *__restrict__ q_sorted, bf16_t *__restrict__ do_sorted,
-                                   int64_t padded, int64_t total_q, int Hq, int G, int D) {
+                                   u32x4 *__restrict__ zero, int64_t zero16, int64_t padded, int64_t total_q, int Hq, int G,
+                                   int D) {
   // D/8 lanes per (slot, head): -Delta = -<dO, O> and log2(e)*LSE in slot order (for the dQ kernel), and for the
   // dK/dV kernel the slot-ordered copies of Q and dO as [block of 64 slots][head][64][D] - the 64-row tile of a
   // (block, head) is one contiguous run, and the tiles of the heads of a block follow each other - with the same two
@@ -49,6 +51,7 @@ __global__ void ca_bwd_prep_kernel(const int32_t *__restrict__ slot_row, const i
   // heads 64/rpk t .. 64/rpk (t + 1) - 1, rpk rows each; the group's remaining tiles are neither written nor read.
   const int lanes = D / 8;
   const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (idx < zero16) zero[idx] = u32x4{0, 0, 0, 0};
   const int64_t pair = idx / lanes;
   const int c = int(idx % lanes);
   const bool ok = pair < padded * Hq;
@@ -89,8 +92,8 @@ __global__ void ca_bwd_prep_kernel(const int32_t *__restrict__ slot_row, const i
       delta_slot[int64_t(h) * padded + slot] = nd;
       l2_slot[int64_t(h) * padded + slot] = l2;
       if (in_tile) {
-        delta_kv[int64_t(th) * padded + blk * BWD_BQ + tr] = nd;
-        l2_kv[int64_t(th) * padded + blk * BWD_BQ + tr] = l2;
+        float *const st = stats_kv + ((blk * Hq + th) * 2 + tr / 32) * 64 + tr % 32;
+        st[0] = l2, st[32] = nd;
       }
     }
   }
@@ -347,9 +350,9 @@ struct DkvSmem {
   static constexpr int TILE = BWD_BQ * 2 * D;       // one Q or dO tile of 64 slots
   static constexpr int Q_OFF = 0;
   static constexpr int DO_OFF = TILE;
-  static constexpr int L2_OFF = 2 * TILE;           // 64 floats each: L2, Delta, position, spare
-  static constexpr int DL_OFF = L2_OFF + 256;
-  static constexpr int POS_OFF = DL_OFF + 256;
+  static constexpr int L2_OFF = 2 * TILE;           // 64 floats each: 32 L2 and 32 -Delta of either half of the rows, positions, spare
+  static constexpr int DL_OFF = L2_OFF + 128;
+  static constexpr int POS_OFF = L2_OFF + 512;
   static constexpr int SPARE_OFF = POS_OFF + 256;
   static constexpr int STAGE = 2 * TILE + 1024;
   static constexpr int TOTAL = NST * STAGE;
@@ -371,10 +374,9 @@ template <int D>
 __device__ __forceinline__ void dkv_workgroup(const int me /* index of the first unit */, const BwdUnit *__restrict__ units,
                                               const int32_t *__restrict__ slot_pos, const bf16_t *__restrict__ Qs,
                                               const bf16_t *__restrict__ K, const bf16_t *__restrict__ V,
-                                              const bf16_t *__restrict__ dOs, const float *__restrict__ l2_slot,
-                                              const float *__restrict__ delta_slot, bf16_t *__restrict__ dK,
-                                              bf16_t *__restrict__ dV, float *__restrict__ parts, int Hq, int Hkv,
-                                              int64_t padded, float scale) {
+                                              const bf16_t *__restrict__ dOs, const float *__restrict__ stats_kv,
+                                              bf16_t *__restrict__ dK,
+                                              bf16_t *__restrict__ dV, float *__restrict__ parts, int Hq, int Hkv, float scale) {
   using S = DkvSmem<D>;
   constexpr int NK = D / 32, ND = D / 16, CH = D / 8, RPI = 64 / CH, NST = S::NST;
   constexpr int NLD = BWD_BQ / (4 * RPI);  // direct loads per wave per Q (or dO) tile
@@ -405,8 +407,8 @@ __device__ __forceinline__ void dkv_workgroup(const int me /* index of the first
     const int n_full = ((u.slot_end - u.slot_full) / BWD_BQ) * Gu;
 
     // Loads of one (block, head): this wave fetches tile rows RPW*wave .. of Q and of dO, RPI rows per load, plus one 64-float
-    // auxiliary array: log2e*LSE (wave 0), -Delta (wave 1), slot positions (wave 2; wave 3 the same into a spare area, so that
-    // every wave issues the same number of loads).  Q and dO come from their slot-ordered copies [block][head][64][D], in which
+    // auxiliary array: log2e*LSE and -Delta of 32 rows each (waves 0 and 1), slot positions (wave 2; wave 3 the same into a spare
+    // area, so that every wave issues the same number of loads).  Q and dO come from their slot-ordered copies [block][head][64][D], in which
     // the tile of a (block, head) is one contiguous run: a load is (wave-uniform tile address) + (per-lane constant).
     const int trow = RPW * wave + lane / CH;
     const uint32_t ld_off = uint32_t(trow * ROWB + 16 * ((lane % CH) ^ tile_sw<D>(trow)));
@@ -414,12 +416,10 @@ __device__ __forceinline__ void dkv_workgroup(const int me /* index of the first
     int ph = 0, pst = 0;
     const int64_t tile0 = (int64_t(u.slot_begin / BWD_BQ + n_blocks - 1) * Hq + hk * G) * head_stride;
     const char *q_tile = reinterpret_cast<const char *>(Qs) + tile0, *do_tile = reinterpret_cast<const char *>(dOs) + tile0;
-    const int64_t aux_hstride = wave < 2 ? padded : 0;
-    const float *aux_ptr = (wave == 0 ? l2_slot + int64_t(hk) * G * padded
-                            : wave == 1 ? delta_slot + int64_t(hk) * G * padded
-                                        : reinterpret_cast<const float *>(slot_pos)) +
-                           u.slot_begin + int64_t(n_blocks - 1) * BWD_BQ;
-    const uint32_t aux_lds = wave == 0 ? S::L2_OFF : wave == 1 ? S::DL_OFF : wave == 2 ? S::POS_OFF : S::SPARE_OFF;
+    const int64_t aux_hstride = wave < 2 ? 128 : 0, aux_bstride = wave < 2 ? int64_t(Hq) * 128 : BWD_BQ;
+    const float *aux_ptr = (wave < 2 ? stats_kv + hk * G * 128 + wave * 64 : reinterpret_cast<const float *>(slot_pos)) +
+                           (u.slot_begin / BWD_BQ + n_blocks - 1) * aux_bstride;
+    const uint32_t aux_lds = wave < 2 ? S::L2_OFF + 256 * wave : wave == 2 ? S::POS_OFF : S::SPARE_OFF;
     auto issue_next = [&]() __attribute__((always_inline)) {
       const uint32_t st = lds0 + pst * S::STAGE;
       uint32_t ld0 = ld_off;
@@ -440,7 +440,7 @@ __device__ __forceinline__ void dkv_workgroup(const int me /* index of the first
       } else {  // first head of the group, previous block
         ph = 0;
         q_tile -= (Gu - 1) * head_stride + block_stride, do_tile -= (Gu - 1) * head_stride + block_stride;
-        aux_ptr -= (Gu - 1) * aux_hstride + BWD_BQ;
+        aux_ptr -= (Gu - 1) * aux_hstride + aux_bstride;
       }
     };
     if (n_it > 0) {
@@ -506,11 +506,11 @@ __device__ __forceinline__ void dkv_workgroup(const int me /* index of the first
         for (int f = 0; f < 2 * NK; ++f) {
           if (f == 2 * NK - 2) {
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt) nd[rt] = lds_ld<f32x4>(S::DL_OFF + (32 * qb + 16 * rt) * 4 + auxo);
+            for (int rt = 0; rt < 2; ++rt) nd[rt] = lds_ld<f32x4>(S::DL_OFF + 256 * qb + 64 * rt + auxo);
           }
           if (f == 2 * NK - 1) {
 #pragma unroll
-            for (int rt = 0; rt < 2; ++rt) l2v[rt] = lds_ld<f32x4>(S::L2_OFF + (32 * qb + 16 * rt) * 4 + auxo);
+            for (int rt = 0; rt < 2; ++rt) l2v[rt] = lds_ld<f32x4>(S::L2_OFF + 256 * qb + 64 * rt + auxo);
           }
 #pragma unroll
           for (int kg = 0; kg < 2; ++kg) sa[f & 1][kg] = mfma16(fr[at % AHEAD], kf[f / 2][kg], f < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : sa[f & 1][kg]);
@@ -614,12 +614,10 @@ __global__ __launch_bounds__(256, 2) void ca_bwd_dkv_kernel(const BwdUnit *__res
                                                             const int32_t *__restrict__ slot_pos,
                                                             const bf16_t *__restrict__ Qs, const bf16_t *__restrict__ K,
                                                             const bf16_t *__restrict__ V, const bf16_t *__restrict__ dOs,
-                                                            const float *__restrict__ l2_slot,
-                                                            const float *__restrict__ delta_slot,
-                                                            bf16_t *__restrict__ dK, bf16_t *__restrict__ dV,
-                                                            float *__restrict__ parts, int Hq, int Hkv, int64_t padded,
+                                                            const float *__restrict__ stats_kv, bf16_t *__restrict__ dK,
+                                                            bf16_t *__restrict__ dV, float *__restrict__ parts, int Hq, int Hkv,
                                                             float scale) {
-  dkv_workgroup<D>(int(blockIdx.x), units, slot_pos, Qs, K, V, dOs, l2_slot, delta_slot, dK, dV, parts, Hq, Hkv, padded, scale);
+  dkv_workgroup<D>(int(blockIdx.x), units, slot_pos, Qs, K, V, dOs, stats_kv, dK, dV, parts, Hq, Hkv, scale);
 }
 
 // dK/dV units and dQ half units (workgroups of 4 groups of 32 rows) in one launch, longest first.  For batches too small to
@@ -634,7 +632,7 @@ struct JointArgs {
   const FwdUnit *dq_units;
   const int32_t *slot_row, *slot_pos, *pos_kv;
   const bf16_t *q, *k, *v, *d_o, *q_sorted, *do_sorted;
-  const float *l2_slot, *delta_slot, *l2_kv, *delta_kv;
+  const float *l2_slot, *delta_slot, *stats_kv;
   bf16_t *dq, *dk, *dv;
   float *parts_dq, *parts_kv;
   int n_dkv, n_dq, hq, hkv;
@@ -655,8 +653,7 @@ __global__ __launch_bounds__(256, 2) void ca_bwd_joint_kernel(const JointArgs a)
     w = -1 - (unit + half * a.n_dq);
   }
   if (w >= 0) {
-    dkv_workgroup<D>(w, a.units, a.pos_kv, a.q_sorted, a.k, a.v, a.do_sorted, a.l2_kv, a.delta_kv, a.dk, a.dv, a.parts_kv, a.hq,
-                     a.hkv, a.padded, a.scale);
+    dkv_workgroup<D>(w, a.units, a.pos_kv, a.q_sorted, a.k, a.v, a.do_sorted, a.stats_kv, a.dk, a.dv, a.parts_kv, a.hq, a.hkv, a.scale);
   } else {
     const int half = -1 - w >= a.n_dq ? 1 : 0;
     dq_workgroup<D, 4>(a.dq_units[-1 - w - half * a.n_dq], half, a.slot_row, a.slot_pos, a.q, a.k, a.v, a.d_o, a.l2_slot,
@@ -721,14 +718,13 @@ static hipError_t set_smem(F kern, int bytes, int device, std::atomic<bool> *don
 template <int D>
 static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k, const void *v, const void *o,
                                const void *d_o, const float *lse, void *dq, void *dk, void *dv, void *ws,
-                               bool split, hipStream_t st, hipEvent_t *ev) {
+                               bool split, bool fused, hipStream_t st, hipEvent_t *ev) {
   if (ev) (void)hipEventRecord(ev[0], st);
   const size_t q_elems = size_t(p->total_q) * p->hq * D, kv_elems = size_t(p->total_kv) * p->hkv * D;
   const int64_t padded = int64_t(p->slot_row.size());
   float *delta_slot = static_cast<float *>(ws);
   float *l2_slot = reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_l2);
-  float *delta_kv = reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_delta_kv);
-  float *l2_kv = reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_l2_kv);
+  float *stats_kv = reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_stats_kv);
   bf16_t *q_sorted = reinterpret_cast<bf16_t *>(static_cast<char *>(ws) + p->ws_off_qs);
   bf16_t *do_sorted = reinterpret_cast<bf16_t *>(static_cast<char *>(ws) + p->ws_off_dos);
   // partial results of cut units, where the caller's workspace has room for them
@@ -753,10 +749,28 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
     const int64_t threads = padded * p->hq * (D / 8);
     hipLaunchKernelGGL(ca_bwd_prep_kernel, dim3(unsigned((threads + 255) / 256)), dim3(256), 0, st, p->d_slot_row,
                        p->d_block_rpk, static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(o),
-                       static_cast<const bf16_t *>(d_o), lse, delta_slot, l2_slot, delta_kv, l2_kv, q_sorted, do_sorted,
-                       padded, p->total_q, p->hq, p->hq / p->hkv, D);
+                       static_cast<const bf16_t *>(d_o), lse, delta_slot, l2_slot, stats_kv, q_sorted, do_sorted,
+                       reinterpret_cast<u32x4 *>(static_cast<char *>(ws) + p->ws_off_flags), fused ? int64_t(p->ws_bwd_fused - p->ws_off_flags) / 16 : int64_t(0), padded, p->total_q, p->hq, p->hq / p->hkv, D);
   }
   if (ev) (void)hipEventRecord(ev[1], st);
+  if (fused) {
+    FusedArgs a = {};
+    a.units = p->d_fused_units;
+    std::copy(p->fused_queue, p->fused_queue + N_XCD + 1, a.queue);
+    a.slot_row = p->d_slot_row, a.pos_kv = p->d_pos_kv;
+    a.k = static_cast<const bf16_t *>(k), a.v = static_cast<const bf16_t *>(v), a.q_sorted = q_sorted, a.do_sorted = do_sorted;
+    a.stats_kv = stats_kv, a.flag_bytes = uint32_t(p->ws_off_ctrl - p->ws_off_flags);
+    a.copy_bytes = uint32_t(p->ws_off_dos - p->ws_off_qs), a.dq_bytes = uint32_t(p->ws_off_flags - p->ws_off_dq_sums);
+    a.dq = static_cast<bf16_t *>(dq), a.dk = static_cast<bf16_t *>(dk), a.dv = static_cast<bf16_t *>(dv);
+    a.dq_sums = reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_dq_sums);
+    a.flags = reinterpret_cast<int *>(static_cast<char *>(ws) + p->ws_off_flags);
+    a.ctrl = reinterpret_cast<int *>(static_cast<char *>(ws) + p->ws_off_ctrl);
+    a.hq = p->hq, a.hkv = p->hkv, a.padded = padded, a.scale = p->scale;
+    hipError_t e = launch_bwd_fused(a, D, p->device, st);
+    if (e != hipSuccess) return e;
+    if (ev) (void)hipEventRecord(ev[2], st), (void)hipEventRecord(ev[3], st);
+    return hipGetLastError();
+  }
   const FwdUnit *const dq_list = parts_dq ? p->d_fwd_pieces : p->d_fwd_units;
   const int n_dq = int(parts_dq ? p->fwd_pieces.size() : p->fwd_units.size());
   const bool joint = p->joint && (split || p->n_fwd_parts + p->n_bwd_parts == 0);
@@ -773,8 +787,8 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
     if (e != hipSuccess) return e;
     args = {p->joint_order.empty() || ev ? nullptr : p->d_joint_order, parts_kv ? p->d_bwd_pieces : p->d_bwd_units, dq_list,
             p->d_slot_row, p->d_slot_pos, p->d_pos_kv, static_cast<const bf16_t *>(q), static_cast<const bf16_t *>(k),
-            static_cast<const bf16_t *>(v), static_cast<const bf16_t *>(d_o), q_sorted, do_sorted, l2_slot, delta_slot, l2_kv,
-            delta_kv, static_cast<bf16_t *>(dq), static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_dq, parts_kv,
+            static_cast<const bf16_t *>(v), static_cast<const bf16_t *>(d_o), q_sorted, do_sorted, l2_slot, delta_slot, stats_kv,
+            static_cast<bf16_t *>(dq), static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_dq, parts_kv,
             n_dkv, n_dq, p->hq, p->hkv, padded, p->scale};
     // (with timing enabled the same workgroups run as two launches, so that each kind has a time)
     launch_joint(ev ? n_dkv : n_dkv + 2 * n_dq);
@@ -786,8 +800,7 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(unsigned(n_dkv)), dim3(256), SMEM, st,
                        parts_kv ? p->d_bwd_pieces : p->d_bwd_units, p->d_pos_kv, q_sorted, static_cast<const bf16_t *>(k), static_cast<const bf16_t *>(v), do_sorted,
-                       l2_kv, delta_kv, static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_kv, p->hq,
-                       p->hkv, padded, p->scale);
+                       stats_kv, static_cast<bf16_t *>(dk), static_cast<bf16_t *>(dv), parts_kv, p->hq, p->hkv, p->scale);
   }
   if (p->shared_parts) combine(false, true);  // before the dQ pieces write over them
   if (ev) (void)hipEventRecord(ev[2], st);
@@ -811,10 +824,10 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
 }
 
 hipError_t launch_bwd(const ca_plan_t *p, const void *q, const void *k, const void *v, const void *o, const void *d_o,
-                      const float *lse, void *dq, void *dk, void *dv, void *ws, bool split, hipStream_t st,
-                      hipEvent_t *ev) {
-  return p->d == 128 ? launch_bwd_t<128>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, st, ev)
-                     : launch_bwd_t<64>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, st, ev);
+                      const float *lse, void *dq, void *dk, void *dv, void *ws, bool split, bool fused,
+                      hipStream_t st, hipEvent_t *ev) {
+  return p->d == 128 ? launch_bwd_t<128>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, fused, st, ev)
+                     : launch_bwd_t<64>(p, q, k, v, o, d_o, lse, dq, dk, dv, ws, split, fused, st, ev);
 }
 
 }  // namespace ca

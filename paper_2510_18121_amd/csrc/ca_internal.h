@@ -77,7 +77,10 @@ struct CombineUnit {
 inline size_t part_bytes(int d) { return size_t(FWD_BM) * d * 4; }
 constexpr size_t FWD_STAT_BYTES = 8 * 64 * 2 * 4;
 
-constexpr int N_CU = 256;
+constexpr int N_CU = 256, N_XCD = 8;
+constexpr int FUSED_BQ = 32;                                        // query rows per step of the one-pass backward
+constexpr size_t FUSED_CTRL_BYTES = 256;                          // per queue: its XCD + 1, and, 128 bytes on, the units taken
+constexpr int fused_waves(int d) { return d == 128 ? 8 : 4; }  // its workgroups, each wave with 32 keys
 // How the forward kernel runs a list of units (the planner chooses, see there)
 struct FwdForm {
   bool halves = false;  // workgroups are halves of units (of 128 rows)
@@ -111,6 +114,12 @@ struct ca_plan {
   ca::FwdForm fwd_form, fwd_piece_form;
   // workspace with which the piece lists are used: forward, and backward, where the parts lie behind ws_bwd
   size_t ws_fwd_split = 0, ws_bwd_split = 0, ws_off_parts_kv = 0, ws_off_parts_dq = 0;
+  // dK, dV and dQ in one pass (ca_bwd_fused.hip): whole units by queue, where each queue begins, and what the pass needs behind ws_bwd
+  bool fused = false;
+  std::vector<ca::BwdUnit> fused_units;
+  int32_t fused_queue[ca::N_XCD + 1] = {};
+  size_t ws_off_dq_sums = 0, ws_off_flags = 0, ws_off_ctrl = 0, ws_bwd_fused = 0;
+  const ca::BwdUnit *d_fused_units = nullptr;
   bool joint = false;  // backward runs dK/dV and dQ units in one launch: dK/dV workgroups, then dQ halves 1, then 0, or,
   // if not empty, in this order: i >= 0: dK/dV workgroup i; below: -1 - (half * dQ units + unit)
   std::vector<int32_t> joint_order;
@@ -125,7 +134,7 @@ struct ca_plan {
   // workspace layout for backward: [Delta fp32 hq*padded_slots][log2e*LSE fp32 hq*padded_slots]
   int slot_align = ca::SLOT_ALIGN, heads_packed = 1;  // padding of a document's slots; hp of the packed units
   size_t ws_fwd = 0, ws_bwd = 0, ws_off_l2 = 0, ws_off_qs = 0, ws_off_dos = 0;
-  size_t ws_off_delta_kv = 0, ws_off_l2_kv = 0;  // the row statistics once more, in the row order of the dK/dV tiles
+  size_t ws_off_stats_kv = 0;  // the row statistics once more: [block][head][half of 32 rows of the dK/dV tile][log2e*LSE, -Delta][32]
   bool q_covered = false, kv_covered = false;  // every packed Q row / KV row belongs to some unit
   // device copies
   int device = -1;

@@ -13,6 +13,7 @@
 #include <functional>
 #include <memory>
 #include <numeric>
+#include <queue>
 #include <sstream>
 
 #include "ca_internal.h"
@@ -280,6 +281,117 @@ std::array<Cut, 2> best_piece(const std::vector<std::pair<int64_t, int64_t>> &un
   return cut;
 }
 
+// ---- the backward in one pass (ca_bwd_fused.hip)
+// The KV tiles of one (document, KV head) are a chain: tile j + 1 adds to a 32-row tile of dQ after tile j, in the L2 of the XCD that
+// runs the chain, so a chain belongs to one of 8 queues, one per XCD, whose workgroups take its units in order.  Chains go, longest
+// first, to the queue with the least work.  In a queue they follow each other by length in groups that can keep the XCD's workgroups
+// busy twice over (a chain of tiles under few query rows cannot: each tile only starts when the one before it is a step or two
+// ahead), and inside a group the longest unit comes first.  All units of a queue by their length, whatever their documents, end a
+// little more evenly and are slower, as fewer of the sums of dQ are still in L2: 8.46 against 8.18 ms (64K tokens of documents
+// of about 2K, 32/8 heads), 31.5 against 30.9 ms (64K tokens of long documents, 64/8), 4.99 against 4.47 ms (lone 64-row shards, 8/2).
+//
+// When does the one pass pay?  It does five contractions instead of seven, but in workgroups of twice the keys (head_dim 128), one to a
+// CU, bound to queues.  A unit costs `fixed`, `per_step` for each 32 rows x head and `per_masked` where they hold the diagonal, and
+// starts at least `lag` after the one before it in its chain; the longest queue is simulated and compared with the simulation of the
+// other kernels.  Microseconds, fitted to 180 drawn batches.  On those the rule took 40 and all were faster, 1.00 to 1.3 times
+// (backward), and the best it left out gained 6 % (head_dim 128) or were shorter than the limit.  At 64 the simulation is less exact
+// (0.78 to 1.34 times at a predicted 1.05 to 1.2, with the diagonal at the price of other steps), so more is asked for.
+struct FusedCost {
+  int slots;  // workgroups per XCD
+  double per_step, per_masked, fixed, lag;
+  double gain, min_us;  // what the one pass has to be faster by, and the least it is taken for
+};
+constexpr FusedCost FUSED_128 = {N_CU / N_XCD, 2.42, 3.3, 14.0, 4.0, 1.08, 1000}, FUSED_64 = {3 * N_CU / N_XCD, 2.05, 4.5, 13.0, 4.0, 1.12, 1500};
+
+class OnePass {
+ public:
+  // tiles: KV tiles, document by document, each document's from its first key on
+  OnePass(const ca_plan_t &plan, std::vector<BwdUnit> kv_tiles) : cost_(plan.d == 128 ? FUSED_128 : FUSED_64), tiles_(std::move(kv_tiles)), hkv_(plan.hkv) {
+    for (size_t t = 0; t < tiles_.size(); ++t) {
+      if (tiles_[t].key_pos0 == 0) docs_.push_back({t, 0, 0});
+      ++docs_.back().n, docs_.back().steps += steps(tiles_[t]);
+    }
+    std::stable_sort(docs_.begin(), docs_.end(), [](const Doc &a, const Doc &b) { return a.steps > b.steps; });
+    std::array<int64_t, N_XCD> load{};
+    for (size_t d = 0; d < docs_.size(); ++d)
+      for (int h = 0; h < hkv_; ++h) {
+        const size_t q = size_t(std::min_element(load.begin(), load.end()) - load.begin());
+        load[q] += docs_[d].steps + int64_t(docs_[d].n);
+        chains_[q].push_back({d, h});
+      }
+    longest_ = size_t(std::max_element(load.begin(), load.end()) - load.begin());
+  }
+  // when the longest queue ends
+  double time() const {
+    double end = 0;
+    std::vector<double> begun(chains_[longest_].size(), -cost_.lag);  // the last unit of each chain
+    std::priority_queue<double, std::vector<double>, std::greater<double>> slots;
+    for (int i = 0; i < cost_.slots; ++i) slots.push(0.0);
+    each_unit(longest_, [&](const Entry &e) {
+      const BwdUnit &u = tiles_[e.tile];
+      const double at = std::max(slots.top(), begun[e.chain] + cost_.lag), masked = double((u.slot_full - u.slot_begin) / FUSED_BQ * u.heads);
+      const double us = cost_.fixed + cost_.per_step * double(e.steps) + (cost_.per_masked - cost_.per_step) * masked;
+      slots.pop(), slots.push(at + us);
+      begun[e.chain] = at, end = std::max(end, at + us);
+    });
+    return end;
+  }
+  void lay_out(ca_plan_t *p) const {
+    for (size_t q = 0; q < N_XCD; ++q) {
+      each_unit(q, [&](const Entry &e) {
+        p->fused_units.push_back(tiles_[e.tile]);
+        p->fused_units.back().kv_head = chains_[q][e.chain].head, p->fused_units.back().count = 1;
+      });
+      p->fused_queue[q + 1] = int32_t(p->fused_units.size());
+    }
+    const size_t tiles32 = p->slot_row.size() / FUSED_BQ * size_t(p->hq);  // 32-row tiles of dQ
+    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+    p->ws_off_dq_sums = p->ws_bwd;
+    p->ws_off_flags = p->ws_off_dq_sums + up(tiles32 * FUSED_BQ * size_t(p->d) * 4);
+    p->ws_off_ctrl = p->ws_off_flags + up(tiles32 * size_t(fused_waves(p->d)) * 4);
+    p->ws_bwd_fused = p->ws_off_ctrl + N_XCD * FUSED_CTRL_BYTES;
+    p->fused = true;
+  }
+
+ private:
+  struct Doc {
+    size_t first, n;  // its tiles
+    int64_t steps;
+  };
+  struct Chain {
+    size_t doc;
+    int32_t head;
+  };
+  struct Entry {
+    int64_t steps;
+    size_t tile, chain;
+  };
+  static int64_t steps(const BwdUnit &u) { return int64_t(u.slot_end - u.slot_begin) / FUSED_BQ * u.heads; }
+  template <class F>
+  void each_unit(size_t q, F f) const {
+    std::vector<Entry> group;
+    double busy = 0;  // workgroups that the group's chains can keep busy
+    for (size_t c = 0; c < chains_[q].size(); ++c) {
+      const Doc &d = docs_[chains_[q][c].doc];
+      for (size_t t = d.first; t < d.first + d.n; ++t) group.push_back({steps(tiles_[t]), t, c});
+      busy += std::min(double(d.n), 1.0 + cost_.per_step * double(steps(tiles_[d.first])) / cost_.lag);
+      if (busy < 2.0 * cost_.slots && c + 1 < chains_[q].size()) continue;
+      std::stable_sort(group.begin(), group.end(), [&](const Entry &a, const Entry &b) {
+        return a.steps != b.steps ? a.steps > b.steps : tiles_[a.tile].key_pos0 < tiles_[b.tile].key_pos0;
+      });
+      for (const Entry &e : group) f(e);
+      group.clear(), busy = 0;
+    }
+  }
+
+  const FusedCost &cost_;
+  std::vector<BwdUnit> tiles_;
+  const int hkv_;
+  std::vector<Doc> docs_;
+  std::array<std::vector<Chain>, N_XCD> chains_;
+  size_t longest_ = 0;
+};
+
 // beyond_static: cut units may take the backward workspace beyond the library's static one where whole units would not.
 // Returns whether the search for cuts saw a tenth less time there.
 bool schedule(ca_plan_t *p, bool beyond_static) {
@@ -312,6 +424,31 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   };
   std::vector<TileRef> ftiles;
   std::vector<BwdUnit> btiles;
+  // A tile of `keys` keys of a document.  Blocks from its slot_full on lie entirely below the diagonal: they see all keys of the
+  // tile, and `beyond` more.
+  struct DocTiles {
+    int64_t s0, s1;
+    int32_t kv_row0, len, cover, heads;
+  };
+  std::vector<DocTiles> doc_tiles;
+  auto kv_tile = [&](const DocTiles &x, int32_t k0, int32_t keys, int32_t beyond) {
+    BwdUnit u{int32_t(x.s1), int32_t(x.s1), int32_t(x.s1), x.kv_row0 + k0, std::min<int32_t>(keys, x.len - k0), k0, 0};
+    u.heads = x.heads;
+    if (k0 < x.cover) {
+      // first slot whose position can see key k0
+      const int32_t *b = p->slot_pos.data() + x.s0, *e = p->slot_pos.data() + x.s1;
+      int64_t first = std::lower_bound(b, e, k0) - b;
+      first = first / BWD_BQ * BWD_BQ;
+      int64_t end = x.s1;
+      while (end - BWD_BQ >= x.s0 + first && p->slot_row[end - BWD_BQ] < 0) end -= BWD_BQ;  // drop pure-padding blocks
+      u.slot_begin = int32_t(x.s0 + first);
+      u.slot_end = int32_t(end);
+      int64_t full = std::lower_bound(b, e, k0 + keys - 1 + beyond) - b;
+      full = (full + BWD_BQ - 1) / BWD_BQ * BWD_BQ;
+      u.slot_full = int32_t(std::min<int64_t>(std::max<int64_t>(x.s0 + full, u.slot_begin), end));
+    }
+    return u;
+  };
   int64_t s = 0, covered_kv = 0, covered_q = 0;
   for (int t = 0; t < p->n_tasks; ++t) covered_q += p->task_q_len[t];
   for (int dd = 0; dd < p->n_docs; ++dd) {
@@ -363,25 +500,9 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     // unit without query blocks, which writes their zero gradient.
     const int32_t cover = last_pos + 1;
     const int32_t doc_len = int32_t(p->doc_kv_len[dd]);
-    for (int32_t k0 = 0; k0 < doc_len; k0 += BWD_BN) {
-      BwdUnit u{int32_t(s1), int32_t(s1), int32_t(s1), kv_row0 + k0, std::min<int32_t>(BWD_BN, doc_len - k0), k0, 0};
-      u.heads = tiles_per_block;
-      if (k0 < cover) {
-        // first slot whose position can see key k0
-        const int32_t *b = p->slot_pos.data() + s0, *e = p->slot_pos.data() + s1;
-        int64_t first = std::lower_bound(b, e, k0) - b;
-        first = first / BWD_BQ * BWD_BQ;
-        int64_t end = s1;
-        while (end - BWD_BQ >= s0 + first && p->slot_row[end - BWD_BQ] < 0) end -= BWD_BQ;  // drop pure-padding blocks
-        u.slot_begin = int32_t(s0 + first);
-        u.slot_end = int32_t(end);
-        // blocks from here on lie entirely below the diagonal of this tile: no mask needed
-        int64_t full = std::lower_bound(b, e, k0 + BWD_BN - 1) - b;
-        full = (full + BWD_BQ - 1) / BWD_BQ * BWD_BQ;
-        u.slot_full = int32_t(std::min<int64_t>(std::max<int64_t>(s0 + full, u.slot_begin), end));
-      }
-      btiles.push_back(u);
-    }
+    const DocTiles doc{s0, s1, kv_row0, doc_len, cover, tiles_per_block};
+    for (int32_t k0 = 0; k0 < doc_len; k0 += BWD_BN) btiles.push_back(kv_tile(doc, k0, BWD_BN, 0));
+    doc_tiles.push_back(doc);
     covered_kv += doc_len;
   }
   // longest first (the hardware dispatcher hands out workgroups in index order, so this is LPT
@@ -413,8 +534,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     p->ws_off_l2 = per;
     p->ws_off_qs = 2 * per;
     p->ws_off_dos = 2 * per + copy;
-    p->ws_off_delta_kv = 2 * per + 2 * copy;
-    p->ws_off_l2_kv = 3 * per + 2 * copy;
+    p->ws_off_stats_kv = 2 * per + 2 * copy;
     return 4 * per + 2 * copy;
   };
   // Partial results are bounded: at most this much more than whole units need, and, unless beyond_static, no more than what the
@@ -424,7 +544,10 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   size_t cut_budget = 0;
   std::array<size_t, 2> limits{};
   bool more = false;
-  double us_apart = 0;  // simulated time of the backward in two launches
+  bool us_wanted = false;
+  std::unique_ptr<OnePass> one_pass;
+  double us_one_pass = 0;
+  double us_apart = 0, us_lists = 0;  // simulated time of the backward in two launches, and as the lists run it
   const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.65, 10.0, 5.0, 4} : CutCost{2 * N_CU, 1.75, 12.0, 5.0, 4};
   const double dq_per_tile = p->d == 128 ? 2.4 : 1.4, dq_fixed = 8.0;  // of the dQ kernel
   const CutCost cost_fwd = {N_CU, p->d == 128 ? 1.9 : 1.1, 8.0, 5.0, 4};
@@ -642,8 +765,28 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     const int slots = cost_dkv.slots;
     double mean = 0;
     for (int64_t s : wg_steps) mean += (cost_dkv.fixed + cost_dkv.per_step * double(s)) * hkv / slots;
+    {
+      // the one pass is worth a look where there is enough work, not too much of it around the steps of its units, and its 32-bit
+      // offsets reach; `level`: both kinds of list, were they spread evenly
+      const FusedCost &cost = p->d == 128 ? FUSED_128 : FUSED_64;
+      const int32_t keys = 32 * fused_waves(p->d);
+      double n_tiles = 0, level = mean;
+      for (const DocTiles &x : doc_tiles) n_tiles += double((x.len + keys - 1) / keys);
+      for (const TileRef &t : ftiles) level += (dq_fixed + dq_per_tile * t.cost) * (hq / t.u.hp) / N_CU;
+      const double in_steps = cost.per_step * 2.0 * double(p->bwd_steps) * BWD_BN / keys / (cost.slots * N_XCD);
+      if (in_steps >= cost.min_us && cost.gain * (in_steps + cost.fixed * n_tiles * hkv / (cost.slots * N_XCD)) < 1.2 * level &&
+          size_t(padded) * size_t(hq) * size_t(p->d) * 4 <= UINT32_MAX) {
+        std::vector<BwdUnit> tiles;
+        for (const DocTiles &x : doc_tiles)
+          for (int32_t k0 = 0; k0 < x.len; k0 += keys) tiles.push_back(kv_tile(x, k0, keys, 1));  // (1: another tile adds to their dQ)
+        one_pass = std::make_unique<OnePass>(*p, std::move(tiles));
+        us_one_pass = one_pass->time();
+      }
+    }
     const bool may_join = mean < (p->d == 128 ? JOINT_MAX_US : JOINT_MAX_US_64);
-    if (!wg_steps.empty() && !p->fwd_units.empty() && (may_join || p->pieces_lost || beyond_static)) {
+    const bool wanted = may_join || p->pieces_lost || beyond_static;
+    us_wanted = wanted;
+    if (!wg_steps.empty() && !p->fwd_units.empty() && (wanted || one_pass)) {
       // groups of equal workgroups that follow each other in their list: (microseconds, how many, first entry of joint_order,
       // step from entry to entry)
       struct Group {
@@ -681,7 +824,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
                                   ? cost_dkv.launch + double(size_t(p->n_fwd_parts + p->n_bwd_parts) * part_bytes(p->d)) / BYTES_PER_US
                                   : 0.0;
       const double apart = makespan(dkv, slots / same, 1e30, JOINT_UNITS) + makespan(dq, N_CU / same, 1e30, JOINT_UNITS) + cost_dkv.launch;
-      p->us_bwd = us_apart = apart + parts_us;
+      us_lists = us_apart = apart + parts_us;
       if (may_join && sum / slots < apart) {
         std::vector<std::pair<double, int64_t>> all;
         auto span_of = [&](double at_most) {
@@ -699,7 +842,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
         }
         const bool order = sorted < goal;
         p->joint = order || listed < apart;
-        if (p->joint) p->us_bwd = (order ? sorted : listed) + parts_us;
+        if (p->joint) us_lists = (order ? sorted : listed) + parts_us;
         if (p->joint && order)
           for (const Group &x : groups)
             for (int32_t i = 0; i < x.n; ++i) p->joint_order.push_back(x.entry + i * x.step);
@@ -716,11 +859,14 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     p->shared_parts = kv > 0 && dq > 0 && kv + dq > cut_budget;
     if (p->shared_parts) {
       p->joint_lost = p->joint;
-      p->joint = false, p->joint_order.clear(), p->us_bwd = us_apart;
+      p->joint = false, p->joint_order.clear(), us_lists = us_apart;
     }
     if (!p->shared_parts) p->ws_off_parts_dq += kv;
     p->ws_bwd_split = std::max(p->ws_off_parts_kv + kv, p->ws_off_parts_dq + dq);
   }
+  if (us_wanted) p->us_bwd = us_lists;
+  // the one pass, where it is faster than the lists above
+  if (one_pass && us_lists > (p->d == 128 ? FUSED_128 : FUSED_64).gain * us_one_pass) one_pass->lay_out(p);
   p->q_covered = covered_q == p->total_q;
   p->kv_covered = covered_kv == p->total_kv;
   return more;
@@ -767,6 +913,8 @@ int build_plan(const ca_batch_desc *desc, ca_plan_t **out) {
       schedule(large.get(), true);
       const double inside = p->us_fwd + p->us_bwd, beyond = large->us_fwd + large->us_bwd;
       if (p->us_bwd > 0 && large->us_bwd > 0 && ((more && beyond < 0.9 * inside) || ((p->joint_lost || p->pieces_lost) && inside - beyond > BEYOND_STATIC_US))) {
+        // (the one pass needs no pieces: what it needs fits behind either plan's whole units, and the larger one offers it)
+        p->fused = false, p->fused_units = {}, p->ws_bwd_fused = 0;
         large->within_static = std::move(p);
         p = std::move(large);
       }
@@ -824,12 +972,12 @@ int ca_plan_info(const ca_plan_t *p, int64_t *out, int n) {
   if (!p) return 0;
   int64_t full_tiles = 0;
   for (auto &u : p->fwd_units) full_tiles += u.hp == 1 && u.head == 0;
-  const int64_t v[18] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
+  const int64_t v[19] = {ca::FWD_BM, full_tiles, int64_t(p->fwd_units.size()),
                          ca::BWD_BN, int64_t(p->bwd_units.size()), ca::FWD_BN, int64_t(p->slot_row.size()),
                          p->fwd_steps, p->bwd_steps, ca::BWD_BQ, p->slot_align, p->heads_packed, p->bwd_workgroups,
-                         p->joint, p->fwd_form.halves, p->fwd_piece_form.halves, p->fwd_form.turns, p->fwd_piece_form.turns};
-  for (int i = 0; i < n && i < 18 && out; ++i) out[i] = v[i];
-  return 18;
+                         p->joint, p->fwd_form.halves, p->fwd_piece_form.halves, p->fwd_form.turns, p->fwd_piece_form.turns, p->fused};
+  for (int i = 0; i < n && i < 19 && out; ++i) out[i] = v[i];
+  return 19;
 }
 
 int64_t ca_plan_rows(const ca_plan_t *p, int32_t *rows, int32_t *pos) {
@@ -859,6 +1007,12 @@ int64_t ca_plan_bwd_pieces(const ca_plan_t *p, int32_t *units, int32_t *n_workgr
   return leading_fields(p->bwd_pieces, units, sizeof(ca::BwdUnit) / 4);
 }
 
+int64_t ca_plan_one_pass_units(const ca_plan_t *p, int32_t *units, int32_t *queue) {
+  if (!p) return 0;
+  if (queue) std::copy(std::begin(p->fused_queue), std::end(p->fused_queue), queue);
+  return leading_fields(p->fused_units, units, sizeof(ca::BwdUnit) / 4);
+}
+
 int64_t ca_plan_combine_units(const ca_plan_t *p, int32_t backward, int32_t *units) {
   return p ? leading_fields(backward ? p->bwd_combine : p->fwd_combine, units, sizeof(ca::CombineUnit) / 4) : 0;
 }
@@ -870,6 +1024,15 @@ int ca_plan_workspace_bytes_split(const ca_plan_t *p, size_t *fwd, size_t *bwd) 
   }
   if (fwd) *fwd = std::max(p->ws_fwd, p->ws_fwd_split);
   if (bwd) *bwd = p->ws_bwd_split;
+  return CA_OK;
+}
+
+int ca_plan_workspace_bytes_one_pass(const ca_plan_t *p, size_t *bwd) {
+  if (!p) {
+    ca::set_error("plan is null");
+    return CA_ERR_INVALID_ARG;
+  }
+  if (bwd) *bwd = p->ws_bwd_fused;
   return CA_OK;
 }
 

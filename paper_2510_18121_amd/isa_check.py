@@ -10,7 +10,7 @@ and verifies:
 2. transcendentals (`check_trans_use`): the instruction directly after a `v_exp_f32` (and its kin) does not read its
    result unless it is itself a transcendental or an `s_nop` (one wait state is required on this architecture).
 
-    python -m paper_2510_18121_amd.isa_check            # compiles csrc/ca_bwd.hip and csrc/ca_fwd.hip, prints findings
+    python -m paper_2510_18121_amd.isa_check            # compiles the attention kernels' sources, prints findings
 """
 from __future__ import annotations
 
@@ -108,7 +108,7 @@ def check_trans_use(asm: str):
 
 def main():
     status = 0
-    for src in ("ca_bwd.hip", "ca_fwd.hip"):
+    for src in ("ca_bwd.hip", "ca_bwd_fused.hip", "ca_fwd.hip"):
         asm = compile_to_asm(src)
         bad = assembly_vector_instructions(asm)
         print(f"{src}: {len(bad)} vector instructions in inline assembly")
