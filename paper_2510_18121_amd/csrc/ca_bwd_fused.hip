@@ -25,6 +25,7 @@
 // across the phases (S alone 1100 -> 480 cycles of a step), addresses are made with few scalar instructions (605 -> 503 instructions per
 // step, 174 -> 163 ms), the turn at dQ is taken early in dV (159 -> 157 ms).  128K tokens in shuffled shards, 32/8 heads, head_dim 128:
 // 177 ms in two kernels, 157 in this one (64K tokens of documents of about 2K: 8.3 -> 7.5 ms; last 1000 rows of 130K: 5.8 -> 5.2 ms).
+// Waves whose keys a block below the diagonal does not see only add dQ there (7.50 -> 7.35 ms on the 64K tokens).
 // Matrix pipe busy 48 % at 1.9 GHz (kernels of ca_bwd.hip: 62 %): what is left is barriers, LDS latency after them, waits for turns.
 // Tried and not kept: workgroups of 128 keys, two to a CU (187 ms: the sums move twice as often); half the waves adding dQ at the
 // start of a step and half at its end (+3 %); dK of a step after the next barrier (+4 %: nothing is left to cover the sums' loads).
@@ -174,6 +175,9 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     uint32_t off;
     issue_q(off), issue_do(off), issue_aux();
   }
+  // steps until the blocks, walked backwards, no longer see the wave's first key (looked up for the first 64 blocks)
+  const int unseen = lane < n_blocks && a.pos_kv[u.slot_begin + lane * BWD_BQ + BWD_BQ - 1] < u.key_pos0 + kw0;
+  const int n_seen = __builtin_amdgcn_readfirstlane(max(n_full, n_it - run_len * __builtin_popcountll(__ballot(unseen))));
   bf16x8 vf[NK][2];
 #pragma unroll
   for (int kg = 0; kg < 2; ++kg) {
@@ -260,6 +264,18 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   auto fetch_ds = [&](int ds_rd, int f) __attribute__((always_inline)) -> bf16x8 {
     const int t = (f % 2 == 0 ? ds_rd : ds_rd ^ 32) + 2048 * (f / 2);
     return join(lds_read_tr4_at(t), lds_read_tr4_at(t + 1024));
+  };
+  // dQ of the step before where nothing else is to be done
+  auto last_dq = [&]() __attribute__((always_inline)) {
+    const int ds_rd = ds_address();
+    bf16x8 g[4];
+    static_for<4>([&](auto f) __attribute__((always_inline)) { g[f] = fetch_ds(ds_rd, f); });
+    static_for<2 * W>([&](auto f) __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < NDW; ++i) dq[i][f % 2] = mfma16(kt[f / 2][i], g[f % 4], dq[i][f % 2]);
+      if constexpr (f + 4 < 2 * W) g[f % 4] = fetch_ds(ds_rd, f + 4);
+    });
   };
   auto store_dq = [&](const bool MAY_END) __attribute__((always_inline)) {
     if (!MAY_END || !prev_final) {
@@ -426,8 +442,21 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     });
   };
 
+  // ... of a step in which no row sees any of the wave's keys: dS is zero
+  auto idle = [&]() __attribute__((always_inline)) {
+    uint32_t off;
+    issue_q(off), issue_do(off), issue_aux();
+    wait_vmcnt<0>();
+    publish();
+    take_turn(-1);
+    const uint32_t ds_wr = lds0 + S::DS_OFF + dsb * S::DS_BYTES + kw0 * 64 + 16 * lane_id_here(), zero = opaque(0);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) *(CA_LDS u32x4 *)(uintptr_t)(ds_wr + 1024 * n) = u32x4{zero, zero, zero, zero};
+    last_dq();
+  };
+
   int it = 0;
-  auto step = [&](const bool MASK) __attribute__((always_inline)) {
+  auto step = [&](const bool MASK, const bool IDLE) __attribute__((always_inline)) {
     // the step's tiles have landed (this wave's part): younger are at most the stores of dQ of the step before the last
     if (!MASK && it > 1) wait_vmcnt<NQ>();
     else wait_vmcnt<0>();
@@ -438,7 +467,8 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
       live = sub_max >= u.key_pos0;                   // some row sees some key of the tile
       final = live && sub_max < u.key_pos0 + KEYS;    // no later tile adds to these rows
     }
-    compute(MASK);
+    if (IDLE) idle();
+    else compute(MASK);
     store_dq(MASK);
     prev = live ? tile : -1, prev_run = run, prev_final = final;
     dsb ^= 1;
@@ -448,18 +478,14 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     stage = stage == NST - 1 ? 0 : stage + 1;
     nb += adv, tb += adv, auxo += adv;
   };
-  for (; it < n_full; ++it) step(false);
-  for (; it < n_it; ++it) step(true);
+  for (; it < n_full; ++it) step(false, false);
+  for (; it < n_seen; ++it) step(true, false);
+  for (; it < n_it; ++it) step(true, true);
   wait_vmcnt<0>();
   publish();
   barrier_nofence();  // dS of the last step
   take_turn(-1);
-#pragma unroll
-  for (int f = 0; f < 2 * W; ++f) {
-    const bf16x8 g = fetch_ds(ds_address(), f);
-#pragma unroll
-    for (int i = 0; i < NDW; ++i) dq[i][f % 2] = mfma16(kt[f / 2][i], g, dq[i][f % 2]);
-  }
+  last_dq();
   store_dq(true);
   wait_vmcnt<0>();
   publish();
