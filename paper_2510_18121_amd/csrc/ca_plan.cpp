@@ -290,18 +290,26 @@ std::array<Cut, 2> best_piece(const std::vector<std::pair<int64_t, int64_t>> &un
 // little more evenly and are slower, as fewer of the sums of dQ are still in L2: 8.46 against 8.18 ms (64K tokens of documents
 // of about 2K, 32/8 heads), 31.5 against 30.9 ms (64K tokens of long documents, 64/8), 4.99 against 4.47 ms (lone 64-row shards, 8/2).
 //
+// At head_dim 64, with three workgroups per CU and short chains, groups are half as long again: 345 -> 319 us (16K tokens of documents
+// of about 2K, 16/16 heads); 128 would lose with that (7.25 -> 7.45 ms).
+//
 // When does the one pass pay?  It does five contractions instead of seven, but in workgroups of twice the keys (head_dim 128), one to a
 // CU, bound to queues.  A unit costs `fixed`, `per_step` for each 32 rows x head and `per_masked` where they hold the diagonal, and
 // starts at least `lag` after the one before it in its chain; the longest queue is simulated and compared with the simulation of the
-// other kernels.  Microseconds, fitted to 180 drawn batches.  On those the rule took 40 and all were faster, 1.00 to 1.3 times
-// (backward), and the best it left out gained 6 % (head_dim 128) or were shorter than the limit.  At 64 the simulation is less exact
-// (0.78 to 1.34 times at a predicted 1.05 to 1.2, with the diagonal at the price of other steps), so more is asked for.
+// other kernels.  Theirs knows only steps, so it is given the time by which moving K and V (read twice), dK and dV prolongs them: 0.4
+// of those bytes at the rate of partial results, from batches of short shards under long contexts (with it 12 measured at 1.03
+// to 1.2 of the simulation, without it at 1.15 to 1.7).  Microseconds, fitted to 330 drawn batches.  Of 139 of 500 others that the rule
+// takes (64 tokens x 2 heads up to 8 TFLOP of work), the two lists were 1.14 times slower on average (backward, geometric mean), and
+// none was faster by more than 2 %; the best that it left out gained 11 %.  (At 64: the diagonal's blocks of the heads of a
+// group cost more than is foreseen, hence the larger gain asked for.)
 struct FusedCost {
   int slots;  // workgroups per XCD
   double per_step, per_masked, fixed, lag;
-  double gain, min_us;  // what the one pass has to be faster by, and the least it is taken for
+  double groups;             // times over that a group of chains keeps the workgroups busy
+  double gain, more, least;  // the lists have to take `more` microseconds more than `gain` times the one pass; the least work worth a look
 };
-constexpr FusedCost FUSED_128 = {N_CU / N_XCD, 2.42, 3.3, 14.0, 4.0, 1.08, 1000}, FUSED_64 = {3 * N_CU / N_XCD, 2.05, 4.5, 13.0, 4.0, 1.12, 1500};
+constexpr FusedCost FUSED_128 = {N_CU / N_XCD, 2.42, 3.3, 12.0, 4.0, 2.0, 1.06, 40, 150},
+                    FUSED_64 = {3 * N_CU / N_XCD, 2.05, 5.5, 11.0, 4.0, 3.0, 1.095, 0, 150};
 
 class OnePass {
  public:
@@ -375,7 +383,7 @@ class OnePass {
       const Doc &d = docs_[chains_[q][c].doc];
       for (size_t t = d.first; t < d.first + d.n; ++t) group.push_back({steps(tiles_[t]), t, c});
       busy += std::min(double(d.n), 1.0 + cost_.per_step * double(steps(tiles_[d.first])) / cost_.lag);
-      if (busy < 2.0 * cost_.slots && c + 1 < chains_[q].size()) continue;
+      if (busy < cost_.groups * cost_.slots && c + 1 < chains_[q].size()) continue;
       std::stable_sort(group.begin(), group.end(), [&](const Entry &a, const Entry &b) {
         return a.steps != b.steps ? a.steps > b.steps : tiles_[a.tile].key_pos0 < tiles_[b.tile].key_pos0;
       });
@@ -547,6 +555,7 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   bool us_wanted = false;
   std::unique_ptr<OnePass> one_pass;
   double us_one_pass = 0;
+  double us_kv = 0;  // (see where it is set)
   double us_apart = 0, us_lists = 0;  // simulated time of the backward in two launches, and as the lists run it
   const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.65, 10.0, 5.0, 4} : CutCost{2 * N_CU, 1.75, 12.0, 5.0, 4};
   const double dq_per_tile = p->d == 128 ? 2.4 : 1.4, dq_fixed = 8.0;  // of the dQ kernel
@@ -774,7 +783,8 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
       for (const DocTiles &x : doc_tiles) n_tiles += double((x.len + keys - 1) / keys);
       for (const TileRef &t : ftiles) level += (dq_fixed + dq_per_tile * t.cost) * (hq / t.u.hp) / N_CU;
       const double in_steps = cost.per_step * 2.0 * double(p->bwd_steps) * BWD_BN / keys / (cost.slots * N_XCD);
-      if (in_steps >= cost.min_us && cost.gain * (in_steps + cost.fixed * n_tiles * hkv / (cost.slots * N_XCD)) < 1.2 * level &&
+      us_kv = 0.4 * 6.0 * double(p->total_kv) * hkv * p->d * 2 / BYTES_PER_US;
+      if (in_steps >= cost.least && cost.gain * (in_steps + cost.fixed * n_tiles * hkv / (cost.slots * N_XCD)) < 1.2 * (level + us_kv) &&
           size_t(padded) * size_t(hq) * size_t(p->d) * 4 <= UINT32_MAX) {
         std::vector<BwdUnit> tiles;
         for (const DocTiles &x : doc_tiles)
@@ -866,7 +876,8 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   }
   if (us_wanted) p->us_bwd = us_lists;
   // the one pass, where it is faster than the lists above
-  if (one_pass && us_lists > (p->d == 128 ? FUSED_128 : FUSED_64).gain * us_one_pass) one_pass->lay_out(p);
+  const FusedCost &cost_one_pass = p->d == 128 ? FUSED_128 : FUSED_64;
+  if (one_pass && us_lists + us_kv > cost_one_pass.gain * us_one_pass + cost_one_pass.more) one_pass->lay_out(p);
   p->q_covered = covered_q == p->total_q;
   p->kv_covered = covered_kv == p->total_kv;
   return more;

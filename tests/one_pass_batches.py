@@ -21,5 +21,8 @@ BATCHES = {
     "gaps_and_keys_nobody_sees": lambda: _documents([6001, 6000] * 3 + EDGES, 77, 16, 8, 128, extra_keys=301, gap=7),
     "windows": lambda: W.split_kv(W.custom([60001, 700, 33], [(0, 59338, 663), (1, 0, 700), (2, 0, 33)], 32, 8, 128), 2253)[0],
     "shards_d64": lambda: W.custom([90001, 89000] + EDGES, [(0, 87829, 2172), (1, 86828, 2172)] + [(2 + i, 0, n) for i, n in enumerate(EDGES)], 32, 8, 64),
+    # where moving K and V costs the other kernels much, and a short list at head_dim 64
+    "short_shards": lambda: W.shard_chunk(61, "distinct", seed=3, chunk_tokens=61 * 140, max_context=3000, hq=16, hkv=16, d=128),
+    "short_documents_d64": lambda: _documents([4001, 3000, 2049, 2048, 2047, 1900, 1500, 1024] + EDGES, 0x7fffffff, 16, 16, 64),
     "documents_d64": lambda: _documents([8001, 8000] * 3 + EDGES, 1029, 16, 16, 64),
 }
