@@ -28,7 +28,10 @@
 // Waves whose keys a block below the diagonal does not see only add dQ there (7.50 -> 7.35 ms on the 64K tokens).
 // Matrix pipe busy 48 % at 1.9 GHz (kernels of ca_bwd.hip: 62 %): what is left is barriers, LDS latency after them, waits for turns.
 // Tried and not kept: workgroups of 128 keys, two to a CU (187 ms: the sums move twice as often); half the waves adding dQ at the
-// start of a step and half at its end (+3 %); dK of a step after the next barrier (+4 %: nothing is left to cover the sums' loads).
+// start of a step and half at its end (+3 %); dK of a step after the next barrier (+4 %: nothing is left to cover the sums' loads), dQ
+// before dK (+3 %); polls by direct loads to LDS at the start of a step (+2 %: older values); every other run of 32 tiles walked
+// forwards (+2.5 %); the next unit's ticket and first tiles on their way before dK and dV are stored (+0.5 %; level on short units).
+// The pause between polls must stay: without it they take the L2 from everybody (5 to 40 times slower); longer ones change nothing.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
