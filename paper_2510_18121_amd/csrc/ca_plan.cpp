@@ -299,7 +299,7 @@ std::array<Cut, 2> best_piece(const std::vector<std::pair<int64_t, int64_t>> &un
 // other kernels.  Theirs knows only steps, so it is given the time by which moving K and V (read twice), dK and dV prolongs them: 0.4
 // of those bytes at the rate of partial results, from batches of short shards under long contexts (with it 12 measured at 1.03
 // to 1.2 of the simulation, without it at 1.15 to 1.7).  Microseconds, fitted to 330 drawn batches.  Of 139 of 500 others that the rule
-// takes (64 tokens x 2 heads up to 8 TFLOP of work), the two lists were 1.14 times slower on average (backward, geometric mean), and
+// takes (0.08 to 8 TFLOP of work), the two lists were 1.14 times slower on average (backward, geometric mean), and
 // none was faster by more than 2 %; the best that it left out gained 11 %.  (At 64: the diagonal's blocks of the heads of a
 // group cost more than is foreseen, hence the larger gain asked for.)
 struct FusedCost {
