@@ -92,9 +92,10 @@ struct FusedSmem {
 };
 
 constexpr int SC1 = 16;  // cache policy of a load of what other CUs of the XCD have written: not from this CU's vector L1
-// Polls (of about a microsecond) after which a wave no longer waits for its turn.  That cannot happen by the order in which units are
-// taken; if it does, dV of the unit becomes NaN.
-constexpr int MAX_POLLS = 1 << 20;
+// Polls (of about a microsecond) that a wave makes in all while it runs a unit.  By the order in which units are taken every turn comes
+// long before.  If one does not, the wave marks its additions as LOST from there on, whoever waits for them does the same, and
+// the last of them writes NaN to dQ: nobody goes on from a sum that lacks some.
+constexpr int MAX_POLLS = 1 << 22, LOST = -1;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *base_uniform, uint32_t bytes) {
   const uint64_t b = (uint64_t)(uintptr_t)base_uniform;
@@ -228,13 +229,13 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   int prev = -1, prev_run = 0;
   bool prev_final = false;
   int pending = -1;   // the tile whose additions are on their way, and not yet made known
-  bool lost = false;  // a turn did not come
+  int polls_left = MAX_POLLS;  // 0: a turn has not come
   int dsb = 0;        // which of the two dS buffers the step writes
   auto flag_at = [&](int t) __attribute__((always_inline)) { return (t * W + wave) * 4; };
   auto publish = [&]() __attribute__((always_inline)) {
     // (the stores have arrived in L2)
     if (pending >= 0) {
-      __builtin_amdgcn_raw_buffer_store_b32(opaque(order + 1), rf, 0, flag_at(pending), 0);  // (all lanes the same)
+      __builtin_amdgcn_raw_buffer_store_b32(opaque(polls_left > 0 ? order + 1 : LOST), rf, 0, flag_at(pending), 0);  // (all lanes the same)
       pending = -1;
     }
   };
@@ -244,15 +245,17 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   // this wave's turn at the tile of dQ: wait for the tile before in the order, then fetch the sums so far
   auto take_turn = [&](int seen) __attribute__((always_inline)) {
     if (order > 0 && prev >= 0 && __builtin_amdgcn_readfirstlane(seen) < order) {
-      for (int polls = 0;; ++polls) {
-        if (__builtin_amdgcn_readfirstlane(__builtin_amdgcn_raw_buffer_load_b32(rf, 0, flag_at(prev), SC1)) >= order) break;
-        if (lost || polls >= MAX_POLLS) {
-          lost = true;
-          acc_dv[0][0][0] = __builtin_nanf("");
+      for (; polls_left > 0; --polls_left) {
+        asm volatile("" ::: "memory");  // every poll is a load of its own
+        const int at = __builtin_amdgcn_readfirstlane(__builtin_amdgcn_raw_buffer_load_b32(rf, 0, flag_at(prev), SC1));
+        if (at >= order) break;
+        if (at == LOST) {
+          polls_left = 0;
           break;
         }
         __builtin_amdgcn_s_sleep(1);
       }
+      asm volatile("" ::: "memory");
     }
     const int il = lane_id_here() * 16;
 #pragma unroll
@@ -291,6 +294,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     } else {
       const int ol = lane_id_here(), rpk = BWD_BQ * u.heads / G;  // rows of a head in the tile: 64, or fewer where heads share it
       const int blk = prev / (2 * a.hq), at = run_len - prev_run;  // the step in its block
+      const float f = polls_left > 0 ? a.scale : __builtin_nanf("");
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
         const int tr = 32 * (at & 1) + 16 * rt + (ol & 15);
@@ -300,8 +304,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
           bf16_t *dst = a.dq + (size_t(row) * a.hq + head) * D + 16 * NDW * wave + 4 * (ol >> 4);
 #pragma unroll
           for (int i = 0; i < NDW; ++i)
-            *reinterpret_cast<u32x2 *>(dst + 16 * i) = u32x2{pack_bf16(dq[i][rt][0] * a.scale, dq[i][rt][1] * a.scale),
-                                                             pack_bf16(dq[i][rt][2] * a.scale, dq[i][rt][3] * a.scale)};
+            *reinterpret_cast<u32x2 *>(dst + 16 * i) = u32x2{pack_bf16(dq[i][rt][0] * f, dq[i][rt][1] * f), pack_bf16(dq[i][rt][2] * f, dq[i][rt][3] * f)};
         }
       }
     }
