@@ -55,12 +55,12 @@ __device__ __forceinline__ void static_for(F f) {
 }
 
 // The order in which a wave uses the fragments of a step: 4 NK of K and Q (S; two of 16 keys and two of 16 rows for 32 columns at a
-// time), 2 NK of dO (dP), ND of dO transposed (dV), ND of Q transposed (dK), 2 W of dS (dQ).  They come from LDS through a ring of
-// R fragments' registers, as far ahead as there is room beside what else is alive.
-template <int D>
+// time), 2 NK of dO (dP), ND of dO transposed (dV), ND of Q transposed (dK), 2 W of dS (dQ; apart from the ring in masked steps).  They
+// come from LDS through a ring of R fragments' registers, as far ahead as there is room beside what else is alive.
+template <int D, bool MASK>
 struct FusedRing {
   static constexpr int NK = D / 32, ND = D / 16;
-  static constexpr int DO = 4 * NK, DV = DO + 2 * NK, DK = DV + ND, DQ = DK + ND, N = DQ + 2 * fused_waves(D);
+  static constexpr int DO = 4 * NK, DV = DO + 2 * NK, DK = DV + ND, DQ = DK + ND, N = MASK ? DQ : DQ + 2 * fused_waves(D);
   static constexpr int R = 7, AHEAD_DP = 2, AHEAD = 4;
   // how many are there or on their way once `used` of them have been used
   static constexpr int fetched(int used) {
@@ -197,16 +197,20 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   for (int s = 0; s < NK; ++s) pin(vf[s][0]), pin(vf[s][1]);
   barrier_nofence();  // K is there
   bf16x8 kt[W][NDW];  // K transposed: the wave's columns of dQ, all keys
+  const auto kt_address = [&]() __attribute__((always_inline)) {
+    const int l = lane_id_here();
+    return int(lds0 + S::K_OFF + (l >> 2) * ROWB + 16 * (((l >> 1) & 1) ^ tile_sw<D>(l >> 2)) + 8 * (l & 1)) ^ (32 * NDW * wave);
+  };
+  auto fetch_kt = [&](int t0, int key, int i) __attribute__((always_inline)) -> bf16x8 {  // of keys `key` (a multiple of 32) .. + 31
+    const int t = (t0 ^ (32 * i)) + key * ROWB;
+    return join(lds_read_tr4_at(t), lds_read_tr4_at(t + HALF));
+  };
   {
-    const int t0 = (lds0 + S::K_OFF + (lane >> 2) * ROWB + 16 * (((lane >> 1) & 1) ^ tile_sw<D>(lane >> 2)) + 8 * (lane & 1)) ^ (32 * NDW * wave);
+    const int t0 = kt_address();
 #pragma unroll
     for (int ks = 0; ks < W; ++ks)
 #pragma unroll
-      for (int i = 0; i < NDW; ++i) {
-        const int t = (t0 ^ (32 * i)) + 32 * ks * ROWB;
-        kt[ks][i] = join(lds_read_tr4_at(t), lds_read_tr4_at(t + HALF));
-        pin(kt[ks][i]);
-      }
+      for (int i = 0; i < NDW; ++i) kt[ks][i] = fetch_kt(t0, 32 * ks, i), pin(kt[ks][i]);
   }
   int kb = lds0 + S::K_OFF + (kw0 + li) * ROWB + 16 * (j ^ tile_sw<D>(li));
   int nb = lds0 + li * ROWB + 16 * (j ^ tile_sw<D>(li));
@@ -225,9 +229,10 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   constexpr int DQ_TILE = FUSED_BQ * D * 4;
   auto dq_at = [&](int t) __attribute__((always_inline)) { return uint32_t(t) * DQ_TILE + wave * (NQ * 1024); };
   int tile = tile0, run = run_len;  // of the step
-  // dQ of the step before: its tile (-1: none), and whether this unit is the last to add to it
-  int prev = -1, prev_run = 0;
-  bool prev_final = false;
+  // dQ of the step before: its tile (-1: none), and the last of this unit's keys that its rows see (ALL_KEYS: some row sees a later
+  // one too; otherwise this unit is the last to add to the tile)
+  constexpr int ALL_KEYS = KEYS + 31;
+  int prev = -1, prev_run = 0, prev_seen = -1;
   int pending = -1;   // the tile whose additions are on their way, and not yet made known
   int polls_left = MAX_POLLS;  // 0: a turn has not come
   int dsb = 0;        // which of the two dS buffers the step writes
@@ -271,20 +276,45 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     const int t = (f % 2 == 0 ? ds_rd : ds_rd ^ 32) + 2048 * (f / 2);
     return join(lds_read_tr4_at(t), lds_read_tr4_at(t + 1024));
   };
-  // dQ of the step before where nothing else is to be done
-  auto last_dq = [&]() __attribute__((always_inline)) {
+  // Zeros do not mask a product with Inf or NaN.  So dQ leaves out the keys that none of a step's rows see, and dS of a key that its
+  // row does not see is zero whatever V holds.
+  // dQ of the step before from the 32 keys of which its rows see some
+  auto rest_of_dq = [&]() __attribute__((always_inline)) {
+    const int begin = (prev_seen + 1) & ~31;
+    if (begin > prev_seen) return;
+    const int at = ds_address() + 64 * begin;
+    const bf16x8 g[2] = {fetch_ds(at, 0), fetch_ds(at, 1)};
+    const int last = prev_seen - begin - 4 * (lane_id_here() >> 4);  // the lane holds keys 0 .. 3 and 16 .. 19 from here on
+#pragma unroll
+    for (int i = 0; i < NDW; ++i) {
+      u32x4 w = __builtin_bit_cast(u32x4, fetch_kt(kt_address(), begin, i));
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const int first = 16 * (n >> 1) + 2 * (n & 1);
+        w[n] = last > first ? w[n] : last == first ? w[n] & 0xffffu : 0u;
+      }
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) dq[i][rt] = mfma16(__builtin_bit_cast(bf16x8, w), g[rt], dq[i][rt]);
+    }
+  };
+  // dQ of the step before, whose rows may not see all keys
+  auto masked_dq = [&]() __attribute__((always_inline)) {
     const int ds_rd = ds_address();
     bf16x8 g[4];
     static_for<4>([&](auto f) __attribute__((always_inline)) { g[f] = fetch_ds(ds_rd, f); });
-    static_for<2 * W>([&](auto f) __attribute__((always_inline)) {
+    static_for<W>([&](auto ks) __attribute__((always_inline)) {
+      constexpr int at = 2 * ks % 4;
       __builtin_amdgcn_sched_barrier(0);
+      if (32 * ks + 31 <= prev_seen) {
 #pragma unroll
-      for (int i = 0; i < NDW; ++i) dq[i][f % 2] = mfma16(kt[f / 2][i], g[f % 4], dq[i][f % 2]);
-      if constexpr (f + 4 < 2 * W) g[f % 4] = fetch_ds(ds_rd, f + 4);
+        for (int i = 0; i < NDW; ++i) dq[i][0] = mfma16(kt[ks][i], g[at], dq[i][0]), dq[i][1] = mfma16(kt[ks][i], g[at + 1], dq[i][1]);
+      }
+      if constexpr (ks + 2 < W) g[at] = fetch_ds(ds_rd, 2 * ks + 4), g[at + 1] = fetch_ds(ds_rd, 2 * ks + 5);
     });
+    rest_of_dq();
   };
   auto store_dq = [&](const bool MAY_END) __attribute__((always_inline)) {
-    if (!MAY_END || !prev_final) {
+    if (!MAY_END || prev_seen == ALL_KEYS || prev < 0) {
       if (prev >= 0) {
         const int il = lane_id_here() * 16;
 #pragma unroll
@@ -311,8 +341,9 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   };
 
   // S, P, dP, dV, dS and dK of a step for the wave's keys, and dQ of the step before for its columns
-  auto compute = [&](const bool MASK) __attribute__((always_inline)) {
-    using F = FusedRing<D>;
+  auto compute = [&](auto mask) __attribute__((always_inline)) {
+    constexpr bool MASK = mask;
+    using F = FusedRing<D, MASK>;
     constexpr int R = F::R;
     bf16x8 fr[R];
     int ds_rd = 0;
@@ -373,7 +404,13 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     auto pack_pair = [&](int rt, int i) __attribute__((always_inline)) {
       const int e = 2 * (i & 1), kg = i >> 1;
       pw[kg][2 * rt + e / 2] = pack_bf16(sa[rt][kg][e], sa[rt][kg][e + 1]);
-      dw[kg][2 * rt + e / 2] = pack_bf16(sa[rt][kg][e] * pa[rt][kg][e], sa[rt][kg][e + 1] * pa[rt][kg][e + 1]);
+      float ds[2];
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        ds[n] = sa[rt][kg][e + n] * pa[rt][kg][e + n];
+        if (MASK) ds[n] = sa[rt][kg][e + n] == 0.f ? 0.f : ds[n];
+      }
+      dw[kg][2 * rt + e / 2] = pack_bf16(ds[0], ds[1]);
       asm volatile("" : "+v"(dw[kg][2 * rt + e / 2]));  // (here: not sunk to where dS is used, with S and dP alive until then)
     };
     static_for<2>([&](auto rt) __attribute__((always_inline)) {
@@ -440,7 +477,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
       }
       used(std::integral_constant<int, at>{}, one);
     });
-    static_for<2 * W>([&](auto f) __attribute__((always_inline)) {
+    if constexpr (!MASK) static_for<2 * W>([&](auto f) __attribute__((always_inline)) {
       constexpr int at = F::DQ + f;
 #pragma unroll
       for (int i = 0; i < NDW; ++i) dq[i][f % 2] = mfma16(kt[f / 2][i], fr[at % R], dq[i][f % 2]);
@@ -458,25 +495,25 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     const uint32_t ds_wr = lds0 + S::DS_OFF + dsb * S::DS_BYTES + kw0 * 64 + 16 * lane_id_here(), zero = opaque(0);
 #pragma unroll
     for (int n = 0; n < 2; ++n) *(CA_LDS u32x4 *)(uintptr_t)(ds_wr + 1024 * n) = u32x4{zero, zero, zero, zero};
-    last_dq();
   };
 
   int it = 0;
-  auto step = [&](const bool MASK, const bool IDLE) __attribute__((always_inline)) {
+  auto step = [&](auto mask, auto idles) __attribute__((always_inline)) {
+    constexpr bool MASK = mask, IDLE = idles;
     // the step's tiles have landed (this wave's part): younger are at most the stores of dQ of the step before the last
     if (!MASK && it > 1) wait_vmcnt<NQ>();
     else wait_vmcnt<0>();
     barrier_nofence();  // ... and everybody else's; everybody is done with the step before, whose dS is complete
-    bool live = true, final = false;
+    int seen = ALL_KEYS;  // the last key of the tile that some row sees
     if (MASK) {
-      const int sub_max = __builtin_amdgcn_readfirstlane(lds_ld<int>(lds0 + stage * S::STAGE + S::POS_OFF + (32 * ((run_len - run) & 1) + 31) * 4));
-      live = sub_max >= u.key_pos0;                   // some row sees some key of the tile
-      final = live && sub_max < u.key_pos0 + KEYS;    // no later tile adds to these rows
+      seen = __builtin_amdgcn_readfirstlane(lds_ld<int>(lds0 + stage * S::STAGE + S::POS_OFF + (32 * ((run_len - run) & 1) + 31) * 4)) - u.key_pos0;
+      if (seen >= KEYS) seen = ALL_KEYS;
     }
-    if (IDLE) idle();
-    else compute(MASK);
+    if constexpr (IDLE) idle();
+    else compute(mask);
+    if constexpr (MASK) masked_dq();
     store_dq(MASK);
-    prev = live ? tile : -1, prev_run = run, prev_final = final;
+    prev = seen >= 0 ? tile : -1, prev_run = run, prev_seen = seen;
     dsb ^= 1;
     ++tile;
     if (--run == 0) run = run_len, tile -= jump;
@@ -484,14 +521,14 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     stage = stage == NST - 1 ? 0 : stage + 1;
     nb += adv, tb += adv, auxo += adv;
   };
-  for (; it < n_full; ++it) step(false, false);
-  for (; it < n_seen; ++it) step(true, false);
-  for (; it < n_it; ++it) step(true, true);
+  for (; it < n_full; ++it) step(std::false_type{}, std::false_type{});
+  for (; it < n_seen; ++it) step(std::true_type{}, std::false_type{});
+  for (; it < n_it; ++it) step(std::true_type{}, std::true_type{});
   wait_vmcnt<0>();
   publish();
   barrier_nofence();  // dS of the last step
   take_turn(-1);
-  last_dq();
+  masked_dq();
   store_dq(true);
   wait_vmcnt<0>();
   publish();

@@ -93,3 +93,64 @@ def test_timing_and_smaller_workspaces():
     for x, y in zip(less, want):
         assert (x.float() - y.float()).norm() <= 1e-2 * y.float().norm()
     assert B.alloc_workspace(p, DEV).numel() >= one
+
+
+def _poisoned(b, x, rows, value):
+    x = x.clone()
+    x[rows] = value
+    return x
+
+
+def _backward(p, q, k, v, o, d_o, lse, n_bytes):
+    out = [torch.full_like(x, 7.0) for x in (q, k, v)]
+    B.ca_backward(p, q, k, v, o, d_o, lse, *out, torch.full((n_bytes,), 0x5A, dtype=torch.uint8, device=DEV))
+    return out
+
+
+@pytest.mark.parametrize("name", ["gaps_and_keys_nobody_sees", "shards_d64"])
+def test_keys_that_nobody_sees_may_hold_anything(name):
+    """NaN or Inf in K and V behind a document's last query: every gradient as with finite values there, zero for those keys."""
+    b, p, (q, k, v, d_o), o, lse, one, base, run = _setup(name)
+    if name == "shards_d64":  # (this batch has no such keys: the same queries without the last rows of each document)
+        n = b.task_q_len.copy()
+        n[n > 40] -= 37
+        b = W.custom(b.doc_kv_len.tolist(), list(zip(b.task_doc.tolist(), b.task_q_pos.tolist(), n.tolist())), b.n_q_heads, b.n_kv_heads, b.head_dim)
+        q, k, v, d_o = W.make_tensors(b, DEV)
+        p = B.ca_plan(b)
+        o, lse = torch.zeros_like(q), torch.zeros(b.n_q_heads, b.total_q, device=DEV)
+        B.ca_forward(p, q, k, v, o, lse)
+        one = p.workspace_bytes_one_pass()
+        assert one > 0
+    unseen = torch.ones(b.total_kv, dtype=torch.bool, device=DEV)
+    for t in range(b.n_tasks):
+        at = int(b.doc_kv_start[b.task_doc[t]])
+        unseen[at:at + int(b.task_q_pos[t] + b.task_q_len[t])] = False
+    assert unseen.any()
+    want = _backward(p, q, k, v, o, d_o, lse, one)
+    for value in (float("nan"), float("inf")):
+        for kk, vv in ((_poisoned(b, k, unseen, value), v), (k, _poisoned(b, v, unseen, value))):
+            got = _backward(p, q, kk, vv, o, d_o, lse, one)
+            for x, y in zip(got, want):
+                assert torch.equal(x, y)
+            assert not got[1][unseen].any() and not got[2][unseen].any()
+
+
+@pytest.mark.parametrize("what", ["k", "v"])
+@pytest.mark.parametrize("name", ["documents", "gaps_and_keys_nobody_sees", "windows", "documents_d64"])
+def test_non_finite_rows_reach_no_further_than_in_whole_units(name, what):
+    """One NaN key or value in every document: what is finite from whole units is the same bits here."""
+    b, p, (q, k, v, d_o), o, lse, one, base, run = _setup(name)
+    x = {"q": q, "k": k, "v": v, "d_o": d_o}
+    rows = []
+    for d in sorted(set(b.task_doc.tolist())):
+        tasks = [t for t in range(b.n_tasks) if b.task_doc[t] == d]
+        t = tasks[len(tasks) * 2 // 3]
+        at = (7 * d + 13) % int(b.task_q_len[t])
+        rows.append(int(b.task_q_start[t]) + at if what in ("q", "d_o") else int(b.doc_kv_start[d] + min(b.task_q_pos[t] + at, b.task_kv_len[t] - 1)))
+    x[what] = _poisoned(b, x[what], torch.tensor(rows, device=DEV), float("nan"))
+    args = (x["q"], x["k"], x["v"], o, x["d_o"], lse)
+    whole, got = _backward(p, *args, base), _backward(p, *args, one)
+    for w, g in zip(whole, got):
+        finite = torch.isfinite(w)
+        assert finite.any() and torch.equal(g[finite], w[finite])
+    assert not all(torch.isfinite(w).all() for w in whole)
