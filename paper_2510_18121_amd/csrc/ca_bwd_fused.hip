@@ -61,7 +61,7 @@ template <int D, bool MASK>
 struct FusedRing {
   static constexpr int NK = D / 32, ND = D / 16;
   static constexpr int DO = 4 * NK, DV = DO + 2 * NK, DK = DV + ND, DQ = DK + ND, N = MASK ? DQ : DQ + 2 * fused_waves(D);
-  static constexpr int R = 7, AHEAD_DP = 2, AHEAD = 4;
+  static constexpr int R = MASK ? 6 : 7, AHEAD_DP = 2, AHEAD = MASK ? 3 : 4;
   // how many are there or on their way once `used` of them have been used
   static constexpr int fetched(int used) {
     if (used <= DO) return used + R < DO + AHEAD_DP ? used + R : DO + AHEAD_DP;
@@ -341,7 +341,8 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   };
 
   // S, P, dP, dV, dS and dK of a step for the wave's keys, and dQ of the step before for its columns
-  auto compute = [&](auto mask) __attribute__((always_inline)) {
+  // (sees: some row of the step sees some key of the wave's)
+  auto compute = [&](auto mask, const bool sees) __attribute__((always_inline)) {
     constexpr bool MASK = mask;
     using F = FusedRing<D, MASK>;
     constexpr int R = F::R;
@@ -367,6 +368,13 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     auto fetch_range = [&](auto from, auto to) __attribute__((always_inline)) {
       static_for<to - from>([&](auto i) __attribute__((always_inline)) { fr[(from + i) % R] = fetch(from + i); });
       __builtin_amdgcn_sched_barrier(0);
+    };
+    // a fragment of Q or dO transposed, or zeros: rows that see none of the wave's keys may hold Inf or NaN as well
+    auto rows_seen = [&](const bf16x8 &x) __attribute__((always_inline)) {
+      u32x4 w = __builtin_bit_cast(u32x4, x);
+#pragma unroll
+      for (int n = 0; n < 4; ++n) w[n] = !MASK || sees ? w[n] : 0u;
+      return __builtin_bit_cast(bf16x8, w);
     };
     // fragments at .. at + n - 1 have been used
     auto used = [&](auto at, auto n) __attribute__((always_inline)) {
@@ -450,7 +458,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     static_for<ND>([&](auto b) __attribute__((always_inline)) {
       constexpr int at = F::DV + b;
 #pragma unroll
-      for (int kg = 0; kg < 2; ++kg) acc_dv[b][kg] = mfma16(fr[at % R], pb[kg], acc_dv[b][kg]);
+      for (int kg = 0; kg < 2; ++kg) acc_dv[b][kg] = mfma16(rows_seen(fr[at % R]), pb[kg], acc_dv[b][kg]);
       used(std::integral_constant<int, at>{}, one);
       if (b == 0) {
         wait_vmcnt<0>();
@@ -465,7 +473,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     static_for<ND>([&](auto b) __attribute__((always_inline)) {
       constexpr int at = F::DK + b;
 #pragma unroll
-      for (int kg = 0; kg < 2; ++kg) acc_dk[b][kg] = mfma16(fr[at % R], db[kg], acc_dk[b][kg]);
+      for (int kg = 0; kg < 2; ++kg) acc_dk[b][kg] = mfma16(rows_seen(fr[at % R]), db[kg], acc_dk[b][kg]);
       if (b == 0) {
         const int wl = lane_id_here();
         const uint32_t ds_wr = lds0 + S::DS_OFF + dsb * S::DS_BYTES + (kw0 + (wl & 15)) * 64 + 8 * ((wl >> 4) ^ (wl & 4) ^ ((wl >> 2) & 2));
@@ -510,7 +518,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
       if (seen >= KEYS) seen = ALL_KEYS;
     }
     if constexpr (IDLE) idle();
-    else compute(mask);
+    else compute(mask, seen >= kw0);
     if constexpr (MASK) masked_dq();
     store_dq(MASK);
     prev = seen >= 0 ? tile : -1, prev_run = run, prev_seen = seen;

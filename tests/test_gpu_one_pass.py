@@ -135,10 +135,10 @@ def test_keys_that_nobody_sees_may_hold_anything(name):
             assert not got[1][unseen].any() and not got[2][unseen].any()
 
 
-@pytest.mark.parametrize("what", ["k", "v"])
+@pytest.mark.parametrize("what", ["k", "v", "q", "d_o"])
 @pytest.mark.parametrize("name", ["documents", "gaps_and_keys_nobody_sees", "windows", "documents_d64"])
 def test_non_finite_rows_reach_no_further_than_in_whole_units(name, what):
-    """One NaN key or value in every document: what is finite from whole units is the same bits here."""
+    """One NaN row of Q or dO, or key or value, in every document: what is finite from whole units is the same bits here."""
     b, p, (q, k, v, d_o), o, lse, one, base, run = _setup(name)
     x = {"q": q, "k": k, "v": v, "d_o": d_o}
     rows = []
