@@ -13,7 +13,6 @@
 #include <functional>
 #include <memory>
 #include <numeric>
-#include <queue>
 #include <sstream>
 
 #include "ca_internal.h"
@@ -133,6 +132,19 @@ struct CutCost {
   int min_steps;
 };
 
+// The least of a heap (the least on top) becomes t, which is no less, and sinks.
+inline void replace_top(std::vector<double> &heap, double t) {
+  const size_t n = heap.size();
+  size_t at = 0;
+  for (size_t c = 1; c < n; c = 2 * at + 1) {
+    if (c + 1 < n && heap[c + 1] < heap[c]) ++c;
+    if (heap[c] >= t) break;
+    heap[at] = heap[c];
+    at = c;
+  }
+  heap[at] = t;
+}
+
 // When the last of `units` ((microseconds, how many), handed out in this order) ends on n_cu CUs, or a time of at least
 // at_most.  A list of more than max_units is simulated with 2, 4, .. neighbours of it as one unit (of their mean length) on as
 // many times fewer CUs: neighbours are of nearly equal length.
@@ -161,14 +173,7 @@ double makespan(const std::vector<std::pair<double, int64_t>> &units, int64_t n_
         end = t;
         if (end >= at_most) return end;
       }
-      size_t at = 0;  // the top takes the unit and sinks
-      for (size_t c = 1; c < n_busy; c = 2 * at + 1) {
-        if (c + 1 < n_busy && busy[c + 1] < busy[c]) ++c;
-        if (busy[c] >= t) break;
-        busy[at] = busy[c];
-        at = c;
-      }
-      busy[at] = t;
+      replace_top(busy, t);
     }
     held = held + count - n * q;
     held_us = n > 0 ? double(held) * unit_us : held_us + double(count) * unit_us;
@@ -315,9 +320,12 @@ class OnePass {
  public:
   // tiles: KV tiles, document by document, each document's from its first key on
   OnePass(const ca_plan_t &plan, std::vector<BwdUnit> kv_tiles) : cost_(plan.d == 128 ? FUSED_128 : FUSED_64), tiles_(std::move(kv_tiles)), hkv_(plan.hkv) {
+    key_.reserve(tiles_.size());
     for (size_t t = 0; t < tiles_.size(); ++t) {
+      const int64_t n = steps(tiles_[t]);
+      key_.push_back(uint64_t(UINT32_MAX - n) << 32 | uint32_t(tiles_[t].key_pos0));
       if (tiles_[t].key_pos0 == 0) docs_.push_back({t, 0, 0});
-      ++docs_.back().n, docs_.back().steps += steps(tiles_[t]);
+      ++docs_.back().n, docs_.back().steps += n;
     }
     std::stable_sort(docs_.begin(), docs_.end(), [](const Doc &a, const Doc &b) { return a.steps > b.steps; });
     std::array<int64_t, N_XCD> load{};
@@ -329,26 +337,29 @@ class OnePass {
       }
     longest_ = size_t(std::max_element(load.begin(), load.end()) - load.begin());
   }
-  // when the longest queue ends
-  double time() const {
+  // when the longest queue ends, or at_most where that would be later
+  double time(double at_most) const {
+    double all = 0;  // no order ends before the mean load
+    for (const Chain &c : chains_[longest_])
+      for (size_t t = docs_[c.doc].first, end = t + docs_[c.doc].n; t < end; ++t) all += us(tiles_[t]);
+    if (all / cost_.slots >= at_most) return at_most;
     double end = 0;
     std::vector<double> begun(chains_[longest_].size(), -cost_.lag);  // the last unit of each chain
-    std::priority_queue<double, std::vector<double>, std::greater<double>> slots;
-    for (int i = 0; i < cost_.slots; ++i) slots.push(0.0);
+    std::vector<double> slots(size_t(cost_.slots), 0.0);
     each_unit(longest_, [&](const Entry &e) {
-      const BwdUnit &u = tiles_[e.tile];
-      const double at = std::max(slots.top(), begun[e.chain] + cost_.lag), masked = double((u.slot_full - u.slot_begin) / FUSED_BQ * u.heads);
-      const double us = cost_.fixed + cost_.per_step * double(e.steps) + (cost_.per_masked - cost_.per_step) * masked;
-      slots.pop(), slots.push(at + us);
-      begun[e.chain] = at, end = std::max(end, at + us);
+      const double at = std::max(slots[0], begun[e.chain] + cost_.lag), t = at + us(tiles_[e.tile]);
+      replace_top(slots, t);
+      begun[e.chain] = at, end = std::max(end, t);
     });
-    return end;
+    return std::min(end, at_most);
   }
   void lay_out(ca_plan_t *p) const {
+    p->fused_units.reserve(tiles_.size() * size_t(hkv_));
     for (size_t q = 0; q < N_XCD; ++q) {
       each_unit(q, [&](const Entry &e) {
-        p->fused_units.push_back(tiles_[e.tile]);
-        p->fused_units.back().kv_head = chains_[q][e.chain].head, p->fused_units.back().count = 1;
+        BwdUnit u = tiles_[e.tile];
+        u.kv_head = chains_[q][e.chain].head, u.count = 1;
+        p->fused_units.push_back(u);
       });
       p->fused_queue[q + 1] = int32_t(p->fused_units.size());
     }
@@ -371,29 +382,45 @@ class OnePass {
     int32_t head;
   };
   struct Entry {
-    int64_t steps;
-    size_t tile, chain;
+    uint64_t key;
+    uint32_t tile, chain;
   };
   static int64_t steps(const BwdUnit &u) { return int64_t(u.slot_end - u.slot_begin) / FUSED_BQ * u.heads; }
+  double us(const BwdUnit &u) const {
+    const double masked = double((u.slot_full - u.slot_begin) / FUSED_BQ * u.heads);
+    return cost_.fixed + cost_.per_step * double(steps(u)) + (cost_.per_masked - cost_.per_step) * masked;
+  }
+  // Inside a group by key_: the longer unit first, of equal ones the one of the earlier keys, then the earlier chain's.  A chain's tiles
+  // are in that order already, so its chains are merged.  (Sorting made up most of what laying out tens of thousands of units takes.)
   template <class F>
   void each_unit(size_t q, F f) const {
-    std::vector<Entry> group;
-    double busy = 0;  // workgroups that the group's chains can keep busy
+    std::vector<Entry> group, merged;
+    std::vector<size_t> runs{0}, fewer;  // where a sorted run begins, and the end
+    double busy = 0;                     // workgroups that the group's chains can keep busy
     for (size_t c = 0; c < chains_[q].size(); ++c) {
       const Doc &d = docs_[chains_[q][c].doc];
-      for (size_t t = d.first; t < d.first + d.n; ++t) group.push_back({steps(tiles_[t]), t, c});
+      for (size_t t = d.first; t < d.first + d.n; ++t) group.push_back({key_[t], uint32_t(t), uint32_t(c)});
+      runs.push_back(group.size());
       busy += std::min(double(d.n), 1.0 + cost_.per_step * double(steps(tiles_[d.first])) / cost_.lag);
       if (busy < cost_.groups * cost_.slots && c + 1 < chains_[q].size()) continue;
-      std::stable_sort(group.begin(), group.end(), [&](const Entry &a, const Entry &b) {
-        return a.steps != b.steps ? a.steps > b.steps : tiles_[a.tile].key_pos0 < tiles_[b.tile].key_pos0;
-      });
+      while (runs.size() > 2) {
+        merged.resize(group.size());
+        fewer.assign(1, 0);
+        for (size_t r = 0; r + 1 < runs.size(); r += 2) {
+          const auto at = [&](size_t i) { return group.begin() + std::ptrdiff_t(runs[std::min(i, runs.size() - 1)]); };
+          std::merge(at(r), at(r + 1), at(r + 1), at(r + 2), merged.begin() + std::ptrdiff_t(runs[r]), [](const Entry &a, const Entry &b) { return a.key < b.key; });
+          fewer.push_back(runs[std::min(r + 2, runs.size() - 1)]);
+        }
+        group.swap(merged), runs.swap(fewer);
+      }
       for (const Entry &e : group) f(e);
-      group.clear(), busy = 0;
+      group.clear(), runs.assign(1, 0), busy = 0;
     }
   }
 
   const FusedCost &cost_;
   std::vector<BwdUnit> tiles_;
+  std::vector<uint64_t> key_;
   const int hkv_;
   std::vector<Doc> docs_;
   std::array<std::vector<Chain>, N_XCD> chains_;
@@ -445,13 +472,14 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
     if (k0 < x.cover) {
       // first slot whose position can see key k0
       const int32_t *b = p->slot_pos.data() + x.s0, *e = p->slot_pos.data() + x.s1;
-      int64_t first = std::lower_bound(b, e, k0) - b;
+      int64_t first = *b >= k0 ? 0 : std::lower_bound(b, e, k0) - b;  // (a shard behind all of them: no search)
       first = first / BWD_BQ * BWD_BQ;
       int64_t end = x.s1;
       while (end - BWD_BQ >= x.s0 + first && p->slot_row[end - BWD_BQ] < 0) end -= BWD_BQ;  // drop pure-padding blocks
       u.slot_begin = int32_t(x.s0 + first);
       u.slot_end = int32_t(end);
-      int64_t full = std::lower_bound(b, e, k0 + keys - 1 + beyond) - b;
+      const int32_t last = k0 + keys - 1 + beyond;
+      int64_t full = *b >= last ? 0 : std::lower_bound(b, e, last) - b;
       full = (full + BWD_BQ - 1) / BWD_BQ * BWD_BQ;
       u.slot_full = int32_t(std::min<int64_t>(std::max<int64_t>(x.s0 + full, u.slot_begin), end));
     }
@@ -553,9 +581,8 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   std::array<size_t, 2> limits{};
   bool more = false;
   bool us_wanted = false;
-  std::unique_ptr<OnePass> one_pass;
-  double us_one_pass = 0;
-  double us_kv = 0;  // (see where it is set)
+  bool one_pass = false;  // worth a look
+  double us_kv = 0;       // (see where it is set)
   double us_apart = 0, us_lists = 0;  // simulated time of the backward in two launches, and as the lists run it
   const CutCost cost_dkv = p->d == 128 ? CutCost{N_CU, 1.65, 10.0, 5.0, 4} : CutCost{2 * N_CU, 1.75, 12.0, 5.0, 4};
   const double dq_per_tile = p->d == 128 ? 2.4 : 1.4, dq_fixed = 8.0;  // of the dQ kernel
@@ -785,13 +812,8 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
       const double in_steps = cost.per_step * 2.0 * double(p->bwd_steps) * BWD_BN / keys / (cost.slots * N_XCD);
       us_kv = 0.4 * 6.0 * double(p->total_kv) * hkv * p->d * 2 / BYTES_PER_US;
       if (in_steps >= cost.least && cost.gain * (in_steps + cost.fixed * n_tiles * hkv / (cost.slots * N_XCD)) < 1.2 * (level + us_kv) &&
-          size_t(padded) * size_t(hq) * size_t(p->d) * 4 <= UINT32_MAX) {
-        std::vector<BwdUnit> tiles;
-        for (const DocTiles &x : doc_tiles)
-          for (int32_t k0 = 0; k0 < x.len; k0 += keys) tiles.push_back(kv_tile(x, k0, keys, 1));  // (1: another tile adds to their dQ)
-        one_pass = std::make_unique<OnePass>(*p, std::move(tiles));
-        us_one_pass = one_pass->time();
-      }
+          size_t(padded) * size_t(hq) * size_t(p->d) * 4 <= UINT32_MAX)
+        one_pass = true;
     }
     const bool may_join = mean < (p->d == 128 ? JOINT_MAX_US : JOINT_MAX_US_64);
     const bool wanted = may_join || p->pieces_lost || beyond_static;
@@ -812,23 +834,24 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
       for (size_t i = 0; i < wg_steps.size(); ++i) {
         const double us = cost_dkv.fixed + cost_dkv.per_step * double(wg_steps[i]);
         dkv.push_back({us, hkv / same});
-        groups.push_back({us, hkv, int32_t(i) * hkv, 1});
+        if (may_join) groups.push_back({us, hkv, int32_t(i) * hkv, 1});
         sum += us * hkv;
         longest = std::max(longest, us);
       }
       const double per_half = p->d == 128 ? 1.2 : 1.4, fixed_half = p->d == 128 ? 4.0 : 7.0;
-      for (int32_t half = 1; half >= 0; --half)
-        for (int32_t i = 0; i < n_dq;) {
+      for (int32_t half = 1; half >= (may_join ? 0 : 1); --half)
+        for (int32_t i = 0, n; i < n_dq; i += n) {
           const FwdUnit &u = units[size_t(i)];
-          const int32_t n = hq / u.hp, tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
+          const int32_t tiles = (u.n_keys + FWD_BN - 1) / FWD_BN;
+          n = hq / u.hp;
           if (half == 1) dq.push_back({dq_fixed + dq_per_tile * tiles, n / same});
+          if (!may_join) continue;
           // the tiles the half's rows see (its last slot has its highest position)
           const int32_t last = p->slot_pos[size_t(u.slot0 + ((4 * half + 3) / u.hp) * 32 + 31)] - u.key0;
           const double us = fixed_half + per_half * std::max(1, std::min(tiles, last / FWD_BN + 1));
           groups.push_back({us, n, -1 - (half * n_dq + i), -1});
           sum += us * n;
           longest = std::max(longest, us);
-          i += n;
         }
       const double parts_us = p->n_fwd_parts + p->n_bwd_parts > 0
                                   ? cost_dkv.launch + double(size_t(p->n_fwd_parts + p->n_bwd_parts) * part_bytes(p->d)) / BYTES_PER_US
@@ -876,8 +899,19 @@ bool schedule(ca_plan_t *p, bool beyond_static) {
   }
   if (us_wanted) p->us_bwd = us_lists;
   // the one pass, where it is faster than the lists above
-  const FusedCost &cost_one_pass = p->d == 128 ? FUSED_128 : FUSED_64;
-  if (one_pass && us_lists + us_kv > cost_one_pass.gain * us_one_pass + cost_one_pass.more) one_pass->lay_out(p);
+  if (one_pass) {
+    const FusedCost &cost = p->d == 128 ? FUSED_128 : FUSED_64;
+    const int32_t keys = 32 * fused_waves(p->d);
+    size_t n_tiles = 0;
+    for (const DocTiles &x : doc_tiles) n_tiles += size_t((x.len + keys - 1) / keys);
+    std::vector<BwdUnit> tiles;
+    tiles.reserve(n_tiles);
+    for (const DocTiles &x : doc_tiles)
+      for (int32_t k0 = 0; k0 < x.len; k0 += keys) tiles.push_back(kv_tile(x, k0, keys, 1));  // (1: another tile adds to their dQ)
+    const OnePass pass(*p, std::move(tiles));
+    const double at_most = (us_lists + us_kv - cost.more) / cost.gain;
+    if (pass.time(at_most) < at_most) pass.lay_out(p);
+  }
   p->q_covered = covered_q == p->total_q;
   p->kv_covered = covered_kv == p->total_kv;
   return more;

@@ -37,6 +37,21 @@ def test_chains(name):
     assert np.array_equal(seen, np.repeat(held[:, None], b.n_kv_heads, 1))
 
 
+@pytest.mark.parametrize("name", sorted(BATCHES))
+def test_longest_first_inside_groups_of_chains(name):
+    """A queue's units: longest first, of equal ones those of the earlier keys; where that starts again, only new chains follow."""
+    units, queue = B.ca_plan_host(BATCHES[name]()).one_pass_units()
+    for q in range(8):
+        done, group, last = set(), set(), None
+        for begin, end, full, row, n, k0, h, follow, count, heads in units[queue[q]:queue[q + 1]].tolist():
+            key = (-(end - begin) * heads, k0)
+            if last is not None and key < last:
+                done, group = done | group, set()
+            group.add((row - k0, h))
+            assert (row - k0, h) not in done
+            last = key
+
+
 def test_workspace():
     """Sums of dQ and a counter per wave and 32 rows lie behind what whole units need; small batches have no one pass."""
     b = BATCHES["documents"]()
