@@ -41,11 +41,11 @@ class AttentionServer:
         o.backward(d_o)                          # q.grad, k.grad, v.grad
 
     `batch` is any object with the descriptor's fields (e.g. workloads.Batch).  Rows of q that belong to no task
-    have undefined output and zero gradient."""
+    have undefined output and zero gradient.  one_pass: see binding.alloc_workspace."""
 
-    def __init__(self, batch, device="cuda"):
+    def __init__(self, batch, device="cuda", one_pass=None):
         self.plan = B.ca_plan(batch)
-        self.ws = B.alloc_workspace(self.plan, device)
+        self.ws = B.alloc_workspace(self.plan, device, one_pass)
         self.fwd_ws_bytes = self.plan.workspace_bytes_split()[0]
 
     def __call__(self, q, k, v):

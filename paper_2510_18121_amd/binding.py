@@ -305,18 +305,30 @@ def _scratch(preferred, needed, device):
     return torch.empty(needed, dtype=torch.uint8, device=device) if needed else None
 
 
-def alloc_workspace(plan: Plan, device="cuda"):
-    """A torch uint8 buffer big enough for both calls, with room for the partial results of units cut into pieces, or for a
-    backward in one pass, where the device has it (torch's allocator returns 256-byte aligned blocks).  Both calls write to it:
-    calls that may overlap in time need one each."""
+def _room_for_sums(n_bytes, device):
+    """Whether n_bytes are at most an eighth of the device memory that nobody holds."""
     import torch
-    one_pass = plan.workspace_bytes_one_pass()
-    if one_pass:
+    if torch.device(device).type != "cuda" or torch.cuda.is_current_stream_capturing():
+        return True
+    unused = torch.cuda.memory_reserved(device) - torch.cuda.memory_allocated(device)  # in torch's cache
+    return n_bytes <= (torch.cuda.mem_get_info(device)[0] + unused) // 8
+
+
+def alloc_workspace(plan: Plan, device="cuda", one_pass=None):
+    """A torch uint8 buffer big enough for both calls, with room for the partial results of units cut into pieces, or for a
+    backward in one pass (torch's allocator returns 256-byte aligned blocks).  The one pass about doubles the buffer: one_pass says
+    whether it may; by default where what it adds is at most an eighth of the device memory that is free, so that what the
+    program allocates later goes on fitting.  Where the device has no room for the larger buffer it is the smaller one.  Both calls
+    write to it: calls that may overlap in time need one each."""
+    import torch
+    needed, split = max(*plan.workspace_bytes(), 256), max(*plan.workspace_bytes_split(), 256)
+    sums = plan.workspace_bytes_one_pass() if one_pass is None or one_pass else 0
+    if sums and (one_pass or _room_for_sums(sums - needed, device)):
         try:
-            return torch.empty(max(one_pass, *plan.workspace_bytes_split()), dtype=torch.uint8, device=device)
+            return torch.empty(max(sums, split), dtype=torch.uint8, device=device)
         except torch.cuda.OutOfMemoryError:
             pass
-    return _scratch(max(*plan.workspace_bytes_split(), 256), max(*plan.workspace_bytes(), 256), device)
+    return _scratch(split, needed, device)
 
 
 def ca_merge_partials(part_rows, o_part, lse_part, o, lse, o_back=None, lse_back=None, stream=None):

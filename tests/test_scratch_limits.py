@@ -5,6 +5,7 @@ import types
 import pytest
 import torch
 
+from one_pass_batches import BATCHES
 from paper_2510_18121_amd import autograd as A
 from paper_2510_18121_amd import binding as B
 from paper_2510_18121_amd import workloads as W
@@ -35,6 +36,28 @@ def test_workspace_without_room_for_partial_results(limit):
     limit["bytes"] = base - 1
     with pytest.raises(torch.cuda.OutOfMemoryError):
         B.alloc_workspace(plan)
+
+
+def test_one_pass_leaves_memory_to_others(limit, monkeypatch):
+    """The workspace holds the one pass's sums where they take at most an eighth of what is free, or where the caller says so."""
+    plan = B.ca_plan_host(BATCHES["documents"]())
+    base, split, one = max(plan.workspace_bytes()), max(plan.workspace_bytes_split()), plan.workspace_bytes_one_pass()
+    assert base < one
+    box = {"free": 0, "reserved": 1 << 30, "allocated": 1 << 30}
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+    monkeypatch.setattr(torch.cuda, "mem_get_info", lambda device=None: (box["free"], 288 << 30))
+    monkeypatch.setattr(torch.cuda, "memory_reserved", lambda device=None: box["reserved"])
+    monkeypatch.setattr(torch.cuda, "memory_allocated", lambda device=None: box["allocated"])
+    box["free"] = 8 * (one - base)
+    assert B.alloc_workspace(plan).numel() == max(one, split)
+    box["free"] -= 1
+    assert B.alloc_workspace(plan).numel() == split
+    assert B.alloc_workspace(plan, one_pass=True).numel() == max(one, split)
+    box["allocated"] -= 1  # what torch holds for itself counts as free
+    assert B.alloc_workspace(plan).numel() == max(one, split)
+    assert B.alloc_workspace(plan, one_pass=False).numel() == split
+    limit["bytes"] = max(one, split) - 1
+    assert B.alloc_workspace(plan, one_pass=True).numel() == split
 
 
 def test_forward_without_room_for_partial_results(limit, monkeypatch):
