@@ -20,11 +20,17 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA peak
 
-# HBM bytes per launch of the one-pass backward kernel on workload 3 as counted by rocprofv3 (FETCH_SIZE / WRITE_SIZE passes,
+# HBM bytes per launch of the backward's main kernel on workload 3 as counted by rocprofv3 (FETCH_SIZE / WRITE_SIZE passes,
 # scaled by the plain-copy calibration): NOT measured in a plain run of this script.  The figure of the last counter
-# passes is quoted under roofline.traffic_profiled with the file it comes from; roofline.traffic itself is null.
-DKV_TRAFFIC_PROFILED = {"bytes": int((214.3 + 130.5) * 2**30), "workload": 3,
-                        "source": "profiles/hot_path_cfg3_hbm_traffic.md"}
+# passes over the kernel that ran is quoted under roofline.traffic_profiled with the file it comes from; roofline.traffic itself is null.
+TRAFFIC_PROFILED_GIB = {"ca_bwd_fused_kernel": 214.3 + 130.5, "ca_bwd_dkv_kernel": 184.8 + 0.50}
+
+
+def traffic_profiled(kernel, workload):
+    if workload != 3 or kernel not in TRAFFIC_PROFILED_GIB:
+        return None
+    return {"bytes": int(TRAFFIC_PROFILED_GIB[kernel] * 2**30), "workload": workload,
+            "source": "profiles/hot_path_cfg3_hbm_traffic.md"}
 
 
 class EngineClockSampler:
@@ -225,6 +231,7 @@ def main():
     # executes 4 of them (S, dP, dV, dK)
     one_pass = bool(plan.info()["one_pass_backward"]) and ws.numel() >= plan.workspace_bytes_one_pass()
     dkv_flops = fl["bwd"] * (1.0 if one_pass else 0.8)
+    kernel = "ca_bwd_fused_kernel" if one_pass else "ca_bwd_dkv_kernel"
     bwd_main_tflops = dkv_flops / (kavg["bwd_dkv_ms"] * 1e-3) / 1e12 if kavg["bwd_dkv_ms"] > 0 else 0.0
     fwd_tflops = fl["fwd"] / (kavg["fwd_kernel_ms"] * 1e-3) / 1e12 if kavg["fwd_kernel_ms"] > 0 else 0.0
     # the dQ kernel executes 3 contractions (S, dP, dQ): 6*D*Hq*pairs flops
@@ -245,10 +252,10 @@ def main():
                    "peak_bf16_tflops_from_device": peak_from_device, "during_timed_steps": clocks.summary()},
         "kernels_ms": kavg, "fwd_only_tflops": fwd_tflops, "bwd_only_tflops": bwd_tflops, "plan_ms": plan_ms, "plan_first_call_ms": plan_first_ms,
         "wall_s_timed": wall,
-        "roofline": {"kernel": "ca_bwd_fused_kernel" if one_pass else "ca_bwd_dkv_kernel", "bound": "mfma", "achieved": bwd_main_tflops,
+        "roofline": {"kernel": kernel, "bound": "mfma", "achieved": bwd_main_tflops,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": bwd_main_tflops / PEAK_BF16_TFLOPS,
                      "traffic": None,
-                     "traffic_profiled": DKV_TRAFFIC_PROFILED if args.workload == DKV_TRAFFIC_PROFILED["workload"] else None},
+                     "traffic_profiled": traffic_profiled(kernel, args.workload)},
     }
     # The metric credits 14*D flops per (pair, head), which is what the one pass executes; where there are two backward kernels they
     # execute 18*D (both recompute S and dP).  Executed rate next to the rate of back-to-back MFMAs measured in this run:

@@ -44,3 +44,15 @@ def test_sampler_without_sysfs_reports_nothing(tmp_path):
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "one GPU" in (r.stderr + r.stdout)
+
+
+def test_profiled_traffic_is_that_of_the_kernel_that_ran():
+    """Quoted on the workload it was counted on only, and for the kernel it was counted for (the files list both)."""
+    table = open(os.path.join(ROOT, "profiles", "hot_path_cfg3_hbm_traffic.md")).read()
+    for kernel, gib in bench.TRAFFIC_PROFILED_GIB.items():
+        assert kernel in table
+        t = bench.traffic_profiled(kernel, 3)
+        assert t["bytes"] == int(gib * 2**30) and os.path.exists(os.path.join(ROOT, t["source"]))
+        assert bench.traffic_profiled(kernel, 2) is None
+    assert bench.traffic_profiled("ca_bwd_fused_kernel", 3) != bench.traffic_profiled("ca_bwd_dkv_kernel", 3)
+    assert bench.traffic_profiled("another_kernel", 3) is None
