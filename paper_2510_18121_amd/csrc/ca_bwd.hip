@@ -766,7 +766,7 @@ static hipError_t launch_bwd_t(const ca_plan_t *p, const void *q, const void *k,
     a.dq_sums = reinterpret_cast<float *>(static_cast<char *>(ws) + p->ws_off_dq_sums);
     a.flags = reinterpret_cast<int *>(static_cast<char *>(ws) + p->ws_off_flags);
     a.ctrl = reinterpret_cast<int *>(static_cast<char *>(ws) + p->ws_off_ctrl);
-    a.hq = p->hq, a.hkv = p->hkv, a.padded = padded, a.scale = p->scale;
+    a.hq = p->hq, a.hkv = p->hkv, a.scale = p->scale;
     hipError_t e = launch_bwd_fused(a, D, p->device, st);
     if (e != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[2], st), (void)hipEventRecord(ev[3], st);

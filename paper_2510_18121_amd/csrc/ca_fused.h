@@ -16,7 +16,6 @@ struct FusedArgs {
   int *flags, *ctrl;
   uint32_t flag_bytes, copy_bytes, dq_bytes;  // (all below 4 GiB: 32-bit offsets)
   int hq, hkv;
-  int64_t padded;
   float scale;
 };
 hipError_t launch_bwd_fused(const FusedArgs &a, int d, int device, hipStream_t st);
