@@ -24,5 +24,7 @@ BATCHES = {
     # where moving K and V costs the other kernels much, and a short list at head_dim 64
     "short_shards": lambda: W.shard_chunk(61, "distinct", seed=3, chunk_tokens=61 * 140, max_context=3000, hq=16, hkv=16, d=128),
     "short_documents_d64": lambda: _documents([4001, 3000, 2049, 2048, 2047, 1900, 1500, 1024] + EDGES, 0x7fffffff, 16, 16, 64),
+    # sums of dQ just within 4 GiB: the largest 32-bit offsets
+    "offsets_up_to_4_gib": lambda: _documents([1023] * 127 + [959], 300, 64, 8, 128),
     "documents_d64": lambda: _documents([8001, 8000] * 3 + EDGES, 1029, 16, 16, 64),
 }

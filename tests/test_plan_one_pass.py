@@ -67,6 +67,15 @@ def test_offsets_beyond_32_bits_take_other_kernels():
     assert B.ca_plan_host(b).info()["one_pass_backward"] == 0
 
 
+@pytest.mark.parametrize("last,taken", [(960, 1), (961, 0)])
+def test_largest_offset(last, taken):
+    """128 documents of whole 64-row blocks, 64 heads: 4 GiB less 2 MiB of sums, and one block more."""
+    lens = [1024] * 127 + [last]
+    info = B.ca_plan_host(W.custom(lens, [(i, 0, n) for i, n in enumerate(lens)], 64, 8, 128)).info()
+    sums = info["padded_rows"] * 64 * 128 * 4
+    assert info["one_pass_backward"] == taken and sums == (1 << 32) - (1 << 21) * taken
+
+
 @pytest.mark.skipif(not os.path.exists(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")), reason="hipcc is needed to produce the assembly")
 def test_kernel_keeps_everything_in_registers():
     asm = C.compile_to_asm("ca_bwd_fused.hip")
