@@ -55,13 +55,13 @@ __device__ __forceinline__ void static_for(F f) {
 }
 
 // The order in which a wave uses the fragments of a step: 4 NK of K and Q (S; two of 16 keys and two of 16 rows for 32 columns at a
-// time), 2 NK of dO (dP), ND of dO transposed (dV), ND of Q transposed (dK), 2 W of dS (dQ; apart from the ring in masked steps).  They
-// come from LDS through a ring of R fragments' registers, as far ahead as there is room beside what else is alive.
-template <int D, bool MASK>
+// time), 2 NK of dO (dP), ND of dO transposed (dV), ND of Q transposed (dK), 2 W of dS (dQ).  They come from LDS through a ring of
+// R fragments' registers, as far ahead as there is room beside what else is alive.
+template <int D>
 struct FusedRing {
   static constexpr int NK = D / 32, ND = D / 16;
-  static constexpr int DO = 4 * NK, DV = DO + 2 * NK, DK = DV + ND, DQ = DK + ND, N = MASK ? DQ : DQ + 2 * fused_waves(D);
-  static constexpr int R = MASK ? 6 : 7, AHEAD_DP = 2, AHEAD = MASK ? 3 : 4;
+  static constexpr int DO = 4 * NK, DV = DO + 2 * NK, DK = DV + ND, DQ = DK + ND, N = DQ + 2 * fused_waves(D);
+  static constexpr int R = 7, AHEAD_DP = 2, AHEAD = 4;
   // how many are there or on their way once `used` of them have been used
   static constexpr int fetched(int used) {
     if (used <= DO) return used + R < DO + AHEAD_DP ? used + R : DO + AHEAD_DP;
@@ -212,6 +212,23 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
 #pragma unroll
       for (int i = 0; i < NDW; ++i) kt[ks][i] = fetch_kt(t0, 32 * ks, i), pin(kt[ks][i]);
   }
+  // A zero masks a product only if the other factor is finite, and what a row does not see may hold Inf or NaN.  So a unit with a
+  // diagonal multiplies the wave's part of K transposed, and V of its keys, by zeros once.  Where that does not give zeros, masked steps
+  // leave out the keys that their rows do not see (last_dq, rest_of_dq), and dS is zero where P is.  (Leaving them out always: shards in
+  // contexts of up to 1K to 3K keys 1.7 % slower.)
+  bool k_finite = true, v_finite = true;
+  if (n_full < n_it) {
+    const bf16x8 zero = __builtin_bit_cast(bf16x8, u32x4{0, 0, 0, 0});
+    f32x4 x[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int ks = 0; ks < W; ++ks)
+#pragma unroll
+      for (int i = 0; i < NDW; ++i) x[0] = mfma16(kt[ks][i], zero, x[0]);
+#pragma unroll
+    for (int s = 0; s < NK; ++s) x[1] = mfma16(zero, vf[s][1], mfma16(zero, vf[s][0], x[1]));
+    auto finite = [&](const f32x4 &y) __attribute__((always_inline)) { return __ballot(y[0] + y[1] + y[2] + y[3] != 0.f) == 0; };
+    k_finite = finite(x[0]), v_finite = finite(x[1]);
+  }
   int kb = lds0 + S::K_OFF + (kw0 + li) * ROWB + 16 * (j ^ tile_sw<D>(li));
   int nb = lds0 + li * ROWB + 16 * (j ^ tile_sw<D>(li));
   int tb = lds0 + (4 * j + (li >> 2)) * ROWB + 16 * (((li >> 1) & 1) ^ tile_sw<D>(4 * j + (li >> 2))) + 8 * (li & 1);
@@ -276,12 +293,10 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     const int t = (f % 2 == 0 ? ds_rd : ds_rd ^ 32) + 2048 * (f / 2);
     return join(lds_read_tr4_at(t), lds_read_tr4_at(t + 1024));
   };
-  // Zeros do not mask a product with Inf or NaN.  So dQ leaves out the keys that none of a step's rows see, and dS of a key that its
-  // row does not see is zero whatever V holds.
-  // dQ of the step before from the 32 keys of which its rows see some
+  // dQ of the step before from the 32 keys of which its rows see some, without the others
   auto rest_of_dq = [&]() __attribute__((always_inline)) {
     const int begin = (prev_seen + 1) & ~31;
-    if (begin > prev_seen) return;
+    if (k_finite || begin > prev_seen) return;
     const int at = ds_address() + 64 * begin;
     const bf16x8 g[2] = {fetch_ds(at, 0), fetch_ds(at, 1)};
     const int last = prev_seen - begin - 4 * (lane_id_here() >> 4);  // the lane holds keys 0 .. 3 and 16 .. 19 from here on
@@ -297,15 +312,15 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
       for (int rt = 0; rt < 2; ++rt) dq[i][rt] = mfma16(__builtin_bit_cast(bf16x8, w), g[rt], dq[i][rt]);
     }
   };
-  // dQ of the step before, whose rows may not see all keys
-  auto masked_dq = [&]() __attribute__((always_inline)) {
+  // dQ of the step before where nothing else is to be done
+  auto last_dq = [&]() __attribute__((always_inline)) {
     const int ds_rd = ds_address();
     bf16x8 g[4];
     static_for<4>([&](auto f) __attribute__((always_inline)) { g[f] = fetch_ds(ds_rd, f); });
     static_for<W>([&](auto ks) __attribute__((always_inline)) {
       constexpr int at = 2 * ks % 4;
       __builtin_amdgcn_sched_barrier(0);
-      if (32 * ks + 31 <= prev_seen) {
+      if (k_finite || 32 * ks + 31 <= prev_seen) {
 #pragma unroll
         for (int i = 0; i < NDW; ++i) dq[i][0] = mfma16(kt[ks][i], g[at], dq[i][0]), dq[i][1] = mfma16(kt[ks][i], g[at + 1], dq[i][1]);
       }
@@ -340,11 +355,9 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     }
   };
 
-  // S, P, dP, dV, dS and dK of a step for the wave's keys, and dQ of the step before for its columns
-  // (sees: some row of the step sees some key of the wave's)
-  auto compute = [&](auto mask, const bool sees) __attribute__((always_inline)) {
-    constexpr bool MASK = mask;
-    using F = FusedRing<D, MASK>;
+  // S, P, dP, dV, dS and dK of a step for the wave's keys (sees: some row sees some of them), and dQ of the step before for its columns
+  auto compute = [&](const bool MASK, const bool sees) __attribute__((always_inline)) {
+    using F = FusedRing<D>;
     constexpr int R = F::R;
     bf16x8 fr[R];
     int ds_rd = 0;
@@ -412,13 +425,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     auto pack_pair = [&](int rt, int i) __attribute__((always_inline)) {
       const int e = 2 * (i & 1), kg = i >> 1;
       pw[kg][2 * rt + e / 2] = pack_bf16(sa[rt][kg][e], sa[rt][kg][e + 1]);
-      float ds[2];
-#pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        ds[n] = sa[rt][kg][e + n] * pa[rt][kg][e + n];
-        if (MASK) ds[n] = sa[rt][kg][e + n] == 0.f ? 0.f : ds[n];
-      }
-      dw[kg][2 * rt + e / 2] = pack_bf16(ds[0], ds[1]);
+      dw[kg][2 * rt + e / 2] = pack_bf16(sa[rt][kg][e] * pa[rt][kg][e], sa[rt][kg][e + 1] * pa[rt][kg][e + 1]);
       asm volatile("" : "+v"(dw[kg][2 * rt + e / 2]));  // (here: not sunk to where dS is used, with S and dP alive until then)
     };
     static_for<2>([&](auto rt) __attribute__((always_inline)) {
@@ -452,6 +459,13 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     bf16x8 pb[2], db[2];
 #pragma unroll
     for (int i = 0; i < 4; ++i) pack_pair(1, i);
+    if (MASK && !(v_finite && sees)) {  // dS is zero where P is, whatever V and dO hold
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t p = pw[i >> 2][i & 3];
+        dw[i >> 2][i & 3] &= (p & 0xffffu ? 0xffffu : 0u) | (p >> 16 ? 0xffff0000u : 0u);
+      }
+    }
 #pragma unroll
     for (int kg = 0; kg < 2; ++kg) pb[kg] = __builtin_bit_cast(bf16x8, u32x4{pw[kg][0], pw[kg][1], pw[kg][2], pw[kg][3]});
     __builtin_amdgcn_sched_barrier(0);
@@ -485,7 +499,8 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
       }
       used(std::integral_constant<int, at>{}, one);
     });
-    if constexpr (!MASK) static_for<2 * W>([&](auto f) __attribute__((always_inline)) {
+    if (MASK && !k_finite) return;  // (to last_dq)
+    static_for<2 * W>([&](auto f) __attribute__((always_inline)) {
       constexpr int at = F::DQ + f;
 #pragma unroll
       for (int i = 0; i < NDW; ++i) dq[i][f % 2] = mfma16(kt[f / 2][i], fr[at % R], dq[i][f % 2]);
@@ -506,8 +521,7 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
   };
 
   int it = 0;
-  auto step = [&](auto mask, auto idles) __attribute__((always_inline)) {
-    constexpr bool MASK = mask, IDLE = idles;
+  auto step = [&](const bool MASK, const bool IDLE) __attribute__((always_inline)) {
     // the step's tiles have landed (this wave's part): younger are at most the stores of dQ of the step before the last
     if (!MASK && it > 1) wait_vmcnt<NQ>();
     else wait_vmcnt<0>();
@@ -517,9 +531,9 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
       seen = __builtin_amdgcn_readfirstlane(lds_ld<int>(lds0 + stage * S::STAGE + S::POS_OFF + (32 * ((run_len - run) & 1) + 31) * 4)) - u.key_pos0;
       if (seen >= KEYS) seen = ALL_KEYS;
     }
-    if constexpr (IDLE) idle();
-    else compute(mask, seen >= kw0);
-    if constexpr (MASK) masked_dq();
+    if (IDLE) idle();
+    else compute(MASK, seen >= kw0);
+    if (MASK && (IDLE || !k_finite)) last_dq();
     store_dq(MASK);
     prev = seen >= 0 ? tile : -1, prev_run = run, prev_seen = seen;
     dsb ^= 1;
@@ -529,14 +543,14 @@ __device__ __forceinline__ void fused_unit(const BwdUnit u, const FusedArgs &a, 
     stage = stage == NST - 1 ? 0 : stage + 1;
     nb += adv, tb += adv, auxo += adv;
   };
-  for (; it < n_full; ++it) step(std::false_type{}, std::false_type{});
-  for (; it < n_seen; ++it) step(std::true_type{}, std::false_type{});
-  for (; it < n_it; ++it) step(std::true_type{}, std::true_type{});
+  for (; it < n_full; ++it) step(false, false);
+  for (; it < n_seen; ++it) step(true, false);
+  for (; it < n_it; ++it) step(true, true);
   wait_vmcnt<0>();
   publish();
   barrier_nofence();  // dS of the last step
   take_turn(-1);
-  masked_dq();
+  last_dq();
   store_dq(true);
   wait_vmcnt<0>();
   publish();
@@ -569,10 +583,10 @@ __global__ __launch_bounds__(64 * fused_waves(D), fused_waves(D) == 8 ? 2 : 3) v
         int was = 0;
         if (__hip_atomic_compare_exchange_strong(ctrl, &was, xcc + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || was == xcc + 1)
           t = __hip_atomic_fetch_add(ctrl + 32, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *(CA_LDS int *)(uintptr_t)(lds0 + S::TICKET_OFF) = t;
+        *(CA_LDS int *)(uintptr_t)(lds0 + opaque(S::TICKET_OFF)) = t;
       }
       __syncthreads();
-      const int t = __builtin_amdgcn_readfirstlane(lds_ld<int>(lds0 + S::TICKET_OFF));
+      const int t = __builtin_amdgcn_readfirstlane(lds_ld<int>(lds0 + opaque(S::TICKET_OFF)));
       if (t >= end - begin) break;
       fused_unit<D>(a.units[begin + t], a, wave);
     }
