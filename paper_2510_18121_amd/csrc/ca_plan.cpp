@@ -295,25 +295,26 @@ std::array<Cut, 2> best_piece(const std::vector<std::pair<int64_t, int64_t>> &un
 // little more evenly and are slower, as fewer of the sums of dQ are still in L2: 8.46 against 8.18 ms (64K tokens of documents
 // of about 2K, 32/8 heads), 31.5 against 30.9 ms (64K tokens of long documents, 64/8), 4.99 against 4.47 ms (lone 64-row shards, 8/2).
 //
-// At head_dim 64, with three workgroups per CU and short chains, groups are half as long again: 345 -> 319 us (16K tokens of documents
-// of about 2K, 16/16 heads); 128 would lose with that (7.25 -> 7.45 ms).
+// At head_dim 64, with three workgroups per CU, groups are half as long again.  Of 63 drawn batches there shards ran 1.5 % slower so than in
+// groups as at 128, but documents 0.8 % faster (geometric means), and short lists, whose last group leaves workgroups idle,
+// up to 19 % (532 -> 447 us); groups half as long again as that lose another 1.2 %.  128 would lose (64K tokens of documents
+// of about 2K 7.25 -> 7.45 ms).
 //
 // When does the one pass pay?  It does five contractions instead of seven, but in workgroups of twice the keys (head_dim 128), one to a
 // CU, bound to queues.  A unit costs `fixed`, `per_step` for each 32 rows x head and `per_masked` where they hold the diagonal, and
 // starts at least `lag` after the one before it in its chain; the longest queue is simulated and compared with the simulation of the
 // other kernels.  Theirs knows only steps, so it is given the time by which moving K and V (read twice), dK and dV prolongs them: 0.4
 // of those bytes at the rate of partial results, from batches of short shards under long contexts (with it 12 measured at 1.03
-// to 1.2 of the simulation, without it at 1.15 to 1.7).  Microseconds, fitted to 330 drawn batches.  Of 139 of 500 others that the rule
-// takes (0.08 to 8 TFLOP of work), the two lists were 1.14 times slower on average (backward, geometric mean), and
-// none was faster by more than 2 %; the best that it left out gained 11 %.  (At 64: the diagonal's blocks of the heads of a
-// group cost more than is foreseen, hence the larger gain asked for.)
+// to 1.2 of the simulation, without it at 1.15 to 1.7).  Microseconds, fitted to drawn batches.  Of 1018 measured in both ways the rule
+// takes 266: the lists were 1.13 (head_dim 128) and 1.20 times (64) slower on average (backward, geometric mean), and faster by
+// more than 2 % on 3 (3.5 % on one).  Of the others 103 would have gained more than 2 %, mostly at 64 and below a millisecond.
 struct FusedCost {
   int slots;  // workgroups per XCD
   double per_step, per_masked, fixed, lag;
   double groups;             // times over that a group of chains keeps the workgroups busy
   double gain, more, least;  // the lists have to take `more` microseconds more than `gain` times the one pass; the least work worth a look
 };
-constexpr FusedCost FUSED_128 = {N_CU / N_XCD, 2.42, 3.3, 12.0, 4.0, 2.0, 1.06, 40, 150},
+constexpr FusedCost FUSED_128 = {N_CU / N_XCD, 2.42, 3.45, 12.0, 4.0, 2.0, 1.03, 120, 150},
                     FUSED_64 = {3 * N_CU / N_XCD, 2.05, 5.5, 11.0, 4.0, 3.0, 1.095, 0, 150};
 
 class OnePass {
