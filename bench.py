@@ -23,7 +23,7 @@ PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA peak
 # HBM bytes per launch of the backward's main kernel on workload 3 as counted by rocprofv3 (FETCH_SIZE / WRITE_SIZE passes,
 # scaled by the plain-copy calibration): NOT measured in a plain run of this script.  The figure of the last counter
 # passes over the kernel that ran is quoted under roofline.traffic_profiled with the file it comes from; roofline.traffic itself is null.
-TRAFFIC_PROFILED_GIB = {"ca_bwd_fused_kernel": 214.3 + 130.5, "ca_bwd_dkv_kernel": 184.8 + 0.50}
+TRAFFIC_PROFILED_GIB = {"ca_bwd_fused_kernel": 219.5 + 132.4, "ca_bwd_dkv_kernel": 184.8 + 0.50}
 
 
 def traffic_profiled(kernel, workload):

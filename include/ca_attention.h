@@ -115,7 +115,7 @@ int ca_plan_workspace_bytes_split(const ca_plan_t *plan, size_t *fwd_bytes, size
  * ca_plan_workspace_bytes_one_pass: workspace with which ca_backward computes dK, dV and dQ in one pass, with S and dP computed once
  * instead of twice; 0 where that would not be faster (small batches).  It holds fp32 sums of dQ, 4 * n_q_heads * padded_rows *
  * head_dim bytes and a little more behind the bwd_bytes of ca_plan_workspace_bytes.  With less the calls do what is said above.  The
- * results are those of whole units, bit for bit.
+ * results are those of whole units, bit for bit, where those are finite.
  */
 int ca_plan_workspace_bytes_one_pass(const ca_plan_t *plan, size_t *bwd_bytes);
 

@@ -22,7 +22,7 @@
 // alike, 128K tokens of long and short documents in shuffled shards (32/8 heads, head_dim 128): dK/dV kernel 108.0 -> 104.2 ms,
 // dQ kernel 82.2 -> 77.4 ms.
 // No atomics and no fp32 dQ accumulation: the price is that S and dP are computed in both kernels (7 contractions
-// instead of the minimal 5).  Results are deterministic.  Batches that fill the chip take five, in ca_bwd_fused.hip, with the same
+// instead of the minimal 5).  Results are deterministic.  All but small batches take five, in ca_bwd_fused.hip, with the same
 // results.
 #include <algorithm>
 #include <atomic>

@@ -1,5 +1,5 @@
 // The backward in one pass: dK, dV and dQ from one recomputation of S and dP (five contractions; the dK/dV and dQ kernels of
-// ca_bwd.hip take seven between them).  For batches that fill the chip (plan_fused in ca_plan.cpp has the rule).
+// ca_bwd.hip take seven between them).  For batches of some hundred microseconds and more (OnePass in ca_plan.cpp has the rule).
 //
 // A workgroup owns a tile of keys of one document and KV head (256 keys and eight waves at head_dim 128, 128 keys and four waves
 // at 64), keeps dK and dV in registers like the dK/dV kernel and walks the document's query rows backwards, 32 rows of one query
@@ -10,24 +10,27 @@
 // The sums of dQ so far are fp32 in memory.  They are added to in the order of the tiles: tile j + 1 waits until tile j has added
 // to the 32-row tile of dQ (a counter per wave and tile), loads the sums as the MFMAs' C operand, and stores them back; the
 // last tile that a row sees writes bf16 dQ.  So dQ is the sum the dQ kernel forms, in its order: all results are
-// the same bit for bit as those of whole units in the other kernels, and from run to run.
+// the same bit for bit as those of whole units in the other kernels, and from run to run.  (Where those are finite: what a NaN or Inf
+// in one row of Q, K, V or dO reaches here is part of what it reaches there.)
 //
 // Why plain loads and stores: all tiles of one (document, KV head) run on one XCD, so the sums live in its L2, the point of
-// coherence of its CUs.  There an ordered load-add-store of 16 KiB tiles by 64 workgroups per XCD runs at 17.9 TB/s read + written over the
+// coherence of its CUs.  There an ordered load-add-store of 16 KiB tiles by 64 workgroups per XCD runs at 15 to 18 TB/s read + written over the
 // chip; fp32 atomic adds retire at 1.36 TB/s.  A load has to bypass the CU's own vector L1 (sc1); a store has arrived in L2
 // when vmcnt says so.  A workgroup asks which XCD it is on and takes units from that XCD's queue; a queue that no XCD has claimed
 // yet is claimed by whoever gets to it, so every unit is run on any partition of the chip.  A unit only waits for units that were
 // taken before it from the same queue, so the first unit that is not finished never waits for one that nobody runs.
 //
 // Why 256 keys at head_dim 128: the sums move once per tile, 16 KiB read and written per 32 rows of a head, half of what 128 keys
-// cost (without them the kernel would take 141 of 160 ms).  One workgroup fills a CU, and its waves leave every barrier together; a wave's priority falls
+// cost (without waiting for, loading and storing them the kernel would take 141 of 157 ms).  One workgroup fills a CU, and its waves leave every barrier together; a wave's priority falls
 // from phase to phase, so the one that is behind goes first (163.0 -> 161.5 ms).  LDS fragments come through a ring of registers
 // across the phases (S alone 1100 -> 480 cycles of a step), addresses are made with few scalar instructions (605 -> 503 instructions per
 // step, 174 -> 163 ms), the turn at dQ is taken early in dV (159 -> 157 ms).  128K tokens in shuffled shards, 32/8 heads, head_dim 128:
 // 177 ms in two kernels, 157 in this one (64K tokens of documents of about 2K: 8.3 -> 7.5 ms; last 1000 rows of 130K: 5.8 -> 5.2 ms).
-// Waves whose keys a block below the diagonal does not see only add dQ there (7.50 -> 7.35 ms on the 64K tokens).
-// Matrix pipe busy 48 % at 1.9 GHz (kernels of ca_bwd.hip: 62 %): what is left is barriers, LDS latency after them, waits for turns.
-// Tried and not kept: workgroups of 128 keys, two to a CU (187 ms: the sums move twice as often); half the waves adding dQ at the
+// Waves whose keys a block below the diagonal does not see only add dQ there (7.50 -> 7.35 ms on the 64K tokens).  That what a row does
+// not see may hold Inf or NaN costs 0.4 % on the 128K tokens, 0.9 % on the 64K, up to 2 % on shards in contexts of 1K.
+// Matrix pipe busy 53 % of the time at 1.9 GHz, 56 % while two waves are there (dK/dV kernel 76 %, dQ kernel 66 %): what is left is
+// barriers, LDS latency after them, waits for turns.
+// Tried and not kept: workgroups of 128 keys, two to a CU (188 ms: the sums move twice as often); half the waves adding dQ at the
 // start of a step and half at its end (+3 %); dK of a step after the next barrier (+4 %: nothing is left to cover the sums' loads), dQ
 // before dK (+3 %); polls by direct loads to LDS at the start of a step (+2 %: older values); every other run of 32 tiles walked
 // forwards (+2.5 %); the next unit's ticket and first tiles on their way before dK and dV are stored (+0.5 %; level on short units).
